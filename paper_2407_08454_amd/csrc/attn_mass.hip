@@ -20,6 +20,7 @@
 // and by power, not by the matrix pipe: at d = 128 a 32x32 block costs 8 MFMAs (256 cycles) and
 // at least 48 VALU instructions (one fma, one exp2, one add per score), and packed fp32
 // arithmetic is not used.  Hence the attention to every VALU instruction in the block loops.
+// Launches too small to fill the chip with 256-row workgroups go to attn_split.hip.
 #include "attn_tile.h"
 
 namespace kvm {
@@ -34,22 +35,6 @@ namespace kvm {
 // overlap of MFMA, exp2 and LDS traffic is left to the hardware interleaving the waves.
 // ------------------------------------------------------------------------------------------
 
-// pass 1: the online (max, sum) of a row absorbs 16 more scores (-inf = masked)
-__device__ __forceinline__ void rowstat_update(const f32x16 &acc, float c, float &m_run, float &l_run) {
-    const float m_new = fmaxf(m_run, max16(acc));
-    const float mc = m_new * c;
-    float p0 = 0.f, p1 = 0.f;
-#pragma unroll
-    for (int i = 0; i < 16; i += 2) {
-        p0 += __builtin_amdgcn_exp2f(fmaf(acc[i], c, -mc));
-        p1 += __builtin_amdgcn_exp2f(fmaf(acc[i + 1], c, -mc));
-    }
-    // (the difference is taken before the scaling: M_INIT * c - round(M_INIT * c), fused, would be
-    // the rounding error of a huge product instead of zero)
-    l_run = l_run * __builtin_amdgcn_exp2f((m_run - m_new) * c) + (p0 + p1);
-    m_run = m_new;
-}
-
 // pass 1 with the reference held: 16 more terms exp2(c s - mc) of a row's sum, no maximum and
 // no rescaling.  Any reference gives the same log-sum-exp as long as no term overflows; the
 // caller checks the finished sums for that.
@@ -61,26 +46,6 @@ __device__ __forceinline__ void rowsum_held(const f32x16 &acc, float c, float mc
         p1 += __builtin_amdgcn_exp2f(fmaf(acc[i + 1], c, -mc));
     }
     l_run += p0 + p1;
-}
-
-// pass 2: the row statistics L of a 32-row block of the streamed tile, in the order of a
-// lane's accumulators (accumulator i of lane l is row 8*(i/4) + 4*(l/32) + i%4)
-struct RowStats { f32x4 v[4]; };
-__device__ __forceinline__ RowStats load_rowstats(const float *lse_tile, int blk, int lane) {
-    RowStats L;
-#pragma unroll
-    for (int r = 0; r < 4; ++r) L.v[r] = *reinterpret_cast<const f32x4 *>(&lse_tile[32 * blk + 8 * r + 4 * (lane >> 5)]);
-    return L;
-}
-// part[0..1] += exp2(c * acc - L)
-__device__ __forceinline__ void colsum_update(const f32x16 &acc, const RowStats &L, float c, float *part) {
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-        part[0] += __builtin_amdgcn_exp2f(fmaf(acc[4 * r], c, -L.v[r][0]));
-        part[1] += __builtin_amdgcn_exp2f(fmaf(acc[4 * r + 1], c, -L.v[r][1]));
-        part[0] += __builtin_amdgcn_exp2f(fmaf(acc[4 * r + 2], c, -L.v[r][2]));
-        part[1] += __builtin_amdgcn_exp2f(fmaf(acc[4 * r + 3], c, -L.v[r][3]));
-    }
 }
 
 constexpr int FRAG_BATCH = 2;            // A fragments fetched from LDS per batch of MFMAs (generic path)
@@ -488,6 +453,11 @@ __global__ void __launch_bounds__(256) lse_import_kernel(const float *__restrict
 
 void launch_colsum_pipe(const kvm_shape &sh, const void *Q, const void *K, const float *neg_lse, float *mass, float *sim_opt,
                         int n_pad, float c, hipStream_t st);
+int attn_split_waves(int dtype, long long full_wgs, int tiles, long long split_wgs, long long chain);
+void launch_lse_split(int waves, const kvm_shape &sh, const void *Q, const void *K, float *lse, int n_pad, float c, float out_scale,
+                      float pad, hipStream_t st);
+void launch_colsum_split(int waves, const kvm_shape &sh, const void *Q, const void *K, const float *lse, float *mass, float *sim_opt,
+                         int n_pad, float c, hipStream_t st);
 
 // From this length on the column sums of 16-bit inputs are taken by attn_colsum_pipe_kernel
 // (attn_pipe.hip): measured 5 % faster at N = 16384, 1-3 % slower at N = 4096, where the eight
@@ -503,7 +473,15 @@ static kvm_status launch_t(const kvm_shape &sh, const void *Q, const void *K, co
     const float c = (float)(1.4426950408889634 / sqrt((double)sh.d));
     const int n_q = sh.B * sh.H_kv * sh.G, n_kv = sh.B * sh.H_kv;
     const int n_pad = attn_lse_stride(sh.N);
-    const bool pipe = Mma<T>::NBLK == 2 && sh.N >= COLSUM_PIPE_MIN_N;
+    // workgroups of the full kernels: every row tile once, or half as many with one long and one short
+    // tile each (measured faster from 8 tiles per slice on; below that the second tile's start-up, which
+    // nothing overlaps, costs more than the even load gains)
+    const int wgs = tiles >= 8 ? (tiles + 1) / 2 : tiles;
+    // launches too small to fill the chip are split four ways (attn_split.hip)
+    const long long split_tiles = (sh.N + 32 * Mma<T>::NBLK - 1) / (32 * Mma<T>::NBLK), chain = (sh.N + 31) / 32;
+    const int split_lse = attn_split_waves(sh.dtype, (long long)n_q * wgs, tiles, n_q * split_tiles, chain);
+    const int split_colsum = attn_split_waves(sh.dtype, (long long)n_kv * wgs, tiles, n_kv * split_tiles, chain * sh.G);
+    const bool pipe = Mma<T>::NBLK == 2 && sh.N >= COLSUM_PIPE_MIN_N && !split_colsum;
     // how the row statistic is stored for the second pass: L_t, or -L_t / c for attn_colsum_pipe_kernel
     const float out_scale = pipe ? -1.f / c : 1.f, pad = pipe ? -INFINITY : INFINITY;
     if (row_lse) {
@@ -513,11 +491,12 @@ static kvm_status launch_t(const kvm_shape &sh, const void *Q, const void *K, co
                            sh.seq_lens, sh.H_kv * sh.G, sh.N, n_pad, per, 1.44269504088896341f * out_scale, pad);
         kvm_status rc = check_launch("lse_import_kernel");
         if (rc != KVM_OK) return rc;
+    } else if (split_lse) {
+        ProfScope prof("attn_lse_split_kernel", st);
+        launch_lse_split(split_lse, sh, Q, K, lse, n_pad, c, out_scale, pad, st);
+        kvm_status rc = check_launch("attn_lse_split_kernel");
+        if (rc != KVM_OK) return rc;
     } else {
-        // long sequences: half as many workgroups, each with one long and one short row tile
-        // (measured faster from 8 tiles per slice on; below that the second tile's start-up,
-        // which nothing overlaps, costs more than the even load gains)
-        const int wgs = tiles >= 8 ? (tiles + 1) / 2 : tiles;
         const long long blocks = (long long)((n_q + 7) / 8) * 8 * wgs;
         int32_t *redo = reinterpret_cast<int32_t *>(lse + (size_t)n_q * n_pad);   // one flag per (query slice, row tile)
         if constexpr (Mma<T>::NBLK == 2) {
@@ -542,8 +521,11 @@ static kvm_status launch_t(const kvm_shape &sh, const void *Q, const void *K, co
         kvm_status rc = check_launch("attn_lse_kernel");
         if (rc != KVM_OK) return rc;
     }
-    {
-        const int wgs = tiles >= 8 ? (tiles + 1) / 2 : tiles;   // as for the row statistics
+    if (split_colsum) {
+        ProfScope prof("attn_colsum_split_kernel", st);
+        launch_colsum_split(split_colsum, sh, Q, K, lse, mass, sim_opt, n_pad, c, st);
+        return check_launch("attn_colsum_split_kernel");
+    } else {
         const long long blocks = (long long)((n_kv + 7) / 8) * 8 * wgs;
         ProfScope prof(pipe ? "attn_colsum_pipe_kernel" : "attn_colsum_kernel", st);
         if (pipe) launch_colsum_pipe(sh, Q, K, lse, mass, sim_opt, n_pad, c, st);

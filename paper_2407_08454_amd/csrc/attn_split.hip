@@ -1,0 +1,305 @@
+// Both score passes of attn_mass.hip for launches that cannot fill the chip with its workgroups
+// (few slices, short sequences; Section 2.4 Eq. (1), Section 4.2 Eq. (7)).
+//
+//   attn_lse_split_kernel     row log-sum-exps, L_t = log2 sum_j exp2(c s_tj)
+//   attn_colsum_split_kernel  column sums, mass_j = sum_g sum_{t>=j} exp2(c s_tj - L_t)
+//
+// What bounds such a launch is the longest serial chain of a workgroup and the number of idle compute
+// units, not a rate: 256 stationary rows per workgroup leave 128 workgroups for 32 slices of 1000
+// tokens, and with G query heads per KV head the one workgroup of a key tile walks all G heads.
+// Here a workgroup owns a QUARTER of the rows (32 per MFMA block, NBLK blocks: 64 rows, 32 for fp32),
+// all its waves hold the same rows in registers and the streamed 32-row tiles are dealt to the waves
+// in turn, so four times as many workgroups run and each wave's chain is 1/W as long.  Every wave has
+// its own two LDS stages and waits for nobody until the partial results are combined through LDS
+// in the order of the waves (deterministic).  Each wave reads its tiles for 64 stationary rows only,
+// where a workgroup of attn_mass.hip reads them once for 256: four times the L2 traffic, which is why
+// full launches stay with those kernels (the rule is at attn_split_waves).
+#include "attn_tile.h"
+
+namespace kvm {
+
+// A wave's private stream: 32 rows of CHUNKS 16-byte chunks per stage, swizzled like Tile.
+template <typename T> struct Stream {
+    static constexpr int CH = Mma<T>::CHUNKS;
+    static constexpr int SLOTS = 32 * CH;
+    static constexpr int LOADS = SLOTS / WAVE;               // global_load_lds instructions per tile
+    static constexpr int ROWS_PER_LOAD = WAVE / CH;
+    // rows [row0, row0+32) of the matrix at `base`; rows past n_valid repeat the last valid one (row0 < n_valid)
+    static __device__ __forceinline__ void issue(const T *base, int row0, int n_valid, u32x4 *stage, int lane) {
+        const int last = n_valid - 1 - row0;
+        const char *first_row = reinterpret_cast<const char *>(base + (size_t)row0 * HEAD_DIM);
+#pragma unroll
+        for (int i = 0; i < LOADS; ++i) {
+            const int row = i * ROWS_PER_LOAD + lane / CH, pos = lane % CH;
+            const uint32_t off = (uint32_t)(min(row, last) * (HEAD_DIM * (int)sizeof(T)) + ((pos ^ (row & (CH - 1))) * 16));
+            __builtin_amdgcn_global_load_lds((gptr_t)(first_row + off), (lptr_t)(stage + i * WAVE), 16, 0, 0);
+        }
+    }
+    static __device__ __forceinline__ u32x4 frag(const u32x4 *stage, int f, int lane) {
+        const int row = lane & 31;
+        return stage[row * CH + ((2 * f + (lane >> 5)) ^ (row & (CH - 1)))];
+    }
+};
+
+// the wave's own tile has landed, and its LDS reads of the stage that is overwritten next are done
+__device__ __forceinline__ void wait_own_tile() { __builtin_amdgcn_s_waitcnt(7 << 4); }   // vmcnt(0) lgkmcnt(0)
+
+// scores of a streamed 32-row block against one stationary block
+template <typename T>
+__device__ __forceinline__ f32x16 stream_scores(const u32x4 *a, const u32x4 *bfrag) {
+    f32x16 acc;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) acc[i] = 0.f;
+#pragma unroll
+    for (int f = 0; f < Mma<T>::FRAGS; ++f) Mma<T>::mma(acc, a[f], bfrag[f]);
+    return acc;
+}
+
+// blockIdx -> (slice, tile): slices vary fastest, so that a slice count divisible by the eight XCDs keeps a
+// slice's tiles on one of them, any other spreads evenly, and the longest tiles of all slices start first.
+template <typename T, int W>
+__global__ __launch_bounds__(W * WAVE, sizeof(T) == 2 && W == 4 ? 2 : 1) void attn_lse_split_kernel(
+    const T *__restrict__ Q, const T *__restrict__ K, float *__restrict__ lse, const int32_t *__restrict__ seq_lens,
+    int n_qslices, int HG, int G, int N, int n_pad, int tiles_per_slice, float c, float out_scale, float pad)
+{
+    using M = Mma<T>;
+    using S = Stream<T>;
+    constexpr int NB = M::NBLK, ROWS = 32 * NB;
+    __shared__ u32x4 lds_a[W][S::SLOTS], lds_b[W][S::SLOTS];  // (two objects: see attn_lse_kernel)
+    __shared__ float part_m[W][ROWS], part_l[W][ROWS];
+
+    const int qslice = blockIdx.x % n_qslices;
+    const int tile = tiles_per_slice - 1 - blockIdx.x / n_qslices;        // the longest rows first
+    const int b = qslice / HG;
+    const int kvslice = b * (HG / G) + (qslice % HG) / G;
+    const int n = clamp_len(seq_lens, b, N);
+    const int q0 = tile * ROWS;
+    if (q0 >= n) return;
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const T *Qs = Q + (size_t)qslice * N * HEAD_DIM;
+    const T *Ks = K + (size_t)kvslice * N * HEAD_DIM;
+
+    const int diag0 = tile * NB;                              // key block on the diagonal of query block 0
+    const int count = min(diag0 + NB, (n + 31) / 32);         // key blocks 0 .. count-1, this wave's: wave, wave+W, ...
+    int next = wave;
+    auto issue_next = [&](u32x4 *stage) {
+        if (next < count) S::issue(Ks, next * 32, n, stage, lane);
+        next += W;
+    };
+    issue_next(lds_a[wave]);
+    u32x4 qf[NB][M::FRAGS];
+#pragma unroll
+    for (int qb = 0; qb < NB; ++qb) load_stationary<T>(Qs, q0 + 32 * qb, n, lane, qf[qb]);
+    float m_run[NB], l_run[NB];
+#pragma unroll
+    for (int qb = 0; qb < NB; ++qb) { m_run[qb] = M_INIT; l_run[qb] = 0.f; }
+
+    auto step = [&](int t, const u32x4 *cur, u32x4 *nxt) {
+        wait_own_tile();
+        issue_next(nxt);
+        u32x4 a[M::FRAGS];
+#pragma unroll
+        for (int f = 0; f < M::FRAGS; ++f) a[f] = S::frag(cur, f, lane);
+#pragma unroll
+        for (int qb = 0; qb < NB; ++qb) {
+            if (t > diag0 + qb) continue;                     // every key of the block is in the future
+            f32x16 acc = stream_scores<T>(a, qf[qb]);
+            if (t == diag0 + qb) mask_rows_above_col(acc, lane);          // accumulator rows are keys, columns queries
+            rowstat_update(acc, c, m_run[qb], l_run[qb]);
+        }
+    };
+    for (int t = wave; t < count; t += 2 * W) {
+        step(t, lds_a[wave], lds_b[wave]);
+        if (t + W < count) step(t + W, lds_b[wave], lds_a[wave]);
+    }
+    // lanes l and l+32 hold the two halves of a row's keys; then the waves are combined
+#pragma unroll
+    for (int qb = 0; qb < NB; ++qb) {
+        const float m_o = __shfl_xor(m_run[qb], 32, WAVE), l_o = __shfl_xor(l_run[qb], 32, WAVE);
+        const float m = fmaxf(m_run[qb], m_o);
+        const float l = l_run[qb] * __builtin_amdgcn_exp2f((m_run[qb] - m) * c) + l_o * __builtin_amdgcn_exp2f((m_o - m) * c);
+        if (lane < 32) { part_m[wave][32 * qb + lane] = m; part_l[wave][32 * qb + lane] = l; }
+    }
+    __syncthreads();
+    const int q = q0 + threadIdx.x;
+    if (threadIdx.x < ROWS && q < n_pad) {
+        float m = part_m[0][threadIdx.x];
+#pragma unroll
+        for (int w = 1; w < W; ++w) m = fmaxf(m, part_m[w][threadIdx.x]);
+        float l = 0.f;
+#pragma unroll
+        for (int w = 0; w < W; ++w) l += part_l[w][threadIdx.x] * __builtin_amdgcn_exp2f((part_m[w][threadIdx.x] - m) * c);
+        lse[(size_t)qslice * n_pad + q] = q < n ? (m * c + __log2f(l)) * out_scale : pad;
+    }
+}
+
+template <typename T, int W>
+__global__ __launch_bounds__(W * WAVE, sizeof(T) == 2 && W == 4 ? 2 : 1) void attn_colsum_split_kernel(
+    const T *__restrict__ Q, const T *__restrict__ K, const float *__restrict__ lse, float *__restrict__ mass,
+    float *__restrict__ sim_opt, const int32_t *__restrict__ seq_lens, int n_kvslices, int H, int G, int N, int n_pad, float c)
+{
+    using M = Mma<T>;
+    using S = Stream<T>;
+    constexpr int NB = M::NBLK, KEYS = 32 * NB;
+    __shared__ u32x4 lds_a[W][S::SLOTS], lds_b[W][S::SLOTS];
+    __shared__ __attribute__((aligned(16))) float lse_a[W][32], lse_b[W][32];
+    __shared__ float part_s[W][KEYS];
+
+    const int kvslice = blockIdx.x % n_kvslices;
+    const int tile = blockIdx.x / n_kvslices;                 // tile 0 has the most rows below it
+    const int b = kvslice / H, h = kvslice % H;
+    const int n = clamp_len(seq_lens, b, N);
+    const int k0 = tile * KEYS;
+    float *mass_s = mass + (size_t)kvslice * N;
+    float *sim_s = sim_opt ? sim_opt + (size_t)kvslice * N : nullptr;
+    if (k0 >= n) {                                            // padding only: defined zeros
+        const int j = k0 + threadIdx.x;
+        if (threadIdx.x < KEYS && j < N) {
+            mass_s[j] = 0.f;
+            if (sim_s) sim_s[j] = 0.f;
+        }
+        return;
+    }
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const T *Ks = K + (size_t)kvslice * N * HEAD_DIM;
+
+    // the 32-row query blocks that see these keys, head after head: block u of the list is block
+    // diag0 + u % per_head of head u / per_head; this wave's: wave, wave+W, ...
+    const int diag0 = tile * NB;
+    const int per_head = (n + 31) / 32 - diag0;
+    const int count = per_head * G;
+    int next = wave, next_g = wave / per_head, next_qb = wave % per_head;
+    auto issue_next = [&](u32x4 *stage, float *stage_lse) {
+        if (next < count) {
+            const size_t qslice = ((size_t)b * H + h) * G + next_g;
+            const int row0 = (diag0 + next_qb) * 32;
+            S::issue(Q + qslice * N * HEAD_DIM, row0, n, stage, lane);
+            if (lane < 32)
+                __builtin_amdgcn_global_load_lds((gptr_t)(lse + qslice * n_pad + row0 + lane), (lptr_t)stage_lse, 4, 0, 0);
+        }
+        next += W;
+        next_qb += W;
+        while (next_qb >= per_head) { next_qb -= per_head; ++next_g; }
+    };
+    issue_next(lds_a[wave], lse_a[wave]);
+    u32x4 kf[NB][M::FRAGS];
+#pragma unroll
+    for (int kb = 0; kb < NB; ++kb) load_stationary<T>(Ks, k0 + 32 * kb, n, lane, kf[kb]);
+    if constexpr (sizeof(T) == 2) {
+        if (sim_s) {                                          // the keys are here anyway: wave kb takes block kb's similarities
+#pragma unroll
+            for (int kb = 0; kb < NB; ++kb)
+                if (wave == kb) {
+                    const u32x4 before = load_predecessor<T>(Ks, k0 + 32 * kb, n, lane);
+                    stationary_cosine<T>(k0 + 32 * kb, n, N, lane, kf[kb], before, sim_s);
+                }
+        }
+    }
+    float part[NB][2];
+#pragma unroll
+    for (int kb = 0; kb < NB; ++kb) part[kb][0] = part[kb][1] = 0.f;
+
+    int qb_cur = wave % per_head;                             // query block of the current step, from diag0
+    auto step = [&](const u32x4 *cur, const float *cur_lse, u32x4 *nxt, float *nxt_lse) {
+        wait_own_tile();
+        issue_next(nxt, nxt_lse);
+        u32x4 a[M::FRAGS];
+#pragma unroll
+        for (int f = 0; f < M::FRAGS; ++f) a[f] = S::frag(cur, f, lane);
+        const RowStats L = load_rowstats(cur_lse, 0, lane);
+#pragma unroll
+        for (int kb = 0; kb < NB; ++kb) {
+            if (qb_cur < kb) continue;                        // every query of the block precedes the keys
+            f32x16 acc = stream_scores<T>(a, kf[kb]);
+            if (qb_cur == kb) mask_rows_below_col(acc, lane); // accumulator rows are queries, columns keys
+            colsum_update(acc, L, c, part[kb]);
+        }
+        qb_cur += W;
+        while (qb_cur >= per_head) qb_cur -= per_head;
+    };
+    for (int u = wave; u < count; u += 2 * W) {
+        step(lds_a[wave], lse_a[wave], lds_b[wave], lse_b[wave]);
+        if (u + W < count) step(lds_b[wave], lse_b[wave], lds_a[wave], lse_a[wave]);
+    }
+#pragma unroll
+    for (int kb = 0; kb < NB; ++kb) {
+        const float colsum = part[kb][0] + part[kb][1];
+        const float total = colsum + __shfl_xor(colsum, 32, WAVE);
+        if (lane < 32) part_s[wave][32 * kb + lane] = total;
+    }
+    __syncthreads();
+    const int key = k0 + threadIdx.x;
+    if (threadIdx.x < KEYS && key < N) {
+        float total = 0.f;
+#pragma unroll
+        for (int w = 0; w < W; ++w) total += part_s[w][threadIdx.x];
+        mass_s[key] = key < n ? total : 0.f;
+    }
+}
+
+// ------------------------------------------------------------------------------------------
+// host launchers
+// ------------------------------------------------------------------------------------------
+
+// Waves per workgroup of a split launch; 0: the full kernels are the better choice.
+//   full_wgs  workgroups the full kernel of this pass would launch;  tiles  its 256-row (fp32: 128) tiles per slice
+//   chain     streamed 32-row blocks of the longest split workgroup
+// Measured per pass, full against split kernel, us: 32 slices of 1000 tokens f16 (128 full workgroups) 30 / 14;
+// 8 slices of 4096 (64) 92 / 35, with G = 4 the column sums 337 / 93; one slice of 16384 (32) 490 / 74; 32 slices
+// of 4096 (256) 102 / 96; but 96 of 2000 (384) 77 / 80 and 160 of 2048 (640) 114 / 140.  Below 8 tiles a full
+// workgroup's load is not evened out by pairing, and the split kernels still win at 384 (96 slices of 1000: 35 / 30;
+// 512 of them, slices of 300: 17 / 19).  fp32, where the matrix pipe is sixteen times slower and the latencies hide behind it:
+// 128 workgroups 289 / 168 (8 slices of 4096), 256 workgroups 84 / 108 (64 of 1000).
+// Eight waves instead of four halve the chain but leave one workgroup per compute unit: worth it where all of them
+// are resident in two rounds and the chain is long (8 slices of 1000, G = 4, column sums: 30 with four, 24 with
+// eight; of 4096: 117 and 93; 32 slices of 1000, chain of 32: 15 and 17).
+int attn_split_waves(int dtype, long long full_wgs, int tiles, long long split_wgs, long long chain)
+{
+    if (dtype == KVM_F32) return full_wgs <= 128 ? 4 : 0;
+    if (full_wgs > (tiles >= 8 ? 256 : 384)) return 0;
+    return split_wgs <= 512 && chain >= 64 ? 8 : 4;
+}
+
+template <typename T, int W>
+static void lse_t(const kvm_shape &sh, const void *Q, const void *K, float *lse, int n_pad, float c, float out_scale, float pad,
+                  hipStream_t st)
+{
+    constexpr int ROWS = 32 * Mma<T>::NBLK;
+    const int tiles = (sh.N + ROWS - 1) / ROWS, n_q = sh.B * sh.H_kv * sh.G;
+    hipLaunchKernelGGL((attn_lse_split_kernel<T, W>), dim3((unsigned)((long long)n_q * tiles)), dim3(W * WAVE), 0, st, (const T *)Q,
+                       (const T *)K, lse, sh.seq_lens, n_q, sh.H_kv * sh.G, sh.G, sh.N, n_pad, tiles, c, out_scale, pad);
+}
+
+template <typename T, int W>
+static void colsum_t(const kvm_shape &sh, const void *Q, const void *K, const float *lse, float *mass, float *sim_opt, int n_pad,
+                     float c, hipStream_t st)
+{
+    constexpr int KEYS = 32 * Mma<T>::NBLK;
+    const int tiles = (sh.N + KEYS - 1) / KEYS, n_kv = sh.B * sh.H_kv;
+    hipLaunchKernelGGL((attn_colsum_split_kernel<T, W>), dim3((unsigned)((long long)n_kv * tiles)), dim3(W * WAVE), 0, st, (const T *)Q,
+                       (const T *)K, lse, mass, sizeof(T) == 2 ? sim_opt : nullptr, sh.seq_lens, n_kv, sh.H_kv, sh.G, sh.N, n_pad, c);
+}
+
+void launch_lse_split(int waves, const kvm_shape &sh, const void *Q, const void *K, float *lse, int n_pad, float c, float out_scale,
+                      float pad, hipStream_t st)
+{
+    if (sh.dtype == KVM_F32) lse_t<float, 4>(sh, Q, K, lse, n_pad, c, out_scale, pad, st);
+    else if (sh.dtype == KVM_F16 && waves == 4) lse_t<half_t, 4>(sh, Q, K, lse, n_pad, c, out_scale, pad, st);
+    else if (sh.dtype == KVM_F16) lse_t<half_t, 8>(sh, Q, K, lse, n_pad, c, out_scale, pad, st);
+    else if (waves == 4) lse_t<bf16_t, 4>(sh, Q, K, lse, n_pad, c, out_scale, pad, st);
+    else lse_t<bf16_t, 8>(sh, Q, K, lse, n_pad, c, out_scale, pad, st);
+}
+
+void launch_colsum_split(int waves, const kvm_shape &sh, const void *Q, const void *K, const float *lse, float *mass, float *sim_opt,
+                         int n_pad, float c, hipStream_t st)
+{
+    if (sh.dtype == KVM_F32) colsum_t<float, 4>(sh, Q, K, lse, mass, sim_opt, n_pad, c, st);
+    else if (sh.dtype == KVM_F16 && waves == 4) colsum_t<half_t, 4>(sh, Q, K, lse, mass, sim_opt, n_pad, c, st);
+    else if (sh.dtype == KVM_F16) colsum_t<half_t, 8>(sh, Q, K, lse, mass, sim_opt, n_pad, c, st);
+    else if (waves == 4) colsum_t<bf16_t, 4>(sh, Q, K, lse, mass, sim_opt, n_pad, c, st);
+    else colsum_t<bf16_t, 8>(sh, Q, K, lse, mass, sim_opt, n_pad, c, st);
+}
+
+}  // namespace kvm

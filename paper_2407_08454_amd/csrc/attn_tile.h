@@ -245,5 +245,40 @@ __device__ __forceinline__ void mask_rows_below_col(f32x16 &acc, int lane) {
         if (acc_row(i, lane) < (lane & 31)) acc[i] = -INFINITY;
 }
 
+// pass 1: the online (max, sum) of a row absorbs 16 more scores (-inf = masked)
+__device__ __forceinline__ void rowstat_update(const f32x16 &acc, float c, float &m_run, float &l_run) {
+    const float m_new = fmaxf(m_run, max16(acc));
+    const float mc = m_new * c;
+    float p0 = 0.f, p1 = 0.f;
+#pragma unroll
+    for (int i = 0; i < 16; i += 2) {
+        p0 += __builtin_amdgcn_exp2f(fmaf(acc[i], c, -mc));
+        p1 += __builtin_amdgcn_exp2f(fmaf(acc[i + 1], c, -mc));
+    }
+    // (the difference is taken before the scaling: M_INIT * c - round(M_INIT * c), fused, would be
+    // the rounding error of a huge product instead of zero)
+    l_run = l_run * __builtin_amdgcn_exp2f((m_run - m_new) * c) + (p0 + p1);
+    m_run = m_new;
+}
+
+// pass 2: the row statistics L of a 32-row block of the streamed tile, in the order of a
+// lane's accumulators (accumulator i of lane l is row 8*(i/4) + 4*(l/32) + i%4)
+struct RowStats { f32x4 v[4]; };
+__device__ __forceinline__ RowStats load_rowstats(const float *lse_tile, int blk, int lane) {
+    RowStats L;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) L.v[r] = *reinterpret_cast<const f32x4 *>(&lse_tile[32 * blk + 8 * r + 4 * (lane >> 5)]);
+    return L;
+}
+// part[0..1] += exp2(c * acc - L)
+__device__ __forceinline__ void colsum_update(const f32x16 &acc, const RowStats &L, float c, float *part) {
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        part[0] += __builtin_amdgcn_exp2f(fmaf(acc[4 * r], c, -L.v[r][0]));
+        part[1] += __builtin_amdgcn_exp2f(fmaf(acc[4 * r + 1], c, -L.v[r][1]));
+        part[0] += __builtin_amdgcn_exp2f(fmaf(acc[4 * r + 2], c, -L.v[r][2]));
+        part[1] += __builtin_amdgcn_exp2f(fmaf(acc[4 * r + 3], c, -L.v[r][3]));
+    }
+}
 
 }  // namespace kvm

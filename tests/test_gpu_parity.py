@@ -180,6 +180,59 @@ def test_mass_large_scores_do_not_overflow():
     assert (np.abs(got - want)[big] / want[big]).max() <= gu.TOL
 
 
+@pytest.mark.parametrize("dtype,G,lens,N,copies", [
+    ("f16", 1, [1], 1, 400), ("bf16", 1, [33, 31], 33, 240), ("f32", 1, [65, 32], 65, 80),   # edges of a 32-row block
+    ("f16", 2, [97, 64, 0], 97, 140), ("bf16", 4, [300, 129, 0, 1, 256], 320, 50), ("f32", 4, [300, 129, 0, 1, 256], 320, 20),
+    ("f16", 1, [2100, 1500, 2049], 2100, 35), ("bf16", 4, [600, 257], 600, 70), ("f32", 2, [257, 600], 600, 20),
+    ("f16", 1, [8200, 5000, 513], 8200, 8), ("bf16", 2, [8704, 8193], 8704, 10)])
+def test_mass_small_and_full_launches(dtype, G, lens, N, copies):
+    """A launch that cannot fill the chip goes to the split kernels (four or eight waves share a row tile), a full one
+    to the kernels that stream a tile for 256 rows (512 from 8192 tokens on): the same slices alone and repeated until
+    the launch is full, both against the oracle (up to 2200 tokens) and against each other, with the similarities and
+    from the caller's row statistics too, on rising scores in one slice.  Between the two only the order of the fp32
+    additions differs: N terms, none above the sum, 2^-24 sqrt(N) < 6e-6 of it and 8 times that as the bar."""
+    _say(f"mass, small and full launch: {dtype} G={G} lens={lens} N={N} x{copies}")
+    B = len(lens)
+    Q, K, _ = _slices(23, B, 1, lens, N, 128, G, dtype)
+    q0, k0 = synth.to_f64(Q[:1], dtype).astype(np.float32), synth.to_f64(K[:1], dtype).astype(np.float32)
+    q0[..., 0], k0[..., 0] = 40.0, np.linspace(0.0, 60.0, N, dtype=np.float32)   # no held maximum fits these
+    Q[:1], K[:1] = synth.to_storage(q0, dtype), synth.to_storage(k0, dtype)
+    Qd, Kd = gu.to_dev(Q, dtype), gu.to_dev(K, dtype)
+
+    def run(rep):
+        q, k = Qd.repeat(rep, 1, 1, 1), Kd.repeat(rep, 1, 1, 1)
+        sh = kb.make_shape(k, G, gu.lens_dev(lens * rep))
+        ws = torch.empty(max(kb.kvm_workspace_bytes(sh), 256), dtype=torch.uint8, device="cuda")
+        out = [torch.full((B * rep, 1, N), float("nan"), dtype=torch.float32, device="cuda") for _ in range(3)]
+        kb.kvm_attn_mass_sim(sh, q, k, out[0], out[1], ws)
+        if N <= 2200:
+            kb.kvm_attn_mass_from_lse(sh, q, k, torch.from_numpy(lse).cuda().repeat(rep, 1, 1), out[2], ws)
+        torch.cuda.synchronize()
+        for t in out:                                        # every copy the same bits
+            assert torch.equal(t.view(torch.int32).view(rep, -1), t.view(torch.int32)[:B].view(1, -1).expand(rep, -1))
+        return [t[:B].cpu().numpy() for t in out]
+
+    def close(got, want, tol):
+        big = want > 1e-6                                     # (columns of the rising slice that receive next to nothing)
+        assert np.isfinite(got).all() and (np.abs(got - want)[big] / want[big]).max() <= tol
+        assert not (~big).any() or np.abs(got[~big]).max() <= 2e-6
+
+    if N <= 2200:
+        lse = ref.row_lse(Q, K, dtype, G=G, seq_lens=lens).astype(np.float32)
+        want = ref.attn_mass(Q, K, dtype, G=G, seq_lens=lens)
+    few, full = run(1), run(copies)
+    if N <= 2200:
+        for got in (few[0], full[0], few[2], full[2]):
+            close(got, want, gu.TOL)
+    for b, n in enumerate(lens):
+        assert (few[0][b, :, n:] == 0).all() and (full[0][b, :, n:] == 0).all()
+    # the rising slice's scores reach 200 in units of the exponent: an fp32 rounding of the score is 2^-16 of a term
+    if B > 1:
+        close(full[0][1:], few[0][1:].astype(np.float64), 5e-5)
+    close(full[0], few[0].astype(np.float64), 2e-3)
+    np.testing.assert_allclose(full[1], few[1], atol=2e-6)
+
+
 @pytest.mark.parametrize("dtype,n", [("f16", 100000), ("bf16", 70001), ("f32", 20000), ("f16", 2 ** 22)])
 def test_mass_long_sequence_against_a_closed_form(dtype, n):
     """Too long for the oracle's n^2 loop, so the scores are given a shape whose column sums have
