@@ -283,9 +283,8 @@ kvm_status kvm_identify_sets(const kvm_shape *shape, const kvm_params *params, c
  *               round-to-nearest-even to dtype.
  *   w_opt       out  (B, H_kv, N) float32 or NULL: key weight of every token
  *               (positions not covered by a stored set are not written)
- *   ws          the work plan (first set of every 64-token tile of a slice, and the
- *               slice's sets of more than 512 tokens, which a whole workgroup merges) is
- *               built there before the merge kernels run
+ *   ws          required as before (kvm_workspace_bytes), not written: the merge kernels find
+ *               the sets of their tokens in set_start themselves
  */
 kvm_status kvm_merge(const kvm_shape *shape, const kvm_params *params, const void *K, const void *V,
                      const int32_t *set_start, const int32_t *pivot, const int32_t *n_sets,
@@ -319,20 +318,11 @@ kvm_status kvm_merge_refresh(const kvm_shape *shape, const kvm_params *params, c
 /*
  * kvm_merge for callers that cannot allocate device memory or may not call an allocator
  * where they run: code under HIP graph capture, tight serving loops, harnesses that forbid
- * hipMalloc.  Same arguments, kernels and results as kvm_merge, without the workspace: the
- * work plan (per slice one int32 per 64-token tile, one per possible set of more than 512
- * tokens, and three more) is kept in a
- * buffer built into the library, KVM_MERGE_STATIC_MAX_PLAN_ENTRIES int32 (8 MiB) on every
- * GPU the library has run this call on, held until the process ends.  The call allocates
- * nothing and frees nothing.
+ * hipMalloc.  Same arguments, kernels and results as kvm_merge, without the workspace.  The
+ * call allocates nothing, frees nothing and keeps nothing: calls on different streams and from
+ * different threads may overlap.
  *   - B * H_kv * (ceil(N / 64) + floor(N / 513) + 3) > KVM_MERGE_STATIC_MAX_PLAN_ENTRIES returns
  *     KVM_ERR_WORKSPACE before any launch (use kvm_merge with a workspace then).
- *   - The buffer belongs to the device that is current at the call (the device the tensors
- *     live on); its address is looked up on the first call on that device.
- *   - All calls on one GPU share the one buffer: two calls whose kernels may overlap on
- *     that GPU (different streams, different threads) race on it.  Calls on one stream,
- *     one after the other, are safe; the buffer keeps the last call's plan and needs no
- *     clearing, since every entry that is read is written by the same call first.
  */
 #define KVM_MERGE_STATIC_MAX_PLAN_ENTRIES (1 << 21)
 kvm_status kvm_merge_static(const kvm_shape *shape, const kvm_params *params, const void *K, const void *V,

@@ -304,7 +304,7 @@ def kvm_merge_refresh(shape: KvmShape, params: KvmParams, K, V, prev_set_id, pre
 
 
 def kvm_merge_static(shape: KvmShape, params: KvmParams, K, V, set_start, pivot, n_sets, K_out, V_out, w_opt):
-    """kvm_merge without a workspace: the work plan lives in a buffer built into the library."""
+    """kvm_merge without a workspace."""
     _check_merge_operands(shape, params, K, V, set_start, pivot, n_sets, K_out, V_out, w_opt)
     _check("kvm_merge_static", load_library().kvm_merge_static(
         ctypes.byref(shape), ctypes.byref(params), _ptr(K), _ptr(V), _ptr(set_start), _ptr(pivot), _ptr(n_sets),

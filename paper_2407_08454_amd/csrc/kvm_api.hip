@@ -337,8 +337,7 @@ kvm_status kvm_merge(const kvm_shape *shape, const kvm_params *params, const voi
         set_error("kvm_merge: workspace of %zu bytes needed, %zu given", merge_workspace_bytes(*shape), ws ? ws_bytes : (size_t)0);
         return KVM_ERR_WORKSPACE;
     }
-    return launch_merge(*shape, *params, cap, K, V, set_start, pivot, n_sets, K_out, V_out, w_opt, (int32_t *)ws,
-                        (hipStream_t)stream);
+    return launch_merge(*shape, *params, cap, K, V, set_start, pivot, n_sets, K_out, V_out, w_opt, (hipStream_t)stream);
 }
 
 kvm_status kvm_merge_refresh(const kvm_shape *shape, const kvm_params *params, const void *K, const void *V,

@@ -2,9 +2,8 @@
 // Eq. (5), (6); Algorithm 2).
 //
 // Work is dealt out by tokens, not by sets, because set lengths are very uneven (most sets
-// are conserved singletons, most tokens sit in sets of 17..128): a small planning kernel
-// finds, for every tile of MERGE_TILE tokens, the first set that starts in it; one wave then
-// owns the sets that start inside its tile.  A row of 128 elements is spread over 16 lanes
+// are conserved singletons, most tokens sit in sets of 17..128): one wave owns the sets that
+// start inside its tile of 16 or 32 tokens, and finds the first of them itself.  A row of 128 elements is spread over 16 lanes
 // (8 elements = 16 B each for 16-bit types), so one wave instruction moves four rows.  Per
 // set: one sweep over its keys for the distances to the pivot (sigma), a second sweep (served
 // by L2, the set was just read) that forms the weights and accumulates keys and values in
@@ -13,23 +12,26 @@
 // are copied bit for bit.  HBM traffic: K once, V once, 2 M rows out.
 //
 // Kernels:
-//   merge_plan_kernel   per slice: first set of every 64-token tile, and the list of sets of more
-//                       than LONG_SET_MIN tokens
 //   merge_kernel        one wave per tile (merge_one_set per set, runs of singletons copied)
-//   merge_long_kernel   the listed long sets, one 1024-thread workgroup per slice
+//   merge_long_kernel   the sets of more than LONG_SET_MIN tokens, one 1024-thread workgroup per slice
 //   refresh_kernel      decode time: compares the new maps with the previous ones, moves the rows of
 //                       unchanged sets in place and merges the changed sets again
-// and the launcher that keeps the plan in a file-scope device array for callers that cannot
-// bring a workspace (kvm_merge_static).
-#include <mutex>
+#include <limits.h>
 
 #include "kvm_common.h"
 
 namespace kvm {
 
 constexpr int MERGE_BLOCK = 64;          // one wave per workgroup: waves finish independently
-constexpr int MERGE_TILE = 64;           // tokens per wave (its sets are those that start in the tile)
-constexpr int PLAN_BLOCK = 256;
+// Tokens per wave (its sets are those that start in the tile).  A wave merges its sets one after the other, a
+// memory round trip or more for each, so short chains of many waves cover the latency better than long ones;
+// against them stands the look-up of the first set, two or three dependent loads a wave.  Measured, us, with
+// tiles of 64 from a table that a launch of its own filled / 32 / 16: 8 slices of 1000 tokens 27.4 / 16.3 /
+// 14.1; 64 of 4096 60 / 47 / 44.5; 256 of 1024 in fp32 110 / 106 / 90; 128 of 4096 110 / 92 / 96; 256 of
+// 4096 201 / 180 / 185; 1024 of 4096 628 / 597 / -.  Tiles of 64 with the look-up: 1024 slices of 4096 1-2 % slower
+// than with the table.  Hence 16 up to 2^18 tokens, where the waves fit the chip four times over, 32 beyond.
+constexpr int MERGE_TILE_FEW = 16, MERGE_TILE = 32;
+constexpr long long MERGE_FEW_TOKENS = 1 << 18;
 // Sets of more than LONG_SET_MIN tokens are left to merge_long_kernel, which puts a whole workgroup
 // on each of them: one wave would stream such a set for hundreds of dependent round trips while
 // the rest of the chip has nothing to do (identical keys make one set of a whole slice).
@@ -40,60 +42,46 @@ constexpr int LONG_SET_BLOCK = 1024;
 // four waves per SIMD with 16-row batches beat two waves with 32-row batches.
 template <typename T> struct MergeUnroll { static constexpr int value = 4; };
 
-// int32 entries of a slice's plan: tiles + 1 tile edges, the number of long sets, their indices
-static int merge_plan_stride(int N)
-{
-    const int tiles = (N + MERGE_TILE - 1) / MERGE_TILE;
-    return tiles + 2 + N / (LONG_SET_MIN + 1) + 1;
-}
+// int32 entries of workspace per slice that the callers of a merge bring.  The refresh keeps its list of long
+// sets in the last N / (LONG_SET_MIN + 1) + 2 of them; a full merge needs none, but its entry points go on
+// asking for the same size (kvm_workspace_bytes, the limit of kvm_merge_static).
+static int long_list_offset(int N) { return (N + 63) / 64 + 1; }   // the number of listed sets, their indices after it
+static __host__ __device__ int max_long_sets(int N) { return N / (LONG_SET_MIN + 1) + 1; }
+static int merge_ws_stride(int N) { return long_list_offset(N) + 1 + max_long_sets(N); }
 
 size_t merge_workspace_bytes(const kvm_shape &sh)
 {
-    return (size_t)sh.B * sh.H_kv * merge_plan_stride(sh.N) * sizeof(int32_t);
+    return (size_t)sh.B * sh.H_kv * merge_ws_stride(sh.N) * sizeof(int32_t);
 }
 
 struct MergeArgs {
     const int32_t *set_start, *pivot, *n_sets, *seq_lens;
     float *w_opt;
-    const int32_t *plan;    // (slices, plan_stride): first set starting at or after each of the tiles_per_slice + 1
-                            // tile edges, then the number of long sets of the slice, then their indices
-    int plan_stride;
-    int H, N, cap_rows, tiles_per_slice;
+    const int32_t *long_list;   // NULL (every long set of the maps is merged), or per slice, list_stride entries
+                                // apart: the number of long sets to merge, then their indices
+    int list_stride;
+    int H, N, cap_rows;
+    int tile, tiles_per_slice;  // tokens per wave (merge_kernel)
     int mode;               // MERGE_ADAPTIVE, MERGE_FIXED (uses inv_two_sigma_sq) or MERGE_AVERAGE
     float inv_two_sigma_sq; // 1 / (2 sigma^2) for the fixed-sigma mode
     int value_scale;
 };
 
-// plan[t] = smallest s with set_start[s] >= t * MERGE_TILE (M if there is none), t = 0..tiles;
-// plan[tiles + 1] = number of sets of more than LONG_SET_MIN tokens, their indices after it (in no
-// particular order: each is merged on its own).
-__global__ __launch_bounds__(PLAN_BLOCK) void merge_plan_kernel(const int32_t *__restrict__ set_start,
-                                                                const int32_t *__restrict__ n_sets,
-                                                                const int32_t *__restrict__ seq_lens, int32_t *__restrict__ plan,
-                                                                int H, int N, int cap_rows, int tiles, int plan_stride)
-{
-    __shared__ int n_long;
-    const int slice = blockIdx.x;
-    const int n = clamp_len(seq_lens, slice / H, N);
-    const int M = min(max(n_sets[slice], 0), cap_rows);
-    const int32_t *sst = set_start + (size_t)slice * (cap_rows + 1);
-    int32_t *pl = plan + (size_t)slice * plan_stride;
-    const int max_long = plan_stride - (tiles + 2);
-    if (threadIdx.x == 0) n_long = 0;
-    __syncthreads();
-    for (int s = threadIdx.x; s <= M; s += PLAN_BLOCK) {
-        const int prev = s > 0 ? min(max(sst[s - 1], 0), n) : -1;
-        const int t_lo = prev < 0 ? 0 : prev / MERGE_TILE + 1;
-        const int here = min(max(sst[s], 0), n);              // (set_start has an entry for s = M too: the end of the last stored set)
-        const int t_hi = s < M ? min(here / MERGE_TILE, tiles) : tiles;
-        for (int t = t_lo; t <= t_hi; ++t) pl[t] = s;
-        if (s > 0 && here - prev > LONG_SET_MIN) {               // set s-1 = [prev, here)
-            const int k = atomicAdd(&n_long, 1);
-            if (k < max_long) pl[tiles + 2 + k] = s - 1;       // (with consistent maps there is always room)
-        }
+// Smallest s in [0, M] with set_start[s] >= edge (M if there is none), by one wave: 64 probes of the
+// remaining range a round, so two dependent loads up to 4096 sets and three up to 262144.  The starts of
+// consistent maps ascend; for any other maps the result is some value in [0, M].
+__device__ __forceinline__ int first_set_at(const int32_t *sst, int M, int edge, int lane) {
+    int lo = 0, len = M;                                     // the result lies in [lo, lo + len]
+    while (len > 0) {
+        const int step = (len + WAVE - 1) / WAVE;
+        const int at = lane * step;
+        const int below = __popcll(__ballot(at < len && sst[lo + min(at, len - 1)] < edge));
+        if (below == 0) break;
+        const int skip = (below - 1) * step + 1;             // <= len: probe below - 1 lies inside the range
+        lo += skip;
+        len = min(step - 1, len - skip);
     }
-    __syncthreads();
-    if (threadIdx.x == 0) pl[tiles + 1] = min(n_long, max_long);
+    return lo;
 }
 
 // Squared distance of 8 elements, summed over the 16 lanes of the row.
@@ -232,17 +220,16 @@ __global__ __launch_bounds__(MERGE_BLOCK) void merge_kernel(const T *__restrict_
     const int slot = lane >> 4;          // which of the four rows of an instruction
     const int c = lane & 15;             // which 8-element chunk of the row
     const int n = clamp_len(a.seq_lens, slice / a.H, a.N);
-    if (tile * MERGE_TILE >= n) return;
+    const int edge = tile * a.tile;
+    if (edge >= n) return;
     const int M = min(max(a.n_sets[slice], 0), a.cap_rows);
-    // sets [s_lo, s_hi) start inside this tile (entries are clamped: the plan may hold garbage
-    // when the maps are inconsistent)
-    const int32_t *pl = a.plan + (size_t)slice * a.plan_stride + tile;
-    const int s_lo = min(max(pl[0], 0), M);
-    const int s_hi = min(max(pl[1], s_lo), M);
-    const int cnt = min(s_hi - s_lo, MERGE_TILE);
+    const int32_t *sst = a.set_start + (size_t)slice * (a.cap_rows + 1);
+    // cnt sets from s_lo on start inside this tile
+    const int s_lo = first_set_at(sst, M, edge, lane);
+    const int start_raw = lane < a.tile && s_lo + lane < M ? sst[s_lo + lane] : INT_MAX;
+    const int cnt = __builtin_ctzll(~__ballot(start_raw < edge + a.tile));  // (a.tile < 64: the ballot has a zero bit)
     if (cnt == 0) return;
 
-    const int32_t *sst = a.set_start + (size_t)slice * (a.cap_rows + 1);
     const int32_t *piv = a.pivot + (size_t)slice * a.cap_rows;
     const T *Ks = K + (size_t)slice * a.N * HEAD_DIM;
     const T *Vs = V + (size_t)slice * a.N * HEAD_DIM;
@@ -250,11 +237,9 @@ __global__ __launch_bounds__(MERGE_BLOCK) void merge_kernel(const T *__restrict_
     T *Vo = V_out + (size_t)slice * a.cap_rows * HEAD_DIM;
     float *wo = WITH_W ? a.w_opt + (size_t)slice * a.N : nullptr;
 
-    // lane i holds the first token of set s_lo+i and its pivot; entries are clamped into the
-    // slice so that inconsistent maps cannot address outside K and V
     int my_start = n, my_piv = 0;
     if (lane < cnt) {
-        my_start = min(max(sst[s_lo + lane], 0), n);
+        my_start = min(max(start_raw, 0), n);
         my_piv = piv[s_lo + lane];
     }
     const int t_end = min(max(sst[s_lo + cnt], 0), n);               // end of the wave's last set
@@ -308,6 +293,8 @@ __global__ __launch_bounds__(MERGE_BLOCK) void merge_kernel(const T *__restrict_
 // 1024-thread workgroup per slice: group g takes the set's rows g, g + 64, ... (four of them in
 // flight), the distance sum and then the weighted sums are added up across the groups through
 // LDS.  Same arithmetic per row as merge_kernel; only the order of the fp32 additions differs.
+// The workgroup looks the long sets up in the maps itself (or takes the refresh's list), 1024 sets
+// at a time, in no particular order: each is merged on its own.
 template <typename T, bool WITH_W, int MODE>
 __global__ __launch_bounds__(LONG_SET_BLOCK) void merge_long_kernel(const T *__restrict__ K, const T *__restrict__ V,
                                                                 T *__restrict__ K_out, T *__restrict__ V_out, MergeArgs a)
@@ -318,10 +305,8 @@ __global__ __launch_bounds__(LONG_SET_BLOCK) void merge_long_kernel(const T *__r
     constexpr int GROUPS = LONG_SET_BLOCK / 16, WAVES = LONG_SET_BLOCK / WAVE;
     __shared__ float red[WAVES][16][17];                     // per wave and chunk lane: 8 key sums, 8 value sums, weight sum
     __shared__ float red1[WAVES];
+    __shared__ int found[LONG_SET_BLOCK], n_found[2];        // (two counters in turn: one is cleared while the other is read)
     const int slice = blockIdx.x;
-    const int32_t *pl = a.plan + (size_t)slice * a.plan_stride + a.tiles_per_slice + 1;
-    const int n_long = min(max(pl[0], 0), a.plan_stride - (a.tiles_per_slice + 2));
-    if (n_long == 0) return;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int c = tid & 15, group = tid >> 4;
     const int n = clamp_len(a.seq_lens, slice / a.H, a.N);
@@ -334,12 +319,26 @@ __global__ __launch_bounds__(LONG_SET_BLOCK) void merge_long_kernel(const T *__r
     T *Vo = V_out + (size_t)slice * a.cap_rows * HEAD_DIM;
     float *wo = WITH_W ? a.w_opt + (size_t)slice * a.N : nullptr;
 
+    const int32_t *pl = a.long_list ? a.long_list + (size_t)slice * a.list_stride : nullptr;
+    int left = max_long_sets(a.N);                            // consistent maps never have more
+    const int candidates = pl ? min(max(pl[0], 0), left) : M;
+    if (candidates == 0) return;
+    if (tid < 2) n_found[tid] = 0;
+    __syncthreads();
+    for (int first = 0, turn = 0; first < candidates; first += LONG_SET_BLOCK, turn ^= 1) {
+    if (first + tid < candidates) {
+        const int s = pl ? pl[1 + first + tid] : first + tid;
+        if (s >= 0 && s < M && min(max(sst[s + 1], 0), n) - min(max(sst[s], 0), n) > LONG_SET_MIN)
+            found[atomicAdd(&n_found[turn], 1)] = s;
+    }
+    __syncthreads();
+    const int n_long = min(n_found[turn], left);
+    left -= n_long;
+    if (tid == 0) n_found[turn ^ 1] = 0;                      // read last before this turn's barrier above
     for (int k = 0; k < n_long; ++k) {
-        const int s = pl[1 + k];
-        if (s < 0 || s >= M) continue;                        // (the same for the whole workgroup)
+        const int s = found[k];
         const int lo = min(max(sst[s], 0), n), hi = min(max(sst[s + 1], 0), n);
         const int m = hi - lo;
-        if (m <= LONG_SET_MIN) continue;
         const int p = min(max(piv[s], lo), hi - 1);
         float kp[8];
         E::to_float(E::load(Ks + (size_t)p * HEAD_DIM, c), kp);
@@ -431,6 +430,8 @@ __global__ __launch_bounds__(LONG_SET_BLOCK) void merge_long_kernel(const T *__r
             for (int row = lo + group; row < hi; row += GROUPS) wo[row] *= inv_g;
         }
     }
+    if (first + LONG_SET_BLOCK < candidates) __syncthreads();  // found is filled again; the cleared counter is seen
+    }
 }
 
 template <typename T>
@@ -474,7 +475,7 @@ static void launch_merge_long_t(const kvm_shape &sh, const void *K, const void *
 
 kvm_status launch_merge(const kvm_shape &sh, const kvm_params &pr, int cap_rows, const void *K, const void *V,
                         const int32_t *set_start, const int32_t *pivot, const int32_t *n_sets, void *K_out,
-                        void *V_out, float *w_opt, int32_t *plan, hipStream_t st)
+                        void *V_out, float *w_opt, hipStream_t st)
 {
     if ((long long)sh.B * sh.H_kv == 0 || cap_rows == 0 || sh.N == 0) return KVM_OK;
     MergeArgs a;
@@ -483,22 +484,16 @@ kvm_status launch_merge(const kvm_shape &sh, const kvm_params &pr, int cap_rows,
     a.n_sets = n_sets;
     a.seq_lens = sh.seq_lens;
     a.w_opt = w_opt;
-    a.plan = plan;
+    a.long_list = nullptr;
     a.H = sh.H_kv;
     a.N = sh.N;
     a.cap_rows = cap_rows;
-    a.tiles_per_slice = (sh.N + MERGE_TILE - 1) / MERGE_TILE;
-    a.plan_stride = merge_plan_stride(sh.N);
+    a.tile = (long long)sh.B * sh.H_kv * sh.N <= MERGE_FEW_TOKENS ? MERGE_TILE_FEW : MERGE_TILE;
+    a.tiles_per_slice = (sh.N + a.tile - 1) / a.tile;
+    a.list_stride = 0;
     a.mode = pr.weights == KVM_WEIGHTS_AVERAGE ? MERGE_AVERAGE : (pr.sigma_mode == KVM_SIGMA_FIXED ? MERGE_FIXED : MERGE_ADAPTIVE);
     a.inv_two_sigma_sq = a.mode == MERGE_FIXED ? 1.f / (2.f * pr.sigma * pr.sigma) : 0.f;
     a.value_scale = pr.value_scale_by_set_size;
-    {
-        ProfScope prof("merge_plan_kernel", st);
-        hipLaunchKernelGGL(merge_plan_kernel, dim3((unsigned)(sh.B * sh.H_kv)), dim3(PLAN_BLOCK), 0, st, set_start, n_sets,
-                           sh.seq_lens, plan, sh.H_kv, sh.N, cap_rows, a.tiles_per_slice, a.plan_stride);
-        kvm_status rc = check_launch("merge_plan_kernel");
-        if (rc != KVM_OK) return rc;
-    }
     switch (sh.dtype) {
     case KVM_F32: launch_merge_t<float>(sh, K, V, K_out, V_out, a, st); break;
     case KVM_F16: launch_merge_t<half_t>(sh, K, V, K_out, V_out, a, st); break;
@@ -538,7 +533,7 @@ struct RefreshArgs {
     const int32_t *prev_set_id, *prev_set_start, *prev_pivot, *prev_n_sets;
     int32_t *src;          // (slices, cap_rows)
     int32_t *lists;        // (slices, cap_rows + 1): number of short sets to merge again, then their indices
-    int32_t *plan;         // what MergeArgs::plan points to; only the long-set part is filled
+    int32_t *long_list;    // what MergeArgs::long_list points to
     int32_t *n_changed;    // (slices) or NULL: sets merged again
 };
 
@@ -567,8 +562,8 @@ __global__ __launch_bounds__(REFRESH_BLOCK, 4) void refresh_kernel(const T *__re
     const int32_t *osid = r.prev_set_id + (size_t)slice * a.N;
     int32_t *src = r.src + (size_t)slice * a.cap_rows;
     int32_t *list = r.lists + (size_t)slice * (a.cap_rows + 1);
-    int32_t *pl = r.plan + (size_t)slice * a.plan_stride + a.tiles_per_slice + 1;
-    const int max_long = a.plan_stride - (a.tiles_per_slice + 2);
+    int32_t *pl = r.long_list + (size_t)slice * a.list_stride;
+    const int max_long = max_long_sets(a.N);
     T *Ko = K_out + (size_t)slice * a.cap_rows * HEAD_DIM;
     T *Vo = V_out + (size_t)slice * a.cap_rows * HEAD_DIM;
 
@@ -689,7 +684,7 @@ static kvm_status launch_refresh_t(const kvm_shape &sh, const void *K, const voi
 
 size_t merge_refresh_workspace_bytes(const kvm_shape &sh, int cap_rows)
 {
-    return (size_t)sh.B * sh.H_kv * ((size_t)merge_plan_stride(sh.N) + 2 * (size_t)cap_rows + 1) * sizeof(int32_t);
+    return (size_t)sh.B * sh.H_kv * ((size_t)merge_ws_stride(sh.N) + 2 * (size_t)cap_rows + 1) * sizeof(int32_t);
 }
 
 kvm_status launch_merge_refresh(const kvm_shape &sh, const kvm_params &pr, int cap_rows, const void *K, const void *V,
@@ -699,15 +694,15 @@ kvm_status launch_merge_refresh(const kvm_shape &sh, const kvm_params &pr, int c
 {
     const size_t slices = (size_t)sh.B * sh.H_kv;
     if (slices == 0 || cap_rows == 0 || sh.N == 0) return KVM_OK;
-    const int plan_stride = merge_plan_stride(sh.N);
+    const int stride = merge_ws_stride(sh.N);
     RefreshArgs ra;
     ra.prev_set_id = prev_set_id;
     ra.prev_set_start = prev_set_start;
     ra.prev_pivot = prev_pivot;
     ra.prev_n_sets = prev_n_sets;
-    ra.src = ws + slices * plan_stride;
+    ra.src = ws + slices * stride;
     ra.lists = ra.src + slices * cap_rows;
-    ra.plan = ws;
+    ra.long_list = ws + long_list_offset(sh.N);
     ra.n_changed = n_changed;
     MergeArgs ma;
     ma.set_start = set_start;
@@ -715,12 +710,12 @@ kvm_status launch_merge_refresh(const kvm_shape &sh, const kvm_params &pr, int c
     ma.n_sets = n_sets;
     ma.seq_lens = sh.seq_lens;
     ma.w_opt = nullptr;
-    ma.plan = ws;
-    ma.plan_stride = plan_stride;
+    ma.long_list = ra.long_list;
+    ma.list_stride = stride;
     ma.H = sh.H_kv;
     ma.N = sh.N;
     ma.cap_rows = cap_rows;
-    ma.tiles_per_slice = (sh.N + MERGE_TILE - 1) / MERGE_TILE;
+    ma.tile = ma.tiles_per_slice = 0;                        // (merge_kernel is not launched)
     ma.mode = pr.weights == KVM_WEIGHTS_AVERAGE ? MERGE_AVERAGE : (pr.sigma_mode == KVM_SIGMA_FIXED ? MERGE_FIXED : MERGE_ADAPTIVE);
     ma.inv_two_sigma_sq = ma.mode == MERGE_FIXED ? 1.f / (2.f * pr.sigma * pr.sigma) : 0.f;
     ma.value_scale = pr.value_scale_by_set_size;
@@ -732,40 +727,11 @@ kvm_status launch_merge_refresh(const kvm_shape &sh, const kvm_params &pr, int c
 }
 
 // ------------------------------------------------------------------------------------------
-// The merge for callers that cannot allocate: the work plan goes into a file-scope device
-// array instead of a caller-supplied workspace.  Every GPU the library runs on holds its own
-// copy of the array at its own address; the address is looked up once per device, with that
-// device current, and host code only ever uses the looked-up pointer.
+// The merge for callers that cannot bring a workspace.  Nothing is kept between its kernels; the size
+// limit of the entry point is part of its contract.
 // ------------------------------------------------------------------------------------------
 
 constexpr size_t STATIC_PLAN_INTS = (size_t)KVM_MERGE_STATIC_MAX_PLAN_ENTRIES;
-static __device__ __align__(256) int32_t scratch[STATIC_PLAN_INTS];
-
-constexpr int STATIC_MAX_DEVICES = 64;
-static std::mutex g_scratch_mutex;
-static int32_t *g_scratch_ptr[STATIC_MAX_DEVICES];           // per device; nullptr = not looked up yet
-
-static kvm_status static_plan_ptr(int32_t **out)
-{
-    int dev = -1;
-    hipError_t e = hipGetDevice(&dev);
-    if (e != hipSuccess || dev < 0 || dev >= STATIC_MAX_DEVICES) {
-        set_error("kvm_merge_static: no usable current device (%s)", e != hipSuccess ? hipGetErrorString(e) : "index out of range");
-        return KVM_ERR_LAUNCH;
-    }
-    std::lock_guard<std::mutex> lock(g_scratch_mutex);
-    if (!g_scratch_ptr[dev]) {
-        void *p = nullptr;
-        e = hipGetSymbolAddress(&p, HIP_SYMBOL(scratch));
-        if (e != hipSuccess || !p) {
-            set_error("kvm_merge_static: hipGetSymbolAddress failed on device %d: %s", dev, hipGetErrorString(e));
-            return KVM_ERR_LAUNCH;
-        }
-        g_scratch_ptr[dev] = static_cast<int32_t *>(p);
-    }
-    *out = g_scratch_ptr[dev];
-    return KVM_OK;
-}
 
 kvm_status launch_merge_static(const kvm_shape &sh, const kvm_params &pr, int cap_rows, const void *K, const void *V,
                                const int32_t *set_start, const int32_t *pivot, const int32_t *n_sets, void *K_out,
@@ -773,16 +739,11 @@ kvm_status launch_merge_static(const kvm_shape &sh, const kvm_params &pr, int ca
 {
     const size_t need = merge_workspace_bytes(sh) / sizeof(int32_t);
     if (need > STATIC_PLAN_INTS) {
-        set_error("kvm_merge_static: the work plan needs %zu entries (B*H_kv*(ceil(N/64)+floor(N/513)+3)), the built-in buffer holds %zu; "
+        set_error("kvm_merge_static: the shape counts %zu (B*H_kv*(ceil(N/64)+floor(N/513)+3)), at most %zu is taken; "
                   "use kvm_merge with a workspace", need, STATIC_PLAN_INTS);
         return KVM_ERR_WORKSPACE;
     }
-    int32_t *plan = nullptr;
-    kvm_status rc = static_plan_ptr(&plan);
-    if (rc != KVM_OK) return rc;
-    // every plan entry a merge wave reads is written by the plan kernel of the same call (or
-    // clamped when the maps are inconsistent), so nothing has to be cleared between calls
-    return launch_merge(sh, pr, cap_rows, K, V, set_start, pivot, n_sets, K_out, V_out, w_opt, plan, st);
+    return launch_merge(sh, pr, cap_rows, K, V, set_start, pivot, n_sets, K_out, V_out, w_opt, st);
 }
 
 }  // namespace kvm

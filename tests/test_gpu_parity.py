@@ -800,6 +800,62 @@ def test_merge_sets_around_the_length_a_workgroup_takes_over(dtype, mode):
     _check_merge(K, V, dtype, o, *res, f"long sets {dtype} {mode}")
 
 
+@pytest.mark.parametrize("sets", [1, 64, 65, 4096, 4097, 8000])
+def test_merge_finds_the_sets_of_a_tile(sets):
+    """A wave looks for the first set of its tile with 64 probes a round: set counts at the edges of one,
+    two and three rounds, set sizes of 1 and 2 with a long set first and one last (the long sets are
+    looked up 1024 at a time, so the last one is found in a later turn), a ragged second row."""
+    rng = np.random.default_rng(sets)
+    sizes = [rng.integers(1, 3, sets), rng.integers(1, 2, sets)]
+    for s in sizes:
+        s[0] += 520
+        s[-1] += 700
+    lens = [int(s.sum()) for s in sizes]
+    n = max(lens)
+    _say(f"merge: {sets} sets over {lens} tokens")
+    Q, K, V = _slices(35, 2, 1, lens, n, 128, 1, "f16", rho=0.97)
+    params = kb.make_params(1.0, 0.0, 0.0, enforce_budget=False)
+    st = np.zeros((2, 1, n + 1), np.int32)
+    pv = np.full((2, 1, n), -1, np.int32)
+    for b in range(2):
+        starts = np.concatenate([[0], np.cumsum(sizes[b])])
+        st[b, 0, :sets + 1], st[b, 0, sets + 1:] = starts, lens[b]
+        pv[b, 0, :sets] = starts[:-1] + rng.integers(0, sizes[b])
+    o = dict(set_start=st, pivot=pv, n_sets=np.full((2, 1), sets, np.int32), cap_rows=n)
+    res = _merge_both(K, V, "f16", params, o, lens)
+    _check_merge(K, V, "f16", o, *res, f"{sets} sets")
+
+
+@pytest.mark.parametrize("slices", [64, 65])
+def test_merge_gives_the_same_bits_for_every_tile_size(slices):
+    """Tiles of 16 tokens up to 2^18 tokens, of 32 beyond: slices of a launch on either side of the line have to
+    give the bits of the same slice merged alone (16-token tiles)."""
+    n = 4096
+    _say(f"merge: {slices} slices of {n} tokens")
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(slices)
+    K = torch.randn((1, slices, n, 128), generator=gen, device="cuda").to(torch.float16)
+    K[:, :, 1::3] = K[:, :, 0::3][:, :, :K[:, :, 1::3].shape[2]]
+    K[:, :, 1000:1700] = K[:, :, 1000:1001]                 # one long set
+    V = torch.randn((1, slices, n, 128), generator=gen, device="cuda").to(torch.float16)
+    params = kb.make_params(1.0, 0.1, 0.1, enforce_budget=False)
+    sh = kb.make_shape(K, 1, None)
+    buf = kb.Buffers(sh, params, "cuda", torch.float16)
+    buf.mass.copy_(torch.rand((1, slices, n), generator=gen, device="cuda"))
+    kb.kvm_identify_sets(sh, params, K, buf.mass, buf.set_id, buf.set_start, buf.pivot, buf.n_sets, None, buf.status, buf.ws)
+    buf.K_out.fill_(7.0)
+    buf.V_out.fill_(7.0)
+    kb.kvm_merge(sh, params, K, V, buf.set_start, buf.pivot, buf.n_sets, buf.K_out, buf.V_out, None, buf.ws)
+    for h in (0, slices // 2, slices - 1):
+        one = slice(h, h + 1)
+        Ki, Vi = K[:, one].contiguous(), V[:, one].contiguous()
+        Ko, Vo = torch.full_like(buf.K_out[:, one], 7.0), torch.full_like(buf.V_out[:, one], 7.0)
+        maps = [t[:, one].contiguous() for t in (buf.set_start, buf.pivot, buf.n_sets)]
+        kb.kvm_merge(kb.make_shape(Ki, 1, None), params, Ki, Vi, *maps, Ko, Vo, None, buf.ws)
+        assert torch.equal(Ko.view(torch.int16), buf.K_out[:, one].contiguous().view(torch.int16))
+        assert torch.equal(Vo.view(torch.int16), buf.V_out[:, one].contiguous().view(torch.int16))
+
+
 def test_merge_tolerates_inconsistent_maps():
     n = 256
     _say("merge: out-of-range map entries are clamped, nothing faults")

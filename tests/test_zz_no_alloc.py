@@ -1,7 +1,6 @@
 """kvm_merge_static -- the merge for callers that cannot allocate -- against kvm_merge, through
 the C ABI.  Both run the same kernels, so the outputs have to be bit-identical; the call is
-made twice in a row, the second time on a smaller input, because the built-in buffer keeps
-the first call's plan.  This file is collected last: a failure here must not hide others."""
+made twice in a row, the second time on a smaller input: nothing may be left of the first.  This file is collected last: a failure here must not hide others."""
 import numpy as np
 import pytest
 import torch
