@@ -739,7 +739,7 @@ kvm_status launch_merge_static(const kvm_shape &sh, const kvm_params &pr, int ca
 {
     const size_t need = merge_workspace_bytes(sh) / sizeof(int32_t);
     if (need > STATIC_PLAN_INTS) {
-        set_error("kvm_merge_static: the shape counts %zu (B*H_kv*(ceil(N/64)+floor(N/513)+3)), at most %zu is taken; "
+        set_error("kvm_merge_static: the work plan needs %zu entries (B*H_kv*(ceil(N/64)+floor(N/513)+3)), the built-in buffer holds %zu; "
                   "use kvm_merge with a workspace", need, STATIC_PLAN_INTS);
         return KVM_ERR_WORKSPACE;
     }
