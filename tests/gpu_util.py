@@ -32,6 +32,18 @@ def lens_dev(seq_lens):
     return None if seq_lens is None else torch.as_tensor(np.asarray(seq_lens, dtype=np.int32)).cuda()
 
 
+def kernels_of(call):
+    """Names of the library's kernels that `call` launches."""
+    torch.cuda.synchronize()
+    kb.kvm_profile_enable(64)
+    try:
+        call()
+        torch.cuda.synchronize()
+        return set(kb.kvm_profile_collect())
+    finally:
+        kb.kvm_profile_disable()
+
+
 def gpu_mass(Q, K, dtype, G=1, seq_lens=None):
     Qd, Kd = to_dev(Q, dtype), to_dev(K, dtype)
     sl = lens_dev(seq_lens)

@@ -233,6 +233,30 @@ def test_mass_small_and_full_launches(dtype, G, lens, N, copies):
     np.testing.assert_allclose(full[1], few[1], atol=2e-6)
 
 
+@pytest.mark.parametrize("dtype,N,G", [("f16", 97, 2), ("bf16", 200, 1), ("f32", 70, 2)])
+def test_mass_split_launch_of_every_slice_count(dtype, N, G):
+    """The split kernels deal the slices out as one, two, four and whole groups of eight: every number of slices up to
+    17 has to give every slice the bits it gets alone (no slice left out or taken twice: the outputs start as NaN)."""
+    _say(f"mass, 1 to 17 slices: {dtype} N={N} G={G}")
+    lens = [N - 3 * (b % 5) for b in range(17)]
+    Q, K, _ = _slices(29, 17, 1, lens, N, 128, G, dtype)
+    Qd, Kd = gu.to_dev(Q, dtype), gu.to_dev(K, dtype)
+
+    def run(rows):
+        q, k = Qd[rows].contiguous(), Kd[rows].contiguous()
+        sh = kb.make_shape(k, G, gu.lens_dev(lens[rows]))
+        ws = torch.full((max(kb.kvm_workspace_bytes(sh), 256),), 255, dtype=torch.uint8, device="cuda")
+        out = torch.full((2, len(lens[rows]), N), float("nan"), dtype=torch.float32, device="cuda")
+        names = gu.kernels_of(lambda: kb.kvm_attn_mass_sim(sh, q, k, out[0].view(-1, 1, N), out[1].view(-1, 1, N), ws))
+        assert {"attn_lse_split_kernel", "attn_colsum_split_kernel"} <= names
+        return out.view(torch.int32)
+
+    alone = torch.cat([run(slice(b, b + 1)) for b in range(17)], dim=1)
+    for count in range(2, 18):
+        assert torch.equal(run(slice(0, count)), alone[:, :count]), f"{count} slices"
+    gu.assert_mass_close(alone[0].view(torch.float32).cpu().numpy()[:, None], ref.attn_mass(Q, K, dtype, G=G, seq_lens=lens), lens, N)
+
+
 @pytest.mark.parametrize("dtype,n", [("f16", 100000), ("bf16", 70001), ("f32", 20000), ("f16", 2 ** 22)])
 def test_mass_long_sequence_against_a_closed_form(dtype, n):
     """Too long for the oracle's n^2 loop, so the scores are given a shape whose column sums have
