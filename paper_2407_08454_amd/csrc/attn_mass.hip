@@ -453,7 +453,7 @@ __global__ void __launch_bounds__(256) lse_import_kernel(const float *__restrict
 
 void launch_colsum_pipe(const kvm_shape &sh, const void *Q, const void *K, const float *neg_lse, float *mass, float *sim_opt,
                         int n_pad, float c, hipStream_t st);
-int attn_split_waves(int dtype, long long full_wgs, int tiles, long long split_wgs, long long chain);
+int attn_split_waves(bool colsum, int dtype, int N, long long slices, int heads, int tiles, long long full_wgs);
 void launch_lse_split(int waves, const kvm_shape &sh, const void *Q, const void *K, float *lse, int n_pad, float c, float out_scale,
                       float pad, hipStream_t st);
 void launch_colsum_split(int waves, const kvm_shape &sh, const void *Q, const void *K, const float *lse, float *mass, float *sim_opt,
@@ -478,9 +478,8 @@ static kvm_status launch_t(const kvm_shape &sh, const void *Q, const void *K, co
     // nothing overlaps, costs more than the even load gains)
     const int wgs = tiles >= 8 ? (tiles + 1) / 2 : tiles;
     // launches too small to fill the chip are split four ways (attn_split.hip)
-    const long long split_tiles = (sh.N + 32 * Mma<T>::NBLK - 1) / (32 * Mma<T>::NBLK), chain = (sh.N + 31) / 32;
-    const int split_lse = attn_split_waves(sh.dtype, (long long)n_q * wgs, tiles, n_q * split_tiles, chain);
-    const int split_colsum = attn_split_waves(sh.dtype, (long long)n_kv * wgs, tiles, n_kv * split_tiles, chain * sh.G);
+    const int split_lse = attn_split_waves(false, sh.dtype, sh.N, n_q, 1, tiles, (long long)n_q * wgs);
+    const int split_colsum = attn_split_waves(true, sh.dtype, sh.N, n_kv, sh.G, tiles, (long long)n_kv * wgs);
     const bool pipe = Mma<T>::NBLK == 2 && sh.N >= COLSUM_PIPE_MIN_N && !split_colsum;
     // how the row statistic is stored for the second pass: L_t, or -L_t / c for attn_colsum_pipe_kernel
     const float out_scale = pipe ? -1.f / c : 1.f, pad = pipe ? -INFINITY : INFINITY;

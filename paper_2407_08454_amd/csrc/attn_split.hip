@@ -12,8 +12,10 @@
 // in turn, so four times as many workgroups run and each wave's chain is 1/W as long.  Every wave has
 // its own two LDS stages and waits for nobody until the partial results are combined through LDS
 // in the order of the waves (deterministic).  Each wave reads its tiles for 64 stationary rows only,
-// where a workgroup of attn_mass.hip reads them once for 256: four times the L2 traffic, which is why
-// full launches stay with those kernels (the rule is at attn_split_waves).
+// where a workgroup of attn_mass.hip reads them once for 256 (attn_pipe.hip: 512): four (eight) times the L2
+// traffic, which is why full launches stay with those kernels (the rule is at attn_split_waves).
+#include <algorithm>
+
 #include "attn_tile.h"
 
 namespace kvm {
@@ -264,22 +266,33 @@ __global__ __launch_bounds__(W * WAVE, sizeof(T) == 2 && W == 4 ? 2 : 1) void at
 // ------------------------------------------------------------------------------------------
 
 // Waves per workgroup of a split launch; 0: the full kernels are the better choice.
-//   full_wgs  workgroups the full kernel of this pass would launch;  tiles  its 256-row (fp32: 128) tiles per slice
-//   chain     streamed 32-row blocks of the longest split workgroup
-// Measured per pass, full against split kernel, us: 32 slices of 1000 tokens f16 (128 full workgroups) 30 / 14;
-// 8 slices of 4096 (64) 92 / 35, with G = 4 the column sums 337 / 93; one slice of 16384 (32) 490 / 74; 32 slices
-// of 4096 (256) 102 / 96; but 96 of 2000 (384) 77 / 80 and 160 of 2048 (640) 114 / 140.  Below 8 tiles a full
-// workgroup's load is not evened out by pairing, and the split kernels still win at 384 (96 slices of 1000: 35 / 30;
-// 512 of them, slices of 300: 17 / 19).  fp32, where the matrix pipe is sixteen times slower and the latencies hide behind it:
-// 128 workgroups 289 / 168 (8 slices of 4096), 256 workgroups 84 / 108 (64 of 1000).
+//   N, slices  stationary rows per slice, slices of the launch;  heads  streamed sequences per slice (G in the column sums, else 1)
+//   tiles      256-row (fp32: 128) tiles per slice of the full kernel;  full_wgs  workgroups it would launch
+// Measured per pass, full against split kernel, us: 32 slices of 1000 tokens f16 (128 full workgroups) 26 / 14; 8 slices of
+// 4096 (64) 91 / 32, with G = 4 the column sums 341 / 92; 32 slices of 4096 (256) 96 / 92, 51 of 2500 (255) 84 / 64; one slice of
+// 16384 (32) 502 / 79, of 131072 (256) 12700 / 3100, 8 of 16384 with G = 4 (256) 2010 / 1220, although the column sums of such
+// lengths have a kernel of 512 keys a workgroup and read every tile eight times as often as that; but 96 of 2000 (384) 77 / 80 and 160 of 2048 (640) 114 / 140.
+// Below 8 tiles a full workgroup's load is not evened out by pairing, and the split kernels still win at 384 (96 slices of
+// 1000: 36 / 29).  In one or two tiles the full kernels' chains are short as well, and the split ones need a chain, heads
+// after each other, to earn their traffic.  G = 1, column sums: 160 slices of 512 22.9 / 21.7, 176 of them 23.1 / 23.4; 128 of 256
+// 11.2 / 8.8, 192 of them 11.3 / 11.7; 256 of 128 8.1 / 8.4, of 64 6.7 / 6.4; both passes: 192 slices of 256 20.2 / 19.5, 256 of
+// them 21.8 / 25.6, 256 of 150 17.1 / 17.3.  G = 2: 256 slices of 256 19.1 / 18.6, 320 of them 23.1 / 24.3, 384 of 200
+// 22.5 / 23.0.  G = 4: 320 slices of 256 34.3 / 34.4, 384 of them 36.1 / 39.5, 384 of 200 34.2 / 31.8.
+// fp32, where the matrix pipe is sixteen times slower and the latencies hide behind it: 128 workgroups 289 / 168 (8 slices
+// of 4096), 256 workgroups 84 / 108 (64 of 1000).
 // Eight waves instead of four halve the chain but leave one workgroup per compute unit: worth it where all of them
 // are resident in two rounds and the chain is long (8 slices of 1000, G = 4, column sums: 30 with four, 24 with
 // eight; of 4096: 117 and 93; 32 slices of 1000, chain of 32: 15 and 17).
-int attn_split_waves(int dtype, long long full_wgs, int tiles, long long split_wgs, long long chain)
+int attn_split_waves(bool colsum, int dtype, int N, long long slices, int heads, int tiles, long long full_wgs)
 {
     if (dtype == KVM_F32) return full_wgs <= 128 ? 4 : 0;
-    if (full_wgs > (tiles >= 8 ? 256 : 384)) return 0;
-    return split_wgs <= 512 && chain >= 64 ? 8 : 4;
+    const int blocks = (N + 31) / 32;                         // streamed 32-row blocks per head
+    int most = tiles >= 8 ? 256 : 384;
+    if (heads == 1 && tiles == 2 && blocks > 14) most = 320;
+    else if (heads == 1 && tiles == 1) most = blocks <= 3 ? 256 : colsum ? 128 : blocks <= 6 ? 256 : 192;
+    else if (tiles == 1) most -= 64 * std::max(0, blocks - (heads < 4 ? 6 : 7));
+    if (full_wgs > most) return 0;
+    return slices * ((blocks + 1) / 2) <= 512 && (long long)blocks * heads >= 64 ? 8 : 4;
 }
 
 template <typename T, int W>

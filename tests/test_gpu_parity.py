@@ -233,6 +233,31 @@ def test_mass_small_and_full_launches(dtype, G, lens, N, copies):
     np.testing.assert_allclose(full[1], few[1], atol=2e-6)
 
 
+# slices of a launch -> does the split kernel take the row statistics, the column sums (else the full kernels do)
+@pytest.mark.parametrize("dtype,N,G,expect", [
+    ("f16", 96, 1, {256: (1, 1), 257: (0, 0)}), ("bf16", 97, 1, {128: (1, 1), 129: (1, 0), 256: (1, 0), 257: (0, 0)}),
+    ("f16", 256, 1, {128: (1, 1), 192: (1, 0), 193: (0, 0)}), ("f16", 448, 1, {192: (1, 1), 193: (0, 0)}),
+    ("bf16", 512, 1, {160: (1, 1), 161: (0, 0)}), ("f16", 1000, 1, {96: (1, 1), 97: (0, 0)}),
+    ("f16", 192, 2, {384: (0, 1), 385: (0, 0)}), ("bf16", 256, 2, {96: (1, 1), 97: (0, 1), 256: (0, 1), 257: (0, 0)}),
+    ("f16", 224, 4, {384: (0, 1), 385: (0, 0)}), ("bf16", 256, 4, {320: (0, 1), 321: (0, 0)}),
+    ("f16", 1800, 1, {64: (1, 1), 65: (0, 0)}), ("f32", 128, 1, {128: (1, 1), 129: (0, 0)})])
+def test_mass_on_both_sides_of_the_split_rule(dtype, N, G, expect):
+    """One slice repeated to the numbers of slices where the choice between split and full kernels turns: which kernels
+    ran, every copy the same bits, and the oracle's scores."""
+    _say(f"mass around the split rule: {dtype} N={N} G={G} {expect}")
+    Q, K, _ = _slices(31, 1, 1, [N], N, 128, G, dtype)
+    want = ref.attn_mass(Q, K, dtype, G=G)
+    for count, (lse, colsum) in expect.items():
+        q, k = gu.to_dev(Q, dtype).repeat(count, 1, 1, 1), gu.to_dev(K, dtype).repeat(count, 1, 1, 1)
+        sh = kb.make_shape(k, G)
+        ws = torch.empty(max(kb.kvm_workspace_bytes(sh), 256), dtype=torch.uint8, device="cuda")
+        mass = torch.full((count, 1, N), float("nan"), dtype=torch.float32, device="cuda")
+        names = gu.kernels_of(lambda: kb.kvm_attn_mass(sh, q, k, mass, ws))
+        assert ("attn_lse_split_kernel" in names, "attn_colsum_split_kernel" in names) == (lse, colsum), (count, names)
+        assert torch.equal(mass.view(torch.int32), mass[:1].view(torch.int32).expand(count, 1, N))
+        gu.assert_mass_close(mass[:1].cpu().numpy(), want, None, N, f"{count} slices")
+
+
 @pytest.mark.parametrize("dtype,N,G", [("f16", 97, 2), ("bf16", 200, 1), ("f32", 70, 2)])
 def test_mass_split_launch_of_every_slice_count(dtype, N, G):
     """The split kernels deal the slices out as one, two, four and whole groups of eight: every number of slices up to
