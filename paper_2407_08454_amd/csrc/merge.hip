@@ -224,27 +224,25 @@ __global__ __launch_bounds__(MERGE_BLOCK) void merge_kernel(const T *__restrict_
     if (edge >= n) return;
     const int M = min(max(a.n_sets[slice], 0), a.cap_rows);
     const int32_t *sst = a.set_start + (size_t)slice * (a.cap_rows + 1);
-    // cnt sets from s_lo on start inside this tile
+    const int32_t *piv = a.pivot + (size_t)slice * a.cap_rows;
+    // lane i looks at set s_lo+i (the pivot is fetched along, before it is known to be needed); cnt sets from
+    // s_lo on start inside this tile, followed by the start of the next set, the end of the last one
     const int s_lo = first_set_at(sst, M, edge, lane);
-    const int start_raw = lane < a.tile && s_lo + lane < M ? sst[s_lo + lane] : INT_MAX;
-    const int cnt = __builtin_ctzll(~__ballot(start_raw < edge + a.tile));  // (a.tile < 64: the ballot has a zero bit)
+    const int start_raw = s_lo + lane <= M ? sst[s_lo + lane] : INT_MAX;
+    const int my_piv = s_lo + lane < M ? piv[s_lo + lane] : 0;
+    const unsigned long long beyond = ~__ballot(s_lo + lane < M && start_raw < edge + a.tile);
+    const int cnt = beyond ? __builtin_ctzll(beyond) : WAVE;
     if (cnt == 0) return;
 
-    const int32_t *piv = a.pivot + (size_t)slice * a.cap_rows;
     const T *Ks = K + (size_t)slice * a.N * HEAD_DIM;
     const T *Vs = V + (size_t)slice * a.N * HEAD_DIM;
     T *Ko = K_out + (size_t)slice * a.cap_rows * HEAD_DIM;
     T *Vo = V_out + (size_t)slice * a.cap_rows * HEAD_DIM;
     float *wo = WITH_W ? a.w_opt + (size_t)slice * a.N : nullptr;
 
-    int my_start = n, my_piv = 0;
-    if (lane < cnt) {
-        my_start = min(max(start_raw, 0), n);
-        my_piv = piv[s_lo + lane];
-    }
-    const int t_end = min(max(sst[s_lo + cnt], 0), n);               // end of the wave's last set
+    const int my_start = min(max(start_raw, 0), n);
     int my_next = __shfl_down(my_start, 1, WAVE);
-    if (lane == cnt - 1) my_next = t_end;
+    if (cnt == WAVE && lane == WAVE - 1) my_next = min(max(sst[s_lo + WAVE], 0), n);
     const unsigned long long single_mask = __ballot(lane < cnt && my_next - my_start == 1);
 
     int i = 0;

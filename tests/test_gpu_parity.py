@@ -905,6 +905,37 @@ def test_merge_gives_the_same_bits_for_every_tile_size(slices):
         assert torch.equal(Vo.view(torch.int16), buf.V_out[:, one].contiguous().view(torch.int16))
 
 
+@pytest.mark.parametrize("slices", [2, 33])
+def test_merge_with_empty_sets_between(slices):
+    """Maps that a caller made itself may hold sets without tokens: up to 64 sets may start in a tile of tokens, whatever
+    its size (16 tokens in a small launch, 32 in a large one), and the sets with tokens have to come out as from the same
+    maps without the empty ones."""
+    n, empty = 8192, 20
+    _say(f"merge: {empty} empty sets at three places, {slices} slices")
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(slices)
+    K, V = (torch.randn((1, slices, n, 128), generator=gen, device="cuda").to(torch.float16) for _ in range(2))
+    starts = np.arange(0, n, 3)
+    at = [0, 1001, len(starts) - 1]                          # empty sets in front of these sets
+    keep = np.arange(len(starts)) + empty * np.searchsorted(at, np.arange(len(starts)), side="right")
+    padded = np.insert(starts, np.repeat(at, empty), np.repeat(starts[at], empty))
+    assert np.array_equal(padded[keep], starts)
+    params = kb.make_params(1.0, 0.0, 0.0, enforce_budget=False)
+    sh = kb.make_shape(K, 1)
+    out = []
+    for st in (starts, padded):
+        set_start = torch.full((1, slices, n + 1), n, dtype=torch.int32, device="cuda")
+        pivot = torch.full((1, slices, n), -1, dtype=torch.int32, device="cuda")
+        set_start[:, :, :len(st)] = pivot[:, :, :len(st)] = torch.from_numpy(st.astype(np.int32)).cuda()
+        n_sets = torch.full((1, slices), len(st), dtype=torch.int32, device="cuda")
+        o = [torch.full((1, slices, n, 128), 7.0, dtype=torch.float16, device="cuda") for _ in range(2)]
+        ws = torch.empty(kb.kvm_workspace_bytes(sh, params), dtype=torch.uint8, device="cuda")
+        kb.kvm_merge(sh, params, K, V, set_start, pivot, n_sets, *o, None, ws)
+        out.append(o)
+    for want, got in zip(*out):
+        assert torch.equal(got[:, :, torch.from_numpy(keep).cuda()].view(torch.int16), want[:, :, :len(starts)].view(torch.int16))
+
+
 def test_merge_tolerates_inconsistent_maps():
     n = 256
     _say("merge: out-of-range map entries are clamped, nothing faults")
