@@ -30,8 +30,17 @@ constexpr int MERGE_BLOCK = 64;          // one wave per workgroup: waves finish
 // 14.1; 64 of 4096 60 / 47 / 44.5; 256 of 1024 in fp32 110 / 106 / 90; 128 of 4096 110 / 92 / 96; 256 of
 // 4096 201 / 180 / 185; 1024 of 4096 628 / 597 / -.  Tiles of 64 with the look-up: 1024 slices of 4096 1-2 % slower
 // than with the table.  Hence 16 up to 2^18 tokens, where the waves fit the chip four times over, 32 beyond.
+// In the larger launches the slices go out in groups of eight, so that a slice's tiles, which read the same map entries,
+// stay on one XCD: workgroups are dealt round-robin to the eight of them.  Dealt out slice by slice, a slice of 256 tokens
+// sends its tile t, with the work of that part of a sequence, to XCD t every time.  Within an XCD two or four tiles a slice
+// fall into step with its units in the same way, so the first tile of a slice moves on with the group, in steps of no period.
+// Launches of 2^18 tokens or fewer are resident at once and gain nothing, and eight long slices at a time, one an XCD, differ too
+// much in their work (256 slices of 16384 576 / 596, 8 of 65536 113 / 117).  Measured, us, slice by slice / in groups / in groups
+// with moving first tile: 4096 slices of 256 tokens, budget 0.35, 221 / 165 / 149 (tiles of 64 from a table: 193); 9000 of 100
+// 232 / 227 / 145 (190); 16000 of 64 198 / 193 / 156 (167); 1024 of 1024 214 / 155 / 155 (216); 1024 of 4096 572 / 532 / 532 (611).
 constexpr int MERGE_TILE_FEW = 16, MERGE_TILE = 32;
 constexpr long long MERGE_FEW_TOKENS = 1 << 18;
+constexpr int MERGE_GROUPED_TILES = 128;                     // per slice
 // Sets of more than LONG_SET_MIN tokens are left to merge_long_kernel, which puts a whole workgroup
 // on each of them: one wave would stream such a set for hundreds of dependent round trips while
 // the rest of the chip has nothing to do (identical keys make one set of a whole slice).
@@ -60,7 +69,7 @@ struct MergeArgs {
     const int32_t *long_list;   // NULL (every long set of the maps is merged), or per slice, list_stride entries
                                 // apart: the number of long sets to merge, then their indices
     int list_stride;
-    int H, N, cap_rows;
+    int slices, H, N, cap_rows;
     int tile, tiles_per_slice;  // tokens per wave (merge_kernel)
     int mode;               // MERGE_ADAPTIVE, MERGE_FIXED (uses inv_two_sigma_sq) or MERGE_AVERAGE
     float inv_two_sigma_sq; // 1 / (2 sigma^2) for the fixed-sigma mode
@@ -214,8 +223,13 @@ __global__ __launch_bounds__(MERGE_BLOCK) void merge_kernel(const T *__restrict_
     using E = Elem<T>;
     using Raw = typename E::Raw;
     constexpr int US = 4;                      // row groups (of 4 rows) in flight in runs of singleton sets
-    const int slice = blockIdx.x / a.tiles_per_slice;
-    const int tile = blockIdx.x - slice * a.tiles_per_slice;
+    int slice = blockIdx.x / a.tiles_per_slice, tile = blockIdx.x - slice * a.tiles_per_slice;
+    const int group = slice / 8;
+    if (a.tile == MERGE_TILE && a.tiles_per_slice <= MERGE_GROUPED_TILES && group < a.slices / 8) {
+        const int at = blockIdx.x - 8 * group * a.tiles_per_slice;
+        slice = 8 * group + at % 8;
+        tile = (at / 8 + group + group / 4 + group / 16) % a.tiles_per_slice;
+    }
     const int lane = threadIdx.x & 63;
     const int slot = lane >> 4;          // which of the four rows of an instruction
     const int c = lane & 15;             // which 8-element chunk of the row
@@ -483,6 +497,7 @@ kvm_status launch_merge(const kvm_shape &sh, const kvm_params &pr, int cap_rows,
     a.seq_lens = sh.seq_lens;
     a.w_opt = w_opt;
     a.long_list = nullptr;
+    a.slices = sh.B * sh.H_kv;
     a.H = sh.H_kv;
     a.N = sh.N;
     a.cap_rows = cap_rows;
@@ -710,6 +725,7 @@ kvm_status launch_merge_refresh(const kvm_shape &sh, const kvm_params &pr, int c
     ma.w_opt = nullptr;
     ma.long_list = ra.long_list;
     ma.list_stride = stride;
+    ma.slices = sh.B * sh.H_kv;
     ma.H = sh.H_kv;
     ma.N = sh.N;
     ma.cap_rows = cap_rows;

@@ -905,6 +905,39 @@ def test_merge_gives_the_same_bits_for_every_tile_size(slices):
         assert torch.equal(Vo.view(torch.int16), buf.V_out[:, one].contiguous().view(torch.int16))
 
 
+@pytest.mark.parametrize("N,copies,rows", [(1, 20200, 13), (40, 600, 13), (100, 210, 13), (256, 80, 13), (700, 29, 13), (4096, 22, 3), (4097, 22, 3)])
+def test_merge_of_large_launches_of_short_slices(N, copies, rows):
+    """Launches of more than 2^18 tokens deal out slices of up to 128 tiles in groups of eight, each group starting at
+    another tile: one to 129 tiles a slice, slice counts that leave a rest, ragged lengths.  Every copy of a slice has to
+    give the bits of that slice in a small launch, and nothing beyond its rows is written."""
+    lens = [N - (N * b) // (2 * rows) for b in range(rows)]
+    _say(f"merge: {copies} copies of {rows} slices of {lens[-1]}..{N} tokens")
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(N)
+    K = torch.randn((rows, 1, N, 128), generator=gen, device="cuda").to(torch.float16)
+    if N > 40:
+        K[:, :, 10:35] = K[:, :, 10:11]                       # a set across the edge of a tile
+    V = torch.randn((rows, 1, N, 128), generator=gen, device="cuda").to(torch.float16)
+    mass = torch.rand((rows, 1, N), generator=gen, device="cuda")
+    params = kb.make_params(1.0, 0.1, 0.1, threshold=0.02, enforce_budget=False)
+
+    def run(rep):
+        k, v = K.repeat(rep, 1, 1, 1), V.repeat(rep, 1, 1, 1)
+        sh = kb.make_shape(k, 1, gu.lens_dev(lens * rep))
+        buf = kb.Buffers(sh, params, "cuda", torch.float16)
+        buf.mass.copy_(mass.repeat(rep, 1, 1))
+        kb.kvm_identify_sets(sh, params, k, buf.mass, buf.set_id, buf.set_start, buf.pivot, buf.n_sets, None, buf.status, buf.ws)
+        w = torch.full((rows * rep, 1, N), 7.0, dtype=torch.float32, device="cuda")
+        buf.K_out.fill_(7.0)
+        buf.V_out.fill_(7.0)
+        kb.kvm_merge(sh, params, k, v, buf.set_start, buf.pivot, buf.n_sets, buf.K_out, buf.V_out, w, buf.ws)
+        return [t.view(rep, rows, -1) for t in (buf.K_out.view(torch.int16), buf.V_out.view(torch.int16), w.view(torch.int32))]
+
+    assert rows * N <= 1 << 18 < rows * N * copies
+    for few, many in zip(run(1), run(copies)):
+        assert torch.equal(many, few.expand_as(many))
+
+
 @pytest.mark.parametrize("slices", [2, 33])
 def test_merge_with_empty_sets_between(slices):
     """Maps that a caller made itself may hold sets without tokens: up to 64 sets may start in a tile of tokens, whatever
