@@ -46,6 +46,7 @@ constexpr int MERGE_GROUPED_TILES = 128;                     // per slice
 // the rest of the chip has nothing to do (identical keys make one set of a whole slice).
 constexpr int LONG_SET_MIN = 512;
 constexpr int LONG_SET_BLOCK = 1024;
+constexpr int LONG_SET_LOOK = 4;         // sets a thread looks at between two barriers of the look-up
 // 4-row groups whose loads are issued together: 16 rows of K and of V.  Larger batches read
 // more sets in a single sweep but cost registers; the kernel is bound by memory latency, and
 // four waves per SIMD with 16-row batches beat two waves with 32-row batches.
@@ -77,7 +78,7 @@ struct MergeArgs {
 };
 
 // Smallest s in [0, M] with set_start[s] >= edge (M if there is none), by one wave: 64 probes of the
-// remaining range a round, so two dependent loads up to 4096 sets and three up to 262144.  The starts of
+// remaining range a round, so two dependent loads up to 4160 sets and three up to 266304.  The starts of
 // consistent maps ascend; for any other maps the result is some value in [0, M].
 __device__ __forceinline__ int first_set_at(const int32_t *sst, int M, int edge, int lane) {
     int lo = 0, len = M;                                     // the result lies in [lo, lo + len]
@@ -305,10 +306,15 @@ __global__ __launch_bounds__(MERGE_BLOCK) void merge_kernel(const T *__restrict_
 // 1024-thread workgroup per slice: group g takes the set's rows g, g + 64, ... (four of them in
 // flight), the distance sum and then the weighted sums are added up across the groups through
 // LDS.  Same arithmetic per row as merge_kernel; only the order of the fp32 additions differs.
-// The workgroup looks the long sets up in the maps itself (or takes the refresh's list), 1024 sets
-// at a time, in no particular order: each is merged on its own.
+// The workgroup looks the long sets up in the maps itself (or takes the refresh's list), 4096 sets
+// at a time, in no particular order: each is merged on its own.  The registers of one workgroup per
+// compute unit are given to it outright (waves_per_eu), because the compiler otherwise saves them by
+// taking the four rows of a group one after the other; a set's number is moved to a scalar, because
+// one that comes out of LDS counts as different in every lane.  Measured, us, this kernel: one
+// slice of 262144 equal keys 1305 / 954 (935 with the sets listed by a launch of 176 us before it), 512
+// of 4096 117 / 97 (98 and 10); one of 2^20 tokens without long sets 292 / 132 (6 and 850).
 template <typename T, bool WITH_W, int MODE>
-__global__ __launch_bounds__(LONG_SET_BLOCK) void merge_long_kernel(const T *__restrict__ K, const T *__restrict__ V,
+__global__ __launch_bounds__(LONG_SET_BLOCK) __attribute__((amdgpu_waves_per_eu(4, 4))) void merge_long_kernel(const T *__restrict__ K, const T *__restrict__ V,
                                                                 T *__restrict__ K_out, T *__restrict__ V_out, MergeArgs a)
 {
     using E = Elem<T>;
@@ -317,7 +323,7 @@ __global__ __launch_bounds__(LONG_SET_BLOCK) void merge_long_kernel(const T *__r
     constexpr int GROUPS = LONG_SET_BLOCK / 16, WAVES = LONG_SET_BLOCK / WAVE;
     __shared__ float red[WAVES][16][17];                     // per wave and chunk lane: 8 key sums, 8 value sums, weight sum
     __shared__ float red1[WAVES];
-    __shared__ int found[LONG_SET_BLOCK], n_found[2];        // (two counters in turn: one is cleared while the other is read)
+    __shared__ int found[LONG_SET_BLOCK * LONG_SET_LOOK], n_found[2];   // (two counters in turn: one is cleared while the other is read)
     const int slice = blockIdx.x;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int c = tid & 15, group = tid >> 4;
@@ -334,21 +340,30 @@ __global__ __launch_bounds__(LONG_SET_BLOCK) void merge_long_kernel(const T *__r
     const int32_t *pl = a.long_list ? a.long_list + (size_t)slice * a.list_stride : nullptr;
     int left = max_long_sets(a.N);                            // consistent maps never have more
     const int candidates = pl ? min(max(pl[0], 0), left) : M;
-    if (candidates == 0) return;
+    if (candidates == 0 || M == 0) return;
     if (tid < 2) n_found[tid] = 0;
     __syncthreads();
-    for (int first = 0, turn = 0; first < candidates; first += LONG_SET_BLOCK, turn ^= 1) {
-    if (first + tid < candidates) {
-        const int s = pl ? pl[1 + first + tid] : first + tid;
-        if (s >= 0 && s < M && min(max(sst[s + 1], 0), n) - min(max(sst[s], 0), n) > LONG_SET_MIN)
-            found[atomicAdd(&n_found[turn], 1)] = s;
+    for (int first = 0, turn = 0; first < candidates; first += LONG_SET_BLOCK * LONG_SET_LOOK, turn ^= 1) {
+    // (all loads before the first test; beyond the last set the last one is looked at again, and not taken)
+    int s_at[LONG_SET_LOOK], from[LONG_SET_LOOK], to[LONG_SET_LOOK];
+#pragma unroll
+    for (int u = 0; u < LONG_SET_LOOK; ++u) s_at[u] = min(first + u * LONG_SET_BLOCK + tid, candidates - 1);
+    if (pl) {
+#pragma unroll
+        for (int u = 0; u < LONG_SET_LOOK; ++u) s_at[u] = min(max(pl[1 + s_at[u]], 0), M - 1);
     }
+#pragma unroll
+    for (int u = 0; u < LONG_SET_LOOK; ++u) { from[u] = sst[s_at[u]]; to[u] = sst[s_at[u] + 1]; }
+#pragma unroll
+    for (int u = 0; u < LONG_SET_LOOK; ++u)
+        if (first + u * LONG_SET_BLOCK + tid < candidates && min(max(to[u], 0), n) - min(max(from[u], 0), n) > LONG_SET_MIN)
+            found[atomicAdd(&n_found[turn], 1)] = s_at[u];
     __syncthreads();
-    const int n_long = min(n_found[turn], left);
+    const int n_long = __builtin_amdgcn_readfirstlane(min(n_found[turn], left));
     left -= n_long;
     if (tid == 0) n_found[turn ^ 1] = 0;                      // read last before this turn's barrier above
     for (int k = 0; k < n_long; ++k) {
-        const int s = found[k];
+        const int s = __builtin_amdgcn_readfirstlane(found[k]);   // scalar, and the loops below with it
         const int lo = min(max(sst[s], 0), n), hi = min(max(sst[s + 1], 0), n);
         const int m = hi - lo;
         const int p = min(max(piv[s], lo), hi - 1);
@@ -442,7 +457,7 @@ __global__ __launch_bounds__(LONG_SET_BLOCK) void merge_long_kernel(const T *__r
             for (int row = lo + group; row < hi; row += GROUPS) wo[row] *= inv_g;
         }
     }
-    if (first + LONG_SET_BLOCK < candidates) __syncthreads();  // found is filled again; the cleared counter is seen
+    if (first + LONG_SET_BLOCK * LONG_SET_LOOK < candidates) __syncthreads();  // found is filled again; the cleared counter is seen
     }
 }
 

@@ -849,11 +849,11 @@ def test_merge_sets_around_the_length_a_workgroup_takes_over(dtype, mode):
     _check_merge(K, V, dtype, o, *res, f"long sets {dtype} {mode}")
 
 
-@pytest.mark.parametrize("sets", [1, 64, 65, 4096, 4097, 8000])
+@pytest.mark.parametrize("sets", [1, 64, 65, 4096, 4097, 4160, 4161, 8000, 8193])
 def test_merge_finds_the_sets_of_a_tile(sets):
-    """A wave looks for the first set of its tile with 64 probes a round: set counts at the edges of one,
-    two and three rounds, set sizes of 1 and 2 with a long set first and one last (the long sets are
-    looked up 1024 at a time, so the last one is found in a later turn), a ragged second row."""
+    """A wave looks for the first set of its tile with 64 probes a round: set counts at the edges of one (64),
+    two (4160) and three rounds, set sizes of 1 and 2 with a long set first and one last (the long sets are
+    looked up 4096 at a time, so from 4097 sets on the last one is found in a later turn), a ragged second row."""
     rng = np.random.default_rng(sets)
     sizes = [rng.integers(1, 3, sets), rng.integers(1, 2, sets)]
     for s in sizes:
