@@ -587,13 +587,15 @@ __global__ __launch_bounds__(SEG_BLOCK) void segment_kernel(SegArgs a)
 
 constexpr int SR_ITEMS = 16;
 
-// Copies of the radix select's histogram.  The leading byte of scores and similarities takes only a handful
-// of values, and LDS atomics of a wave on one address are served one after the other: lane l counts in copy
-// l % 8, whose bins are four banks further on, so eight lanes with the same digit go in parallel.  Up to
-// 2048 tokens one copy is used: clearing and adding up eight costs more than the conflicts.
-// Identification on given similarities, us, one copy / eight: 8 slices of 16384 tokens 30.3 / 24.0, 1024 of
-// 4096 39.6 / 33.9, 32 of 4096 14.7 / 13.7, 24 of 2500 14.1 / 14.0, 32 of 1000 13.1 / 13.9.
-constexpr int SR_SPREAD_MIN_N = 2049;
+// Copies of the radix select's histogram for the first digit.  The leading byte of scores and similarities takes
+// only a handful of values, and LDS atomics of a wave on one address are served one after the other: lane l counts
+// in copy l % 8, whose bins are four banks further on, so eight lanes with the same digit go in parallel.  The
+// later digits count only the keys that share the digits before, and those spread: one copy, as for all digits of
+// short slices, where clearing and adding up eight costs more than the conflicts.  Identification on given
+// similarities, us, one copy / eight in all digits / eight in the first: 8 slices of 16384 tokens 30.7 / 24.4 /
+// 24.0, 1024 of 4096 39.8 / 34.5 / 33.5, 32 of 4096 14.9 / 13.9 / 13.2, 32 of 2200 13.9 / 14.3 / 13.5, with random keys 18.9 /
+// 19.9 / 18.7; one copy / eight in the first: 32 of 1800 13.6 / 13.3, of 1500 13.4 / 13.3, of 1000 13.3 / 13.4.
+constexpr int SR_SPREAD_MIN_N = 1536;
 constexpr int SR_HISTS = 8;
 constexpr int SR_HIST_STRIDE = 256 + 4;
 
@@ -639,9 +641,10 @@ __device__ void select_kth_largest_reg(const uint32_t *key, uint32_t valid, int 
 {
     uint32_t prefix = 0, mask = 0;
     int remaining = k, gt = 0;
-    int *mine = sh.hist + (spread ? threadIdx.x % SR_HISTS : 0) * SR_HIST_STRIDE;
-    const int clear = spread ? SR_HISTS * SR_HIST_STRIDE / 4 : 256 / 4;
     for (int shift = 24; shift >= 0; shift -= 8) {
+        const bool copies = spread && shift == 24;
+        int *mine = sh.hist + (copies ? threadIdx.x % SR_HISTS : 0) * SR_HIST_STRIDE;
+        const int clear = copies ? SR_HISTS * SR_HIST_STRIDE / 4 : 256 / 4;
         for (int i = threadIdx.x; i < clear; i += BLOCK)
             reinterpret_cast<int4 *>(sh.hist)[i] = make_int4(0, 0, 0, 0);
         __syncthreads();
@@ -653,7 +656,7 @@ __device__ void select_kth_largest_reg(const uint32_t *key, uint32_t valid, int 
             const int lane = threadIdx.x;
             const int4 own = *reinterpret_cast<const int4 *>(&sh.hist[lane * 4]);
             int h[4] = {own.x, own.y, own.z, own.w};
-            if (spread) {
+            if (copies) {
 #pragma unroll
                 for (int q = 1; q < SR_HISTS; ++q) {
                     const int4 v = *reinterpret_cast<const int4 *>(&sh.hist[q * SR_HIST_STRIDE + lane * 4]);

@@ -543,6 +543,23 @@ def test_identify_ties_in_mass():
         gu.compare_maps(g, o, None, n, params.threshold, f"ties budget {budget}")
 
 
+@pytest.mark.parametrize("n", [1535, 1536, 4096, 4097])
+def test_identify_select_on_both_sides_of_the_histogram_copies(n):
+    """The radix select counts its first digit in eight copies from 1536 tokens on: scores that agree in no, one, two,
+    three or all four bytes of their order-preserving key (the top-k threshold then falls in each digit in turn), and
+    random keys, whose fallback selects among similarities of both signs."""
+    _say(f"identify: digits of the select, n={n}")
+    rng = np.random.default_rng(n)
+    K = synth.to_storage(rng.standard_normal((1, 5, n, 128)).astype(np.float32), "f16")
+    mass = np.empty((1, 5, n), np.float32)
+    mass[0, 0] = np.exp2(rng.uniform(-60, 60, n))
+    for h, low_bits in enumerate((24, 16, 8, 0), 1):
+        mass[0, h] = (0x3f000000 + rng.integers(0, 1 << low_bits, n)).astype(np.uint32).view(np.float32)
+    params = kb.kvm_params_for_budget(0.35)
+    g, o = _identify_both(K, mass.astype(np.float64), "f16", params)
+    gu.compare_maps(g, o, None, n, params.threshold, f"n={n}")
+
+
 @pytest.mark.parametrize("case", ["fallback", "fallback_ties", "no_enforce"])
 def test_identify_budget_rule(case):
     n = 1500
