@@ -44,16 +44,25 @@ def kernels_of(call):
         kb.kvm_profile_disable()
 
 
-def gpu_mass(Q, K, dtype, G=1, seq_lens=None):
-    Qd, Kd = to_dev(Q, dtype), to_dev(K, dtype)
-    sl = lens_dev(seq_lens)
+def gpu_mass(Q, K, dtype, G=1, seq_lens=None, copies=1, kernels=None):
+    """Scores of the slices, taken in a launch of `copies` copies of them (small launches and full ones go to different
+    kernels), which all have to come out with the same bits; `kernels`: names that have to be among those launched."""
+    Qd, Kd = to_dev(Q, dtype).repeat(copies, 1, 1, 1), to_dev(K, dtype).repeat(copies, 1, 1, 1)
+    sl = lens_dev(None if seq_lens is None else list(seq_lens) * copies)
     sh = kb.make_shape(Kd, G, sl)
     B, H, N, _ = K.shape
-    mass = torch.full((B, H, N), float("nan"), dtype=torch.float32, device="cuda")
+    mass = torch.full((B * copies, H, N), float("nan"), dtype=torch.float32, device="cuda")
     ws = torch.empty(max(kb.kvm_workspace_bytes(sh), 256), dtype=torch.uint8, device="cuda")
-    kb.kvm_attn_mass(sh, Qd, Kd, mass, ws)
+    if kernels is None:
+        kb.kvm_attn_mass(sh, Qd, Kd, mass, ws)
+    else:
+        names = kernels_of(lambda: kb.kvm_attn_mass(sh, Qd, Kd, mass, ws))
+        assert set(kernels) <= names, f"{names} ran, not {kernels}"
     torch.cuda.synchronize()
-    return mass.cpu().numpy()
+    if copies > 1:
+        bits = mass.view(torch.int32).view(copies, -1)
+        assert torch.equal(bits, bits[:1].expand_as(bits))
+    return mass[:B].cpu().numpy()
 
 
 def gpu_mass_from_lse(Q, K, row_lse32, dtype, G=1, seq_lens=None):
