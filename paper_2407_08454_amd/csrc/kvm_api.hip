@@ -178,7 +178,7 @@ int32_t kvm_out_capacity(const kvm_shape *shape, const kvm_params *params)
 size_t kvm_workspace_bytes(const kvm_shape *shape, const kvm_params *params)
 {
     if (check_shape(shape, "kvm_workspace_bytes") != KVM_OK) return 0;
-    // (the refresh of a compacted cache needs two ints per output row on top of the merge plan; without
+    // (the refresh of a compacted cache needs two ints per output row on top of what kvm_merge asks for; without
     // params the capacity is taken as N)
     const int cap = params && check_params(params, "kvm_workspace_bytes") == KVM_OK ? capacity(shape, params) : shape->N;
     const size_t a = ws_attn(shape), b = ws_identify(shape), c = merge_refresh_workspace_bytes(*shape, cap);

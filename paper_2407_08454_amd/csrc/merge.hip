@@ -757,19 +757,19 @@ kvm_status launch_merge_refresh(const kvm_shape &sh, const kvm_params &pr, int c
 
 // ------------------------------------------------------------------------------------------
 // The merge for callers that cannot bring a workspace.  Nothing is kept between its kernels; the size
-// limit of the entry point is part of its contract.
+// limit of the entry point, once that of a work plan in a buffer of the library, is part of its contract.
 // ------------------------------------------------------------------------------------------
 
-constexpr size_t STATIC_PLAN_INTS = (size_t)KVM_MERGE_STATIC_MAX_PLAN_ENTRIES;
+constexpr size_t STATIC_MAX_ENTRIES = (size_t)KVM_MERGE_STATIC_MAX_PLAN_ENTRIES;
 
 kvm_status launch_merge_static(const kvm_shape &sh, const kvm_params &pr, int cap_rows, const void *K, const void *V,
                                const int32_t *set_start, const int32_t *pivot, const int32_t *n_sets, void *K_out,
                                void *V_out, float *w_opt, hipStream_t st)
 {
     const size_t need = merge_workspace_bytes(sh) / sizeof(int32_t);
-    if (need > STATIC_PLAN_INTS) {
-        set_error("kvm_merge_static: the work plan needs %zu entries (B*H_kv*(ceil(N/64)+floor(N/513)+3)), the built-in buffer holds %zu; "
-                  "use kvm_merge with a workspace", need, STATIC_PLAN_INTS);
+    if (need > STATIC_MAX_ENTRIES) {
+        set_error("kvm_merge_static: the shape counts %zu entries (B*H_kv*(ceil(N/64)+floor(N/513)+3)), the limit of this call is %zu "
+                  "(the size of a built-in buffer it once used); use kvm_merge with a workspace", need, STATIC_MAX_ENTRIES);
         return KVM_ERR_WORKSPACE;
     }
     return launch_merge(sh, pr, cap_rows, K, V, set_start, pivot, n_sets, K_out, V_out, w_opt, st);
