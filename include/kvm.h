@@ -152,7 +152,15 @@ size_t kvm_workspace_bytes(const kvm_shape *shape, const kvm_params *params);
  *   K     in   (B, H_kv, N, d)   dtype
  *   mass  out  (B, H_kv, N) float32; 0 at positions >= n_b
  * Scores are accumulated in fp32 from the stored inputs; the map is never
- * materialised.  Deterministic (no atomics).
+ * materialised.  Deterministic (no atomics) for a given shape: repeated calls
+ * give the same bits.  The order of the fp32 additions of a slice follows from
+ * dtype and N and, because launches too small to fill the chip run kernels that
+ * split a slice's work further, from the numbers of slices B * H_kv and
+ * B * H_kv * G.  The same slice in a call that covers fewer or more slices can
+ * therefore differ in the last bits of its scores (about 1e-6 of a score), and
+ * with them the top-k and pivot choices of kvm_identify_sets where two scores tie
+ * that closely.  (16-bit types: the change lies between 128 and 384 workgroups of 256
+ * rows, by length; fp32: at 128 workgroups of 128 rows.)
  */
 kvm_status kvm_attn_mass(const kvm_shape *shape, const void *Q, const void *K, float *mass,
                          void *ws, size_t ws_bytes, void *stream);
@@ -283,8 +291,8 @@ kvm_status kvm_identify_sets(const kvm_shape *shape, const kvm_params *params, c
  *               round-to-nearest-even to dtype.
  *   w_opt       out  (B, H_kv, N) float32 or NULL: key weight of every token
  *               (positions not covered by a stored set are not written)
- *   ws          required as before (kvm_workspace_bytes), not written: the merge kernels find
- *               the sets of their tokens in set_start themselves
+ *   ws          required (kvm_workspace_bytes; KVM_ERR_WORKSPACE without it) but neither read nor
+ *               written: the merge kernels find the sets of their tokens in set_start themselves
  */
 kvm_status kvm_merge(const kvm_shape *shape, const kvm_params *params, const void *K, const void *V,
                      const int32_t *set_start, const int32_t *pivot, const int32_t *n_sets,
@@ -322,7 +330,8 @@ kvm_status kvm_merge_refresh(const kvm_shape *shape, const kvm_params *params, c
  * call allocates nothing, frees nothing and keeps nothing: calls on different streams and from
  * different threads may overlap.
  *   - B * H_kv * (ceil(N / 64) + floor(N / 513) + 3) > KVM_MERGE_STATIC_MAX_PLAN_ENTRIES returns
- *     KVM_ERR_WORKSPACE before any launch (use kvm_merge with a workspace then).
+ *     KVM_ERR_WORKSPACE before any launch (use kvm_merge with a workspace then).  The limit is that of
+ *     a buffer the call once kept its work plan in; it stays so that callers see the same answers.
  */
 #define KVM_MERGE_STATIC_MAX_PLAN_ENTRIES (1 << 21)
 kvm_status kvm_merge_static(const kvm_shape *shape, const kvm_params *params, const void *K, const void *V,
