@@ -366,7 +366,7 @@ __global__ __launch_bounds__(LONG_SET_BLOCK) __attribute__((amdgpu_waves_per_eu(
         const int s = __builtin_amdgcn_readfirstlane(found[k]);   // scalar, and the loops below with it
         const int lo = min(max(sst[s], 0), n), hi = min(max(sst[s + 1], 0), n);
         const int m = hi - lo;
-        const int p = min(max(piv[s], lo), hi - 1);
+        const int p = max(min(max(piv[s], lo), hi - 1), 0);   // (the bounds are read a second time: inside the slice whatever they are)
         float kp[8];
         E::to_float(E::load(Ks + (size_t)p * HEAD_DIM, c), kp);
         float inv_mean = 0.f;
