@@ -58,14 +58,24 @@ __device__ __forceinline__ f32x16 stream_scores(const u32x4 *a, const u32x4 *bfr
 }
 
 // blockIdx -> (slice, rank), rank 0 the longest tile.  Workgroups are dealt round-robin to the eight XCDs, each with its own
-// L2, so p slices that take turns, p a power of two up to eight, leave a slice's tiles on 8 / p of them.  The slices are dealt
-// out as one, two and four of them, as their number needs, and then in whole groups of eight, in each part the longest tiles of
-// all its slices first: an even spread for few slices, one XCD a slice for many.  With all slices in turn an odd number puts
-// every slice on every XCD: column sums of 51 slices of 2500 tokens, G = 4, 385 us (full kernel 301), like this 202; both
-// passes of 31 slices of 4096 229 (180) and 178, of 53 slices of 1500 83 (77) and 60.
+// L2, so p slices that take turns, p a power of two up to eight, leave a slice's tiles on 8 / p of them.  All slices in turn,
+// longest tiles first, does that for multiples of four; an odd number puts every slice on every XCD: column sums of 51
+// slices of 2500 tokens, G = 4, 385 us (full kernel 301), both passes of 31 slices of 4096 229 (180), of 53 slices of 1500 83
+// (77).  Other numbers of slices therefore go out as one, two and four of them, as needed, and then in whole groups of eight, in
+// each part the longest tiles first: 202, 178 and 60.  In turn the work is spread evenly, though, which is worth more where the
+// lengths differ (by the first 64 rows of the batch: 21 slices of up to 6000 tokens 148 in turn, 214 in parts; all 6000 long
+// 294 and 235) and for fp32, where the traffic hides behind the matrix pipe (5 slices of 3000: 121 and 135).
 struct SplitBlock { int slice, rank; };
-__device__ __forceinline__ SplitBlock split_block(int n_slices, int tiles) {
-    int i = blockIdx.x, first = 0, p = 1;
+template <typename T>
+__device__ __forceinline__ SplitBlock split_block(int n_slices, int tiles, const int32_t *seq_lens, int rows, int lane) {
+    int i = blockIdx.x;
+    bool in_turn = sizeof(T) == 4 || n_slices % 4 == 0 || n_slices <= 2;
+    if (!in_turn && seq_lens) {
+        const int len = seq_lens[min(lane, rows - 1)];
+        in_turn = __ballot(len != __builtin_amdgcn_readfirstlane(len)) != 0;
+    }
+    if (in_turn) return {i % n_slices, i / n_slices};
+    int first = 0, p = 1;
     for (; p < 8; p *= 2) {
         if (!(n_slices & p)) continue;
         if (i < p * tiles) break;
@@ -87,7 +97,8 @@ __global__ __launch_bounds__(W * WAVE, sizeof(T) == 2 && W == 4 ? 2 : 1) void at
     __shared__ u32x4 lds_a[W][S::SLOTS], lds_b[W][S::SLOTS];  // (two objects: see attn_lse_kernel)
     __shared__ float part_m[W][ROWS], part_l[W][ROWS];
 
-    const SplitBlock sb = split_block(n_qslices, tiles_per_slice);
+    const int lane = threadIdx.x & 63;
+    const SplitBlock sb = split_block<T>(n_qslices, tiles_per_slice, seq_lens, n_qslices / HG, lane);
     const int qslice = sb.slice;
     const int tile = tiles_per_slice - 1 - sb.rank;           // the last tile has the longest rows
     const int b = qslice / HG;
@@ -95,7 +106,6 @@ __global__ __launch_bounds__(W * WAVE, sizeof(T) == 2 && W == 4 ? 2 : 1) void at
     const int n = clamp_len(seq_lens, b, N);
     const int q0 = tile * ROWS;
     if (q0 >= n) return;
-    const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const T *Qs = Q + (size_t)qslice * N * HEAD_DIM;
     const T *Ks = K + (size_t)kvslice * N * HEAD_DIM;
@@ -167,7 +177,8 @@ __global__ __launch_bounds__(W * WAVE, sizeof(T) == 2 && W == 4 ? 2 : 1) void at
     __shared__ __attribute__((aligned(16))) float lse_a[W][32], lse_b[W][32];
     __shared__ float part_s[W][KEYS];
 
-    const SplitBlock sb = split_block(n_kvslices, tiles_per_slice);
+    const int lane = threadIdx.x & 63;
+    const SplitBlock sb = split_block<T>(n_kvslices, tiles_per_slice, seq_lens, n_kvslices / H, lane);
     const int kvslice = sb.slice;
     const int tile = sb.rank;                                 // tile 0 has the most rows below it
     const int b = kvslice / H, h = kvslice % H;
@@ -183,7 +194,6 @@ __global__ __launch_bounds__(W * WAVE, sizeof(T) == 2 && W == 4 ? 2 : 1) void at
         }
         return;
     }
-    const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const T *Ks = K + (size_t)kvslice * N * HEAD_DIM;
 

@@ -285,17 +285,19 @@ def test_maps_of_a_slice_alone_and_in_a_full_launch():
 
 
 @pytest.mark.parametrize("dtype,N,G", [("f16", 97, 2), ("bf16", 200, 1), ("f32", 70, 2)])
-def test_mass_split_launch_of_every_slice_count(dtype, N, G):
-    """The split kernels deal the slices out as one, two, four and whole groups of eight: every number of slices up to
-    17 has to give every slice the bits it gets alone (no slice left out or taken twice: the outputs start as NaN)."""
-    _say(f"mass, 1 to 17 slices: {dtype} N={N} G={G}")
-    lens = [N - 3 * (b % 5) for b in range(17)]
+@pytest.mark.parametrize("lengths", ["none", "equal", "different"])
+def test_mass_split_launch_of_every_slice_count(dtype, N, G, lengths):
+    """The split kernels deal the slices out in turn, or (16-bit types, equal lengths) as one, two, four and whole groups
+    of eight: every number of slices up to 17 has to give every slice the bits it gets alone (no slice left out or
+    taken twice: the outputs start as NaN)."""
+    _say(f"mass, 1 to 17 slices: {dtype} N={N} G={G} lengths: {lengths}")
+    lens = [N - (3 * (b % 5) if lengths == "different" else 0) for b in range(17)]
     Q, K, _ = _slices(29, 17, 1, lens, N, 128, G, dtype)
     Qd, Kd = gu.to_dev(Q, dtype), gu.to_dev(K, dtype)
 
     def run(rows):
         q, k = Qd[rows].contiguous(), Kd[rows].contiguous()
-        sh = kb.make_shape(k, G, gu.lens_dev(lens[rows]))
+        sh = kb.make_shape(k, G, None if lengths == "none" else gu.lens_dev(lens[rows]))
         ws = torch.full((max(kb.kvm_workspace_bytes(sh), 256),), 255, dtype=torch.uint8, device="cuda")
         out = torch.full((2, len(lens[rows]), N), float("nan"), dtype=torch.float32, device="cuda")
         names = gu.kernels_of(lambda: kb.kvm_attn_mass_sim(sh, q, k, out[0].view(-1, 1, N), out[1].view(-1, 1, N), ws))
