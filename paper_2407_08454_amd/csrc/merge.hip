@@ -34,6 +34,8 @@ constexpr int MERGE_BLOCK = 64;          // one wave per workgroup: waves finish
 // stay on one XCD: workgroups are dealt round-robin to the eight of them.  Dealt out slice by slice, a slice of 256 tokens
 // sends its tile t, with the work of that part of a sequence, to XCD t every time.  Within an XCD two or four tiles a slice
 // fall into step with its units in the same way, so the first tile of a slice moves on with the group, in steps of no period.
+// The XCD of a slice's place in its group moves on as well: lengths that repeat every four rows would leave the same XCDs idle
+// (300 slices of 1024 to 4096 tokens 168 / 131, slice by slice 136; 9000 of 25 to 100 126 / 100).
 // Launches of 2^18 tokens or fewer are resident at once and gain nothing, and eight long slices at a time, one an XCD, differ too
 // much in their work (256 slices of 16384 576 / 596, 8 of 65536 113 / 117).  Measured, us, slice by slice / in groups / in groups
 // with moving first tile: 4096 slices of 256 tokens, budget 0.35, 221 / 165 / 149 (tiles of 64 from a table: 193); 9000 of 100
@@ -228,7 +230,7 @@ __global__ __launch_bounds__(MERGE_BLOCK) void merge_kernel(const T *__restrict_
     const int group = slice / 8;
     if (a.tile == MERGE_TILE && a.tiles_per_slice <= MERGE_GROUPED_TILES && group < a.slices / 8) {
         const int at = blockIdx.x - 8 * group * a.tiles_per_slice;
-        slice = 8 * group + at % 8;
+        slice = 8 * group + (at + group) % 8;
         tile = (at / 8 + group + group / 4 + group / 16) % a.tiles_per_slice;
     }
     const int lane = threadIdx.x & 63;
