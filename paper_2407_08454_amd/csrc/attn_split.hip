@@ -62,28 +62,34 @@ __device__ __forceinline__ f32x16 stream_scores(const u32x4 *a, const u32x4 *bfr
 // longest tiles first, does that for multiples of four; an odd number puts every slice on every XCD: column sums of 51
 // slices of 2500 tokens, G = 4, 385 us (full kernel 301), both passes of 31 slices of 4096 229 (180), of 53 slices of 1500 83
 // (77).  Other numbers of slices therefore go out as one, two and four of them, as needed, and then in whole groups of eight, in
-// each part the longest tiles first: 202, 178 and 60.  In turn the work is spread evenly, though, which is worth more where the
-// lengths differ (by the first 64 rows of the batch: 21 slices of up to 6000 tokens 148 in turn, 214 in parts; all 6000 long
-// 294 and 235) and for fp32, where the traffic hides behind the matrix pipe (5 slices of 3000: 121 and 135).
+// each part the longest tiles first: 202, 178 and 60.  Fewer than eight slices do so eight ranks at a time, or the short tiles of
+// one part would start before the long ones of the next (6 slices of 8192: 139 in turn, 157 in parts, 141 like this; 7 of 6000 115,
+// 107 and 97), and not below 32 tiles, where they find everything in any L2 (7 of 600: 15.0 in turn, 15.3).
+// In turn the work is spread evenly, though, which is worth more where the lengths differ (by the first 64 rows of the
+// batch: 21 slices of up to 6000 tokens 148 in turn, 214 in parts; all 6000 long 294 and 235) and for fp32, where the
+// traffic hides behind the matrix pipe (5 slices of 3000: 121 and 135).
 struct SplitBlock { int slice, rank; };
 template <typename T>
 __device__ __forceinline__ SplitBlock split_block(int n_slices, int tiles, const int32_t *seq_lens, int rows, int lane) {
     int i = blockIdx.x;
-    bool in_turn = sizeof(T) == 4 || n_slices % 4 == 0 || n_slices <= 2;
+    bool in_turn = sizeof(T) == 4 || n_slices % 4 == 0 || n_slices <= 2 || (n_slices < 8 && tiles < 32);
     if (!in_turn && seq_lens) {
         const int len = seq_lens[min(lane, rows - 1)];
         in_turn = __ballot(len != __builtin_amdgcn_readfirstlane(len)) != 0;
     }
     if (in_turn) return {i % n_slices, i / n_slices};
+    const int chunk = n_slices < 8 ? 8 : tiles;              // ranks that are dealt out before the next
+    const int rank0 = i / (chunk * n_slices) * chunk, ranks = min(chunk, tiles - rank0);
+    i -= rank0 * n_slices;
     int first = 0, p = 1;
     for (; p < 8; p *= 2) {
         if (!(n_slices & p)) continue;
-        if (i < p * tiles) break;
-        i -= p * tiles;
+        if (i < p * ranks) break;
+        i -= p * ranks;
         first += p;
     }
     if (p == 8) p = n_slices - first;
-    return {first + i % p, i / p};
+    return {first + i % p, rank0 + i / p};
 }
 
 template <typename T, int W>

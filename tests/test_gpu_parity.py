@@ -284,12 +284,12 @@ def test_maps_of_a_slice_alone_and_in_a_full_launch():
         gu.compare_maps(g, o, None, N, params.threshold, "maps on this launch's scores")
 
 
-@pytest.mark.parametrize("dtype,N,G", [("f16", 97, 2), ("bf16", 200, 1), ("f32", 70, 2)])
+@pytest.mark.parametrize("dtype,N,G", [("f16", 97, 2), ("bf16", 200, 1), ("f32", 70, 2), ("bf16", 2016, 1)])
 @pytest.mark.parametrize("lengths", ["none", "equal", "different"])
 def test_mass_split_launch_of_every_slice_count(dtype, N, G, lengths):
     """The split kernels deal the slices out in turn, or (16-bit types, equal lengths) as one, two, four and whole groups
-    of eight: every number of slices up to 17 has to give every slice the bits it gets alone (no slice left out or
-    taken twice: the outputs start as NaN)."""
+    of eight (fewer than eight slices from 32 tiles on): every number of slices up to 17 has to give every slice the bits
+    it gets alone (no slice left out or taken twice: the outputs start as NaN)."""
     _say(f"mass, 1 to 17 slices: {dtype} N={N} G={G} lengths: {lengths}")
     lens = [N - (3 * (b % 5) if lengths == "different" else 0) for b in range(17)]
     Q, K, _ = _slices(29, 17, 1, lens, N, 128, G, dtype)
