@@ -32,7 +32,7 @@ constexpr int COS_ROWS_PER_BLOCK = COS_GROUPS * COS_ROWS_PER_GROUP;
 
 
 
-template <typename T>
+template <typename T, bool STREAM>
 __global__ __launch_bounds__(COS_BLOCK) void cosine_scan_kernel(const T *__restrict__ K, float *__restrict__ sim,
                                                                  float *__restrict__ inv_norm_out,
                                                                  const int32_t *__restrict__ seq_lens, int H, int N,
@@ -63,7 +63,7 @@ __global__ __launch_bounds__(COS_BLOCK) void cosine_scan_kernel(const T *__restr
     // never used), plus the row before the workgroup's first for group 0
     Raw raw[COS_ROWS_PER_GROUP];
 #pragma unroll
-    for (int i = 0; i < COS_ROWS_PER_GROUP; ++i) raw[i] = Elem<T>::load(Ks + (size_t)min(j0 + i, n - 1) * HEAD_DIM, c);
+    for (int i = 0; i < COS_ROWS_PER_GROUP; ++i) raw[i] = load_once<T, STREAM>(Ks + (size_t)min(j0 + i, n - 1) * HEAD_DIM, c);
     Raw prev = raw[0];
     if (group == 0 && j0 >= 1) prev = Elem<T>::load(Ks + (size_t)(j0 - 1) * HEAD_DIM, c);
     last_row[group][c] = raw[COS_ROWS_PER_GROUP - 1];
@@ -1165,14 +1165,21 @@ kvm_status launch_evict(const kvm_shape &sh, const kvm_params &pr, int cap_rows,
 // host launcher
 // ------------------------------------------------------------------------------------------
 
+// Keys that do not fit the last-level cache are read with the non-temporal hint: the merge could not find them there
+// anyway, and the stream runs at 6.0-6.5 TB/s instead of 5.1 (1 GiB: 208 us / 164-179).  Smaller launches keep the plain loads,
+// because the merge reads the same keys next and finds them in the cache (32 slices of 8192 tokens, 64 MiB: the same 16 us, but the
+// merge 46 / 54; at 192 MiB scan and merge 275 / 281, at 256 369 / 366, at 512 444 / 431).
 template <typename T>
 static void launch_cosine(const kvm_shape &sh, const void *K, float *sim, float *inv_norm, hipStream_t st)
 {
     const int tiles = (sh.N + COS_ROWS_PER_BLOCK - 1) / COS_ROWS_PER_BLOCK;
     const long long blocks = (long long)sh.B * sh.H_kv * tiles;
     ProfScope prof("cosine_scan_kernel", st);
-    hipLaunchKernelGGL(cosine_scan_kernel<T>, dim3((unsigned)blocks), dim3(COS_BLOCK), 0, st, (const T *)K, sim, inv_norm,
-                       sh.seq_lens, sh.H_kv, sh.N, tiles);
+    const dim3 grid((unsigned)blocks), block(COS_BLOCK);
+    if (key_bytes(sh) >= LLC_BYTES)
+        hipLaunchKernelGGL((cosine_scan_kernel<T, true>), grid, block, 0, st, (const T *)K, sim, inv_norm, sh.seq_lens, sh.H_kv, sh.N, tiles);
+    else
+        hipLaunchKernelGGL((cosine_scan_kernel<T, false>), grid, block, 0, st, (const T *)K, sim, inv_norm, sh.seq_lens, sh.H_kv, sh.N, tiles);
 }
 
 template <typename T>

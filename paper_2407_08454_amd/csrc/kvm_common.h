@@ -20,6 +20,8 @@ typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 
 // ---- a lane's 8 consecutive elements of a 128-wide row (chunk c of 16) --------------
+// load_stream / store_stream carry the non-temporal hint: data that this launch touches once.  On plain streams of 1 GiB
+// the hint gives 7.1-7.3 TB/s for reads (6.4 without) and 6.0-6.2 for copies (5.5-5.8).
 
 template <typename T> struct Elem;
 
@@ -31,6 +33,12 @@ template <> struct Elem<half_t> {
     }
     static __device__ __forceinline__ void store(half_t *row, int c, const Raw &r) {
         *reinterpret_cast<u32x4 *>(row + c * 8) = r.v;
+    }
+    static __device__ __forceinline__ Raw load_stream(const half_t *row, int c) {
+        return Raw{__builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(row + c * 8))};
+    }
+    static __device__ __forceinline__ void store_stream(half_t *row, int c, const Raw &r) {
+        __builtin_nontemporal_store(r.v, reinterpret_cast<u32x4 *>(row + c * 8));
     }
     static __device__ __forceinline__ void to_float(const Raw &r, float *x) {
         f16x8 h = __builtin_bit_cast(f16x8, r.v);
@@ -53,6 +61,12 @@ template <> struct Elem<bf16_t> {
     }
     static __device__ __forceinline__ void store(bf16_t *row, int c, const Raw &r) {
         *reinterpret_cast<u32x4 *>(row + c * 8) = r.v;
+    }
+    static __device__ __forceinline__ Raw load_stream(const bf16_t *row, int c) {
+        return Raw{__builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(row + c * 8))};
+    }
+    static __device__ __forceinline__ void store_stream(bf16_t *row, int c, const Raw &r) {
+        __builtin_nontemporal_store(r.v, reinterpret_cast<u32x4 *>(row + c * 8));
     }
     static __device__ __forceinline__ void to_float(const Raw &r, float *x) {
 #pragma unroll
@@ -85,6 +99,15 @@ template <> struct Elem<float> {
         f32x4 *p = reinterpret_cast<f32x4 *>(row + c * 8);
         p[0] = r.a;
         p[1] = r.b;
+    }
+    static __device__ __forceinline__ Raw load_stream(const float *row, int c) {
+        const f32x4 *p = reinterpret_cast<const f32x4 *>(row + c * 8);
+        return Raw{__builtin_nontemporal_load(p), __builtin_nontemporal_load(p + 1)};
+    }
+    static __device__ __forceinline__ void store_stream(float *row, int c, const Raw &r) {
+        f32x4 *p = reinterpret_cast<f32x4 *>(row + c * 8);
+        __builtin_nontemporal_store(r.a, p);
+        __builtin_nontemporal_store(r.b, p + 1);
     }
     static __device__ __forceinline__ void to_float(const Raw &r, float *x) {
 #pragma unroll
@@ -173,7 +196,20 @@ __device__ __forceinline__ int clamp_len(const int32_t *seq_lens, int b, int N) 
     return n < 0 ? 0 : (n > N ? N : n);
 }
 
+// A row that is read once by this launch.  STREAM: with the non-temporal hint (Elem::load_stream).
+template <typename T, bool STREAM> __device__ __forceinline__ typename Elem<T>::Raw load_once(const T *row, int c) {
+    if constexpr (STREAM) return Elem<T>::load_stream(row, c);
+    else return Elem<T>::load(row, c);
+}
+
 // ---- host side -----------------------------------------------------------------------
+
+// Keys of the launch in bytes, against the 256 MB last-level cache: the rules for the non-temporal loads of the scan and of
+// the decode-time scores.
+constexpr long long LLC_BYTES = 256ll << 20;
+inline long long key_bytes(const kvm_shape &sh) {
+    return (long long)sh.B * sh.H_kv * sh.N * HEAD_DIM * (sh.dtype == KVM_F32 ? 4 : 2);
+}
 
 void set_error(const char *fmt, ...);
 kvm_status check_launch(const char *what);

@@ -212,8 +212,11 @@ __device__ __forceinline__ void merge_one_set(const T *Ks, const T *Vs, T *k_row
         ak[e] = rows4_sum(ak[e]) * inv_g;
         av[e] = rows4_sum(av[e]) * vscale;
     }
-    if (slot == 0) E::store(k_row, c, E::from_float(ak));
-    if (slot == 1) E::store(v_row, c, E::from_float(av));
+    // (the hint keeps the merged rows, which nothing reads soon, out of the caches that hold the keys for their second sweep and what is
+    // left of the inputs: merge of 128 slices of 2048 tokens 45.2 / 44.5 us without / with it, 64 of 4096 in fp32 83 / 71, 32 of 16000
+    // 85.5 / 74.5, 1600 of 500 114 / 107.5, 1024 of 4096 588 / 574)
+    if (slot == 0) E::store_stream(k_row, c, E::from_float(ak));
+    if (slot == 1) E::store_stream(v_row, c, E::from_float(av));
     if (WITH_W && c == 0) {                                        // each writer normalises its own g_j
         for (int row = lo + slot; row < hi; row += 4) wo[row] *= inv_g;
     }
@@ -283,8 +286,8 @@ __global__ __launch_bounds__(MERGE_BLOCK) void merge_kernel(const T *__restrict_
             for (int u = 0; u < US; ++u) {
                 const int r = 4 * u + slot;
                 if (r < run) {
-                    E::store(Ko + (size_t)(s_lo + i + r) * HEAD_DIM, c, rk[u]);
-                    E::store(Vo + (size_t)(s_lo + i + r) * HEAD_DIM, c, rv[u]);
+                    E::store_stream(Ko + (size_t)(s_lo + i + r) * HEAD_DIM, c, rk[u]);
+                    E::store_stream(Vo + (size_t)(s_lo + i + r) * HEAD_DIM, c, rv[u]);
                     if (WITH_W && c == 0) wo[src[u]] = 1.f;
                 }
             }

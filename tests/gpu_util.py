@@ -224,3 +224,10 @@ def check_partition(g, lens, N, cap_rows, what=""):
             assert np.array_equal(st[:k], starts[:k]), what
             ends = np.append(starts[1:], n)
             assert ((pv[:k] >= starts[:k]) & (pv[:k] < ends[:k])).all(), what
+
+
+def randn_gpu(shape, dtype, seed):
+    """N(0, 1) on the GPU, for inputs that are too large to be drawn on the host."""
+    gen = torch.Generator("cuda")
+    gen.manual_seed(seed)
+    return torch.randn(shape, generator=gen, device="cuda", dtype=torch.float32).to(dtype)

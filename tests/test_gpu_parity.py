@@ -399,6 +399,31 @@ def test_mass_append_continues_the_prefill_pass():
     assert np.abs(mass - direct).max() <= 1e-4 * np.abs(direct).max()
 
 
+@pytest.mark.parametrize("dtype,H", [("f16", 64), ("bf16", 32), ("f32", 16)])
+def test_streamed_launches_give_the_bits_of_small_ones(dtype, H):
+    """From 128 MiB of keys (decode-time scores) and 256 MiB (scan) on, rows are read with the non-temporal hint; nothing
+    else differs, so every slice has the bits it gets in a call of its own, ragged last tiles included."""
+    B, N = 2, 16381 if dtype == "f32" else 16384
+    esz = 4 if dtype == "f32" else 2
+    _say(f"streamed launches: {dtype}, {B * H} slices of {N} ({B * H * N * 128 * esz >> 20} MiB of keys)")
+    dt = {"f32": torch.float32, "f16": torch.float16, "bf16": torch.bfloat16}[dtype]
+    K = gu.randn_gpu((B, H, N, 128), dt, 41)
+    q = gu.randn_gpu((B, H, 128), dt, 42)
+    params = kb.kvm_params_for_budget(0.35)
+    results = []
+    for K_part, q_part in ((K, q), (K[1:, H - 1:].contiguous(), q[1:, H - 1:].contiguous())):
+        lens = torch.tensor([N, N - 77][-K_part.shape[0]:], dtype=torch.int32, device="cuda")
+        shape = kb.make_shape(K_part, 1, lens)
+        buf = kb.Buffers(shape, params, "cuda", dt, with_sim=True)
+        buf.mass.fill_(0.25)
+        kb.kvm_attn_mass_append(shape, q_part, K_part, buf.mass, buf.ws)
+        kb.kvm_identify_sets(shape, params, K_part, buf.mass, buf.set_id, buf.set_start, buf.pivot, buf.n_sets, buf.sim,
+                             buf.status, buf.ws)
+        results.append([t[-1, -1].cpu() for t in (buf.mass, buf.sim, buf.set_id, buf.set_start, buf.pivot)])
+    for name, a, b in zip(("mass", "sim", "set_id", "set_start", "pivot"), *results):
+        assert torch.equal(a, b), name
+
+
 def test_mass_append_large_scores():
     n, dtype = 700, "bf16"
     _say("mass append: scores in the hundreds")
