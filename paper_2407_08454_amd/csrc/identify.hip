@@ -12,7 +12,7 @@
 //                       fallback, and a segmented arg-max scan for the pivots.  All integer
 //                       outputs are deterministic.
 //   segment_reg_kernel  the same for the adjacent rule and up to 16384 tokens with the slice held
-//                       in registers (16 tokens per thread)
+//                       in registers (4 to 16 tokens per thread)
 //   sim_append_kernel   decode time: the one new similarity
 //   evict_select_kernel, gather_rows_kernel, gather_merge_values_kernel
 //                       comparison workloads (eviction by score; evicted values averaged into the
@@ -578,124 +578,154 @@ __global__ __launch_bounds__(SEG_BLOCK) void segment_kernel(SegArgs a)
 //
 // segment_kernel above walks a slice in tiles and goes back to memory for the scores, the
 // similarities and the flag bytes in every one of its passes; with 1024 threads per slice each of
-// its ~40 barriers is expensive and only two slices fit a CU.  Here a thread owns 16 consecutive
+// its ~40 barriers is expensive and only two slices fit a CU.  Here a thread owns ITEMS consecutive
 // tokens and keeps their score keys, similarities and flag bits in registers from one coalesced
-// read to the final write; a workgroup has just enough threads for the slice (256 for 4096
-// tokens: four slices per CU, the whole headline workload resident at once), and the same steps
+// read to the final write; a workgroup has just enough threads for the slice, and the same steps
 // -- exact top-k by radix select, boundary test, budget rule, set numbering, segmented arg-max --
 // run on the registers.  Same results bit for bit.
-
-constexpr int SR_ITEMS = 16;
+//
+// What bounds it is one long dependent chain per slice, not a rate: so scans run on DPP moves instead of
+// cross-lane LDS traffic, every wave scans the histograms and the waves' totals for itself instead of waiting for
+// the one that does, a digit of the select that settles the threshold ends it, and a step that only ties or the budget
+// rule need is taken only then: six barriers for a slice without either, where there were 25.
 
 // Copies of the radix select's histogram for the first digit.  The leading byte of scores and similarities takes
 // only a handful of values, and LDS atomics of a wave on one address are served one after the other: lane l counts
 // in copy l % 8, whose bins are four banks further on, so eight lanes with the same digit go in parallel.  The
-// later digits count only the keys that share the digits before, and those spread: one copy, as for all digits of
-// short slices, where clearing and adding up eight costs more than the conflicts.  Identification on given
-// similarities, us, one copy / eight in all digits / eight in the first: 8 slices of 16384 tokens 30.7 / 24.4 /
-// 24.0, 1024 of 4096 39.8 / 34.5 / 33.5, 32 of 4096 14.9 / 13.9 / 13.2, 32 of 2200 13.9 / 14.3 / 13.5, with random keys 18.9 /
-// 19.9 / 18.7; one copy / eight in the first: 32 of 1800 13.6 / 13.3, of 1500 13.4 / 13.3, of 1000 13.3 / 13.4.
+// later digits count only the keys that share the digits before, and those spread: one copy.
 constexpr int SR_SPREAD_MIN_N = 1536;
 constexpr int SR_HISTS = 8;
 constexpr int SR_HIST_STRIDE = 256 + 4;
+constexpr int SR_HIST_INTS = SR_HISTS * SR_HIST_STRIDE + 3 * 256;   // the first digit's copies, then one histogram per later digit
 
 template <int BLOCK> struct SegRegShared {
-    alignas(16) int hist[SR_HISTS * SR_HIST_STRIDE];
+    alignas(16) int hist[SR_HIST_INTS];
     int wave_i[BLOCK / WAVE];
-    int wave_i2[BLOCK / WAVE];
-    unsigned long long wave_k[BLOCK / WAVE];
     int wave_f[BLOCK / WAVE];
-    int bc[2];
-    unsigned long long bck;
-    uint32_t bits[BLOCK + 1];            // one 16-bit mask per thread, handed to the neighbour
+    unsigned long long wave_k[BLOCK / WAVE];
+    int last_bit[BLOCK / WAVE + 1];      // conserved bit of a wave's last token, one place up
+    int first_head[BLOCK / WAVE + 1];    // head bit of a wave's first token
 };
 
-template <int WAVES>
-__device__ __forceinline__ int block_exclusive_sum_w(int v, int &total, int *wave_slots) {
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    int inc = v;
-#pragma unroll
-    for (int off = 1; off < WAVE; off <<= 1) {
-        int t = __shfl_up(inc, off, WAVE);
-        if (lane >= off) inc += t;
-    }
-    __syncthreads();                                         // wave_slots may still be read from a previous use
-    if (lane == WAVE - 1) wave_slots[w] = inc;
-    __syncthreads();
-    int before = 0, all = 0;
-#pragma unroll
-    for (int i = 0; i < WAVES; ++i) {
-        int a = wave_slots[i];
-        if (i < w) before += a;
-        all += a;
-    }
-    total = all;
-    return before + inc - v;
+// Inclusive prefix sum over the 64 lanes of a wave (DPP: within rows of 16, then across them).
+template <int CTRL, int ROWS> __device__ __forceinline__ int dpp_i(int v) {
+    return __builtin_amdgcn_update_dpp(0, v, CTRL, ROWS, 0xF, false);
+}
+__device__ __forceinline__ int row_inclusive_sum(int v) {
+    v += dpp_i<0x111, 0xF>(v);      // row_shr:1
+    v += dpp_i<0x112, 0xF>(v);      // row_shr:2
+    v += dpp_i<0x114, 0xF>(v);      // row_shr:4
+    v += dpp_i<0x118, 0xF>(v);      // row_shr:8
+    return v;
+}
+__device__ __forceinline__ int wave_inclusive_sum(int v) {
+    v = row_inclusive_sum(v);
+    v += dpp_i<0x142, 0xA>(v);      // row_bcast:15 into rows 1 and 3
+    v += dpp_i<0x143, 0xC>(v);      // row_bcast:31 into rows 2 and 3
+    return v;
+}
+// One step of the segmented maximum: (f, k) absorbs the value CTRL moves in from lower lanes.
+template <int CTRL, int ROWS> __device__ __forceinline__ void segmax_step(int &f, unsigned long long &k) {
+    const int f2 = dpp_i<CTRL, ROWS>(f);
+    const uint32_t lo = (uint32_t)dpp_i<CTRL, ROWS>((int)(uint32_t)k), hi = (uint32_t)dpp_i<CTRL, ROWS>((int)(uint32_t)(k >> 32));
+    const unsigned long long k2 = ((unsigned long long)hi << 32) | lo;
+    if (!f && k2 > k) k = k2;
+    f |= f2;
+}
+__device__ __forceinline__ void row_segmax(int &f, unsigned long long &k) {
+    segmax_step<0x111, 0xF>(f, k);
+    segmax_step<0x112, 0xF>(f, k);
+    segmax_step<0x114, 0xF>(f, k);
+    segmax_step<0x118, 0xF>(f, k);
+}
+__device__ __forceinline__ unsigned long long readlane_u64(unsigned long long k, int lane) {
+    const uint32_t lo = __builtin_amdgcn_readlane((int)(uint32_t)k, lane), hi = __builtin_amdgcn_readlane((int)(uint32_t)(k >> 32), lane);
+    return ((unsigned long long)hi << 32) | lo;
 }
 
-// k-th largest (k >= 1) of the keys whose bit is set in `valid` (16 keys per thread).  Needs
-// k <= number of valid keys.  Returns the key value T and the number of valid keys greater than T.
+// The waves' totals `slots` (up to 16 of them, at least one barrier old): sum of those before wave w, and of all.
+template <int WAVES>
+__device__ __forceinline__ int sum_before(const int *slots, int w, int &total) {
+    const int lane = threadIdx.x & 63;
+    const int inc = row_inclusive_sum(lane < WAVES ? slots[lane] : 0);
+    total = __builtin_amdgcn_readlane(inc, WAVES - 1);
+    return w ? __builtin_amdgcn_readlane(inc, w - 1) : 0;
+}
+
+// Exclusive prefix sum of one int per thread over the block; total returned to all threads.
+template <int WAVES>
+__device__ __forceinline__ int block_exclusive_sum_w(int v, int w, int &total, int *wave_slots) {
+    const int inc = wave_inclusive_sum(v);
+    __syncthreads();                                         // wave_slots may still be read from a previous use
+    if ((threadIdx.x & 63) == WAVE - 1) wave_slots[w] = inc;
+    __syncthreads();
+    return sum_before<WAVES>(wave_slots, w, total) + inc - v;
+}
+
 template <int BLOCK>
-__device__ void select_kth_largest_reg(const uint32_t *key, uint32_t valid, int k, uint32_t &T, int &greater,
+__device__ __forceinline__ void clear_histograms(SegRegShared<BLOCK> &sh) {
+    for (int i = threadIdx.x; i < SR_HIST_INTS / 4; i += BLOCK) reinterpret_cast<int4 *>(sh.hist)[i] = make_int4(0, 0, 0, 0);
+}
+
+// k-th largest (k >= 1) of the keys whose bit is set in `valid` (ITEMS keys per thread).  Needs k <= number of valid
+// keys and cleared histograms, a barrier ago.  The k largest are the keys above T and take_eq of the keys equal to it, or, with
+// take_eq < 0, the keys from T on.
+template <int BLOCK, int ITEMS>
+__device__ __forceinline__ void select_kth_largest_reg(const uint32_t *key, uint32_t valid, int k, uint32_t &T, int &take_eq,
                                        SegRegShared<BLOCK> &sh, bool spread)
 {
+    const int lane = threadIdx.x & 63;
     uint32_t prefix = 0, mask = 0;
-    int remaining = k, gt = 0;
+    int remaining = k;
+    take_eq = -1;
     for (int shift = 24; shift >= 0; shift -= 8) {
         const bool copies = spread && shift == 24;
-        int *mine = sh.hist + (copies ? threadIdx.x % SR_HISTS : 0) * SR_HIST_STRIDE;
-        const int clear = copies ? SR_HISTS * SR_HIST_STRIDE / 4 : 256 / 4;
-        for (int i = threadIdx.x; i < clear; i += BLOCK)
-            reinterpret_cast<int4 *>(sh.hist)[i] = make_int4(0, 0, 0, 0);
-        __syncthreads();
+        int *hist = shift == 24 ? sh.hist : sh.hist + SR_HISTS * SR_HIST_STRIDE + 256 * (2 - (shift >> 3));
+        int *mine = hist + (copies ? threadIdx.x % SR_HISTS : 0) * SR_HIST_STRIDE;
 #pragma unroll
-        for (int i = 0; i < SR_ITEMS; ++i)
+        for (int i = 0; i < ITEMS; ++i)
             if (((valid >> i) & 1u) && (key[i] & mask) == prefix) atomicAdd(&mine[(key[i] >> shift) & 255u], 1);
         __syncthreads();
-        if (threadIdx.x < WAVE) {
-            const int lane = threadIdx.x;
-            const int4 own = *reinterpret_cast<const int4 *>(&sh.hist[lane * 4]);
-            int h[4] = {own.x, own.y, own.z, own.w};
-            if (copies) {
+        const int4 own = *reinterpret_cast<const int4 *>(&hist[lane * 4]);
+        int h[4] = {own.x, own.y, own.z, own.w};
+        if (copies) {
 #pragma unroll
-                for (int q = 1; q < SR_HISTS; ++q) {
-                    const int4 v = *reinterpret_cast<const int4 *>(&sh.hist[q * SR_HIST_STRIDE + lane * 4]);
-                    h[0] += v.x; h[1] += v.y; h[2] += v.z; h[3] += v.w;
-                }
-            }
-            const int s = h[0] + h[1] + h[2] + h[3];
-            int suf = s;                                     // inclusive suffix sum over lanes
-#pragma unroll
-            for (int off = 1; off < WAVE; off <<= 1) {
-                int t = __shfl_down(suf, off, WAVE);
-                if (lane + off < WAVE) suf += t;
-            }
-            int above = suf - s;                             // keys in higher-numbered lanes' bins
-#pragma unroll
-            for (int i = 3; i >= 0; --i) {
-                if (above < remaining && remaining <= above + h[i]) { sh.bc[0] = lane * 4 + i; sh.bc[1] = above; }
-                above += h[i];
+            for (int q = 1; q < SR_HISTS; ++q) {
+                const int4 v = *reinterpret_cast<const int4 *>(&hist[q * SR_HIST_STRIDE + lane * 4]);
+                h[0] += v.x; h[1] += v.y; h[2] += v.z; h[3] += v.w;
             }
         }
-        __syncthreads();
-        const int digit = sh.bc[0], above = sh.bc[1];
-        gt += above;
-        remaining -= above;
+        const int inc = wave_inclusive_sum(h[0] + h[1] + h[2] + h[3]);
+        int above = __builtin_amdgcn_readlane(inc, WAVE - 1) - inc;    // keys in higher-numbered lanes' bins
+        int digit = -1, over = 0, count = 0;
+#pragma unroll
+        for (int i = 3; i >= 0; --i) {
+            if (above < remaining && remaining <= above + h[i]) { digit = lane * 4 + i; over = above; count = h[i]; }
+            above += h[i];
+        }
+        const unsigned long long at = __ballot(digit >= 0);
+        const int src = at ? __builtin_ctzll(at) : 0;
+        digit = __builtin_amdgcn_readlane(digit, src);
+        remaining -= __builtin_amdgcn_readlane(over, src);
+        count = __builtin_amdgcn_readlane(count, src);
         prefix |= (uint32_t)digit << shift;
         mask |= 255u << shift;
+        if (count == remaining) break;                       // the whole bin is among the k largest: keys from `prefix` on
+        if (shift == 0) take_eq = remaining;
     }
     T = prefix;
-    greater = gt;
 }
 
-template <int BLOCK>
+template <int BLOCK, int ITEMS>
 __global__ __launch_bounds__(BLOCK) void segment_reg_kernel(SegArgs a)
 {
+    static_assert(ITEMS % 4 == 0 && ITEMS <= 16, "whole vectors, 16-bit masks");
     constexpr int WAVES = BLOCK / WAVE;
+    constexpr uint32_t ALL = (1u << ITEMS) - 1u;
     __shared__ SegRegShared<BLOCK> sh;
     const int slice = blockIdx.x;
     const int tid = threadIdx.x;
-    const int lane = tid & 63, w = tid >> 6;
+    const int lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int n = clamp_len(a.seq_lens, slice / a.H, a.N);
     const float *mass = a.mass + (size_t)slice * a.N;
     const float *sim = a.sim + (size_t)slice * a.N;
@@ -704,22 +734,15 @@ __global__ __launch_bounds__(BLOCK) void segment_reg_kernel(SegArgs a)
     int32_t *pivot = a.pivot + (size_t)slice * a.cap_rows;
     const float eps = a.threshold;
 
-    int n_recent = (int)floor(a.recent_ratio * (double)n);
-    if (n_recent > n) n_recent = n;
-    int n_heavy = (int)floor(a.heavy_ratio * (double)n);
-    const int pre = n - n_recent;                            // the top-k is taken over [0, pre)
-    if (n_heavy > pre) n_heavy = pre;
-    const int cap = (int)floor(a.budget * (double)n);
-
-    // this thread's tokens jb .. jb+15: score keys and similarities, read once (16 bytes at a time
+    // this thread's tokens jb .. jb+ITEMS-1: score keys and similarities, read once (16 bytes at a time
     // where the rows are aligned for it)
-    const int jb = tid * SR_ITEMS;
+    const int jb = tid * ITEMS;
     const bool vec = (a.N & 3) == 0 && ((reinterpret_cast<uintptr_t>(a.mass) | reinterpret_cast<uintptr_t>(a.sim) |
                                          reinterpret_cast<uintptr_t>(a.set_id)) & 15) == 0;
-    uint32_t key[SR_ITEMS];
-    float sm[SR_ITEMS];
+    uint32_t key[ITEMS];
+    float sm[ITEMS];
 #pragma unroll
-    for (int v = 0; v < SR_ITEMS / 4; ++v) {
+    for (int v = 0; v < ITEMS / 4; ++v) {
         f32x4 m4 = {0.f, 0.f, 0.f, 0.f}, s4 = {0.f, 0.f, 0.f, 0.f};
         if (vec && jb + 4 * v + 3 < a.N) {                   // (N is the row stride: whole vectors stay inside the row)
             m4 = *reinterpret_cast<const f32x4 *>(mass + jb + 4 * v);
@@ -736,150 +759,157 @@ __global__ __launch_bounds__(BLOCK) void segment_reg_kernel(SegArgs a)
             sm[4 * v + e] = s4[e];
         }
     }
-    uint32_t in_n = 0, in_pre = 0;                           // bit i: token jb+i < n, < pre
-#pragma unroll
-    for (int i = 0; i < SR_ITEMS; ++i) {
-        in_n |= (jb + i < n ? 1u : 0u) << i;
-        in_pre |= (jb + i < pre ? 1u : 0u) << i;
-    }
+    clear_histograms(sh);                                    // (while the loads are on their way)
+
+    int n_recent = (int)floor(a.recent_ratio * (double)n);
+    if (n_recent > n) n_recent = n;
+    int n_heavy = (int)floor(a.heavy_ratio * (double)n);
+    const int pre = n - n_recent;                            // the top-k is taken over [0, pre)
+    if (n_heavy > pre) n_heavy = pre;
+    const int cap = (int)floor(a.budget * (double)n);
+    auto bits_below = [&](int end) -> uint32_t {             // bit i: token jb+i < end
+        const int c = min(max(end - jb, 0), ITEMS);
+        return (1u << c) - 1u;
+    };
+    const uint32_t in_n = bits_below(n), in_pre = bits_below(pre);
     for (int j = n + tid; j < a.N; j += BLOCK) set_id[j] = -1;
+    __syncthreads();                                         // the histograms are clear
 
     // ---- conserved tokens: the recent window and the exact top-k of the scores before it --------
     uint32_t prot = in_n & ~in_pre;
     if (n_heavy > 0) {
         uint32_t T1;
-        int gt1;
-        select_kth_largest_reg<BLOCK>(key, in_pre, n_heavy, T1, gt1, sh, n >= SR_SPREAD_MIN_N);
-        const int take_eq1 = n_heavy - gt1;
-        int eq_cnt = 0;
+        int take_eq1;
+        select_kth_largest_reg<BLOCK, ITEMS>(key, in_pre, n_heavy, T1, take_eq1, sh, n >= SR_SPREAD_MIN_N);
+        uint32_t eq = 0;
 #pragma unroll
-        for (int i = 0; i < SR_ITEMS; ++i) eq_cnt += (((in_pre >> i) & 1u) && key[i] == T1) ? 1 : 0;
-        int total;
-        int rank = block_exclusive_sum_w<WAVES>(eq_cnt, total, sh.wave_i);
+        for (int i = 0; i < ITEMS; ++i) {
+            prot |= (key[i] > T1 ? 1u << i : 0u) & in_pre;
+            eq |= (key[i] == T1 ? 1u << i : 0u) & in_pre;
+        }
+        if (take_eq1 < 0) {
+            prot |= eq;
+        } else {                                             // ties at the threshold: the first take_eq1 of them
+            int total;
+            int rank = block_exclusive_sum_w<WAVES>(__popc(eq), w, total, sh.wave_i);
 #pragma unroll
-        for (int i = 0; i < SR_ITEMS; ++i) {
-            if (!((in_pre >> i) & 1u)) continue;
-            if (key[i] > T1) prot |= 1u << i;
-            else if (key[i] == T1) { if (rank < take_eq1) prot |= 1u << i; ++rank; }
+            for (int i = 0; i < ITEMS; ++i)
+                if ((eq >> i) & 1u) { if (rank < take_eq1) prot |= 1u << i; ++rank; }
         }
     }
     // the neighbour's last token
+    if (lane == WAVE - 1) sh.last_bit[w + 1] = (int)(prot >> (ITEMS - 1));
+    if (tid == 0) { sh.last_bit[0] = 0; sh.first_head[WAVES] = 1; }
     __syncthreads();
-    sh.bits[tid + 1] = prot;
-    if (tid == 0) sh.bits[0] = 0;
-    __syncthreads();
-    const uint32_t prot_prev = (prot << 1) | ((sh.bits[tid] >> (SR_ITEMS - 1)) & 1u);   // bit i: token jb+i-1 is conserved
+    uint32_t before = (uint32_t)dpp_i<0x138, 0xF>((int)(prot >> (ITEMS - 1)));   // wave_shr:1
+    if (lane == 0) before = (uint32_t)sh.last_bit[w];
+    const uint32_t prot_prev = ((prot << 1) | before) & ALL;  // bit i: token jb+i-1 is conserved
 
     // j-1 and j may share a set (before the budget rule); "natural" boundary = both free, sim <= eps
-    uint32_t joins = 0, natural = 0;
+    uint32_t joins = 0;
 #pragma unroll
-    for (int i = 0; i < SR_ITEMS; ++i) {
-        const bool both_free = jb + i >= 1 && jb + i < n && !((prot >> i) & 1u) && !((prot_prev >> i) & 1u);
-        const bool above = sm[i] > eps;
-        joins |= (both_free && above ? 1u : 0u) << i;
-        natural |= (both_free && !above ? 1u : 0u) << i;
-    }
-    int M0, n_nat;
-    (void)block_exclusive_sum_w<WAVES>(__popc(in_n & ~joins), M0, sh.wave_i);
-    (void)block_exclusive_sum_w<WAVES>(__popc(natural), n_nat, sh.wave_i2);
-    int status = 0;
+    for (int i = 0; i < ITEMS; ++i) joins |= sm[i] > eps ? 1u << i : 0u;
+    const uint32_t both_free = in_n & ~prot & ~prot_prev & ~(jb == 0 ? 1u : 0u);
+    const uint32_t natural = both_free & ~joins;
+    joins &= both_free;
 
-    // ---- budget rule: remove the most similar natural boundaries (ties: higher index first) ------
-    uint32_t removed = 0;
-    if (a.enforce && M0 > cap) {
-        const int r = M0 - cap;
-        const bool all = n_nat <= r;
+    // ---- number the sets; if there are more than the budget allows, remove boundaries and number them again ------
+    // token j starts a set unless it joins its predecessor or its boundary was removed; the position
+    // after the last token closes the last set
+    int status = 0, M, s_first;
+    uint32_t removed = 0, head;
+    unsigned long long cur;
+    for (int round = 0;; ++round) {
+        head = (in_n & ~(joins | removed)) | (~in_n & ALL);
+        // thread summary for the segmented max scan: (any head, max of the trailing open segment)
+        int f = (head & in_n) ? 1 : 0;
+        // (score key above, complement of the position below: of equal scores the first wins)
+        uint32_t best = key[0];
+        int best_i = 0;
+#pragma unroll
+        for (int i = 1; i < ITEMS; ++i) {
+            const bool take = ((in_n >> i) & 1u) && (((head >> i) & 1u) || key[i] > best);
+            best = take ? key[i] : best;
+            best_i = take ? i : best_i;
+        }
+        unsigned long long k = in_n ? ((unsigned long long)best << 32) | ~(uint32_t)(jb + best_i) : 0;
+        const int heads = __popc(head & in_n);
+        const int inc = wave_inclusive_sum(heads);
+        row_segmax(f, k);
+        segmax_step<0x142, 0xA>(f, k);
+        segmax_step<0x143, 0xC>(f, k);
+        if (lane == WAVE - 1) { sh.wave_i[w] = inc; sh.wave_f[w] = f; sh.wave_k[w] = k; }
+        if (lane == 0) sh.first_head[w] = (int)(head & 1u);
+        // exclusive within the wave
+        const int fe = dpp_i<0x138, 0xF>(f);
+        const uint32_t ke_lo = (uint32_t)dpp_i<0x138, 0xF>((int)(uint32_t)k), ke_hi = (uint32_t)dpp_i<0x138, 0xF>((int)(uint32_t)(k >> 32));
+        const unsigned long long ke = ((unsigned long long)ke_hi << 32) | ke_lo;
+        __syncthreads();
+        s_first = sum_before<WAVES>(sh.wave_i, w, M) + inc - heads - 1;
+        // everything before this wave
+        int wf = lane < WAVES ? sh.wave_f[lane] : 0;
+        unsigned long long wk = lane < WAVES ? sh.wave_k[lane] : 0;
+        row_segmax(wf, wk);
+        const unsigned long long kp = w ? readlane_u64(wk, w - 1) : 0;
+        cur = fe ? ke : (kp > ke ? kp : ke);
+        if (round > 0 || !a.enforce || M <= cap) break;
+        // ---- budget rule: remove the most similar natural boundaries (ties: higher index first) ------
+        const int r = M - cap;
+        int n_nat;
+        (void)block_exclusive_sum_w<WAVES>(__popc(natural), w, n_nat, sh.wave_i);
         if (n_nat < r) status |= KVM_SLICE_INFEASIBLE;
         if (n_nat > 0) status |= KVM_SLICE_FALLBACK;
-        if (all) {
+        if (n_nat <= r) {
             removed = natural;
         } else {
-            uint32_t skey[SR_ITEMS];
+            uint32_t skey[ITEMS];
 #pragma unroll
-            for (int i = 0; i < SR_ITEMS; ++i) skey[i] = sortable_key(sm[i]);
+            for (int i = 0; i < ITEMS; ++i) skey[i] = sortable_key(sm[i]);
+            clear_histograms(sh);                            // (last read before the barriers above)
+            __syncthreads();
             uint32_t T2;
-            int gt2;
-            select_kth_largest_reg<BLOCK>(skey, natural, r, T2, gt2, sh, n >= SR_SPREAD_MIN_N);
-            const int take_eq2 = r - gt2;
-            int eq_cnt = 0;
+            int take_eq2;
+            select_kth_largest_reg<BLOCK, ITEMS>(skey, natural, r, T2, take_eq2, sh, n >= SR_SPREAD_MIN_N);
+            uint32_t eq = 0;
 #pragma unroll
-            for (int i = 0; i < SR_ITEMS; ++i) eq_cnt += (((natural >> i) & 1u) && skey[i] == T2) ? 1 : 0;
-            int total_eq2;
-            int rank = block_exclusive_sum_w<WAVES>(eq_cnt, total_eq2, sh.wave_i);
+            for (int i = 0; i < ITEMS; ++i) {
+                removed |= (skey[i] > T2 ? 1u << i : 0u) & natural;
+                eq |= (skey[i] == T2 ? 1u << i : 0u) & natural;
+            }
+            if (take_eq2 < 0) {
+                removed |= eq;
+            } else {
+                int total_eq2;
+                int rank = block_exclusive_sum_w<WAVES>(__popc(eq), w, total_eq2, sh.wave_i);
 #pragma unroll
-            for (int i = 0; i < SR_ITEMS; ++i) {
-                if (!((natural >> i) & 1u)) continue;
-                if (skey[i] > T2) removed |= 1u << i;
-                else if (skey[i] == T2) { if (total_eq2 - 1 - rank < take_eq2) removed |= 1u << i; ++rank; }
+                for (int i = 0; i < ITEMS; ++i)
+                    if ((eq >> i) & 1u) { if (total_eq2 - 1 - rank < take_eq2) removed |= 1u << i; ++rank; }
             }
         }
+        __syncthreads();                                     // the waves' totals are written again
     }
 
     // ---- set ids, set starts, pivots -----------------------------------------------------------
-    // token j starts a set unless it joins its predecessor or its boundary was removed; the position
-    // after the last token closes the last set
-    const uint32_t head = (in_n & ~(joins | removed)) | (~in_n & 0xFFFFu);
-    __syncthreads();
-    sh.bits[tid] = head;
-    if (tid == 0) sh.bits[BLOCK] = 0xFFFFu;
-    __syncthreads();
-    const uint32_t head_next = (head >> 1) | ((sh.bits[tid + 1] & 1u) << (SR_ITEMS - 1));   // bit i: token jb+i+1 starts a set
-    const int heads = __popc(head & in_n);
-    unsigned long long mkey[SR_ITEMS];
+    uint32_t after = (uint32_t)dpp_i<0x130, 0xF>((int)(head & 1u));      // wave_shl:1
+    if (lane == WAVE - 1) after = (uint32_t)sh.first_head[w + 1];
+    const uint32_t head_next = (head >> 1) | (after << (ITEMS - 1));      // bit i: token jb+i+1 starts a set
+    int s = s_first;
+    uint32_t best = (uint32_t)(cur >> 32);                   // of the set that is open, and where
+    int best_j = (int)~(uint32_t)cur;
+    int32_t ids[ITEMS];
 #pragma unroll
-    for (int i = 0; i < SR_ITEMS; ++i) mkey[i] = ((unsigned long long)key[i] << 32) | (uint32_t)(0xFFFFFFFFu - (uint32_t)(jb + i));
-    // thread summary for the segmented max scan: (any head, max of the trailing open segment)
-    int f = 0;
-    unsigned long long k = 0;
-#pragma unroll
-    for (int i = 0; i < SR_ITEMS; ++i) {
-        if (!((in_n >> i) & 1u)) break;
-        if ((head >> i) & 1u) { f = 1; k = mkey[i]; }
-        else k = k > mkey[i] ? k : mkey[i];
-    }
-    int M;
-    const int sets_before = block_exclusive_sum_w<WAVES>(heads, M, sh.wave_i);
-    int fi = f;
-    unsigned long long ki = k;
-#pragma unroll
-    for (int off = 1; off < WAVE; off <<= 1) {
-        int f2 = __shfl_up(fi, off, WAVE);
-        unsigned long long k2 = shfl_up_u64(ki, off);
-        if (lane >= off) {
-            if (!fi) ki = ki > k2 ? ki : k2;
-            fi |= f2;
-        }
-    }
-    if (lane == WAVE - 1) { sh.wave_f[w] = fi; sh.wave_k[w] = ki; }
-    int fe = __shfl_up(fi, 1, WAVE);                         // exclusive within the wave
-    unsigned long long ke = shfl_up_u64(ki, 1);
-    if (lane == 0) { fe = 0; ke = 0; }
-    __syncthreads();
-    unsigned long long kp = 0;                               // everything before this wave
-    for (int i = 0; i < w; ++i) {
-        if (sh.wave_f[i]) kp = sh.wave_k[i];
-        else kp = kp > sh.wave_k[i] ? kp : sh.wave_k[i];
-    }
-    unsigned long long cur = fe ? ke : (kp > ke ? kp : ke);
-    int s = sets_before - 1;
-    int32_t ids[SR_ITEMS];
-#pragma unroll
-    for (int i = 0; i < SR_ITEMS; ++i) {
+    for (int i = 0; i < ITEMS; ++i) {
         const int j = jb + i;
-        if ((in_n >> i) & 1u) {
-            if ((head >> i) & 1u) {
-                ++s;
-                cur = mkey[i];
-                if (s <= a.cap_rows) set_start[s] = j;
-            } else {
-                cur = cur > mkey[i] ? cur : mkey[i];
-            }
-            if (((head_next >> i) & 1u) && s < a.cap_rows) pivot[s] = (int32_t)(0xFFFFFFFFu - (uint32_t)cur);
-        }
+        const bool starts = ((head & in_n) >> i) & 1u, take = starts || key[i] > best;
+        s += starts ? 1 : 0;
+        best = take ? key[i] : best;
+        best_j = take ? j : best_j;
+        if (starts && s <= a.cap_rows) set_start[s] = j;
+        if (((head_next & in_n) >> i) & 1u && s < a.cap_rows) pivot[s] = best_j;
         ids[i] = s;
     }
 #pragma unroll
-    for (int v = 0; v < SR_ITEMS / 4; ++v) {
+    for (int v = 0; v < ITEMS / 4; ++v) {
         if (vec && jb + 4 * v + 3 < n) {
             int4 o = {ids[4 * v], ids[4 * v + 1], ids[4 * v + 2], ids[4 * v + 3]};
             *reinterpret_cast<int4 *>(set_id + jb + 4 * v) = o;
@@ -1284,13 +1314,23 @@ kvm_status launch_identify(const kvm_shape &sh, const kvm_params &pr, int cap_ro
             walk_lds_bytes = (size_t)sh.N * 3;
         }
     }
-    const bool in_registers = !anchor && sh.N > 0 && sh.N <= 1024 * SR_ITEMS;
+    const bool in_registers = !anchor && sh.N > 0 && sh.N <= 1024 * 16;
     ProfScope prof(in_registers ? "segment_reg_kernel" : "segment_kernel", st);
     if (in_registers) {
-        // 16 tokens per thread in registers: as many threads as the slice needs
-        if (sh.N <= 256 * SR_ITEMS) hipLaunchKernelGGL(segment_reg_kernel<256>, dim3((unsigned)slices), dim3(256), 0, st, a);
-        else if (sh.N <= 512 * SR_ITEMS) hipLaunchKernelGGL(segment_reg_kernel<512>, dim3((unsigned)slices), dim3(512), 0, st, a);
-        else hipLaunchKernelGGL(segment_reg_kernel<1024>, dim3((unsigned)slices), dim3(1024), 0, st, a);
+        // Four tokens a thread, eight and sixteen only where 1024 threads are not enough: the chain of a thread is what a slice
+        // waits for, also where the launch fills the chip.  us, sixteen a thread (first form of this kernel: 25 barriers) / four: one
+        // slice of 512 tokens 15.7 / 6.9, 32 of 1000 15.9 / 7.6, 32 of 4000 15.9 / 9.0, 256 of 4000 19.9 / 11.4, 1024 of 4096 35.6 / 23.7,
+        // 1600 of 500 31.4 / 11.6; eight a thread instead of four: 1024 of 4096 26.5, 400 of 2000 11.2 against 10.6.
+        const auto run = [&](auto kernel, int block) {
+            hipLaunchKernelGGL(kernel, dim3((unsigned)slices), dim3(block), 0, st, a);
+        };
+        if (sh.N <= 256) run(segment_reg_kernel<64, 4>, 64);
+        else if (sh.N <= 512) run(segment_reg_kernel<128, 4>, 128);
+        else if (sh.N <= 1024) run(segment_reg_kernel<256, 4>, 256);
+        else if (sh.N <= 2048) run(segment_reg_kernel<512, 4>, 512);
+        else if (sh.N <= 4096) run(segment_reg_kernel<1024, 4>, 1024);
+        else if (sh.N <= 8192) run(segment_reg_kernel<1024, 8>, 1024);
+        else run(segment_reg_kernel<1024, 16>, 1024);
     } else {
         hipLaunchKernelGGL(segment_kernel, dim3((unsigned)slices), dim3(SEG_BLOCK), walk_lds_bytes, st, a);
     }

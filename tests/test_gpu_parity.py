@@ -614,6 +614,27 @@ def test_identify_select_on_both_sides_of_the_histogram_copies(n):
     gu.compare_maps(g, o, None, n, params.threshold, f"n={n}")
 
 
+@pytest.mark.parametrize("n", [255, 256, 257, 512, 513, 1024, 1025, 2048, 2049, 4096, 4097, 8192, 8193, 16384])
+def test_identify_on_both_sides_of_the_workgroup_sizes(n):
+    """A slice gets as many threads as it needs, of 4, 8 or 16 tokens: sets, sets' ends and pivots that cross a thread's, a
+    wave's and the last thread's edge, thresholds that a digit of the select settles early and ties that none does, with
+    and without the budget rule, in rows as long as the stride and one shorter."""
+    _say(f"identify: workgroup sizes, n={n}")
+    rng = np.random.default_rng(n)
+    base = rng.standard_normal((3, 128)).astype(np.float32)
+    K = rng.standard_normal((2, 3, n, 128)).astype(np.float32)
+    K[:, 1] = base[np.arange(n) % 3]                          # adjacent similarities of three values: ties in the budget rule
+    K[:, 2] = base[np.arange(n) // 97 % 3] * rng.uniform(0.5, 2, (n, 1))   # runs of 97 keys of one direction
+    K = synth.to_storage(K, "f16")
+    mass = np.exp(rng.standard_normal((2, 3, n))).astype(np.float32)
+    mass[:, 1] = rng.integers(1, 4, n)                        # ties in the top-k and the pivots
+    for budget in (0.5, 0.35):
+        params = kb.kvm_params_for_budget(budget)
+        lens = [n, n - 1]
+        g, o = _identify_both(K, mass.astype(np.float64), "f16", params, lens)
+        gu.compare_maps(g, o, lens, n, params.threshold, f"n={n} budget {budget}")
+
+
 @pytest.mark.parametrize("case", ["fallback", "fallback_ties", "no_enforce"])
 def test_identify_budget_rule(case):
     n = 1500
