@@ -112,11 +112,19 @@ def _check(fn, rc):
 
 
 def _ptr(t):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()               # (the argument types make it a void pointer)
+
+
+# torch.cuda.current_stream() builds a Stream object by way of the device's name: 2.8 us, as much as a launch.  The handle alone
+# takes 0.2, where torch offers it.
+_current_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
 
 
 def _stream():
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    """Handle of the current stream of the current device."""
+    if _current_raw_stream is None:
+        return torch.cuda.current_stream().cuda_stream
+    return _current_raw_stream(torch.cuda.current_device())
 
 
 def kvm_params_for_budget(budget: float) -> KvmParams:
@@ -166,14 +174,16 @@ def _same_device(*ts):
             continue
         if not t.is_cuda or not t.is_contiguous():
             raise ValueError("tensors must be contiguous and on the GPU")
-        dev = dev or t.device
-        if t.device != dev:
+        index = t.get_device()
+        if dev is None:
+            dev = index
+        elif index != dev:
             raise ValueError("tensors must share one device")
 
 
 def _check_attn_operands(shape: KvmShape, Q, K, mass):
     B, H, G, N, d = shape.B, shape.H_kv, shape.G, shape.N, shape.d
-    if tuple(Q.shape) != (B, H * G, N, d) or tuple(K.shape) != (B, H, N, d) or tuple(mass.shape) != (B, H, N):
+    if Q.shape != (B, H * G, N, d) or K.shape != (B, H, N, d) or mass.shape != (B, H, N):
         raise ValueError("operand shapes do not match the shape descriptor")
     if mass.dtype != torch.float32 or Q.dtype != K.dtype or _TORCH_DTYPE[K.dtype] != shape.dtype:
         raise ValueError("dtype mismatch")
@@ -212,7 +222,7 @@ def kvm_attn_mass_append(shape: KvmShape, q_new, K, mass, ws):
     """mass (B, H_kv, N) float32 += the attention row of the newest token (its key already stored at n_b - 1)."""
     _same_device(q_new, K, mass, ws)
     B, H, G, N, d = shape.B, shape.H_kv, shape.G, shape.N, shape.d
-    if tuple(q_new.shape) != (B, H * G, d) or tuple(K.shape) != (B, H, N, d) or tuple(mass.shape) != (B, H, N):
+    if q_new.shape != (B, H * G, d) or K.shape != (B, H, N, d) or mass.shape != (B, H, N):
         raise ValueError("operand shapes do not match the shape descriptor")
     if mass.dtype != torch.float32 or q_new.dtype != K.dtype or _TORCH_DTYPE[K.dtype] != shape.dtype:
         raise ValueError("dtype mismatch")
@@ -225,7 +235,7 @@ def kvm_sim_append(shape: KvmShape, K, sim):
     """sim[b, h, n_b - 1] <- cosine similarity of the newest key and its predecessor; nothing else is written."""
     _same_device(K, sim)
     B, H, N, d = shape.B, shape.H_kv, shape.N, shape.d
-    if tuple(K.shape) != (B, H, N, d) or tuple(sim.shape) != (B, H, N):
+    if K.shape != (B, H, N, d) or sim.shape != (B, H, N):
         raise ValueError("operand shapes do not match the shape descriptor")
     if sim.dtype != torch.float32 or _TORCH_DTYPE[K.dtype] != shape.dtype:
         raise ValueError("dtype mismatch")
@@ -243,7 +253,7 @@ def kvm_identify_sets(shape: KvmShape, params: KvmParams, K, mass, set_id, set_s
     if sim_opt is not None:
         want["sim_opt"] = (sim_opt, (B, H, N))
     for name, (t, shp) in want.items():
-        if tuple(t.shape) != shp:
+        if t.shape != shp:
             raise ValueError(f"{name} has shape {tuple(t.shape)}, expected {shp}")
     for t in (set_id, set_start, pivot, n_sets, slice_status):
         if t.dtype != torch.int32:
@@ -267,7 +277,7 @@ def _check_merge_operands(shape, params, K, V, set_start, pivot, n_sets, K_out, 
     if w_opt is not None:
         want["w_opt"] = (w_opt, (B, H, N))
     for name, (t, shp) in want.items():
-        if tuple(t.shape) != shp:
+        if t.shape != shp:
             raise ValueError(f"{name} has shape {tuple(t.shape)}, expected {shp}")
     for t in (set_start, pivot, n_sets):
         if t.dtype != torch.int32:
@@ -282,7 +292,7 @@ def kvm_merge(shape: KvmShape, params: KvmParams, K, V, set_start, pivot, n_sets
     _check_merge_operands(shape, params, K, V, set_start, pivot, n_sets, K_out, V_out, w_opt, ws)
     _check("kvm_merge", load_library().kvm_merge(
         ctypes.byref(shape), ctypes.byref(params), _ptr(K), _ptr(V), _ptr(set_start), _ptr(pivot), _ptr(n_sets),
-        _ptr(K_out), _ptr(V_out), _ptr(w_opt), None if ws is None else _ptr(ws),
+        _ptr(K_out), _ptr(V_out), _ptr(w_opt), _ptr(ws),
         0 if ws is None else ws.numel() * ws.element_size(), _stream()))
 
 
@@ -295,7 +305,7 @@ def kvm_merge_refresh(shape: KvmShape, params: KvmParams, K, V, prev_set_id, pre
     B, H, N = shape.B, shape.H_kv, shape.N
     for t, other, shp in ((prev_set_id, None, (B, H, N)), (prev_set_start, set_start, None), (prev_pivot, pivot, None),
                           (prev_n_sets, n_sets, None)) + (((n_changed, None, (B, H)),) if n_changed is not None else ()):
-        if t.dtype != torch.int32 or tuple(t.shape) != (shp if shp is not None else tuple(other.shape)):
+        if t.dtype != torch.int32 or t.shape != (shp if shp is not None else other.shape):
             raise ValueError("previous maps must be int32 tensors shaped like the new ones")
     _check("kvm_merge_refresh", load_library().kvm_merge_refresh(
         ctypes.byref(shape), ctypes.byref(params), _ptr(K), _ptr(V), _ptr(prev_set_id), _ptr(prev_set_start),
@@ -318,7 +328,7 @@ def _evict(fn: str, shape: KvmShape, params: KvmParams, K, V, mass, kept, n_kept
     want = {"K": (K, (B, H, N, d)), "V": (V, (B, H, N, d)), "mass": (mass, (B, H, N)), "kept": (kept, (B, H, cap)),
             "n_kept": (n_kept, (B, H)), "K_out": (K_out, (B, H, cap, d)), "V_out": (V_out, (B, H, cap, d))}
     for name, (t, shp) in want.items():
-        if tuple(t.shape) != shp:
+        if t.shape != shp:
             raise ValueError(f"{name} has shape {tuple(t.shape)}, expected {shp}")
     if kept.dtype != torch.int32 or n_kept.dtype != torch.int32 or mass.dtype != torch.float32:
         raise ValueError("kept and n_kept must be int32, mass float32")
@@ -326,7 +336,7 @@ def _evict(fn: str, shape: KvmShape, params: KvmParams, K, V, mass, kept, n_kept
         raise ValueError("dtype mismatch")
     _check(fn, getattr(load_library(), fn)(
         ctypes.byref(shape), ctypes.byref(params), _ptr(K), _ptr(V), _ptr(mass), _ptr(kept), _ptr(n_kept), _ptr(K_out),
-        _ptr(V_out), None if ws is None else _ptr(ws), 0 if ws is None else ws.numel() * ws.element_size(), _stream()))
+        _ptr(V_out), _ptr(ws), 0 if ws is None else ws.numel() * ws.element_size(), _stream()))
 
 
 def kvm_evict(shape: KvmShape, params: KvmParams, K, V, mass, kept, n_kept, K_out, V_out, ws):
