@@ -75,16 +75,11 @@ template <> struct Elem<bf16_t> {
             x[2 * i + 1] = __builtin_bit_cast(float, r.v[i] & 0xFFFF0000u);
         }
     }
-    static __device__ __forceinline__ uint32_t rne(float f) {
-        uint32_t u = __builtin_bit_cast(uint32_t, f);
-        if ((u & 0x7FFFFFFFu) > 0x7F800000u) return (u >> 16) | 0x40u;   // NaN stays NaN
-        return (u + 0x7FFFu + ((u >> 16) & 1u)) >> 16;
-    }
     static __device__ __forceinline__ Raw from_float(const float *x) {
-        Raw r;
+        bf16x8 h;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) r.v[i] = rne(x[2 * i]) | (rne(x[2 * i + 1]) << 16);
-        return r;
+        for (int i = 0; i < 8; ++i) h[i] = (bf16_t)x[i];   // round to nearest even (v_cvt_pk_bf16_f32)
+        return Raw{__builtin_bit_cast(u32x4, h)};
     }
 };
 
@@ -178,11 +173,16 @@ __device__ __forceinline__ float row16_sum(float v) {
     return v;
 }
 
-// Sum over the four 16-lane rows of a wave (same lane position in each row).
+// Sum over the four 16-lane rows of a wave (same lane position in each row), on the vector ALU: a swap of one value with itself
+// leaves its even rows in one result and its odd rows in the other.
 __device__ __forceinline__ float rows4_sum(float v) {
-    v += __shfl_xor(v, 16, WAVE);
-    v += __shfl_xor(v, 32, WAVE);
-    return v;
+    const uint32_t a = __builtin_bit_cast(uint32_t, v);
+    const auto r = __builtin_amdgcn_permlane16_swap(a, a, false, false);
+    const uint32_t r0 = r[0], r1 = r[1];
+    const uint32_t b = __builtin_bit_cast(uint32_t, __builtin_bit_cast(float, r0) + __builtin_bit_cast(float, r1));
+    const auto t = __builtin_amdgcn_permlane32_swap(b, b, false, false);
+    const uint32_t t0 = t[0], t1 = t[1];
+    return __builtin_bit_cast(float, t0) + __builtin_bit_cast(float, t1);
 }
 
 // Order-preserving map of a finite float onto uint32 (-0 and +0 map to the same key).

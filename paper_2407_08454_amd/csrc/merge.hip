@@ -96,6 +96,13 @@ __device__ __forceinline__ int first_set_at(const int32_t *sst, int M, int edge,
     return lo;
 }
 
+// LDS written by some lanes of a wave is read by others of the same wave after this: the hardware keeps a wave's LDS operations
+// in order, so it only holds the compiler.
+__device__ __forceinline__ void wave_lds_fence() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
 // Squared distance of 8 elements, summed over the 16 lanes of the row.
 __device__ __forceinline__ float sq_dist16(const float *kp, const float *x) {
     float d[8];
@@ -117,7 +124,7 @@ enum { MERGE_ADAPTIVE = 0, MERGE_FIXED = 1, MERGE_AVERAGE = 2 };
 // the same bits wherever it is merged.
 template <typename T, bool WITH_W, int MODE>
 __device__ __forceinline__ void merge_one_set(const T *Ks, const T *Vs, T *k_row, T *v_row, float *wo, int lo, int hi, int p,
-                                              const MergeArgs &a, int lane)
+                                              const MergeArgs &a, int lane, float *set_w)
 {
     using E = Elem<T>;
     using Raw = typename E::Raw;
@@ -183,20 +190,58 @@ __device__ __forceinline__ void merge_one_set(const T *Ks, const T *Vs, T *k_row
             inv_mean = dsum > 0.f ? (float)m / dsum : 0.f;
         }
         accumulate(lo, k0, v0);
+    } else if (MODE == MERGE_ADAPTIVE) {
+        // sweep 1: the distances to the pivot, kept in LDS for the weights, and their sum.  (With distances worked out again in
+        // sweep 2, sixteen times over in the lanes of a row, a lone wave's arithmetic took as long as its loads: us, before / now, this and
+        // the sums on swaps instead of LDS moves together, one slice of 512 fp32 tokens 15.1 / 13.6, 1 of 16000 17.4 / 14.2, 32 of 2000
+        // 31.8 / 29.4, 1600 of 500 in bf16, now four waves a SIMD instead of three, 115 / 103.)
+        E::to_float(kp_raw, kp);
+        float dsum = 0.f;
+        for (int j0 = lo; j0 < hi; j0 += 4 * U) {
+            Raw kr[U];
+            load_rows(Ks, j0, kr);
+            float acc = 0.f, mine = 0.f;                      // lane c of a row group keeps the distance of row group c
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                float x[8];
+                E::to_float(kr[u], x);
+                const float dist = __builtin_amdgcn_sqrtf(sq_dist16(kp, x));
+                acc += (j0 + 4 * u + slot < hi) ? dist : 0.f;
+                mine = c == u ? dist : mine;
+            }
+            dsum += acc;
+            if (c < U) set_w[j0 - lo + 4 * c + slot] = mine;
+        }
+        dsum = rows4_sum(dsum);
+        inv_mean = dsum > 0.f ? (float)m / dsum : 0.f;
+        wave_lds_fence();
+        // the weights, one row a lane; zero past the end of the set
+        for (int i = lane; i < ((m + 4 * U - 1) & -(4 * U)); i += WAVE) {
+            const float r = set_w[i] * inv_mean;
+            const float g = i < m ? __expf(-r * r) : 0.f;
+            set_w[i] = g;
+            if (WITH_W && i < m) wo[lo + i] = g;
+        }
+        wave_lds_fence();
+        // sweep 2: the weighted sums (K again, now from L2; V for the first time)
+        for (int j0 = lo; j0 < hi; j0 += 4 * U) {
+            Raw kr[U], vr[U];
+            load_rows(Ks, j0, kr);
+            load_rows(Vs, j0, vr);
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const float g = set_w[j0 - lo + 4 * u + slot];
+                float x[8], v[8];
+                E::to_float(kr[u], x);
+                E::to_float(vr[u], v);
+                gsum += g;
+#pragma unroll
+                for (int e = 0; e < 8; ++e) { ak[e] = fmaf(g, x[e], ak[e]); av[e] = fmaf(g, v[e], av[e]); }
+            }
+        }
+        wave_lds_fence();                                     // the next set's distances come to the same place
     } else {
         E::to_float(kp_raw, kp);
-        if (MODE == MERGE_ADAPTIVE) {
-            // sweep 1: sum of the distances to the pivot
-            float dsum = 0.f;
-            for (int j0 = lo; j0 < hi; j0 += 4 * U) {
-                Raw kr[U];
-                load_rows(Ks, j0, kr);
-                dsum += distances(j0, kr);
-            }
-            dsum = rows4_sum(dsum);
-            inv_mean = dsum > 0.f ? (float)m / dsum : 0.f;
-        }
-        // sweep 2: weights and weighted sums (K again, now from L2; V for the first time)
         for (int j0 = lo; j0 < hi; j0 += 4 * U) {
             Raw kr[U], vr[U];
             load_rows(Ks, j0, kr);
@@ -229,6 +274,7 @@ __global__ __launch_bounds__(MERGE_BLOCK) void merge_kernel(const T *__restrict_
     using E = Elem<T>;
     using Raw = typename E::Raw;
     constexpr int US = 4;                      // row groups (of 4 rows) in flight in runs of singleton sets
+    __shared__ float set_w[LONG_SET_MIN];      // (merge_one_set)
     int slice = blockIdx.x / a.tiles_per_slice, tile = blockIdx.x - slice * a.tiles_per_slice;
     const int group = slice / 8;
     if (a.tile == MERGE_TILE && a.tiles_per_slice <= MERGE_GROUPED_TILES && group < a.slices / 8) {
@@ -302,7 +348,7 @@ __global__ __launch_bounds__(MERGE_BLOCK) void merge_kernel(const T *__restrict_
         int p = __builtin_amdgcn_readlane(my_piv, i);
         p = min(max(p, lo), hi - 1);
         merge_one_set<T, WITH_W, MODE>(Ks, Vs, Ko + (size_t)(s_lo + i) * HEAD_DIM, Vo + (size_t)(s_lo + i) * HEAD_DIM, wo, lo, hi, p, a,
-                                       lane);
+                                       lane, set_w);
         ++i;
     }
 }
@@ -583,6 +629,7 @@ __global__ __launch_bounds__(REFRESH_BLOCK, 4) void refresh_kernel(const T *__re
     constexpr int MOVE_PER_GROUP = MovePerGroup<T>::value;
     constexpr int MOVE_BATCH = (REFRESH_BLOCK / 16) * MOVE_PER_GROUP;   // rows the workgroup moves per batch
     __shared__ int n_short, n_long, first_moved, any_up, any_down;
+    __shared__ float set_w[REFRESH_BLOCK / WAVE][LONG_SET_MIN];
     const int slice = blockIdx.x;
     const int tid = threadIdx.x, c = tid & 15, group = tid >> 4;
     const int n = clamp_len(a.seq_lens, slice / a.H, a.N);
@@ -692,7 +739,7 @@ __global__ __launch_bounds__(REFRESH_BLOCK, 4) void refresh_kernel(const T *__re
         const int lo = min(max(sst[s], 0), n), hi = min(max(sst[s + 1], 0), n);
         if (hi - lo <= 0 || hi - lo > LONG_SET_MIN) continue;
         const int p = min(max(piv[s], lo), hi - 1);
-        merge_one_set<T, false, MODE>(Ks, Vs, Ko + (size_t)s * HEAD_DIM, Vo + (size_t)s * HEAD_DIM, nullptr, lo, hi, p, a, lane);
+        merge_one_set<T, false, MODE>(Ks, Vs, Ko + (size_t)s * HEAD_DIM, Vo + (size_t)s * HEAD_DIM, nullptr, lo, hi, p, a, lane, set_w[tid >> 6]);
     }
 }
 
