@@ -12,7 +12,8 @@
 // are copied bit for bit.  HBM traffic: K once, V once, 2 M rows out.
 //
 // Kernels:
-//   merge_kernel        one wave per tile (merge_one_set per set, runs of singletons copied)
+//   merge_kernel        one wave per tile (merge_one_set per set, runs of singletons copied); in small launches
+//                       four tiles a workgroup, whose waves merge the longer sets together (merge_set_team)
 //   merge_long_kernel   the sets of more than LONG_SET_MIN tokens, one 1024-thread workgroup per slice
 //   refresh_kernel      decode time: compares the new maps with the previous ones, moves the rows of
 //                       unchanged sets in place and merges the changed sets again
@@ -22,7 +23,6 @@
 
 namespace kvm {
 
-constexpr int MERGE_BLOCK = 64;          // one wave per workgroup: waves finish independently
 // Tokens per wave (its sets are those that start in the tile).  A wave merges its sets one after the other, a
 // memory round trip or more for each, so short chains of many waves cover the latency better than long ones;
 // against them stands the look-up of the first set, two or three dependent loads a wave.  Measured, us, with
@@ -43,6 +43,13 @@ constexpr int MERGE_BLOCK = 64;          // one wave per workgroup: waves finish
 constexpr int MERGE_TILE_FEW = 16, MERGE_TILE = 32;
 constexpr long long MERGE_FEW_TOKENS = 1 << 18;
 constexpr int MERGE_GROUPED_TILES = 128;                     // per slice
+// In a small launch the longest set is what everything waits for: a wave takes about 1200 cycles for 16 of its rows and sweep, 15 us
+// for 250 tokens, when the median wave is done in one.  So up to 96 K tokens four waves share a workgroup, and after their
+// tiles merge the sets of more than SPLIT_SET_MIN tokens together, a quarter each.  us, one wave a workgroup / four: one slice of 512
+// fp32 tokens 13.8 / 10.8, 32 of 1000 20.9 / 16.2, of 2000 29.4 / 22.0, of 3000 27.6 / 25.9 (fp32 33.1 / 33.0), 8 of 8000 29.1 / 21.5;
+// beyond, where the waves of a workgroup that wait for the slowest leave their places empty: 100 of 1000 26.5 / 29.5, 32 of 4000
+// 26.6 / 28.7, 64 of 8000 75 / 91, 1024 of 4096 577 / 980.
+constexpr long long MERGE_TEAM_TOKENS = 3 << 15;
 // Sets of more than LONG_SET_MIN tokens are left to merge_long_kernel, which puts a whole workgroup
 // on each of them: one wave would stream such a set for hundreds of dependent round trips while
 // the rest of the chip has nothing to do (identical keys make one set of a whole slice).
@@ -119,165 +126,269 @@ __device__ __forceinline__ float sq_dist16(const float *kp, const float *x) {
 // branches and the compiler can interleave the independent rows.
 enum { MERGE_ADAPTIVE = 0, MERGE_FIXED = 1, MERGE_AVERAGE = 2 };
 
-// One set [lo, hi) of 1 .. LONG_SET_MIN tokens with pivot p (lo <= p < hi), merged by one wave into
-// the rows k_row, v_row.  Shared by merge_kernel and the refresh of single sets, so that a set gives
-// the same bits wherever it is merged.
-template <typename T, bool WITH_W, int MODE>
-__device__ __forceinline__ void merge_one_set(const T *Ks, const T *Vs, T *k_row, T *v_row, float *wo, int lo, int hi, int p,
-                                              const MergeArgs &a, int lane, float *set_w)
-{
+// Partial sums of a set, of the rows a lane has seen (8 columns of every fourth row): keys, values, weights.
+struct SetSums { float k[8], v[8], g; };
+__device__ __forceinline__ void clear(SetSums &s) {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) s.k[e] = s.v[e] = 0.f;
+    s.g = 0.f;
+}
+// a lane's sums in LDS: 17 floats, WAVE apart
+constexpr int PARKED = 17 * WAVE;
+__device__ __forceinline__ void park(const SetSums &s, float *at) {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) { at[e * WAVE] = s.k[e]; at[(8 + e) * WAVE] = s.v[e]; }
+    at[16 * WAVE] = s.g;
+}
+__device__ __forceinline__ void add_parked(SetSums &s, const float *at) {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) { s.k[e] += at[e * WAVE]; s.v[e] += at[(8 + e) * WAVE]; }
+    s.g += at[16 * WAVE];
+}
+
+// A set of more than SPLIT_SET_MIN tokens is summed in four parts, whole 16-row batches, and the parts are added
+// up in order: by one wave, one part after the other, or by four waves at once.  Either way a set gets the same bits.
+constexpr int SPLIT_SET_MIN = 128;
+constexpr int SPLIT_PARTS = 4;
+__device__ __forceinline__ int part_rows(int m) { return ((m + 15) / 16 + SPLIT_PARTS - 1) / SPLIT_PARTS * 16; }
+
+// The steps of merging one set [lo, hi) with pivot p, 16 rows at a time, each for its rows [from, to) (counted from lo, from a
+// multiple of 16).
+template <typename T, bool WITH_W, int MODE> struct SetMerge {
     using E = Elem<T>;
     using Raw = typename E::Raw;
-    constexpr int U = MergeUnroll<T>::value;   // row groups (of 4 rows) in flight
-    const int slot = lane >> 4;          // which of the four rows of an instruction
-    const int c = lane & 15;             // which 8-element chunk of the row
-    const int m = hi - lo;
-    const Raw kp_raw = E::load(Ks + (size_t)p * HEAD_DIM, c);
+    static constexpr int U = MergeUnroll<T>::value;            // row groups (of 4 rows) in flight
+    const T *Ks, *Vs;
+    float *wo;
+    const MergeArgs &a;
+    int lo, hi, lane, slot, c;                                 // slot: which of the four rows of an instruction; c: which 8-element chunk of the row
     float kp[8];
-    float ak[8], av[8], gsum = 0.f, inv_mean = 0.f;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) { ak[e] = 0.f; av[e] = 0.f; }
+
+    __device__ __forceinline__ SetMerge(const T *Ks, const T *Vs, float *wo, const MergeArgs &a, int lo, int hi, int lane)
+        : Ks(Ks), Vs(Vs), wo(wo), a(a), lo(lo), hi(hi), lane(lane), slot(lane >> 4), c(lane & 15) {}
     // Rows past the end of the set are clamped to its last row and given weight zero, so
     // that every lane runs the same straight-line code.
-    auto load_rows = [&](const T *base, int j0, Raw *r) {
+    __device__ __forceinline__ void load_rows(const T *base, int j0, Raw *r) const {
 #pragma unroll
         for (int u = 0; u < U; ++u) r[u] = E::load(base + (size_t)min(j0 + 4 * u + slot, hi - 1) * HEAD_DIM, c);
-    };
-    auto distances = [&](int j0, const Raw *kr) {
-        float acc = 0.f;
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            float x[8];
-            E::to_float(kr[u], x);
-            const float dist = __builtin_amdgcn_sqrtf(sq_dist16(kp, x));
-            acc += (j0 + 4 * u + slot < hi) ? dist : 0.f;
-        }
-        return acc;
-    };
-    // g_j = exp(-D_j^2 / (2 sigma^2)); with sigma = dsum / (sqrt(2) m) that is exp(-(D_j m / dsum)^2)
-    auto accumulate = [&](int j0, const Raw *kr, const Raw *vr) {
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int row = j0 + 4 * u + slot;
-            float x[8], v[8];
-            E::to_float(kr[u], x);
-            float g;
-            if (MODE == MERGE_AVERAGE) {
-                g = 1.f;
-            } else if (MODE == MERGE_FIXED) {
-                g = __expf(-sq_dist16(kp, x) * a.inv_two_sigma_sq);
-            } else {
-                const float r = __builtin_amdgcn_sqrtf(sq_dist16(kp, x)) * inv_mean;
-                g = __expf(-r * r);
-            }
-            g = row < hi ? g : 0.f;
-            gsum += g;
-            E::to_float(vr[u], v);
-#pragma unroll
-            for (int e = 0; e < 8; ++e) { ak[e] = fmaf(g, x[e], ak[e]); av[e] = fmaf(g, v[e], av[e]); }
-            if (WITH_W && c == 0 && row < hi) wo[row] = g;
-        }
-    };
-
-    if (m <= 4 * U) {
-        // the whole set is read once: all loads issued together, both sweeps from registers
-        Raw k0[U], v0[U];
-        load_rows(Ks, lo, k0);
-        load_rows(Vs, lo, v0);
-        E::to_float(kp_raw, kp);
-        if (MODE == MERGE_ADAPTIVE) {
-            const float dsum = rows4_sum(distances(lo, k0));
-            inv_mean = dsum > 0.f ? (float)m / dsum : 0.f;
-        }
-        accumulate(lo, k0, v0);
-    } else if (MODE == MERGE_ADAPTIVE) {
-        // sweep 1: the distances to the pivot, kept in LDS for the weights, and their sum.  (With distances worked out again in
-        // sweep 2, sixteen times over in the lanes of a row, a lone wave's arithmetic took as long as its loads: us, before / now, this and
-        // the sums on swaps instead of LDS moves together, one slice of 512 fp32 tokens 15.1 / 13.6, 1 of 16000 17.4 / 14.2, 32 of 2000
-        // 31.8 / 29.4, 1600 of 500 in bf16, now four waves a SIMD instead of three, 115 / 103.)
-        E::to_float(kp_raw, kp);
-        float dsum = 0.f;
-        for (int j0 = lo; j0 < hi; j0 += 4 * U) {
+    }
+    // distances to the pivot -> dist (LDS, one per row)
+    __device__ __forceinline__ void distances(int from, int to, float *dist) const {
+        for (int j0 = lo + from; j0 < lo + to; j0 += 4 * U) {
             Raw kr[U];
             load_rows(Ks, j0, kr);
-            float acc = 0.f, mine = 0.f;                      // lane c of a row group keeps the distance of row group c
+            float mine = 0.f;                                 // lane c of a row group keeps the distance of row group c
 #pragma unroll
             for (int u = 0; u < U; ++u) {
                 float x[8];
                 E::to_float(kr[u], x);
-                const float dist = __builtin_amdgcn_sqrtf(sq_dist16(kp, x));
-                acc += (j0 + 4 * u + slot < hi) ? dist : 0.f;
-                mine = c == u ? dist : mine;
+                const float d = __builtin_amdgcn_sqrtf(sq_dist16(kp, x));
+                mine = c == u ? d : mine;
             }
-            dsum += acc;
-            if (c < U) set_w[j0 - lo + 4 * c + slot] = mine;
+            if (c < U) dist[j0 - lo + 4 * c + slot] = mine;
         }
-        dsum = rows4_sum(dsum);
-        inv_mean = dsum > 0.f ? (float)m / dsum : 0.f;
-        wave_lds_fence();
-        // the weights, one row a lane; zero past the end of the set
-        for (int i = lane; i < ((m + 4 * U - 1) & -(4 * U)); i += WAVE) {
-            const float r = set_w[i] * inv_mean;
+    }
+    // g_j = exp(-D_j^2 / (2 sigma^2)); with sigma = dsum / (sqrt(2) m) that is exp(-(D_j m / dsum)^2).  One row a lane; zero past
+    // the end of the set.  From the distances of all rows.
+    __device__ __forceinline__ void weights(int from, int to, const float *dist, float *w) const {
+        const int m = hi - lo;
+        float dsum = 0.f;
+        for (int i = lane; i < m; i += WAVE) dsum += dist[i];
+        dsum = rows4_sum(row16_sum(dsum));
+        const float inv_mean = dsum > 0.f ? (float)m / dsum : 0.f;
+        for (int i = from + lane; i < ((to + 4 * U - 1) & -(4 * U)); i += WAVE) {
+            const float r = dist[i] * inv_mean;
             const float g = i < m ? __expf(-r * r) : 0.f;
-            set_w[i] = g;
+            w[i] = g;
             if (WITH_W && i < m) wo[lo + i] = g;
         }
-        wave_lds_fence();
-        // sweep 2: the weighted sums (K again, now from L2; V for the first time)
-        for (int j0 = lo; j0 < hi; j0 += 4 * U) {
+    }
+    // weighted sums; the weights from LDS, or for the fixed modes as they come
+    __device__ __forceinline__ void sums(int from, int to, const float *w, SetSums &s) const {
+        clear(s);
+        for (int j0 = lo + from; j0 < lo + to; j0 += 4 * U) {
             Raw kr[U], vr[U];
             load_rows(Ks, j0, kr);
             load_rows(Vs, j0, vr);
+            __builtin_amdgcn_sched_barrier(0);                // (left alone, the compiler saves registers by taking the groups one by one)
 #pragma unroll
             for (int u = 0; u < U; ++u) {
-                const float g = set_w[j0 - lo + 4 * u + slot];
-                float x[8], v[8];
+                const int row = j0 + 4 * u + slot;
+                float x[8], v[8], g;
                 E::to_float(kr[u], x);
+                if (MODE == MERGE_ADAPTIVE) {
+                    g = w[row - lo];
+                } else {
+                    g = MODE == MERGE_AVERAGE ? 1.f : __expf(-sq_dist16(kp, x) * a.inv_two_sigma_sq);
+                    g = row < hi ? g : 0.f;
+                    if (WITH_W && c == 0 && row < hi) wo[row] = g;
+                }
                 E::to_float(vr[u], v);
-                gsum += g;
+                s.g += g;
 #pragma unroll
-                for (int e = 0; e < 8; ++e) { ak[e] = fmaf(g, x[e], ak[e]); av[e] = fmaf(g, v[e], av[e]); }
+                for (int e = 0; e < 8; ++e) { s.k[e] = fmaf(g, x[e], s.k[e]); s.v[e] = fmaf(g, v[e], s.v[e]); }
+            }
+        }
+    }
+    // a set of up to 16 tokens is read once: all loads issued together, both sweeps from registers
+    __device__ __forceinline__ void sums_short(int p, SetSums &s) {
+        clear(s);
+        const Raw kp_raw = E::load(Ks + (size_t)p * HEAD_DIM, c);
+        Raw kr[U], vr[U];
+        load_rows(Ks, lo, kr);
+        load_rows(Vs, lo, vr);
+        E::to_float(kp_raw, kp);
+        float d[U], inv_mean = 0.f;
+        if (MODE != MERGE_AVERAGE) {
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                float x[8];
+                E::to_float(kr[u], x);
+                d[u] = sq_dist16(kp, x);
+            }
+        }
+        if (MODE == MERGE_ADAPTIVE) {
+            float dsum = 0.f;
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                d[u] = __builtin_amdgcn_sqrtf(d[u]);
+                dsum += lo + 4 * u + slot < hi ? d[u] : 0.f;
+            }
+            dsum = rows4_sum(dsum);
+            inv_mean = dsum > 0.f ? (float)(hi - lo) / dsum : 0.f;
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int row = lo + 4 * u + slot;
+            float x[8], v[8], g = 1.f;
+            if (MODE == MERGE_FIXED) g = __expf(-d[u] * a.inv_two_sigma_sq);
+            if (MODE == MERGE_ADAPTIVE) {
+                const float r = d[u] * inv_mean;
+                g = __expf(-r * r);
+            }
+            g = row < hi ? g : 0.f;
+            if (WITH_W && c == 0 && row < hi) wo[row] = g;
+            E::to_float(kr[u], x);
+            E::to_float(vr[u], v);
+            s.g += g;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) { s.k[e] = fmaf(g, x[e], s.k[e]); s.v[e] = fmaf(g, v[e], s.v[e]); }
+        }
+    }
+    __device__ __forceinline__ void load_pivot(int p) { E::to_float(E::load(Ks + (size_t)p * HEAD_DIM, c), kp); }
+    // the merged rows (each writer of a weight normalises its own: rows from lo + slot, of one wave)
+    __device__ __forceinline__ void finish(SetSums &s, T *k_row, T *v_row) const {
+        const int m = hi - lo;
+        const float inv_g = 1.f / rows4_sum(s.g);
+        const float vscale = a.value_scale ? inv_g * (float)m : inv_g;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            s.k[e] = rows4_sum(s.k[e]) * inv_g;
+            s.v[e] = rows4_sum(s.v[e]) * vscale;
+        }
+        // (the hint keeps the merged rows, which nothing reads soon, out of the caches that hold the keys for their second sweep and what is
+        // left of the inputs: merge of 128 slices of 2048 tokens 45.2 / 44.5 us without / with it, 64 of 4096 in fp32 83 / 71, 32 of 16000
+        // 85.5 / 74.5, 1600 of 500 114 / 107.5, 1024 of 4096 588 / 574)
+        if (slot == 0) E::store_stream(k_row, c, E::from_float(s.k));
+        if (slot == 1) E::store_stream(v_row, c, E::from_float(s.v));
+        if (WITH_W) {
+            for (int i = lane; i < m; i += WAVE) wo[lo + i] *= inv_g;
+        }
+    }
+};
+
+// One set [lo, hi) of 1 .. LONG_SET_MIN tokens with pivot p (lo <= p < hi), merged by one wave into
+// the rows k_row, v_row.  Shared by merge_kernel and the refresh of single sets, so that a set gives
+// the same bits wherever it is merged.  set_w: LDS of the wave, a float per token (a multiple of 16).
+// Sets of more than 16 tokens take two sweeps; the first leaves the distances in LDS, one lane a row turns them into weights, and the
+// second is multiply-adds.  (With distances worked out again in the second sweep, sixteen times over in the lanes of a row, a lone
+// wave's arithmetic took as long as its loads: us, before / now, this and the sums on swaps instead of LDS moves together, one slice
+// of 512 fp32 tokens 15.1 / 13.6, 1 of 16000 17.4 / 14.2, 32 of 2000 31.8 / 29.4, 1600 of 500 in bf16, now four waves a SIMD
+// instead of three, 115 / 103.)
+template <typename T, bool WITH_W, int MODE, bool ANY_LENGTH>
+__device__ __forceinline__ void merge_one_set(const T *Ks, const T *Vs, T *k_row, T *v_row, float *wo, int lo, int hi, int p,
+                                              const MergeArgs &a, int lane, float *set_w)
+{
+    SetMerge<T, WITH_W, MODE> set(Ks, Vs, wo, a, lo, hi, lane);
+    constexpr int BATCH = 4 * SetMerge<T, WITH_W, MODE>::U;
+    const int m = hi - lo;
+    SetSums s;
+    if (m <= BATCH) {
+        set.sums_short(p, s);
+    } else {
+        set.load_pivot(p);
+        if (MODE == MERGE_ADAPTIVE) {
+            set.distances(0, m, set_w);
+            wave_lds_fence();
+            set.weights(0, m, set_w, set_w);
+            wave_lds_fence();
+        }
+        if (!ANY_LENGTH || m <= SPLIT_SET_MIN) {
+            set.sums(0, m, set_w, s);
+        } else {
+            // (the running totals wait in LDS: in registers they cost every set of the kernel its fourth wave a SIMD, or spills)
+            float *total = set_w + LONG_SET_MIN + lane;
+            for (int from = 0;;) {
+                const int to = min(from + part_rows(m), m);
+                set.sums(from, to, set_w, s);
+                if (from > 0) add_parked(s, total);
+                if (to == m) break;
+                park(s, total);
+                from = to;
             }
         }
         wave_lds_fence();                                     // the next set's distances come to the same place
-    } else {
-        E::to_float(kp_raw, kp);
-        for (int j0 = lo; j0 < hi; j0 += 4 * U) {
-            Raw kr[U], vr[U];
-            load_rows(Ks, j0, kr);
-            load_rows(Vs, j0, vr);
-            accumulate(j0, kr, vr);
-        }
     }
-    gsum = rows4_sum(gsum);
-    const float inv_g = 1.f / gsum;
-    const float vscale = a.value_scale ? inv_g * (float)m : inv_g;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-        ak[e] = rows4_sum(ak[e]) * inv_g;
-        av[e] = rows4_sum(av[e]) * vscale;
+    if (WITH_W) wave_lds_fence();
+    set.finish(s, k_row, v_row);
+}
+
+// The same for a set of more than SPLIT_SET_MIN tokens by four waves of a workgroup, one part each.  All threads of the workgroup call
+// it together (barriers inside); a team without a set passes an empty one.
+struct TeamShared {
+    float dist[LONG_SET_MIN], w[LONG_SET_MIN];
+    float part[SPLIT_PARTS - 1][PARKED];
+};
+template <typename T, bool WITH_W, int MODE>
+__device__ __forceinline__ void merge_set_team(const T *Ks, const T *Vs, T *k_row, T *v_row, float *wo, int lo, int hi, int p,
+                                               const MergeArgs &a, int lane, int part_id, TeamShared &sh)
+{
+    SetMerge<T, WITH_W, MODE> set(Ks, Vs, wo, a, lo, hi, lane);
+    SetSums s;
+    const int from = part_id * part_rows(hi - lo), to = min(from + part_rows(hi - lo), hi - lo);   // (may be empty)
+    if (hi > lo) set.load_pivot(p);
+    if (MODE == MERGE_ADAPTIVE) {
+        set.distances(from, to, sh.dist);
+        __syncthreads();
+        if (hi > lo) set.weights(from, to, sh.dist, sh.w);
+        wave_lds_fence();                                     // a wave reads its own weights only
     }
-    // (the hint keeps the merged rows, which nothing reads soon, out of the caches that hold the keys for their second sweep and what is
-    // left of the inputs: merge of 128 slices of 2048 tokens 45.2 / 44.5 us without / with it, 64 of 4096 in fp32 83 / 71, 32 of 16000
-    // 85.5 / 74.5, 1600 of 500 114 / 107.5, 1024 of 4096 588 / 574)
-    if (slot == 0) E::store_stream(k_row, c, E::from_float(ak));
-    if (slot == 1) E::store_stream(v_row, c, E::from_float(av));
-    if (WITH_W && c == 0) {                                        // each writer normalises its own g_j
-        for (int row = lo + slot; row < hi; row += 4) wo[row] *= inv_g;
+    set.sums(from, to, sh.w, s);
+    if (MODE != MERGE_ADAPTIVE) __syncthreads();              // the first wave has taken the parts of the set before
+    if (part_id > 0) park(s, sh.part[part_id - 1] + lane);
+    __syncthreads();
+    if (part_id == 0 && hi > lo) {
+        for (int q = 0; q < SPLIT_PARTS - 1; ++q) add_parked(s, sh.part[q] + lane);
+        set.finish(s, k_row, v_row);
     }
 }
 
-template <typename T, bool WITH_W, int MODE>
-__global__ __launch_bounds__(MERGE_BLOCK) void merge_kernel(const T *__restrict__ K, const T *__restrict__ V,
+// WAVES 1: a wave is a workgroup of its own.  WAVES 4: four tiles a workgroup, whose waves then merge the sets of more than
+// SPLIT_SET_MIN tokens together.
+template <typename T, bool WITH_W, int MODE, int WAVES>
+__global__ __launch_bounds__(WAVES * WAVE, sizeof(T) == 2 ? 4 : 2) void merge_kernel(const T *__restrict__ K, const T *__restrict__ V,
                                                             T *__restrict__ K_out, T *__restrict__ V_out, MergeArgs a)
 {
     using E = Elem<T>;
     using Raw = typename E::Raw;
     constexpr int US = 4;                      // row groups (of 4 rows) in flight in runs of singleton sets
-    __shared__ float set_w[LONG_SET_MIN];      // (merge_one_set)
-    int slice = blockIdx.x / a.tiles_per_slice, tile = blockIdx.x - slice * a.tiles_per_slice;
+    constexpr bool TEAM = WAVES == SPLIT_PARTS;
+    __shared__ float set_w[WAVES][TEAM ? SPLIT_SET_MIN : LONG_SET_MIN + PARKED];   // (merge_one_set)
+    const int wave = TEAM ? (int)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6) : 0;
+    const int per_slice = (a.tiles_per_slice + WAVES - 1) / WAVES;        // workgroups
+    int slice = blockIdx.x / per_slice, tile = (blockIdx.x - slice * per_slice) * WAVES + wave;
     const int group = slice / 8;
-    if (a.tile == MERGE_TILE && a.tiles_per_slice <= MERGE_GROUPED_TILES && group < a.slices / 8) {
+    if (!TEAM && a.tile == MERGE_TILE && a.tiles_per_slice <= MERGE_GROUPED_TILES && group < a.slices / 8) {
         const int at = blockIdx.x - 8 * group * a.tiles_per_slice;
         slice = 8 * group + (at + group) % 8;
         tile = (at / 8 + group + group / 4 + group / 16) % a.tiles_per_slice;
@@ -287,8 +398,8 @@ __global__ __launch_bounds__(MERGE_BLOCK) void merge_kernel(const T *__restrict_
     const int c = lane & 15;             // which 8-element chunk of the row
     const int n = clamp_len(a.seq_lens, slice / a.H, a.N);
     const int edge = tile * a.tile;
-    if (edge >= n) return;
-    const int M = min(max(a.n_sets[slice], 0), a.cap_rows);
+    if (!TEAM && edge >= n) return;
+    const int M = edge < n ? min(max(a.n_sets[slice], 0), a.cap_rows) : 0;
     const int32_t *sst = a.set_start + (size_t)slice * (a.cap_rows + 1);
     const int32_t *piv = a.pivot + (size_t)slice * a.cap_rows;
     // lane i looks at set s_lo+i (the pivot is fetched along, before it is known to be needed); cnt sets from
@@ -298,7 +409,7 @@ __global__ __launch_bounds__(MERGE_BLOCK) void merge_kernel(const T *__restrict_
     const int my_piv = s_lo + lane < M ? piv[s_lo + lane] : 0;
     const unsigned long long beyond = ~__ballot(s_lo + lane < M && start_raw < edge + a.tile);
     const int cnt = beyond ? __builtin_ctzll(beyond) : WAVE;
-    if (cnt == 0) return;
+    if (!TEAM && cnt == 0) return;
 
     const T *Ks = K + (size_t)slice * a.N * HEAD_DIM;
     const T *Vs = V + (size_t)slice * a.N * HEAD_DIM;
@@ -311,6 +422,14 @@ __global__ __launch_bounds__(MERGE_BLOCK) void merge_kernel(const T *__restrict_
     if (cnt == WAVE && lane == WAVE - 1) my_next = min(max(sst[s_lo + WAVE], 0), n);
     const unsigned long long single_mask = __ballot(lane < cnt && my_next - my_start == 1);
 
+    struct Posted { int s, lo, hi, p; };
+    __shared__ Posted posted[TEAM ? WAVES * WAVE : 1];        // (a wave looks at no more than 64 sets)
+    __shared__ int n_posted;
+    __shared__ char team_mem[TEAM ? sizeof(TeamShared) : 1] __attribute__((aligned(16)));
+    if (TEAM) {
+        if (threadIdx.x == 0) n_posted = 0;
+        __syncthreads();
+    }
     int i = 0;
     while (i < cnt) {
         // ---- runs of singleton sets: plain copy, up to 4*U sets per step, all loads in flight ------
@@ -347,9 +466,24 @@ __global__ __launch_bounds__(MERGE_BLOCK) void merge_kernel(const T *__restrict_
         if (m <= 0 || m > LONG_SET_MIN) { ++i; continue; }                // inconsistent map: nothing to merge; long set: merge_long_kernel
         int p = __builtin_amdgcn_readlane(my_piv, i);
         p = min(max(p, lo), hi - 1);
-        merge_one_set<T, WITH_W, MODE>(Ks, Vs, Ko + (size_t)(s_lo + i) * HEAD_DIM, Vo + (size_t)(s_lo + i) * HEAD_DIM, wo, lo, hi, p, a,
-                                       lane, set_w);
+        if (TEAM && m > SPLIT_SET_MIN) {
+            if (lane == 0) posted[atomicAdd(&n_posted, 1)] = {s_lo + i, lo, hi, p};
+            ++i;
+            continue;
+        }
+        merge_one_set<T, WITH_W, MODE, !TEAM>(Ks, Vs, Ko + (size_t)(s_lo + i) * HEAD_DIM, Vo + (size_t)(s_lo + i) * HEAD_DIM, wo, lo, hi, p,
+                                              a, lane, set_w[wave]);
         ++i;
+    }
+    if constexpr (TEAM) {
+        __syncthreads();
+        const int n_team = n_posted;
+        for (int k = 0; k < n_team; ++k) {
+            const int s = __builtin_amdgcn_readfirstlane(posted[k].s), lo = __builtin_amdgcn_readfirstlane(posted[k].lo);
+            const int hi = __builtin_amdgcn_readfirstlane(posted[k].hi), p = __builtin_amdgcn_readfirstlane(posted[k].p);
+            merge_set_team<T, WITH_W, MODE>(Ks, Vs, Ko + (size_t)s * HEAD_DIM, Vo + (size_t)s * HEAD_DIM, wo, lo, hi, p, a, lane, wave,
+                                            *reinterpret_cast<TeamShared *>(team_mem));
+        }
     }
 }
 
@@ -512,23 +646,23 @@ __global__ __launch_bounds__(LONG_SET_BLOCK) __attribute__((amdgpu_waves_per_eu(
     }
 }
 
-template <typename T>
+template <typename T, int WAVES>
 static void launch_merge_t(const kvm_shape &sh, const void *K, const void *V, void *K_out, void *V_out,
                            const MergeArgs &a, hipStream_t st)
 {
-    const long long blocks = (long long)sh.B * sh.H_kv * a.tiles_per_slice;
+    const long long blocks = (long long)sh.B * sh.H_kv * ((a.tiles_per_slice + WAVES - 1) / WAVES);
     ProfScope prof("merge_kernel", st);
-    const dim3 grid((unsigned)blocks), block(MERGE_BLOCK);
-    const T *k = (const T *)K, *v = (const T *)V;
-    T *ko = (T *)K_out, *vo = (T *)V_out;
+    const auto run = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(WAVES * WAVE), 0, st, (const T *)K, (const T *)V, (T *)K_out, (T *)V_out, a);
+    };
     if (a.w_opt) {
-        if (a.mode == MERGE_AVERAGE) hipLaunchKernelGGL((merge_kernel<T, true, MERGE_AVERAGE>), grid, block, 0, st, k, v, ko, vo, a);
-        else if (a.mode == MERGE_FIXED) hipLaunchKernelGGL((merge_kernel<T, true, MERGE_FIXED>), grid, block, 0, st, k, v, ko, vo, a);
-        else hipLaunchKernelGGL((merge_kernel<T, true, MERGE_ADAPTIVE>), grid, block, 0, st, k, v, ko, vo, a);
+        if (a.mode == MERGE_AVERAGE) run(merge_kernel<T, true, MERGE_AVERAGE, WAVES>);
+        else if (a.mode == MERGE_FIXED) run(merge_kernel<T, true, MERGE_FIXED, WAVES>);
+        else run(merge_kernel<T, true, MERGE_ADAPTIVE, WAVES>);
     } else {
-        if (a.mode == MERGE_AVERAGE) hipLaunchKernelGGL((merge_kernel<T, false, MERGE_AVERAGE>), grid, block, 0, st, k, v, ko, vo, a);
-        else if (a.mode == MERGE_FIXED) hipLaunchKernelGGL((merge_kernel<T, false, MERGE_FIXED>), grid, block, 0, st, k, v, ko, vo, a);
-        else hipLaunchKernelGGL((merge_kernel<T, false, MERGE_ADAPTIVE>), grid, block, 0, st, k, v, ko, vo, a);
+        if (a.mode == MERGE_AVERAGE) run(merge_kernel<T, false, MERGE_AVERAGE, WAVES>);
+        else if (a.mode == MERGE_FIXED) run(merge_kernel<T, false, MERGE_FIXED, WAVES>);
+        else run(merge_kernel<T, false, MERGE_ADAPTIVE, WAVES>);
     }
 }
 
@@ -573,10 +707,11 @@ kvm_status launch_merge(const kvm_shape &sh, const kvm_params &pr, int cap_rows,
     a.mode = pr.weights == KVM_WEIGHTS_AVERAGE ? MERGE_AVERAGE : (pr.sigma_mode == KVM_SIGMA_FIXED ? MERGE_FIXED : MERGE_ADAPTIVE);
     a.inv_two_sigma_sq = a.mode == MERGE_FIXED ? 1.f / (2.f * pr.sigma * pr.sigma) : 0.f;
     a.value_scale = pr.value_scale_by_set_size;
+    const bool team = (long long)sh.B * sh.H_kv * sh.N <= MERGE_TEAM_TOKENS;
     switch (sh.dtype) {
-    case KVM_F32: launch_merge_t<float>(sh, K, V, K_out, V_out, a, st); break;
-    case KVM_F16: launch_merge_t<half_t>(sh, K, V, K_out, V_out, a, st); break;
-    default: launch_merge_t<bf16_t>(sh, K, V, K_out, V_out, a, st); break;
+    case KVM_F32: team ? launch_merge_t<float, 4>(sh, K, V, K_out, V_out, a, st) : launch_merge_t<float, 1>(sh, K, V, K_out, V_out, a, st); break;
+    case KVM_F16: team ? launch_merge_t<half_t, 4>(sh, K, V, K_out, V_out, a, st) : launch_merge_t<half_t, 1>(sh, K, V, K_out, V_out, a, st); break;
+    default: team ? launch_merge_t<bf16_t, 4>(sh, K, V, K_out, V_out, a, st) : launch_merge_t<bf16_t, 1>(sh, K, V, K_out, V_out, a, st); break;
     }
     kvm_status rc = check_launch("merge_kernel");
     if (rc != KVM_OK || sh.N <= LONG_SET_MIN) return rc;          // (no slice can hold a long set)
@@ -616,6 +751,7 @@ struct RefreshArgs {
     int32_t *n_changed;    // (slices) or NULL: sets merged again
 };
 
+constexpr int REFRESH_POSTED = 256;                          // sets that are merged again in one turn
 constexpr int REFRESH_BLOCK = 512;                           // two workgroups per compute unit (128 registers each)
 template <typename T> struct MovePerGroup { static constexpr int value = 16 / sizeof(T); };   // rows a 16-lane group moves per batch
 
@@ -629,7 +765,10 @@ __global__ __launch_bounds__(REFRESH_BLOCK, 4) void refresh_kernel(const T *__re
     constexpr int MOVE_PER_GROUP = MovePerGroup<T>::value;
     constexpr int MOVE_BATCH = (REFRESH_BLOCK / 16) * MOVE_PER_GROUP;   // rows the workgroup moves per batch
     __shared__ int n_short, n_long, first_moved, any_up, any_down;
-    __shared__ float set_w[REFRESH_BLOCK / WAVE][LONG_SET_MIN];
+    constexpr int TEAMS = REFRESH_BLOCK / WAVE / SPLIT_PARTS;
+    __shared__ float set_w[REFRESH_BLOCK / WAVE][SPLIT_SET_MIN];
+    __shared__ TeamShared team_mem[TEAMS];
+    __shared__ int posted[REFRESH_POSTED], n_posted;
     const int slice = blockIdx.x;
     const int tid = threadIdx.x, c = tid & 15, group = tid >> 4;
     const int n = clamp_len(a.seq_lens, slice / a.H, a.N);
@@ -730,16 +869,36 @@ __global__ __launch_bounds__(REFRESH_BLOCK, 4) void refresh_kernel(const T *__re
     if (moves_up || moves_down) __syncthreads();              // a row merged below may be one that was a source above
 
     // ---- merge the listed sets again -------------------------------------------------------------
-    const int lane = tid & 63;
+    // (a wave each; sets of more than SPLIT_SET_MIN tokens are left for teams of four waves)
+    const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const T *Ks = K + (size_t)slice * a.N * HEAD_DIM;
     const T *Vs = V + (size_t)slice * a.N * HEAD_DIM;
-    for (int k = tid >> 6; k < cnt; k += REFRESH_BLOCK / WAVE) {
-        const int s = list[1 + k];
-        if (s < 0 || s >= M) continue;                        // (the same for the whole wave)
-        const int lo = min(max(sst[s], 0), n), hi = min(max(sst[s + 1], 0), n);
-        if (hi - lo <= 0 || hi - lo > LONG_SET_MIN) continue;
-        const int p = min(max(piv[s], lo), hi - 1);
-        merge_one_set<T, false, MODE>(Ks, Vs, Ko + (size_t)s * HEAD_DIM, Vo + (size_t)s * HEAD_DIM, nullptr, lo, hi, p, a, lane, set_w[tid >> 6]);
+    for (int base = 0; base < cnt; base += REFRESH_POSTED) {  // (the same for the whole workgroup)
+        __syncthreads();                                      // the list of the turn before has been read
+        if (tid == 0) n_posted = 0;
+        __syncthreads();
+        for (int k = base + wave; k < min(base + REFRESH_POSTED, cnt); k += REFRESH_BLOCK / WAVE) {
+            const int s = __builtin_amdgcn_readfirstlane(list[1 + k]);
+            if (s < 0 || s >= M) continue;                    // (the same for the whole wave)
+            const int lo = min(max(sst[s], 0), n), hi = min(max(sst[s + 1], 0), n);
+            if (hi - lo <= 0 || hi - lo > LONG_SET_MIN) continue;
+            if (hi - lo > SPLIT_SET_MIN) {
+                if (lane == 0) posted[atomicAdd(&n_posted, 1)] = s;
+                continue;
+            }
+            const int p = min(max(piv[s], lo), hi - 1);
+            merge_one_set<T, false, MODE, false>(Ks, Vs, Ko + (size_t)s * HEAD_DIM, Vo + (size_t)s * HEAD_DIM, nullptr, lo, hi, p, a, lane,
+                                                 set_w[wave]);
+        }
+        __syncthreads();
+        const int n_team = n_posted;
+        for (int k = wave / SPLIT_PARTS; k < (n_team + TEAMS - 1) / TEAMS * TEAMS; k += TEAMS) {   // (as many turns for every team)
+            const int s = __builtin_amdgcn_readfirstlane(posted[min(k, n_team - 1)]);
+            const int lo = min(max(sst[s], 0), n), hi = k < n_team ? max(min(max(sst[s + 1], 0), n), lo) : lo;
+            const int p = max(min(max(piv[s], lo), hi - 1), 0);
+            merge_set_team<T, false, MODE>(Ks, Vs, Ko + (size_t)s * HEAD_DIM, Vo + (size_t)s * HEAD_DIM, nullptr, lo, min(hi, lo + LONG_SET_MIN), p, a,
+                                           lane, wave % SPLIT_PARTS, team_mem[wave / SPLIT_PARTS]);
+        }
     }
 }
 

@@ -997,6 +997,52 @@ def test_merge_gives_the_same_bits_for_every_tile_size(slices):
         assert torch.equal(Vo.view(torch.int16), buf.V_out[:, one].contiguous().view(torch.int16))
 
 
+@pytest.mark.parametrize("dtype", ["f16", "bf16", "f32"])
+@pytest.mark.parametrize("mode", ["adaptive", "fixed", "average"])
+def test_merge_gives_the_same_bits_by_one_wave_four_or_the_refresh(dtype, mode):
+    """Sets of more than 128 tokens are summed in four parts: by four waves in launches of up to 96 K tokens and in the
+    refresh, one after the other by one wave beyond.  Sizes at the edges of a batch, of the split and of its parts (the last
+    ones of which are empty for 129 to 144 tokens), rows and weights bit for bit the same, and the oracle's."""
+    _say(f"merge: the same bits by one wave, four and the refresh, {dtype} {mode}")
+    sizes = np.array([1, 16, 17, 2, 64, 65, 127, 128, 129, 144, 145, 1, 1, 160, 176, 177, 192, 193, 255, 256, 257, 31, 400, 497, 511, 512, 3])
+    n, M = int(sizes.sum()), len(sizes)
+    copies = 3 * 2 ** 15 // n + 1
+    dt = {"f32": torch.float32, "f16": torch.float16, "bf16": torch.bfloat16}[dtype]
+    rng = np.random.default_rng(5)
+    Q, K, V = _slices(36, 1, 1, [n], n, 128, 1, dtype, rho=0.9)
+    starts = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int32)
+    piv = (starts[:-1] + rng.integers(0, sizes)).astype(np.int32)
+    params = kb.make_params(1.0, 0.0, 0.0, enforce_budget=False)
+    if mode == "fixed":
+        params.sigma_mode, params.sigma = kb.KVM_SIGMA_FIXED, 9.0
+    if mode == "average":
+        params.weights = kb.KVM_WEIGHTS_AVERAGE
+    results = []
+    for S in (1, copies):
+        Kd, Vd = (gu.to_dev(x, dtype).expand(1, S, n, 128).contiguous() for x in (K, V))
+        sh = kb.make_shape(Kd, 1, None)
+        b = kb.Buffers(sh, params, "cuda", dt, with_debug=True)
+        for t, v, fill in ((b.set_start, starts, n), (b.pivot, piv, -1)):
+            t.fill_(fill)
+            t[0, :, :len(v)] = torch.from_numpy(v).cuda()
+        b.n_sets.fill_(M)
+        kb.kvm_merge(sh, params, Kd, Vd, b.set_start, b.pivot, b.n_sets, b.K_out, b.V_out, b.w, b.ws)
+        results.append([t[0, -1].clone() for t in (b.K_out[:, :, :M], b.V_out[:, :, :M], b.w)])
+        b.K_out.zero_()
+        b.V_out.zero_()
+        none = [torch.full_like(t, -1) for t in (b.set_id, b.set_start, b.pivot)] + [torch.zeros_like(b.n_sets)]
+        kb.kvm_merge_refresh(sh, params, Kd, Vd, *none, b.set_start, b.pivot, b.n_sets, b.K_out, b.V_out, None, b.ws)
+        results.append([t[0, -1].clone() for t in (b.K_out[:, :, :M], b.V_out[:, :, :M])])
+    for other in results[1:]:
+        for name, x, y in zip("KVw", results[0], other):
+            assert torch.equal(x, y), name
+    rk, rv, _ = ref.merge(K, V, dtype, starts[None, None], piv[None, None], np.full((1, 1), M, np.int32), sigma_mode=params.sigma_mode,
+                          sigma=params.sigma, weights=params.weights)
+    for got, want in zip(results[0], (rk, rv)):
+        err = np.abs(got.double().cpu().numpy() - want[0, 0, :M]).max(axis=-1) / np.abs(want[0, 0, :M]).max(axis=-1)
+        assert err.max() <= gu.TOL + 2.0 ** (-8 if dtype == "bf16" else -11)      # fp32 arithmetic, one rounding to the cache type
+
+
 @pytest.mark.parametrize("N,copies,rows", [(1, 20200, 13), (40, 600, 13), (100, 210, 13), (256, 80, 13), (700, 29, 13), (4096, 22, 3), (4097, 22, 3)])
 def test_merge_of_large_launches_of_short_slices(N, copies, rows):
     """Launches of more than 2^18 tokens deal out slices of up to 128 tiles in groups of eight, each group starting at
