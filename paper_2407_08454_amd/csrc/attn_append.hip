@@ -12,7 +12,7 @@
 //                             (base-2 logarithm units) go to the workspace, with the maximum
 //                             and the sum of exponentials of every wave's 64 keys beside them
 //                             (no exchange between waves, so no barrier).
-//   append_accumulate_kernel  merges the waves' statistics of a query head into its
+//   append_accumulate_kernel  merges the pieces' statistics of every query head into its
 //                             log-sum-exp and adds exp2(score - lse) of all G heads to mass.
 #include "kvm_common.h"
 
@@ -21,7 +21,8 @@ namespace kvm {
 constexpr int APP_BLOCK = 256;
 constexpr int APP_ROWS_PER_GROUP = 16;                      // one row per lane of the group in the end
 constexpr int APP_WAVES = APP_BLOCK / WAVE;
-constexpr int ACC_PER_THREAD = 8;                           // keys per thread of the second kernel
+constexpr int ACC_PER_THREAD = 4;                           // keys per thread of the second kernel
+constexpr int ACC_HEADS = 16;                               // query heads between two barriers of it
 constexpr int ACC_CHUNK = APP_BLOCK * ACC_PER_THREAD;
 
 int attn_lse_stride(int N);
@@ -82,58 +83,87 @@ __global__ __launch_bounds__(APP_BLOCK) void append_scores_kernel(const T *__res
     }
 }
 
+// log-sum-exp of a query row from the statistics of its 64-key pieces, by one wave (maximum first, sums scaled to it)
+__device__ __forceinline__ float row_lse(const float *st, int pieces) {
+    const int lane = threadIdx.x & 63;
+    float tm = -INFINITY;
+    for (int t = lane; t < pieces; t += WAVE) tm = fmaxf(tm, st[2 * t]);
+    const float m = wave_max(tm);
+    float tl = 0.f;
+    for (int t = lane; t < pieces; t += WAVE) tl += st[2 * t + 1] * __builtin_amdgcn_exp2f(st[2 * t] - m);
+    return m + __log2f(wave_sum(tl));
+}
+
+// The waves take the query heads in turn, ACC_HEADS between two barriers; a single head is worked out by every wave for itself.
+// (All waves on one head after the other with three barriers each, and eight keys a thread, before / now, us: 32 slices of 3000
+// keys, G = 4, 18.4 / 7.3; 8 of 1000, G = 8, 20.9 / 9.3; 64 of 16000, G = 2, 14.3 / 8.5; 1024 of 4096 18.2 / 15.2.)
 __global__ __launch_bounds__(APP_BLOCK) void append_accumulate_kernel(const float *__restrict__ scores,
                                                                        const float *__restrict__ stats, float *__restrict__ mass,
                                                                        const int32_t *__restrict__ seq_lens, int H, int G, int N,
                                                                        int n_pad, int chunks_per_slice)
 {
-    __shared__ float slots[2 * APP_WAVES];
+    __shared__ float lse_of[ACC_HEADS];
     const int slice = blockIdx.x / chunks_per_slice;
     const int chunk = blockIdx.x - slice * chunks_per_slice;
     const int n = clamp_len(seq_lens, slice / H, N);
     const int j_block = chunk * ACC_CHUNK;
     if (j_block >= n) return;
-    const int valid_tiles = (n + WAVE - 1) / WAVE;           // statistics come per 64 keys
+    const int pieces = (n + WAVE - 1) / WAVE;                // statistics come per 64 keys
     const int stats_per_row = n_pad / WAVE;
-    float add[ACC_PER_THREAD];
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const float *row = scores + (size_t)slice * G * n_pad, *st = stats + (size_t)slice * G * stats_per_row * 2;
+    float *a = mass + (size_t)slice * N;
+    float add[ACC_PER_THREAD], before[ACC_PER_THREAD];
 #pragma unroll
-    for (int u = 0; u < ACC_PER_THREAD; ++u) add[u] = 0.f;
-    for (int g = 0; g < G; ++g) {
-        const size_t qslice = (size_t)slice * G + g;
-        const float *st = stats + qslice * stats_per_row * 2;
-        // log-sum-exp of the row from the waves' statistics: threads take them in turn, then the
-        // workgroup reduces (two steps of the same rule: maximum first, sums scaled to it)
-        float tm = -INFINITY;
-        for (int t = threadIdx.x; t < valid_tiles; t += APP_BLOCK) tm = fmaxf(tm, st[2 * t]);
-        const float wm = wave_max(tm);
-        __syncthreads();
-        if ((threadIdx.x & 63) == 0) slots[threadIdx.x >> 6] = wm;
-        __syncthreads();
-        float m = slots[0];
-#pragma unroll
-        for (int i = 1; i < APP_WAVES; ++i) m = fmaxf(m, slots[i]);
-        float tl = 0.f;
-        for (int t = threadIdx.x; t < valid_tiles; t += APP_BLOCK) tl += st[2 * t + 1] * __builtin_amdgcn_exp2f(st[2 * t] - m);
-        const float wl = wave_sum(tl);
-        if ((threadIdx.x & 63) == 0) slots[APP_WAVES + (threadIdx.x >> 6)] = wl;
-        __syncthreads();
-        float l = 0.f;
-#pragma unroll
-        for (int i = 0; i < APP_WAVES; ++i) l += slots[APP_WAVES + i];
-        const float lse = m + __log2f(l);
+    for (int u = 0; u < ACC_PER_THREAD; ++u) {
+        const int j = j_block + u * APP_BLOCK + threadIdx.x;
+        add[u] = 0.f;
+        before[u] = j < n - 1 ? a[j] : 0.f;                  // the newest token's entry starts here
+    }
+    for (int g0 = 0; g0 < G; g0 += ACC_HEADS) {
+        const int heads = min(ACC_HEADS, G - g0);
+        float x[ACC_PER_THREAD];                             // the first head's scores, on their way meanwhile
 #pragma unroll
         for (int u = 0; u < ACC_PER_THREAD; ++u) {
             const int j = j_block + u * APP_BLOCK + threadIdx.x;
-            if (j < n) add[u] += __builtin_amdgcn_exp2f(scores[qslice * n_pad + j] - lse);
+            x[u] = j < n ? row[(size_t)g0 * n_pad + j] : -INFINITY;
+        }
+        float lse = 0.f;
+        if (heads == 1) {
+            lse = row_lse(st + (size_t)g0 * stats_per_row * 2, pieces);
+        } else {
+            if (g0 > 0) __syncthreads();                      // the heads before have been read
+            for (int g = wave; g < heads; g += APP_WAVES) {
+                const float v = row_lse(st + (size_t)(g0 + g) * stats_per_row * 2, pieces);
+                if (lane == 0) lse_of[g] = v;
+            }
+            __syncthreads();
+            lse = lse_of[0];
+        }
+        for (int g = 0;;) {
+            const float l = lse;
+            float next[ACC_PER_THREAD];
+            const bool more = g + 1 < heads;
+            if (more) {
+                lse = lse_of[g + 1];
+#pragma unroll
+                for (int u = 0; u < ACC_PER_THREAD; ++u) {
+                    const int j = j_block + u * APP_BLOCK + threadIdx.x;
+                    next[u] = j < n ? row[(size_t)(g0 + g + 1) * n_pad + j] : -INFINITY;
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < ACC_PER_THREAD; ++u) add[u] += __builtin_amdgcn_exp2f(x[u] - l);
+            if (!more) break;
+            ++g;
+#pragma unroll
+            for (int u = 0; u < ACC_PER_THREAD; ++u) x[u] = next[u];
         }
     }
 #pragma unroll
     for (int u = 0; u < ACC_PER_THREAD; ++u) {
         const int j = j_block + u * APP_BLOCK + threadIdx.x;
-        if (j < n) {
-            float *a = mass + (size_t)slice * N + j;
-            *a = j == n - 1 ? add[u] : *a + add[u];          // the newest token's entry starts here
-        }
+        if (j < n) a[j] = before[u] + add[u];
     }
 }
 
