@@ -110,26 +110,24 @@ __global__ __launch_bounds__(ATT_BLOCK, ATT_MIN_BLOCKS) void attn_lse_kernel(con
     const int b = qslice / HG;
     const int kvslice = b * (HG / G) + (qslice % HG) / G;
     const int n = clamp_len(seq_lens, b, N);
-    const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);     // scalar: per-wave branches stay scalar
     const T *Qs = Q + (size_t)qslice * N * HEAD_DIM;
     const T *Ks = K + (size_t)kvslice * N * HEAD_DIM;
-    const typename TL::Offsets off = TL::offsets(wave, lane);
-    const FragSlots fs = frag_slots<T>(lane);
 
-    // Workgroup t of a slice takes row tile tiles-1-t, the one with the longest rows left; with
+    // Workgroup t of a slice takes row tile used-1-t, the one with the longest rows left; with
     // fewer workgroups than tiles it then also takes tile t, the shortest left, so that all
-    // workgroups of a launch carry the same load.
+    // workgroups of a slice carry the same load (tiles past the slice's end are not counted: PairedTiles).
     // The repeat launch (redo given, no HOLD) has one workgroup per slice, which looks at all
     // of the slice's flags.
-    const bool paired = wgs_per_slice < tiles_per_slice;
+    const PairedTiles pt(n, ROWS_PER_BLOCK, tiles_per_slice, wgs_per_slice, tm.tile);
     const bool repeat = !HOLD && redo;
-    const int passes = repeat ? tiles_per_slice : 2;
+    const int passes = repeat ? pt.used : pt.count;
     for (int pass = 0; pass < passes; ++pass) {
-    const int tile = repeat ? pass : (pass == 0 ? tiles_per_slice - 1 - tm.tile : tm.tile);
-    if (!repeat && pass == 1 && (!paired || tm.tile >= tiles_per_slice - 1 - tm.tile)) break;
+    int lane = fresh_lane();
+    const typename TL::Offsets off = TL::offsets(wave, lane);
+    const FragSlots fs = frag_slots<T>(lane);
+    const int tile = repeat ? pass : (pass == 0 ? pt.used - 1 - tm.tile : tm.tile);
     const int q_begin = tile * ROWS_PER_BLOCK;
-    if (q_begin >= n) continue;
     if (repeat && !redo[(size_t)qslice * tiles_per_slice + tile]) continue;
     const int q0 = q_begin + wave * 32 * NB;                  // first query row of this wave
 
@@ -283,28 +281,20 @@ __global__ __launch_bounds__(ATT_BLOCK, ATT_MIN_BLOCKS) void attn_colsum_kernel(
     const int kvslice = tm.slice;
     const int b = kvslice / H, h = kvslice % H;
     const int n = clamp_len(seq_lens, b, N);
-    const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);     // scalar: per-wave branches stay scalar
     float *mass_s = mass + (size_t)kvslice * N;
     float *sim_s = sim_opt ? sim_opt + (size_t)kvslice * N : nullptr;
     const T *Ks = K + (size_t)kvslice * N * HEAD_DIM;
+    // workgroup t takes key tile t (tile 0 has the most rows below it) and, when there are fewer
+    // workgroups than tiles, then also tile used-1-t (see attn_lse_kernel)
+    const PairedTiles pt(n, KEYS_PER_BLOCK, tiles_per_slice, wgs_per_slice, tm.tile);
+    for (int pass = 0; pass < pt.count; ++pass) {
+    int lane = fresh_lane();
     const typename TL::Offsets off = TL::offsets(wave, lane);
     const FragSlots fs = frag_slots<T>(lane);
-    // workgroup t takes key tile t (tile 0 has the most rows below it) and, when there are fewer
-    // workgroups than tiles, then also tile tiles-1-t (see attn_lse_kernel)
-    const bool paired = wgs_per_slice < tiles_per_slice;
-    for (int pass = 0; pass < 2; ++pass) {
-    const int tile = pass == 0 ? tm.tile : tiles_per_slice - 1 - tm.tile;
-    if (pass == 1 && (!paired || tm.tile >= tiles_per_slice - 1 - tm.tile)) break;
+    const int tile = pass == 0 ? tm.tile : pt.used - 1 - tm.tile;
     const int k_begin = tile * KEYS_PER_BLOCK;
     const int k0 = k_begin + wave * 32 * NB;
-    if (k_begin >= n) {                                       // padding only: defined zeros
-        for (int j = k_begin + threadIdx.x; j < min(k_begin + KEYS_PER_BLOCK, N); j += ATT_BLOCK) {
-            mass_s[j] = 0.f;
-            if (sim_s) sim_s[j] = 0.f;
-        }
-        continue;
-    }
 
     // Query tiles first .. last see these keys.  They are streamed from the last one down, head
     // after head: every workgroup of a slice then starts at the same tile and walks down in step
@@ -427,6 +417,7 @@ __global__ __launch_bounds__(ATT_BLOCK, ATT_MIN_BLOCKS) void attn_colsum_kernel(
     }
     barrier_no_fence();                                       // everybody is done with LDS before the next tile's loads
     }
+    zero_padding(pt.used * KEYS_PER_BLOCK, N, tm.tile, wgs_per_slice, mass_s, sim_s);
 }
 
 // ------------------------------------------------------------------------------------------

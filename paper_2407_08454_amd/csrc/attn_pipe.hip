@@ -247,30 +247,22 @@ __global__ __launch_bounds__(ATT_BLOCK, PIPE_WGS_PER_CU) void attn_colsum_pipe_k
     const int kvslice = tm.slice;
     const int b = kvslice / H, h = kvslice % H;
     const int n = clamp_len(seq_lens, b, N);
-    const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     float *mass_s = mass + (size_t)kvslice * N;
     float *sim_s = sim_opt ? sim_opt + (size_t)kvslice * N : nullptr;
     const T *Ks = K + (size_t)kvslice * N * HEAD_DIM;
-    const int slot0 = frag_slot0(lane);
     int blk_of[PIPE_R];                                       // the wave's blocks, ascending (scalar)
 #pragma unroll
     for (int i = 0; i < PIPE_R; ++i) blk_of[i] = owned_block(wave, i);
 
     // workgroup t takes key tile t (the one with the most rows below it) and, when there are fewer
-    // workgroups than tiles, then also tile tiles-1-t, so that all workgroups carry the same load
-    const bool paired = wgs_per_slice < tiles_per_slice;
-    for (int pass = 0; pass < 2; ++pass) {
-    const int tile = pass == 0 ? tm.tile : tiles_per_slice - 1 - tm.tile;
-    if (pass == 1 && (!paired || tm.tile >= tiles_per_slice - 1 - tm.tile)) break;
+    // workgroups than tiles, then also tile used-1-t, so that all workgroups of a slice carry the same load
+    const PairedTiles pt(n, PIPE_ROWS, tiles_per_slice, wgs_per_slice, tm.tile);
+    for (int pass = 0; pass < pt.count; ++pass) {
+    int lane = fresh_lane();
+    const int slot0 = frag_slot0(lane);
+    const int tile = pass == 0 ? tm.tile : pt.used - 1 - tm.tile;
     const int k_begin = tile * PIPE_ROWS;
-    if (k_begin >= n) {                                       // padding only: defined zeros
-        for (int j = k_begin + threadIdx.x; j < min(k_begin + PIPE_ROWS, N); j += ATT_BLOCK) {
-            mass_s[j] = 0.f;
-            if (sim_s) sim_s[j] = 0.f;
-        }
-        continue;
-    }
     // Query tiles first .. last see these keys; tiles first .. first+7 hold the diagonal.  They are
     // streamed from the last one down, head after head: every workgroup of a slice starts at the
     // same tile and walks down in step with the others, so a tile is fetched from memory once.
@@ -378,6 +370,7 @@ __global__ __launch_bounds__(ATT_BLOCK, PIPE_WGS_PER_CU) void attn_colsum_pipe_k
     }
     barrier_no_fence();                                       // everybody is done with LDS before the next tile's loads
     }
+    zero_padding(pt.used * PIPE_ROWS, N, tm.tile, wgs_per_slice, mass_s, sim_s);
 }
 
 // ------------------------------------------------------------------------------------------

@@ -205,6 +205,37 @@ __device__ __forceinline__ TileMap map_block(int n_slices, int tiles_per_slice) 
     return m;
 }
 
+// The tiles of workgroup t of a slice: of the `used` tiles that hold tokens one, or, in launches with fewer workgroups than
+// tiles, two, the t-th longest and the t-th shortest (the middle one of an odd number alone).  They are counted off
+// from the slice's own last tile: paired over the N of the launch, the long tiles of a shorter slice met tiles that
+// hold nothing, and its other pairs stayed as long as those of the longest slice.  Both passes, us, paired over N / over
+// the slice's length (lengths 1, 3/4, 1/2, 1/4 of N): 24 slices of up to 2500 tokens, G = 4, row statistics 78 / 70; of up to 8000
+// 1196 / 1126; 256 of up to 16384 7621 / 7315; equal lengths as before.
+struct PairedTiles {
+    int used, count;                     // count: tiles of this workgroup (0: none left for it)
+    __device__ __forceinline__ PairedTiles(int n, int rows, int tiles_per_slice, int wgs_per_slice, int t) {
+        used = (n + rows - 1) / rows;
+        const int partner = used - 1 - t;
+        if (wgs_per_slice < tiles_per_slice) count = t < partner ? 2 : (t == partner ? 1 : 0);
+        else count = partner >= 0 ? 1 : 0;
+    }
+};
+
+// The lane number, read anew for each of a workgroup's tiles: what is computed from it then does not stay in registers, or
+// in scratch, across the tiles (spilled registers of the column sums 16 -> 7, of attn_colsum_pipe_kernel 11 -> 1: 2-3 % there).
+__device__ __forceinline__ int fresh_lane() {
+    int lane = threadIdx.x & 63;
+    asm volatile("" : "+v"(lane));
+    return lane;
+}
+
+// Scores (and similarities) of the tokens [first, N) that no tile holds: defined zeros, dealt to the slice's workgroups.
+__device__ __forceinline__ void zero_padding(int first, int N, int wg, int wgs, float *mass_s, float *sim_s) {
+    for (int j = first + wg * ATT_BLOCK + (int)threadIdx.x; j < N; j += wgs * ATT_BLOCK) {
+        mass_s[j] = 0.f;
+        if (sim_s) sim_s[j] = 0.f;
+    }
+}
 
 __device__ __forceinline__ float max16(const f32x16 &v) {
     const float a = fmaxf(fmaxf(v[0], v[1]), v[2]), b = fmaxf(fmaxf(v[3], v[4]), v[5]);
@@ -270,15 +301,15 @@ __device__ __forceinline__ RowStats load_rowstats(const float *lse_tile, int blk
     for (int r = 0; r < 4; ++r) L.v[r] = *reinterpret_cast<const f32x4 *>(&lse_tile[32 * blk + 8 * r + 4 * (lane >> 5)]);
     return L;
 }
-// part[0..1] += exp2(c * acc - L)
-__device__ __forceinline__ void colsum_update(const f32x16 &acc, const RowStats &L, float c, float *part) {
+// part[0..1] += exp2(c * acc - L), in place and one operation at a time: written as one expression a term, the block whose next
+// fragments are on their way was scheduled as thirteen chains of exp2, wait, add
+__device__ __forceinline__ void colsum_update(f32x16 &acc, const RowStats &L, float c, float *part) {
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
-        part[0] += __builtin_amdgcn_exp2f(fmaf(acc[4 * r], c, -L.v[r][0]));
-        part[1] += __builtin_amdgcn_exp2f(fmaf(acc[4 * r + 1], c, -L.v[r][1]));
-        part[0] += __builtin_amdgcn_exp2f(fmaf(acc[4 * r + 2], c, -L.v[r][2]));
-        part[1] += __builtin_amdgcn_exp2f(fmaf(acc[4 * r + 3], c, -L.v[r][3]));
-    }
+    for (int i = 0; i < 16; ++i) acc[i] = fmaf(acc[i], c, -L.v[i >> 2][i & 3]);
+#pragma unroll
+    for (int i = 0; i < 16; ++i) acc[i] = __builtin_amdgcn_exp2f(acc[i]);
+#pragma unroll
+    for (int i = 0; i < 16; i += 2) { part[0] += acc[i]; part[1] += acc[i + 1]; }
 }
 
 }  // namespace kvm

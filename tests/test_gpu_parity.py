@@ -190,6 +190,24 @@ def test_mass_large_scores_do_not_overflow():
         assert (np.abs(got - want)[big] / want[big]).max() <= gu.TOL
 
 
+@pytest.mark.parametrize("dtype,G,lens,N,copies,kernels", [
+    ("f16", 1, [2304, 0, 2048, 1, 1793, 1025, 257, 512], 2304, 7, ["attn_lse_kernel", "attn_colsum_kernel"]),
+    ("bf16", 2, [2100, 1800, 1, 0, 700, 2304], 2304, 9, ["attn_lse_kernel", "attn_colsum_kernel"]),
+    ("f32", 1, [1200, 0, 1, 1024, 897, 129], 1200, 5, ["attn_lse_kernel", "attn_colsum_kernel"]),
+    ("f16", 1, [8704, 0, 4097, 1, 513, 7000], 8704, 3, ["attn_lse_kernel", "attn_colsum_pipe_kernel"])])
+def test_mass_tiles_paired_within_a_slice(dtype, G, lens, N, copies, kernels):
+    """Full launches pair the long and the short tiles of every slice by its own length: even and odd numbers of tiles, one,
+    none.  Against the split kernels, which pair nothing (other order of N fp32 additions: 8 * 2^-24 sqrt(N) of a sum);
+    every padded token is a zero."""
+    _say(f"mass, paired tiles: {dtype} G={G} lens={lens} N={N} x{copies}")
+    Q, K, _ = _slices(29, len(lens), 1, lens, N, 128, G, dtype)
+    small = gu.gpu_mass(Q, K, dtype, G=G, seq_lens=lens)
+    full = gu.gpu_mass(Q, K, dtype, G=G, seq_lens=lens, copies=copies, kernels=kernels)
+    for b, n in enumerate(lens):
+        assert (full[b, :, n:] == 0).all() and (full[b, :, :n] > 0).all()
+        assert (np.abs(full[b, :, :n] - small[b, :, :n]) <= 8 * 2.0 ** -24 * math.sqrt(N) * small[b, :, :n]).all()
+
+
 @pytest.mark.parametrize("dtype,G,lens,N,copies", [
     ("f16", 1, [1], 1, 400), ("bf16", 1, [33, 31], 33, 240), ("f32", 1, [65, 32], 65, 80),   # edges of a 32-row block
     ("f16", 2, [97, 64, 0], 97, 140), ("bf16", 4, [300, 129, 0, 1, 256], 320, 50), ("f32", 4, [300, 129, 0, 1, 256], 320, 20),
