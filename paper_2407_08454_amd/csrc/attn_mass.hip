@@ -35,19 +35,6 @@ namespace kvm {
 // overlap of MFMA, exp2 and LDS traffic is left to the hardware interleaving the waves.
 // ------------------------------------------------------------------------------------------
 
-// pass 1 with the reference held: 16 more terms exp2(c s - mc) of a row's sum, no maximum and
-// no rescaling.  Any reference gives the same log-sum-exp as long as no term overflows; the
-// caller checks the finished sums for that.
-__device__ __forceinline__ void rowsum_held(const f32x16 &acc, float c, float mc, float &l_run) {
-    float p0 = __builtin_amdgcn_exp2f(fmaf(acc[0], c, -mc)), p1 = __builtin_amdgcn_exp2f(fmaf(acc[1], c, -mc));
-#pragma unroll
-    for (int i = 2; i < 16; i += 2) {
-        p0 += __builtin_amdgcn_exp2f(fmaf(acc[i], c, -mc));
-        p1 += __builtin_amdgcn_exp2f(fmaf(acc[i + 1], c, -mc));
-    }
-    l_run += p0 + p1;
-}
-
 constexpr int FRAG_BATCH = 2;            // A fragments fetched from LDS per batch of MFMAs (generic path)
 
 // one 32x32 block of scores: A fragments from the LDS tile, B fragments from registers

@@ -292,6 +292,19 @@ __device__ __forceinline__ void rowstat_update(const f32x16 &acc, float c, float
     m_run = m_new;
 }
 
+// pass 1 with the reference held: 16 more terms exp2(c s - mc) of a row's sum, no maximum and
+// no rescaling.  Any reference gives the same log-sum-exp as long as no term overflows; the
+// caller checks the finished sums for that.
+__device__ __forceinline__ void rowsum_held(const f32x16 &acc, float c, float mc, float &l_run) {
+    float p0 = __builtin_amdgcn_exp2f(fmaf(acc[0], c, -mc)), p1 = __builtin_amdgcn_exp2f(fmaf(acc[1], c, -mc));
+#pragma unroll
+    for (int i = 2; i < 16; i += 2) {
+        p0 += __builtin_amdgcn_exp2f(fmaf(acc[i], c, -mc));
+        p1 += __builtin_amdgcn_exp2f(fmaf(acc[i + 1], c, -mc));
+    }
+    l_run += p0 + p1;
+}
+
 // pass 2: the row statistics L of a 32-row block of the streamed tile, in the order of a
 // lane's accumulators (accumulator i of lane l is row 8*(i/4) + 4*(l/32) + i%4)
 struct RowStats { f32x4 v[4]; };

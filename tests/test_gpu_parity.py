@@ -190,6 +190,26 @@ def test_mass_large_scores_do_not_overflow():
         assert (np.abs(got - want)[big] / want[big]).max() <= gu.TOL
 
 
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+@pytest.mark.parametrize("orders", [40.0, 63.5, 64.5, 100.0, 126.9, 128.5, 300.0])
+def test_mass_split_held_reference(dtype, orders):
+    """The split row statistics hold a wave's reference from its first block on: late keys around and beyond the 2^64 at
+    which a workgroup starts again with the maximum updated, in one wave or in two, after it or on its last block."""
+    _say(f"mass, held reference: {dtype} {orders} binary orders")
+    n = 600
+    q, k = np.zeros((1, 3, n, 128), np.float32), np.zeros((1, 3, n, 128), np.float32)
+    q[:, :, :, 2] = 30.0
+    top = orders * math.sqrt(128.0) / (30.0 * math.log2(math.e))
+    k[0, 0, 300, 2] = top                                     # one wave sees it
+    k[0, 1, [200, 330], 2] = top                              # two waves, the other two stay with zeros
+    k[0, 2, [255, 575], 2] = top, 2 * top                     # again and higher, late
+    Q, K = synth.to_storage(q, dtype), synth.to_storage(k, dtype)
+    got, want = gu.gpu_mass(Q, K, dtype, kernels=["attn_lse_split_kernel"]), ref.attn_mass(Q, K, dtype)
+    big = want > 1e-6
+    assert np.isfinite(got).all() and (np.abs(got[big] - want[big]) / want[big]).max() <= gu.TOL
+    assert np.abs(got[~big]).max(initial=0.0) <= 2e-6
+
+
 @pytest.mark.parametrize("dtype,G,lens,N,copies,kernels", [
     ("f16", 1, [2304, 0, 2048, 1, 1793, 1025, 257, 512], 2304, 7, ["attn_lse_kernel", "attn_colsum_kernel"]),
     ("bf16", 2, [2100, 1800, 1, 0, 700, 2304], 2304, 9, ["attn_lse_kernel", "attn_colsum_kernel"]),
