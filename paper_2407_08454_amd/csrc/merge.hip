@@ -110,6 +110,14 @@ __device__ __forceinline__ void wave_lds_fence() {
     __builtin_amdgcn_wave_barrier();
 }
 
+// Chunk c of a row of a slice.  A slice has less than 2^32 bytes, so scalar base and 32-bit offset: half the address arithmetic and a
+// register instead of two.
+template <typename T>
+__device__ __forceinline__ typename Elem<T>::Raw row_chunk(const T *slice, int row, int c) {
+    const uint32_t at = (uint32_t)row * (uint32_t)(HEAD_DIM * sizeof(T)) + (uint32_t)c * (uint32_t)(8 * sizeof(T));
+    return Elem<T>::load(reinterpret_cast<const T *>(reinterpret_cast<const char *>(slice) + at), 0);
+}
+
 // Squared distance of 8 elements, summed over the 16 lanes of the row.
 __device__ __forceinline__ float sq_dist16(const float *kp, const float *x) {
     float d[8];
@@ -170,22 +178,35 @@ template <typename T, bool WITH_W, int MODE> struct SetMerge {
     // that every lane runs the same straight-line code.
     __device__ __forceinline__ void load_rows(const T *base, int j0, Raw *r) const {
 #pragma unroll
-        for (int u = 0; u < U; ++u) r[u] = E::load(base + (size_t)min(j0 + 4 * u + slot, hi - 1) * HEAD_DIM, c);
+        for (int u = 0; u < U; ++u) r[u] = row_chunk<T>(base, min(j0 + 4 * u + slot, hi - 1), c);
     }
     // distances to the pivot -> dist (LDS, one per row)
+    __device__ __forceinline__ void batch_distances(int j0, const Raw *kr, float *dist) const {
+        float mine = 0.f;                                     // lane c of a row group keeps the distance of row group c
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            float x[8];
+            E::to_float(kr[u], x);
+            const float d = __builtin_amdgcn_sqrtf(sq_dist16(kp, x));
+            mine = c == u ? d : mine;
+        }
+        if (c < U) dist[j0 - lo + 4 * c + slot] = mine;
+    }
+    // (two batches on their way at a time: there are registers for them here, not in the sums)
     __device__ __forceinline__ void distances(int from, int to, float *dist) const {
-        for (int j0 = lo + from; j0 < lo + to; j0 += 4 * U) {
+        int j0 = lo + from;
+        for (; j0 + 4 * U < lo + to; j0 += 8 * U) {
+            Raw kr[2][U];
+            load_rows(Ks, j0, kr[0]);
+            load_rows(Ks, j0 + 4 * U, kr[1]);
+            __builtin_amdgcn_sched_barrier(0);
+            batch_distances(j0, kr[0], dist);
+            batch_distances(j0 + 4 * U, kr[1], dist);
+        }
+        if (j0 < lo + to) {
             Raw kr[U];
             load_rows(Ks, j0, kr);
-            float mine = 0.f;                                 // lane c of a row group keeps the distance of row group c
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                float x[8];
-                E::to_float(kr[u], x);
-                const float d = __builtin_amdgcn_sqrtf(sq_dist16(kp, x));
-                mine = c == u ? d : mine;
-            }
-            if (c < U) dist[j0 - lo + 4 * c + slot] = mine;
+            batch_distances(j0, kr, dist);
         }
     }
     // g_j = exp(-D_j^2 / (2 sigma^2)); with sigma = dsum / (sqrt(2) m) that is exp(-(D_j m / dsum)^2).  One row a lane; zero past
@@ -204,36 +225,63 @@ template <typename T, bool WITH_W, int MODE> struct SetMerge {
         }
     }
     // weighted sums; the weights from LDS, or for the fixed modes as they come
-    __device__ __forceinline__ void sums(int from, int to, const float *w, SetSums &s) const {
-        clear(s);
+    __device__ __forceinline__ void batch_sums(int j0, const Raw *kr, const Raw *vr, const float *w, SetSums &s) const {
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int row = j0 + 4 * u + slot;
+            float x[8], v[8], g;
+            E::to_float(kr[u], x);
+            if (MODE == MERGE_ADAPTIVE) {
+                g = w[row - lo];
+            } else {
+                g = MODE == MERGE_AVERAGE ? 1.f : __expf(-sq_dist16(kp, x) * a.inv_two_sigma_sq);
+                g = row < hi ? g : 0.f;
+                if (WITH_W && c == 0 && row < hi) wo[row] = g;
+            }
+            E::to_float(vr[u], v);
+            s.g += g;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) { s.k[e] = fmaf(g, x[e], s.k[e]); s.v[e] = fmaf(g, v[e], s.v[e]); }
+        }
+    }
+    __device__ __forceinline__ void add_sums(int from, int to, const float *w, SetSums &s) const {
         for (int j0 = lo + from; j0 < lo + to; j0 += 4 * U) {
             Raw kr[U], vr[U];
             load_rows(Ks, j0, kr);
             load_rows(Vs, j0, vr);
             __builtin_amdgcn_sched_barrier(0);                // (left alone, the compiler saves registers by taking the groups one by one)
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const int row = j0 + 4 * u + slot;
-                float x[8], v[8], g;
-                E::to_float(kr[u], x);
-                if (MODE == MERGE_ADAPTIVE) {
-                    g = w[row - lo];
-                } else {
-                    g = MODE == MERGE_AVERAGE ? 1.f : __expf(-sq_dist16(kp, x) * a.inv_two_sigma_sq);
-                    g = row < hi ? g : 0.f;
-                    if (WITH_W && c == 0 && row < hi) wo[row] = g;
-                }
-                E::to_float(vr[u], v);
-                s.g += g;
-#pragma unroll
-                for (int e = 0; e < 8; ++e) { s.k[e] = fmaf(g, x[e], s.k[e]); s.v[e] = fmaf(g, v[e], s.v[e]); }
-            }
+            batch_sums(j0, kr, vr, w, s);
         }
+    }
+    __device__ __forceinline__ void sums(int from, int to, const float *w, SetSums &s) const {
+        clear(s);
+        add_sums(from, to, w, s);
+    }
+    // A set of two batches (17 .. 32 tokens): the second batch stays in registers from the distances to the sums, with its values, so half
+    // the keys are read once, and the first one's second read is a batch after its first.  (Both batches in registers spill, 29 to
+    // 50 of them, and so does the first batch's reload if it may start before the second's sums: hence the fence.  A last batch
+    // kept for every length helps these and hurts the longer ones: 1024 slices of up to 16384 tokens 1216 / 1317.)  us, two
+    // sweeps / this, the two batches on their way in distances and the 32-bit row offsets together: 1024 slices of 4096 565 / 547,
+    // 256 of them 161 / 152, 1600 of 4096 in bf16 780 / 760, 1600 of 500 116 / 108, 64 of 4096 in fp32 72.6 / 68.8.
+    __device__ __forceinline__ void sums_pair(int p, float *set_w, SetSums &s) {
+        Raw k1[U], v1[U];
+        load_rows(Ks, lo + 4 * U, k1);
+        load_rows(Vs, lo + 4 * U, v1);
+        load_pivot(p);
+        distances(0, 4 * U, set_w);
+        batch_distances(lo + 4 * U, k1, set_w);
+        wave_lds_fence();
+        weights(0, hi - lo, set_w, set_w);
+        wave_lds_fence();
+        clear(s);
+        batch_sums(lo + 4 * U, k1, v1, set_w, s);
+        __builtin_amdgcn_sched_barrier(0);
+        add_sums(0, 4 * U, set_w, s);
     }
     // a set of up to 16 tokens is read once: all loads issued together, both sweeps from registers
     __device__ __forceinline__ void sums_short(int p, SetSums &s) {
         clear(s);
-        const Raw kp_raw = E::load(Ks + (size_t)p * HEAD_DIM, c);
+        const Raw kp_raw = row_chunk<T>(Ks, p, c);
         Raw kr[U], vr[U];
         load_rows(Ks, lo, kr);
         load_rows(Vs, lo, vr);
@@ -275,7 +323,7 @@ template <typename T, bool WITH_W, int MODE> struct SetMerge {
             for (int e = 0; e < 8; ++e) { s.k[e] = fmaf(g, x[e], s.k[e]); s.v[e] = fmaf(g, v[e], s.v[e]); }
         }
     }
-    __device__ __forceinline__ void load_pivot(int p) { E::to_float(E::load(Ks + (size_t)p * HEAD_DIM, c), kp); }
+    __device__ __forceinline__ void load_pivot(int p) { E::to_float(row_chunk<T>(Ks, p, c), kp); }
     // the merged rows (each writer of a weight normalises its own: rows from lo + slot, of one wave)
     __device__ __forceinline__ void finish(SetSums &s, T *k_row, T *v_row) const {
         const int m = hi - lo;
@@ -315,6 +363,9 @@ __device__ __forceinline__ void merge_one_set(const T *Ks, const T *Vs, T *k_row
     SetSums s;
     if (m <= BATCH) {
         set.sums_short(p, s);
+    } else if (MODE == MERGE_ADAPTIVE && m <= 2 * BATCH) {
+        set.sums_pair(p, set_w, s);
+        wave_lds_fence();
     } else {
         set.load_pivot(p);
         if (MODE == MERGE_ADAPTIVE) {
@@ -434,8 +485,8 @@ __global__ __launch_bounds__(WAVES * WAVE, sizeof(T) == 2 ? 4 : 2) void merge_ke
     while (i < cnt) {
         // ---- runs of singleton sets: plain copy, up to 4*U sets per step, all loads in flight ------
         if ((single_mask >> i) & 1ull) {
-            int run = 1;
-            while (run < 4 * US && i + run < cnt && ((single_mask >> (i + run)) & 1ull)) ++run;
+            const unsigned long long others = ~(single_mask >> i);        // (no bit of the mask is set beyond cnt)
+            const int run = min(others ? __builtin_ctzll(others) : WAVE, 4 * US);
             Raw rk[US], rv[US];
             int src[US];
 #pragma unroll
@@ -443,8 +494,8 @@ __global__ __launch_bounds__(WAVES * WAVE, sizeof(T) == 2 ? 4 : 2) void merge_ke
                 const int r = 4 * u + slot;
                 src[u] = __shfl(my_start, i + min(r, run - 1), WAVE);
                 if (r < run) {
-                    rk[u] = E::load(Ks + (size_t)src[u] * HEAD_DIM, c);
-                    rv[u] = E::load(Vs + (size_t)src[u] * HEAD_DIM, c);
+                    rk[u] = row_chunk<T>(Ks, src[u], c);
+                    rv[u] = row_chunk<T>(Vs, src[u], c);
                 }
             }
 #pragma unroll

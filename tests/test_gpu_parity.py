@@ -1081,6 +1081,41 @@ def test_merge_gives_the_same_bits_by_one_wave_four_or_the_refresh(dtype, mode):
         assert err.max() <= gu.TOL + 2.0 ** (-8 if dtype == "bf16" else -11)      # fp32 arithmetic, one rounding to the cache type
 
 
+@pytest.mark.parametrize("dtype", ["f16", "bf16", "f32"])
+def test_merge_sets_of_two_batches(dtype):
+    """Sets of 17 to 32 tokens keep their second batch in registers: all sizes around them, the pivot in either batch, rows
+    the same with and without the weights written, by the refresh, and the oracle's (fp32 sums, one rounding to the type)."""
+    _say(f"merge: sets of two batches, {dtype}")
+    rng = np.random.default_rng(8)
+    sizes = np.concatenate([np.arange(14, 36), [1, 1, 1], np.arange(35, 13, -1), [48, 49]])
+    n, M = int(sizes.sum()), len(sizes)
+    Q, K, V = _slices(41, 1, 1, [n], n, 128, 1, dtype, rho=0.9)
+    starts = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int32)
+    piv = (starts[:-1] + rng.integers(0, sizes)).astype(np.int32)
+    params = kb.make_params(1.0, 0.0, 0.0, enforce_budget=False)
+    Kd, Vd = gu.to_dev(K, dtype), gu.to_dev(V, dtype)
+    sh = kb.make_shape(Kd, 1, None)
+    b = kb.Buffers(sh, params, "cuda", Kd.dtype, with_debug=True)
+    for t, v, fill in ((b.set_start, starts, n), (b.pivot, piv, -1)):
+        t.fill_(fill)
+        t[0, 0, :len(v)] = torch.from_numpy(v).cuda()
+    b.n_sets.fill_(M)
+    results = []
+    for w in (b.w, None):
+        kb.kvm_merge(sh, params, Kd, Vd, b.set_start, b.pivot, b.n_sets, b.K_out, b.V_out, w, b.ws)
+        results.append([t[0, 0, :M].clone() for t in (b.K_out, b.V_out)])
+    none = [torch.full_like(t, -1) for t in (b.set_id, b.set_start, b.pivot)] + [torch.zeros_like(b.n_sets)]
+    kb.kvm_merge_refresh(sh, params, Kd, Vd, *none, b.set_start, b.pivot, b.n_sets, b.K_out, b.V_out, None, b.ws)
+    results.append([t[0, 0, :M].clone() for t in (b.K_out, b.V_out)])
+    for other in results[1:]:
+        assert all(torch.equal(x, y) for x, y in zip(results[0], other))
+    rk, rv, rw = ref.merge(K, V, dtype, starts[None, None], piv[None, None], np.full((1, 1), M, np.int32))
+    for got, want in zip(results[0], (rk, rv)):
+        err = np.abs(got.double().cpu().numpy() - want[0, 0, :M]).max(axis=-1) / np.abs(want[0, 0, :M]).max(axis=-1)
+        assert err.max() <= gu.TOL + 2.0 ** (-8 if dtype == "bf16" else -11)
+    assert np.abs(b.w.cpu().numpy() - rw).max() <= gu.TOL
+
+
 @pytest.mark.parametrize("N,copies,rows", [(1, 20200, 13), (40, 600, 13), (100, 210, 13), (256, 80, 13), (700, 29, 13), (4096, 22, 3), (4097, 22, 3)])
 def test_merge_of_large_launches_of_short_slices(N, copies, rows):
     """Launches of more than 2^18 tokens deal out slices of up to 128 tiles in groups of eight, each group starting at
