@@ -2,6 +2,7 @@
 // (few slices, short sequences; Section 2.4 Eq. (1), Section 4.2 Eq. (7)).
 //
 //   attn_lse_split_kernel     row log-sum-exps, L_t = log2 sum_j exp2(c s_tj)
+//   attn_lse_split16_kernel, attn_colsum_split16_kernel  the same with 16 rows a workgroup, the smallest fp32 launches
 //   attn_colsum_split_kernel  column sums, mass_j = sum_g sum_{t>=j} exp2(c s_tj - L_t)
 //
 // What bounds such a launch is the longest serial chain of a workgroup and the number of idle compute
@@ -296,8 +297,207 @@ __global__ __launch_bounds__(W * WAVE, sizeof(T) == 2 && W == 4 ? 2 : 1) void at
 }
 
 // ------------------------------------------------------------------------------------------
+// fp32, the smallest launches: 16 rows a workgroup
+// ------------------------------------------------------------------------------------------
+//
+// In fp32 the chain of a workgroup is matrix time: a 32x32 block is 64 MFMAs of 64 cycles on the one pipe of a wave, and more waves
+// share the same four pipes.  What shortens it is more compute units: blocks of 16x16 (32 MFMAs 16x16x4 of 32 cycles, the same
+// rate) put half the rows on each of twice as many workgroups, against twice the tile traffic.
+struct Rows16 {
+    static constexpr int CH = 32;                            // 16-byte chunks per row
+    static constexpr int SLOTS = 16 * CH;
+    static constexpr int FRAGS = 8;                          // fragment f of lane l: chunk 4 f + l / 16 of row l % 16
+    // rows [row0, row0+16) of the matrix at `base` -> a stage, swizzled; rows past n_valid repeat the last valid one
+    static __device__ __forceinline__ void issue(const float *base, int row0, int n_valid, u32x4 *stage, int lane) {
+        const int last = n_valid - 1 - row0;
+        const char *first_row = reinterpret_cast<const char *>(base + (size_t)row0 * HEAD_DIM);
+#pragma unroll
+        for (int i = 0; i < SLOTS / WAVE; ++i) {
+            const int row = 2 * i + lane / CH, pos = lane % CH;
+            const uint32_t off = (uint32_t)(min(row, last) * (HEAD_DIM * 4) + ((pos ^ row) * 16));
+            __builtin_amdgcn_global_load_lds((gptr_t)(first_row + off), (lptr_t)(stage + i * WAVE), 16, 0, 0);
+        }
+    }
+    static __device__ __forceinline__ u32x4 frag(const u32x4 *stage, int f, int lane) {
+        const int row = lane & 15;
+        return stage[row * CH + ((4 * f + (lane >> 4)) ^ row)];
+    }
+    static __device__ __forceinline__ void stationary(const float *base, int row0, int n_valid, int lane, u32x4 *frags) {
+        const int row = row0 + (lane & 15);
+#pragma unroll
+        for (int f = 0; f < FRAGS; ++f) {
+            u32x4 v = {0u, 0u, 0u, 0u};
+            if (row < n_valid)
+                v = *reinterpret_cast<const u32x4 *>(reinterpret_cast<const char *>(base + (size_t)row * HEAD_DIM) + (4 * f + (lane >> 4)) * 16);
+            frags[f] = v;
+        }
+    }
+    // Result i of lane l is streamed row 4 (l / 16) + i, stationary row l % 16.  (Two chains: an MFMA does not wait for the one before.)
+    static __device__ __forceinline__ f32x4 scores(const u32x4 *stage, const u32x4 *b, int lane) {
+        u32x4 a[FRAGS];
+#pragma unroll
+        for (int f = 0; f < FRAGS; ++f) a[f] = frag(stage, f, lane);
+        f32x4 acc[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+#pragma unroll
+        for (int f = 0; f < FRAGS; ++f)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const uint32_t ai = a[f][i], bi = b[f][i];
+                acc[i & 1] = __builtin_amdgcn_mfma_f32_16x16x4f32(__builtin_bit_cast(float, ai), __builtin_bit_cast(float, bi), acc[i & 1], 0, 0, 0);
+            }
+        return acc[0] + acc[1];
+    }
+};
+
+template <int W>
+__global__ __launch_bounds__(W * WAVE, 1) void attn_lse_split16_kernel(
+    const float *__restrict__ Q, const float *__restrict__ K, float *__restrict__ lse, const int32_t *__restrict__ seq_lens,
+    int n_qslices, int HG, int G, int N, int n_pad, int tiles_per_slice, float c, float out_scale, float pad)
+{
+    __shared__ u32x4 lds_a[W][Rows16::SLOTS], lds_b[W][Rows16::SLOTS];
+    __shared__ float part_m[W][16], part_l[W][16];
+    const int lane = threadIdx.x & 63;
+    const int qslice = blockIdx.x % n_qslices;
+    const int tile = tiles_per_slice - 1 - (int)(blockIdx.x / n_qslices);    // the last tile has the longest rows
+    const int b = qslice / HG;
+    const int kvslice = b * (HG / G) + (qslice % HG) / G;
+    const int n = clamp_len(seq_lens, b, N);
+    const int q0 = tile * 16;
+    const int q = q0 + (int)threadIdx.x;
+    if (q0 >= n) {                                            // (the second pass may read them, in a streamed block of 32 rows)
+        if (threadIdx.x < 16 && q < n_pad) lse[(size_t)qslice * n_pad + q] = pad;
+        return;
+    }
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const float *Ks = K + (size_t)kvslice * N * HEAD_DIM;
+    const int count = tile + 1;                               // key blocks 0 .. tile, this wave's: wave, wave+W, ...
+    int next = wave;
+    auto issue_next = [&](u32x4 *stage) {
+        if (next < count) Rows16::issue(Ks, next * 16, n, stage, lane);
+        next += W;
+    };
+    issue_next(lds_a[wave]);
+    u32x4 qf[Rows16::FRAGS];
+    Rows16::stationary(Q + (size_t)qslice * N * HEAD_DIM, q0, n, lane, qf);
+    float m_run = M_INIT, l_run = 0.f;
+    auto step = [&](int t, const u32x4 *cur, u32x4 *nxt) {
+        wait_own_tile();
+        issue_next(nxt);
+        f32x4 s = Rows16::scores(cur, qf, lane);
+        if (t == tile) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                if (4 * (lane >> 4) + i > (lane & 15)) s[i] = -INFINITY;
+        }
+        const float m = fmaxf(m_run, fmaxf(fmaxf(s[0], s[1]), fmaxf(s[2], s[3])));
+        float p = 0.f;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) p += __builtin_amdgcn_exp2f(fmaf(s[i], c, -m * c));
+        l_run = l_run * __builtin_amdgcn_exp2f((m_run - m) * c) + p;
+        m_run = m;
+    };
+    for (int t = wave; t < count; t += 2 * W) {
+        step(t, lds_a[wave], lds_b[wave]);
+        if (t + W < count) step(t + W, lds_b[wave], lds_a[wave]);
+    }
+    // the four lanes l % 16 hold the quarters of a row's keys; then the waves are combined
+#pragma unroll
+    for (int off = 16; off <= 32; off *= 2) {
+        const float m_o = __shfl_xor(m_run, off, WAVE), l_o = __shfl_xor(l_run, off, WAVE);
+        const float m = fmaxf(m_run, m_o);
+        l_run = l_run * __builtin_amdgcn_exp2f((m_run - m) * c) + l_o * __builtin_amdgcn_exp2f((m_o - m) * c);
+        m_run = m;
+    }
+    if (lane < 16) { part_m[wave][lane] = m_run; part_l[wave][lane] = l_run; }
+    __syncthreads();
+    if (threadIdx.x < 16 && q < n_pad) {
+        float m = part_m[0][threadIdx.x];
+#pragma unroll
+        for (int w = 1; w < W; ++w) m = fmaxf(m, part_m[w][threadIdx.x]);
+        float l = 0.f;
+#pragma unroll
+        for (int w = 0; w < W; ++w) l += part_l[w][threadIdx.x] * __builtin_amdgcn_exp2f((part_m[w][threadIdx.x] - m) * c);
+        lse[(size_t)qslice * n_pad + q] = q < n ? (m * c + __log2f(l)) * out_scale : pad;
+    }
+}
+
+template <int W>
+__global__ __launch_bounds__(W * WAVE, 1) void attn_colsum_split16_kernel(
+    const float *__restrict__ Q, const float *__restrict__ K, const float *__restrict__ lse, float *__restrict__ mass,
+    const int32_t *__restrict__ seq_lens, int n_kvslices, int H, int G, int N, int n_pad, int tiles_per_slice, float c)
+{
+    __shared__ u32x4 lds_a[W][Rows16::SLOTS], lds_b[W][Rows16::SLOTS];
+    __shared__ __attribute__((aligned(16))) float lse_a[W][16], lse_b[W][16];
+    __shared__ float part_s[W][16];
+    const int lane = threadIdx.x & 63;
+    const int kvslice = blockIdx.x % n_kvslices, tile = blockIdx.x / n_kvslices;   // tile 0 has the most rows below it
+    const int b = kvslice / H, h = kvslice % H;
+    const int n = clamp_len(seq_lens, b, N);
+    const int k0 = tile * 16;
+    float *mass_s = mass + (size_t)kvslice * N;
+    const int key = k0 + (int)threadIdx.x;
+    if (k0 >= n) {                                            // padding only: defined zeros
+        if (threadIdx.x < 16 && key < N) mass_s[key] = 0.f;
+        return;
+    }
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    // the 16-row query blocks that see these keys, head after head (see attn_colsum_split_kernel)
+    const int per_head = (n + 15) / 16 - tile;
+    const int count = per_head * G;
+    int next = wave, next_g = wave / per_head, next_qb = wave % per_head;
+    auto issue_next = [&](u32x4 *stage, float *stage_lse) {
+        if (next < count) {
+            const size_t qslice = ((size_t)b * H + h) * G + next_g;
+            const int row0 = (tile + next_qb) * 16;
+            Rows16::issue(Q + qslice * N * HEAD_DIM, row0, n, stage, lane);
+            if (lane < 16)
+                __builtin_amdgcn_global_load_lds((gptr_t)(lse + qslice * n_pad + row0 + lane), (lptr_t)stage_lse, 4, 0, 0);
+        }
+        next += W;
+        next_qb += W;
+        while (next_qb >= per_head) { next_qb -= per_head; ++next_g; }
+    };
+    issue_next(lds_a[wave], lse_a[wave]);
+    u32x4 kf[Rows16::FRAGS];
+    Rows16::stationary(K + (size_t)kvslice * N * HEAD_DIM, k0, n, lane, kf);
+    float part = 0.f;
+    int qb_cur = wave % per_head;
+    auto step = [&](const u32x4 *cur, const float *cur_lse, u32x4 *nxt, float *nxt_lse) {
+        wait_own_tile();
+        issue_next(nxt, nxt_lse);
+        f32x4 s = Rows16::scores(cur, kf, lane);
+        const f32x4 L = *reinterpret_cast<const f32x4 *>(&cur_lse[4 * (lane >> 4)]);
+        if (qb_cur == 0) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                if (4 * (lane >> 4) + i < (lane & 15)) s[i] = -INFINITY;
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) part += __builtin_amdgcn_exp2f(fmaf(s[i], c, -L[i]));
+        qb_cur += W;
+        while (qb_cur >= per_head) qb_cur -= per_head;
+    };
+    for (int u = wave; u < count; u += 2 * W) {
+        step(lds_a[wave], lse_a[wave], lds_b[wave], lse_b[wave]);
+        if (u + W < count) step(lds_b[wave], lse_b[wave], lds_a[wave], lse_a[wave]);
+    }
+    part += __shfl_xor(part, 16, WAVE);
+    part += __shfl_xor(part, 32, WAVE);
+    if (lane < 16) part_s[wave][lane] = part;
+    __syncthreads();
+    if (threadIdx.x < 16 && key < N) {
+        float total = 0.f;
+#pragma unroll
+        for (int w = 0; w < W; ++w) total += part_s[w][threadIdx.x];
+        mass_s[key] = key < n ? total : 0.f;
+    }
+}
+
+// ------------------------------------------------------------------------------------------
 // host launchers
 // ------------------------------------------------------------------------------------------
+
+constexpr int SPLIT16 = 16;              // added to the waves: the fp32 kernels of 16 rows
 
 // Waves per workgroup of a split launch; 0: the full kernels are the better choice.
 //   N, slices  stationary rows per slice, slices of the launch;  heads  streamed sequences per slice (G in the column sums, else 1)
@@ -313,14 +513,21 @@ __global__ __launch_bounds__(W * WAVE, sizeof(T) == 2 && W == 4 ? 2 : 1) void at
 // them 21.8 / 25.6, 256 of 150 17.1 / 17.3.  G = 2: 256 slices of 256 19.1 / 18.6, 320 of them 23.1 / 24.3, 384 of 200
 // 22.5 / 23.0.  G = 4: 320 slices of 256 34.3 / 34.4, 384 of them 36.1 / 39.5, 384 of 200 34.2 / 31.8.
 // fp32, where the matrix pipe is sixteen times slower and the latencies hide behind it: 128 workgroups 289 / 168 (8 slices
-// of 4096), 256 workgroups 84 / 108 (64 of 1000).
+// of 4096), 256 workgroups 84 / 108 (64 of 1000).  The kernels of 16 rows, both passes, 32 rows / 16 rows and four waves / eight: one slice
+// of 130 16.9 / 11.2 / 11.9, of 1000 44 / 31 / 28.5, of 4000 145 / 100 / 85.5, 8 of 1000 (256 workgroups of 32 rows) 45.5 / 39.7 / 36.5,
+// 16 of 512 (256, short chains) 27.0 / 23.7 / 25.4, 32 of 200 18.2 / 14.8 / 18.5, 4 of 3000 (376) 112 / 103 / 113; and 16 of 1000 (512) 55 / 58 /
+// 65: hence up to 384, eight waves where every workgroup has a compute unit to itself and its chain is long.
 // Eight waves instead of four halve the chain but leave one workgroup per compute unit: worth it where all of them
 // are resident in two rounds and the chain is long (8 slices of 1000, G = 4, column sums: 30 with four, 24 with
 // eight; of 4096: 117 and 93; 32 slices of 1000, chain of 32: 15 and 17).
 int attn_split_waves(bool colsum, int dtype, int N, long long slices, int heads, int tiles, long long full_wgs)
 {
-    if (dtype == KVM_F32) return full_wgs <= 128 ? 4 : 0;
     const int blocks = (N + 31) / 32;                         // streamed 32-row blocks per head
+    if (dtype == KVM_F32) {
+        if (full_wgs > 128) return 0;
+        if (slices * blocks <= 256 && (long long)blocks * heads >= 24) return SPLIT16 + 8;
+        return slices * blocks <= 384 ? SPLIT16 + 4 : 4;
+    }
     int most = tiles >= 8 ? 256 : 384;
     if (heads == 1 && tiles == 2 && blocks > 14) most = 320;
     else if (heads == 1 && tiles == 1) most = blocks <= 3 ? 256 : colsum ? 128 : blocks <= 6 ? 256 : 192;
@@ -349,10 +556,29 @@ static void colsum_t(const kvm_shape &sh, const void *Q, const void *K, const fl
                        (const T *)K, lse, mass, sizeof(T) == 2 ? sim_opt : nullptr, sh.seq_lens, n_kv, sh.H_kv, sh.G, sh.N, n_pad, tiles, c);
 }
 
+template <int W>
+static void lse16_t(const kvm_shape &sh, const void *Q, const void *K, float *lse, int n_pad, float c, float out_scale, float pad,
+                    hipStream_t st)
+{
+    const int tiles = (sh.N + 31) / 32 * 2, n_q = sh.B * sh.H_kv * sh.G;   // (whole 32-row blocks: the second pass may be the other kernel)
+    hipLaunchKernelGGL(attn_lse_split16_kernel<W>, dim3((unsigned)((long long)n_q * tiles)), dim3(W * WAVE), 0, st, (const float *)Q,
+                       (const float *)K, lse, sh.seq_lens, n_q, sh.H_kv * sh.G, sh.G, sh.N, n_pad, tiles, c, out_scale, pad);
+}
+
+template <int W>
+static void colsum16_t(const kvm_shape &sh, const void *Q, const void *K, const float *lse, float *mass, int n_pad, float c, hipStream_t st)
+{
+    const int tiles = (sh.N + 15) / 16, n_kv = sh.B * sh.H_kv;
+    hipLaunchKernelGGL(attn_colsum_split16_kernel<W>, dim3((unsigned)((long long)n_kv * tiles)), dim3(W * WAVE), 0, st, (const float *)Q,
+                       (const float *)K, lse, mass, sh.seq_lens, n_kv, sh.H_kv, sh.G, sh.N, n_pad, tiles, c);
+}
+
 void launch_lse_split(int waves, const kvm_shape &sh, const void *Q, const void *K, float *lse, int n_pad, float c, float out_scale,
                       float pad, hipStream_t st)
 {
-    if (sh.dtype == KVM_F32) lse_t<float, 4>(sh, Q, K, lse, n_pad, c, out_scale, pad, st);
+    if (sh.dtype == KVM_F32 && waves == SPLIT16 + 8) lse16_t<8>(sh, Q, K, lse, n_pad, c, out_scale, pad, st);
+    else if (sh.dtype == KVM_F32 && waves > SPLIT16) lse16_t<4>(sh, Q, K, lse, n_pad, c, out_scale, pad, st);
+    else if (sh.dtype == KVM_F32) lse_t<float, 4>(sh, Q, K, lse, n_pad, c, out_scale, pad, st);
     else if (sh.dtype == KVM_F16 && waves == 4) lse_t<half_t, 4>(sh, Q, K, lse, n_pad, c, out_scale, pad, st);
     else if (sh.dtype == KVM_F16) lse_t<half_t, 8>(sh, Q, K, lse, n_pad, c, out_scale, pad, st);
     else if (waves == 4) lse_t<bf16_t, 4>(sh, Q, K, lse, n_pad, c, out_scale, pad, st);
@@ -362,7 +588,9 @@ void launch_lse_split(int waves, const kvm_shape &sh, const void *Q, const void 
 void launch_colsum_split(int waves, const kvm_shape &sh, const void *Q, const void *K, const float *lse, float *mass, float *sim_opt,
                          int n_pad, float c, hipStream_t st)
 {
-    if (sh.dtype == KVM_F32) colsum_t<float, 4>(sh, Q, K, lse, mass, sim_opt, n_pad, c, st);
+    if (sh.dtype == KVM_F32 && waves == SPLIT16 + 8) colsum16_t<8>(sh, Q, K, lse, mass, n_pad, c, st);
+    else if (sh.dtype == KVM_F32 && waves > SPLIT16) colsum16_t<4>(sh, Q, K, lse, mass, n_pad, c, st);
+    else if (sh.dtype == KVM_F32) colsum_t<float, 4>(sh, Q, K, lse, mass, sim_opt, n_pad, c, st);
     else if (sh.dtype == KVM_F16 && waves == 4) colsum_t<half_t, 4>(sh, Q, K, lse, mass, sim_opt, n_pad, c, st);
     else if (sh.dtype == KVM_F16) colsum_t<half_t, 8>(sh, Q, K, lse, mass, sim_opt, n_pad, c, st);
     else if (waves == 4) colsum_t<bf16_t, 4>(sh, Q, K, lse, mass, sim_opt, n_pad, c, st);

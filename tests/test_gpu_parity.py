@@ -210,6 +210,22 @@ def test_mass_split_held_reference(dtype, orders):
     assert np.abs(got[~big]).max(initial=0.0) <= 2e-6
 
 
+@pytest.mark.parametrize("G,lens,N,copies", [
+    (1, [1], 1, 1), (1, [15], 16, 1), (2, [17, 16, 0], 17, 1), (1, [40, 33, 31], 48, 2), (4, [49, 130], 130, 1), (3, [350, 1, 0, 256], 350, 1),
+    (1, [700, 513], 770, 3), (4, [600], 600, 4), (2, [500, 250, 37], 500, 4), (2, [500, 250, 37], 500, 5)])
+def test_mass_fp32_smallest_launches(G, lens, N, copies):
+    """The fp32 kernels of 16 rows, four and eight waves, alone and with the other pass in the kernels of 32 rows (G > 1 and many
+    copies: the row statistics have G times the slices): edges of a 16-row block, padding, heads, against the oracle
+    (fp32 sums of N terms: 8 * 2^-24 sqrt(N) of a column's sum, and the exponent's own 1e-5)."""
+    _say(f"mass, smallest fp32 launches: G={G} lens={lens} N={N} x{copies}")
+    Q, K, _ = _slices(31, len(lens), 1, lens, N, 128, G, "f32")
+    got = gu.gpu_mass(Q, K, "f32", G=G, seq_lens=lens, copies=copies, kernels=["attn_lse_split_kernel", "attn_colsum_split_kernel"])
+    want = ref.attn_mass(Q, K, "f32", G=G, seq_lens=lens)
+    for b, n in enumerate(lens):
+        assert (got[b, :, n:] == 0).all()
+        assert (np.abs(got[b, :, :n] - want[b, :, :n]) <= (1e-5 + 8 * 2.0 ** -24 * math.sqrt(N)) * want[b, :, :n]).all()
+
+
 @pytest.mark.parametrize("dtype,G,lens,N,copies,kernels", [
     ("f16", 1, [2304, 0, 2048, 1, 1793, 1025, 257, 512], 2304, 7, ["attn_lse_kernel", "attn_colsum_kernel"]),
     ("bf16", 2, [2100, 1800, 1, 0, 700, 2304], 2304, 9, ["attn_lse_kernel", "attn_colsum_kernel"]),
