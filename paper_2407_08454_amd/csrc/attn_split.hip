@@ -131,11 +131,11 @@ __global__ __launch_bounds__(W * WAVE, sizeof(T) == 2 && W == 4 ? 2 : 1) void at
     float m_run[NB], l_run[NB];
 
     // 16-bit types: the reference of a wave's sums is the maximum of its first block and is held to the diagonal (see
-    // rowsum_held).  Should a later score be so far above it that a sum leaves the range in which the waves' sums can be
-    // put on one reference without loss, the workgroup does all of it once more with the maximum updated at every block.
+    // rowsum_held).  Should a later score be so far above it that a sum leaves the range in which it can be put on
+    // another reference without loss (HELD_SUM_MAX), the workgroup does all of it once more with the maximum updated at every
+    // block.  That is looked at before the diagonal, whose maximum may scale the held sum to nothing, and before the waves' sums are combined.
     // Held or not, us: 32 slices of 4000 tokens 87.5 / 92.0, 16 of 2000 18.6 / 19.9, one of 16384 63.9 / 69.5.
-    constexpr float HELD_SUM_MAX = 0x1p64f;                   // what is lost then is below 2^-62 of a row's sum
-    bool hold = sizeof(T) == 2;
+    bool hold = sizeof(T) == 2, fits = true;
     auto step = [&](int t, const u32x4 *cur, u32x4 *nxt) {
         wait_own_tile();
         issue_next(nxt);
@@ -146,6 +146,10 @@ __global__ __launch_bounds__(W * WAVE, sizeof(T) == 2 && W == 4 ? 2 : 1) void at
 #pragma unroll
             for (int qb = 0; qb < NB; ++qb) rowsum_held(stream_scores<T>(a, qf[qb]), c, m_run[qb] * c, l_run[qb]);
             return;
+        }
+        if (sizeof(T) == 2 && hold) {
+#pragma unroll
+            for (int qb = 0; qb < NB; ++qb) fits = fits && l_run[qb] <= HELD_SUM_MAX;
         }
 #pragma unroll
         for (int qb = 0; qb < NB; ++qb) {
@@ -163,7 +167,6 @@ __global__ __launch_bounds__(W * WAVE, sizeof(T) == 2 && W == 4 ? 2 : 1) void at
             if (t + W < count) step(t + W, lds_b[wave], lds_a[wave]);
         }
         // lanes l and l+32 hold the two halves of a row's keys; then the waves are combined
-        bool fits = true;
 #pragma unroll
         for (int qb = 0; qb < NB; ++qb) {
             fits = fits && l_run[qb] <= HELD_SUM_MAX;         // false for NaN

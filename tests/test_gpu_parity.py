@@ -190,24 +190,40 @@ def test_mass_large_scores_do_not_overflow():
         assert (np.abs(got - want)[big] / want[big]).max() <= gu.TOL
 
 
-@pytest.mark.parametrize("dtype", ["f16", "bf16"])
-@pytest.mark.parametrize("orders", [40.0, 63.5, 64.5, 100.0, 126.9, 128.5, 300.0])
-def test_mass_split_held_reference(dtype, orders):
-    """The split row statistics hold a wave's reference from its first block on: late keys around and beyond the 2^64 at
-    which a workgroup starts again with the maximum updated, in one wave or in two, after it or on its last block."""
-    _say(f"mass, held reference: {dtype} {orders} binary orders")
-    n = 600
-    q, k = np.zeros((1, 3, n, 128), np.float32), np.zeros((1, 3, n, 128), np.float32)
+def _held_reference_case(dtype, orders, n):
+    """Equal queries and, among zero keys, a few whose scores lie `orders` binary orders above theirs (rounded to the type)."""
+    q, k = np.zeros((1, 6, n, 128), np.float32), np.zeros((1, 6, n, 128), np.float32)
     q[:, :, :, 2] = 30.0
     top = orders * math.sqrt(128.0) / (30.0 * math.log2(math.e))
     k[0, 0, 300, 2] = top                                     # one wave sees it
-    k[0, 1, [200, 330], 2] = top                              # two waves, the other two stay with zeros
+    k[0, 1, [200, 300], 2] = top                              # two waves, the others stay with zeros
     k[0, 2, [255, 575], 2] = top, 2 * top                     # again and higher, late
+    # one wave sees both, the second on the diagonal of 64 rows that all see it: what was held before is scaled down there
+    k[0, 3, [200, 320], 2] = top                              # (blocks 6 and 10 of 32 keys: the same wave of four; the same half of its lanes)
+    k[0, 4, [328, 576], 2] = top                              # (blocks 10 and 18: of eight as well)
+    k[0, 5, [204, 320], 2] = top                              # (in the two halves of the lanes)
     Q, K = synth.to_storage(q, dtype), synth.to_storage(k, dtype)
-    got, want = gu.gpu_mass(Q, K, dtype, kernels=["attn_lse_split_kernel"]), ref.attn_mass(Q, K, dtype)
+    return Q, K, ref.attn_mass(Q, K, dtype)
+
+
+def _check_held_reference(got, want):
     big = want > 1e-6
     assert np.isfinite(got).all() and (np.abs(got[big] - want[big]) / want[big]).max() <= gu.TOL
     assert np.abs(got[~big]).max(initial=0.0) <= 2e-6
+
+
+HELD_ORDERS = [40.0, 63.5, 64.5, 100.0, 126.3, 126.9, 128.5, 300.0]
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+@pytest.mark.parametrize("orders", HELD_ORDERS)
+@pytest.mark.parametrize("n", [600, 2100])                    # four waves a workgroup, eight
+def test_mass_split_held_reference(dtype, orders, n):
+    """The split row statistics hold a wave's reference from its first block on: late keys around and beyond the 2^64 at
+    which a workgroup starts again with the maximum updated, in one wave or in two, after it or on its last block."""
+    _say(f"mass, held reference: {dtype} {orders} binary orders, n={n}")
+    Q, K, want = _held_reference_case(dtype, orders, n)
+    _check_held_reference(gu.gpu_mass(Q, K, dtype, kernels=["attn_lse_split_kernel"]), want)
 
 
 @pytest.mark.parametrize("G,lens,N,copies", [
