@@ -71,8 +71,8 @@ __device__ __forceinline__ f32x16 score_block8(const u32x4 *a, const u32x4 *bfra
 
 // HOLD (16-bit types only): the running maximum is taken from key tile 0 and held for the tiles
 // below the diagonal, which saves the maximum and the rescaling of every block; the diagonal
-// tile updates it again.  Should a later score exceed the held maximum by so much that a term
-// overflows, the sums are not finite: the workgroup then records the row tile in `redo`, and a
+// tile updates it again.  Should a later score exceed the held maximum by so much that a held sum
+// passes HELD_SUM_MAX, or the result is not finite, the workgroup records the row tile in `redo`, and a
 // second launch without HOLD, which looks only at recorded tiles, computes it with the maximum
 // updated at every block.  Without HOLD and with redo == NULL every tile is computed.
 template <typename T, bool HOLD>
@@ -138,6 +138,8 @@ __global__ __launch_bounds__(ATT_BLOCK, ATT_MIN_BLOCKS) void attn_lse_kernel(con
     // without valid rows computes nothing
     const int diag = q0 < n ? q0 / TR : -1;
 
+    bool good = true;                                         // the held sums, before the diagonal may scale them away, and the results
+
     auto step = [&](int s, const u32x4 *cur, u32x4 *nxt) {
         // this thread's part of tile s has landed; after the barrier everybody's part has, and
         // everybody is done with the stage that tile s+1 now overwrites
@@ -179,6 +181,7 @@ __global__ __launch_bounds__(ATT_BLOCK, ATT_MIN_BLOCKS) void attn_lse_kernel(con
                 acc = score_block8<T>(a, qf[1]);
                 rowstat_update(acc, c, m_run[1], l_run[1]);
             } else if (s == diag) {                           // two blocks on the diagonal, one below it
+                if (HOLD) good = l_run[0] <= HELD_SUM_MAX && l_run[1] <= HELD_SUM_MAX;     // (false for NaN)
                 u32x4 a[8];
                 load_frags8<T>(cur, 0, fs, a);              // keys q0 .. q0+31
                 f32x16 acc = score_block8<T>(a, qf[0]);
@@ -223,7 +226,6 @@ __global__ __launch_bounds__(ATT_BLOCK, ATT_MIN_BLOCKS) void attn_lse_kernel(con
     // lanes l and l+32 hold the two halves of a row's keys.  The statistic is stored as
     // out_scale * L_t; rows in [n, n_pad) get `pad`, the infinity whose sign makes the second pass
     // weigh them with exp2(-inf) = 0.
-    bool finite = true;
 #pragma unroll
     for (int qb = 0; qb < NB; ++qb) {
         const float m_o = __shfl_xor(m_run[qb], 32, WAVE), l_o = __shfl_xor(l_run[qb], 32, WAVE);
@@ -232,11 +234,11 @@ __global__ __launch_bounds__(ATT_BLOCK, ATT_MIN_BLOCKS) void attn_lse_kernel(con
         const float L = m * c + __log2f(l);
         const int q = q0 + 32 * qb + (lane & 31);
         // (checked on the combined sum: two finite halves can still add up to infinity)
-        if (q < n) finite = finite && fabsf(L) <= 3.0e38f;    // false for infinities and NaN
+        if (q < n) good = good && fabsf(L) <= 3.0e38f;    // false for infinities and NaN
         if (lane < 32 && q < n_pad) lse[(size_t)qslice * n_pad + q] = q < n ? L * out_scale : pad;
     }
     if constexpr (HOLD) {
-        const int bad = __syncthreads_or(finite ? 0 : 1);
+        const int bad = __syncthreads_or(good ? 0 : 1);
         if (threadIdx.x == 0) redo[(size_t)qslice * tiles_per_slice + tile] = bad;
     }
     barrier_no_fence();                                       // everybody is done with LDS before the next tile's loads

@@ -226,6 +226,17 @@ def test_mass_split_held_reference(dtype, orders, n):
     _check_held_reference(gu.gpu_mass(Q, K, dtype, kernels=["attn_lse_split_kernel"]), want)
 
 
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+@pytest.mark.parametrize("orders", HELD_ORDERS)
+@pytest.mark.parametrize("n,copies", [(600, 26), (2100, 11)])
+def test_mass_full_held_reference(dtype, orders, n, copies):
+    """The full row statistics hold the reference of the first 64 keys to the diagonal, and leave a tile whose held sums
+    passed 2^64 to the repeat launch."""
+    _say(f"mass, held reference in full launches: {dtype} {orders} binary orders, n={n}")
+    Q, K, want = _held_reference_case(dtype, orders, n)
+    _check_held_reference(gu.gpu_mass(Q, K, dtype, copies=copies, kernels=["attn_lse_kernel", "attn_lse_redo_kernel"]), want)
+
+
 @pytest.mark.parametrize("G,lens,N,copies", [
     (1, [1], 1, 1), (1, [15], 16, 1), (2, [17, 16, 0], 17, 1), (1, [40, 33, 31], 48, 2), (4, [49, 130], 130, 1), (3, [350, 1, 0, 256], 350, 1),
     (1, [700, 513], 770, 3), (4, [600], 600, 4), (2, [500, 250, 37], 500, 4), (2, [500, 250, 37], 500, 5)])
