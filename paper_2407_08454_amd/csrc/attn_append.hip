@@ -14,6 +14,8 @@
 //                             (no exchange between waves, so no barrier).
 //   append_accumulate_kernel  merges the pieces' statistics of every query head into its
 //                             log-sum-exp and adds exp2(score - lse) of all G heads to mass.
+#include <algorithm>
+
 #include "kvm_common.h"
 
 namespace kvm {
@@ -24,6 +26,8 @@ constexpr int APP_WAVES = APP_BLOCK / WAVE;
 constexpr int ACC_PER_THREAD = 4;                           // keys per thread of the second kernel
 constexpr int ACC_HEADS = 16;                               // query heads between two barriers of it
 constexpr int ACC_CHUNK = APP_BLOCK * ACC_PER_THREAD;
+constexpr int ACC_MAX_CHUNKS = 256;                         // workgroups per slice
+constexpr int ACC_SHARED_PIECES = 512;                      // longer lists of statistics may be walked by all waves
 
 int attn_lse_stride(int N);
 
@@ -83,36 +87,77 @@ __global__ __launch_bounds__(APP_BLOCK) void append_scores_kernel(const T *__res
     }
 }
 
-// log-sum-exp of a query row from the statistics of its 64-key pieces, by one wave (maximum first, sums scaled to it)
-__device__ __forceinline__ float row_lse(const float *st, int pieces) {
+// Statistics [first, last) of a query row put on their maximum m, by one wave: the sum of exponentials (maximum first, sums
+// scaled to it).  Every lane gets both.
+__device__ __forceinline__ float row_sum(const float *st, int first, int last, float &m) {
     const int lane = threadIdx.x & 63;
     float tm = -INFINITY;
-    for (int t = lane; t < pieces; t += WAVE) tm = fmaxf(tm, st[2 * t]);
-    const float m = wave_max(tm);
+    for (int t = first + lane; t < last; t += WAVE) tm = fmaxf(tm, st[2 * t]);
+    m = wave_max(tm);
     float tl = 0.f;
-    for (int t = lane; t < pieces; t += WAVE) tl += st[2 * t + 1] * __builtin_amdgcn_exp2f(st[2 * t] - m);
-    return m + __log2f(wave_sum(tl));
+    for (int t = first + lane; t < last; t += WAVE) tl += st[2 * t + 1] * __builtin_amdgcn_exp2f(st[2 * t] - m);
+    return wave_sum(tl);
 }
 
-// The waves take the query heads in turn, ACC_HEADS between two barriers; a single head is worked out by every wave for itself.
+// The log-sum-exps of query heads [g0, g0 + heads), heads <= ACC_HEADS, by a workgroup, -> lse_of in LDS.  The waves take the heads in
+// turn.  SHARED: a quarter of every list a wave, for long lists and heads that do not come out even, where the waves without a list
+// would wait for the others.  us, in turn / shared: one slice of 131072 keys, one head, 15.1 / 8.3, two 16.9 / 11.9, four 17.9 / 19.4,
+// eight 30.8 / 34.0; of 32768, one head 7.6 / 6.1, three 8.7 / 9.0, four 9.4 / 10.5.
+template <bool SHARED>
+__device__ __forceinline__ void row_lses(const float *stats, int stats_per_row, int g0, int heads, int pieces, float *lse_of, float2 (*part)[APP_WAVES]) {
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    if (!SHARED) {
+        for (int g = wave; g < heads; g += APP_WAVES) {
+            float m;
+            const float l = row_sum(stats + (size_t)(g0 + g) * stats_per_row * 2, 0, pieces, m);
+            if (lane == 0) lse_of[g] = m + __log2f(l);
+        }
+        __syncthreads();
+        return;
+    }
+    const int quarter = (pieces + APP_WAVES - 1) / APP_WAVES;
+    for (int g = 0; g < heads; ++g) {
+        float m;
+        const float l = row_sum(stats + (size_t)(g0 + g) * stats_per_row * 2, wave * quarter, min((wave + 1) * quarter, pieces), m);
+        if (lane == 0) part[g][wave] = make_float2(m, l);
+    }
+    __syncthreads();
+    if ((int)threadIdx.x < heads) {
+        float m = -INFINITY, l = 0.f;
+#pragma unroll
+        for (int w = 0; w < APP_WAVES; ++w) m = fmaxf(m, part[threadIdx.x][w].x);
+#pragma unroll
+        for (int w = 0; w < APP_WAVES; ++w) l += part[threadIdx.x][w].y * __builtin_amdgcn_exp2f(part[threadIdx.x][w].x - m);
+        lse_of[threadIdx.x] = m + __log2f(l);
+    }
+    __syncthreads();
+}
+
+// ACC_HEADS query heads between two barriers; a single head of a short list is worked out by every wave for itself.
 // (All waves on one head after the other with three barriers each, and eight keys a thread, before / now, us: 32 slices of 3000
 // keys, G = 4, 18.4 / 7.3; 8 of 1000, G = 8, 20.9 / 9.3; 64 of 16000, G = 2, 14.3 / 8.5; 1024 of 4096 18.2 / 15.2.)
+// Every workgroup needs the statistics of all keys, N / 64 pairs a head, so no slice gets more than ACC_MAX_CHUNKS of them: beyond,
+// they take several chunks of keys each, or the reads would grow with the square of N (us, a workgroup per chunk / this, and the lists
+// shared: one slice of 262144 keys 28.6 / 12.0, of 1048576 99.8 / 31.6, of 4194304 1113 / 115).  LONG: rows that may need either.
+template <bool LONG>
 __global__ __launch_bounds__(APP_BLOCK) void append_accumulate_kernel(const float *__restrict__ scores,
                                                                        const float *__restrict__ stats, float *__restrict__ mass,
                                                                        const int32_t *__restrict__ seq_lens, int H, int G, int N,
                                                                        int n_pad, int chunks_per_slice)
 {
     __shared__ float lse_of[ACC_HEADS];
+    __shared__ float2 part[ACC_HEADS][APP_WAVES];
     const int slice = blockIdx.x / chunks_per_slice;
-    const int chunk = blockIdx.x - slice * chunks_per_slice;
     const int n = clamp_len(seq_lens, slice / H, N);
-    const int j_block = chunk * ACC_CHUNK;
-    if (j_block >= n) return;
+    const int keys = LONG ? (n + ACC_CHUNK * ACC_MAX_CHUNKS - 1) / (ACC_CHUNK * ACC_MAX_CHUNKS) * ACC_CHUNK : ACC_CHUNK;   // of this workgroup
+    const int j_first = (blockIdx.x - slice * chunks_per_slice) * keys;
+    if (j_first >= n) return;
     const int pieces = (n + WAVE - 1) / WAVE;                // statistics come per 64 keys
     const int stats_per_row = n_pad / WAVE;
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const float *row = scores + (size_t)slice * G * n_pad, *st = stats + (size_t)slice * G * stats_per_row * 2;
     float *a = mass + (size_t)slice * N;
+    float own_lse = 0.f;
+    for (int j_block = j_first; j_block < min(j_first + keys, n); j_block += ACC_CHUNK) {
     float add[ACC_PER_THREAD], before[ACC_PER_THREAD];
 #pragma unroll
     for (int u = 0; u < ACC_PER_THREAD; ++u) {
@@ -128,18 +173,19 @@ __global__ __launch_bounds__(APP_BLOCK) void append_accumulate_kernel(const floa
             const int j = j_block + u * APP_BLOCK + threadIdx.x;
             x[u] = j < n ? row[(size_t)g0 * n_pad + j] : -INFINITY;
         }
-        float lse = 0.f;
-        if (heads == 1) {
-            lse = row_lse(st + (size_t)g0 * stats_per_row * 2, pieces);
-        } else {
-            if (g0 > 0) __syncthreads();                      // the heads before have been read
-            for (int g = wave; g < heads; g += APP_WAVES) {
-                const float v = row_lse(st + (size_t)(g0 + g) * stats_per_row * 2, pieces);
-                if (lane == 0) lse_of[g] = v;
+        const bool shared = LONG && pieces > ACC_SHARED_PIECES && heads % APP_WAVES != 0, alone = heads == 1 && !shared;
+        if (j_block == j_first || G > ACC_HEADS) {           // (else they are there from the chunk before)
+            if (alone) {
+                float m;
+                const float l = row_sum(st + (size_t)g0 * stats_per_row * 2, 0, pieces, m);
+                own_lse = m + __log2f(l);
+            } else {
+                if (g0 > 0 || j_block > j_first) __syncthreads();   // the heads before have been read
+                if (shared) row_lses<true>(st, stats_per_row, g0, heads, pieces, lse_of, part);
+                else row_lses<false>(st, stats_per_row, g0, heads, pieces, lse_of, part);
             }
-            __syncthreads();
-            lse = lse_of[0];
         }
+        float lse = alone ? own_lse : lse_of[0];
         for (int g = 0;;) {
             const float l = lse;
             float next[ACC_PER_THREAD];
@@ -164,6 +210,7 @@ __global__ __launch_bounds__(APP_BLOCK) void append_accumulate_kernel(const floa
     for (int u = 0; u < ACC_PER_THREAD; ++u) {
         const int j = j_block + u * APP_BLOCK + threadIdx.x;
         if (j < n) a[j] = before[u] + add[u];
+    }
     }
 }
 
@@ -191,9 +238,13 @@ static kvm_status launch_t(const kvm_shape &sh, const void *q_new, const void *K
     kvm_status rc = check_launch("append_scores_kernel");
     if (rc != KVM_OK) return rc;
     ProfScope prof("append_accumulate_kernel", st);
-    const int chunks = (sh.N + ACC_CHUNK - 1) / ACC_CHUNK;
-    hipLaunchKernelGGL(append_accumulate_kernel, dim3((unsigned)((long long)sh.B * sh.H_kv * chunks)), dim3(APP_BLOCK), 0, st,
-                       (const float *)scores, (const float *)stats, mass, sh.seq_lens, sh.H_kv, sh.G, sh.N, n_pad, chunks);
+    const int chunks = std::min((sh.N + ACC_CHUNK - 1) / ACC_CHUNK, ACC_MAX_CHUNKS);
+    const auto run = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3((unsigned)((long long)sh.B * sh.H_kv * chunks)), dim3(APP_BLOCK), 0, st, (const float *)scores,
+                           (const float *)stats, mass, sh.seq_lens, sh.H_kv, sh.G, sh.N, n_pad, chunks);
+    };
+    if (sh.N > ACC_SHARED_PIECES * WAVE) run(append_accumulate_kernel<true>);
+    else run(append_accumulate_kernel<false>);
     return check_launch("append_accumulate_kernel");
 }
 

@@ -464,6 +464,34 @@ def test_mass_append_one_query_row(dtype, G, lens, N):
             assert added == pytest.approx(G, rel=1e-3)
 
 
+@pytest.mark.parametrize("dtype,G,lens,N", [
+    ("f16", 8, [300, 0, 65], 300), ("bf16", 17, [129, 1, 1100], 1100), ("f16", 33, [200], 256),   # more heads than waves, than ACC_HEADS
+    ("f16", 1, [32768, 32769], 32832), ("bf16", 3, [32769, 700, 40001], 40001), ("f32", 4, [33000], 33000), ("f16", 17, [33000], 33000),
+    ("f16", 1, [262144, 262145], 270000), ("bf16", 2, [527000], 527000), ("f16", 17, [263000], 263000)])
+def test_mass_append_many_heads_and_long_rows(dtype, G, lens, N):
+    """Decode-time update where the waves of a workgroup take several heads, in several turns, where they share the statistics
+    of a row (beyond 512 * 64 keys) and where a workgroup takes several chunks of keys (beyond 256 * 1024)."""
+    _say(f"mass append, heads and lengths: {dtype} G={G} lens={lens} N={N}")
+    rng = np.random.default_rng(N + G)
+    B = len(lens)
+    K = synth.to_storage(rng.standard_normal((B, 1, N, 128), dtype=np.float32), dtype)
+    q_new = synth.to_storage(rng.standard_normal((B, G, 128), dtype=np.float32), dtype)
+    before = (rng.random((B, 1, N)) * 1e-3).astype(np.float32)
+    for b, n in enumerate(lens):
+        before[b, :, n:] = -5.0
+    got = gu.gpu_mass_append(q_new, K, before, dtype, G=G, seq_lens=lens)
+    want = ref.attn_mass_append(q_new, K, before.astype(np.float64), dtype, G=G, seq_lens=lens)
+    for b, n in enumerate(lens):
+        assert np.all(got[b, :, n:] == -5.0), "entries past the length were touched"
+        if n:
+            # what was added, to the rounding of the sum with what was there (2^-24 of 1e-3, far below an average entry of G / n)
+            add, want_add = (x[b, 0, :n].astype(np.float64) for x in (got, want))
+            add[:n - 1] -= before[b, 0, :n - 1]
+            want_add[:n - 1] -= before[b, 0, :n - 1]
+            assert (np.abs(add - want_add) <= 1e-4 * want_add + 2.0 ** -23 * want[b, 0, :n]).all()
+            assert add.sum() == pytest.approx(G, rel=1e-5)
+
+
 def test_mass_append_continues_the_prefill_pass():
     """Prefill scores of the first n0 tokens, then appends token by token: the result has to be
     the prefill scores of all n1 tokens (both from the library; the oracle checks the end state)."""
