@@ -42,11 +42,11 @@ __device__ __forceinline__ float wave_sum(float v) {
     return v;
 }
 
-template <typename T, bool STREAM>
+template <typename T>
 __global__ __launch_bounds__(APP_BLOCK) void append_scores_kernel(const T *__restrict__ q_new, const T *__restrict__ K,
                                                                    float *__restrict__ scores, float *__restrict__ stats,
                                                                    const int32_t *__restrict__ seq_lens, int H, int G,
-                                                                   int N, int n_pad, int tiles_per_slice, float c)
+                                                                   int N, int n_pad, int tiles_per_slice, int stream_from, float c)
 {
     typedef typename Elem<T>::Raw Raw;
     const int slice = blockIdx.x / tiles_per_slice;          // (b, h)
@@ -61,8 +61,7 @@ __global__ __launch_bounds__(APP_BLOCK) void append_scores_kernel(const T *__res
 
     // all rows of the group at once; rows past the end repeat the last valid one and are masked below
     Raw raw[APP_ROWS_PER_GROUP];
-#pragma unroll
-    for (int i = 0; i < APP_ROWS_PER_GROUP; ++i) raw[i] = load_once<T, STREAM>(Ks + (size_t)min(j0 + i, n - 1) * HEAD_DIM, lane16);
+    load_rows_once<T, APP_ROWS_PER_GROUP>(Ks, j0, n, lane16, stream_from, raw);
 
     const int j = tile * APP_BLOCK + threadIdx.x;            // the key whose score this thread keeps
     const int stats_per_row = n_pad / WAVE;
@@ -225,15 +224,11 @@ static kvm_status launch_t(const kvm_shape &sh, const void *q_new, const void *K
     const long long blocks = (long long)sh.B * sh.H_kv * tiles;
     {
         ProfScope prof("append_scores_kernel", st);
-        const dim3 grid((unsigned)blocks), block(APP_BLOCK);
-        const T *q = (const T *)q_new, *k = (const T *)K;
         // From half the last-level cache on the keys are read with the non-temporal hint: with them the compacted rows that
         // the refresh moves next, as large again, would not fit.  Token loop, us, plain / hint: 32 slices of 8192 tokens
         // (64 MiB) 92 / 93, of 12288 114 / 117, of 16384 151 / 143, of 32768 442 / 364; 1024 of 4096 449 / 403 (this kernel 236 / 190).
-        if (key_bytes(sh) >= LLC_BYTES / 2)
-            hipLaunchKernelGGL((append_scores_kernel<T, true>), grid, block, 0, st, q, k, scores, stats, sh.seq_lens, sh.H_kv, sh.G, sh.N, n_pad, tiles, c);
-        else
-            hipLaunchKernelGGL((append_scores_kernel<T, false>), grid, block, 0, st, q, k, scores, stats, sh.seq_lens, sh.H_kv, sh.G, sh.N, n_pad, tiles, c);
+        hipLaunchKernelGGL(append_scores_kernel<T>, dim3((unsigned)blocks), dim3(APP_BLOCK), 0, st, (const T *)q_new, (const T *)K,
+                           scores, stats, sh.seq_lens, sh.H_kv, sh.G, sh.N, n_pad, tiles, stream_length(sh, LLC_BYTES / 2), c);
     }
     kvm_status rc = check_launch("append_scores_kernel");
     if (rc != KVM_OK) return rc;

@@ -32,11 +32,11 @@ constexpr int COS_ROWS_PER_BLOCK = COS_GROUPS * COS_ROWS_PER_GROUP;
 
 
 
-template <typename T, bool STREAM>
+template <typename T>
 __global__ __launch_bounds__(COS_BLOCK) void cosine_scan_kernel(const T *__restrict__ K, float *__restrict__ sim,
                                                                  float *__restrict__ inv_norm_out,
                                                                  const int32_t *__restrict__ seq_lens, int H, int N,
-                                                                 int tiles_per_slice)
+                                                                 int tiles_per_slice, int stream_from)
 {
     typedef typename Elem<T>::Raw Raw;
     __shared__ Raw last_row[COS_GROUPS][16];                // the last row of every group, for its successor
@@ -62,8 +62,7 @@ __global__ __launch_bounds__(COS_BLOCK) void cosine_scan_kernel(const T *__restr
     // every row of the group at once (rows past the end are replaced by the last valid one and
     // never used), plus the row before the workgroup's first for group 0
     Raw raw[COS_ROWS_PER_GROUP];
-#pragma unroll
-    for (int i = 0; i < COS_ROWS_PER_GROUP; ++i) raw[i] = load_once<T, STREAM>(Ks + (size_t)min(j0 + i, n - 1) * HEAD_DIM, c);
+    load_rows_once<T, COS_ROWS_PER_GROUP>(Ks, j0, n, c, stream_from, raw);
     Raw prev = raw[0];
     if (group == 0 && j0 >= 1) prev = Elem<T>::load(Ks + (size_t)(j0 - 1) * HEAD_DIM, c);
     last_row[group][c] = raw[COS_ROWS_PER_GROUP - 1];
@@ -1205,11 +1204,8 @@ static void launch_cosine(const kvm_shape &sh, const void *K, float *sim, float 
     const int tiles = (sh.N + COS_ROWS_PER_BLOCK - 1) / COS_ROWS_PER_BLOCK;
     const long long blocks = (long long)sh.B * sh.H_kv * tiles;
     ProfScope prof("cosine_scan_kernel", st);
-    const dim3 grid((unsigned)blocks), block(COS_BLOCK);
-    if (key_bytes(sh) >= LLC_BYTES)
-        hipLaunchKernelGGL((cosine_scan_kernel<T, true>), grid, block, 0, st, (const T *)K, sim, inv_norm, sh.seq_lens, sh.H_kv, sh.N, tiles);
-    else
-        hipLaunchKernelGGL((cosine_scan_kernel<T, false>), grid, block, 0, st, (const T *)K, sim, inv_norm, sh.seq_lens, sh.H_kv, sh.N, tiles);
+    hipLaunchKernelGGL(cosine_scan_kernel<T>, dim3((unsigned)blocks), dim3(COS_BLOCK), 0, st, (const T *)K, sim, inv_norm,
+                       sh.seq_lens, sh.H_kv, sh.N, tiles, stream_length(sh, LLC_BYTES));
 }
 
 template <typename T>

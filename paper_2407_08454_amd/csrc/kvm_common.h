@@ -196,19 +196,33 @@ __device__ __forceinline__ int clamp_len(const int32_t *seq_lens, int b, int N) 
     return n < 0 ? 0 : (n > N ? N : n);
 }
 
-// A row that is read once by this launch.  STREAM: with the non-temporal hint (Elem::load_stream).
-template <typename T, bool STREAM> __device__ __forceinline__ typename Elem<T>::Raw load_once(const T *row, int c) {
-    if constexpr (STREAM) return Elem<T>::load_stream(row, c);
-    else return Elem<T>::load(row, c);
+// Chunk c of rows j0 .. j0 + ROWS - 1 of a slice of n tokens, all loads in flight together; rows past the end repeat the last
+// one.  With the non-temporal hint (Elem::load_stream) for slices of stream_from tokens and more (see stream_length).  (The empty
+// statements keep the compiler from merging the two branches' loads, which drops the hint.)
+template <typename T, int ROWS>
+__device__ __forceinline__ void load_rows_once(const T *slice, int j0, int n, int c, int stream_from, typename Elem<T>::Raw *raw) {
+    if (n >= stream_from) {                                  // (the same for the whole workgroup)
+        asm volatile("");
+#pragma unroll
+        for (int i = 0; i < ROWS; ++i) raw[i] = Elem<T>::load_stream(slice + (size_t)min(j0 + i, n - 1) * HEAD_DIM, c);
+        asm volatile("");
+    } else {
+#pragma unroll
+        for (int i = 0; i < ROWS; ++i) raw[i] = Elem<T>::load(slice + (size_t)min(j0 + i, n - 1) * HEAD_DIM, c);
+    }
 }
 
 // ---- host side -----------------------------------------------------------------------
 
-// Keys of the launch in bytes, against the 256 MB last-level cache: the rules for the non-temporal loads of the scan and of
-// the decode-time scores.
-constexpr long long LLC_BYTES = 256ll << 20;
-inline long long key_bytes(const kvm_shape &sh) {
-    return (long long)sh.B * sh.H_kv * sh.N * HEAD_DIM * (sh.dtype == KVM_F32 ? 4 : 2);
+// The rule for the non-temporal loads of the scan and of the decode-time scores: a slice takes its own length for that of all
+// and streams from the one on at which their keys come to `bytes`.  The lengths are on the device, and N is no measure of them: a cache
+// that is allocated for N tokens a slice may hold few.  us, by N / by the slice's length: sets and merge of 32 slices of 2000 fp32 tokens allocated for
+// 32768 80 / 70, of 8 of 4000 for 131072 84 / 77, of 128 of 1000 fp16 tokens for 16384 100 / 95; their decode-time scores and a read of the merged rows 41 /
+// 32, 32 / 26, 47 / 40; full caches as before.
+constexpr long long LLC_BYTES = 256ll << 20;                 // last-level cache
+inline int stream_length(const kvm_shape &sh, long long bytes) {
+    const long long per_token = (long long)sh.B * sh.H_kv * HEAD_DIM * (sh.dtype == KVM_F32 ? 4 : 2);
+    return (int)((bytes + per_token - 1) / per_token);       // (below 2^20: a token has at least 256 bytes)
 }
 
 void set_error(const char *fmt, ...);

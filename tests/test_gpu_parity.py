@@ -508,9 +508,11 @@ def test_mass_append_continues_the_prefill_pass():
     assert np.abs(mass - direct).max() <= 1e-4 * np.abs(direct).max()
 
 
+@pytest.mark.parametrize("cut", [77, 6000, 9000, 16000])
 @pytest.mark.parametrize("dtype,H", [("f16", 64), ("bf16", 32), ("f32", 16)])
-def test_streamed_launches_give_the_bits_of_small_ones(dtype, H):
-    """From 128 MiB of keys (decode-time scores) and 256 MiB (scan) on, rows are read with the non-temporal hint; nothing
+def test_streamed_launches_give_the_bits_of_small_ones(dtype, H, cut):
+    """From 128 MiB of keys (decode-time scores) and 256 MiB (scan) on, rows are read with the non-temporal hint, each slice
+    by its own length: with its second row shorter by `cut` a batch streams in both kernels, in one, in none of that row.  Nothing
     else differs, so every slice has the bits it gets in a call of its own, ragged last tiles included."""
     B, N = 2, 16381 if dtype == "f32" else 16384
     esz = 4 if dtype == "f32" else 2
@@ -521,7 +523,7 @@ def test_streamed_launches_give_the_bits_of_small_ones(dtype, H):
     params = kb.kvm_params_for_budget(0.35)
     results = []
     for K_part, q_part in ((K, q), (K[1:, H - 1:].contiguous(), q[1:, H - 1:].contiguous())):
-        lens = torch.tensor([N, N - 77][-K_part.shape[0]:], dtype=torch.int32, device="cuda")
+        lens = torch.tensor([N, N - cut][-K_part.shape[0]:], dtype=torch.int32, device="cuda")
         shape = kb.make_shape(K_part, 1, lens)
         buf = kb.Buffers(shape, params, "cuda", dt, with_sim=True)
         buf.mass.fill_(0.25)
