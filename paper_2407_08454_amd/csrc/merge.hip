@@ -278,42 +278,42 @@ template <typename T, bool WITH_W, int MODE> struct SetMerge {
         __builtin_amdgcn_sched_barrier(0);
         add_sums(0, 4 * U, set_w, s);
     }
-    // a set of up to 16 tokens is read once: all loads issued together, both sweeps from registers
+    // a set of up to 16 tokens is read once: all loads issued together, both sweeps from registers.  (Left alone, the compiler
+    // moves the pivot's load and the wait for it ahead of the branch on the length, and in fp16 takes the rows of the fixed mode
+    // one by one, a round trip each: 512 slices of 4096 tokens in sets of three, fixed sigma, fp16, 880 / 544 us.)
     __device__ __forceinline__ void sums_short(int p, SetSums &s) {
+        if constexpr (sizeof(T) == 2) asm volatile("");
         clear(s);
         const Raw kp_raw = row_chunk<T>(Ks, p, c);
         Raw kr[U], vr[U];
         load_rows(Ks, lo, kr);
         load_rows(Vs, lo, vr);
+        if (MODE == MERGE_FIXED) __builtin_amdgcn_sched_barrier(0);
         E::to_float(kp_raw, kp);
-        float d[U], inv_mean = 0.f;
-        if (MODE != MERGE_AVERAGE) {
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                float x[8];
-                E::to_float(kr[u], x);
-                d[u] = sq_dist16(kp, x);
-            }
+        if (MODE != MERGE_ADAPTIVE) {
+            batch_sums(lo, kr, vr, nullptr, s);
+            return;
         }
-        if (MODE == MERGE_ADAPTIVE) {
-            float dsum = 0.f;
+        float d[U], dsum = 0.f;
 #pragma unroll
-            for (int u = 0; u < U; ++u) {
-                d[u] = __builtin_amdgcn_sqrtf(d[u]);
-                dsum += lo + 4 * u + slot < hi ? d[u] : 0.f;
-            }
-            dsum = rows4_sum(dsum);
-            inv_mean = dsum > 0.f ? (float)(hi - lo) / dsum : 0.f;
+        for (int u = 0; u < U; ++u) {
+            float x[8];
+            E::to_float(kr[u], x);
+            d[u] = sq_dist16(kp, x);
         }
 #pragma unroll
         for (int u = 0; u < U; ++u) {
+            d[u] = __builtin_amdgcn_sqrtf(d[u]);
+            dsum += lo + 4 * u + slot < hi ? d[u] : 0.f;
+        }
+        dsum = rows4_sum(dsum);
+        const float inv_mean = dsum > 0.f ? (float)(hi - lo) / dsum : 0.f;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
             const int row = lo + 4 * u + slot;
-            float x[8], v[8], g = 1.f;
-            if (MODE == MERGE_FIXED) g = __expf(-d[u] * a.inv_two_sigma_sq);
-            if (MODE == MERGE_ADAPTIVE) {
-                const float r = d[u] * inv_mean;
-                g = __expf(-r * r);
-            }
+            float x[8], v[8];
+            const float r = d[u] * inv_mean;
+            float g = __expf(-r * r);
             g = row < hi ? g : 0.f;
             if (WITH_W && c == 0 && row < hi) wo[row] = g;
             E::to_float(kr[u], x);
@@ -426,8 +426,13 @@ __device__ __forceinline__ void merge_set_team(const T *Ks, const T *Vs, T *k_ro
 
 // WAVES 1: a wave is a workgroup of its own.  WAVES 4: four tiles a workgroup, whose waves then merge the sets of more than
 // SPLIT_SET_MIN tokens together.
+// Four waves a SIMD in 16 bit; three where fixed sigma with the weights written would spill for it (512 slices of 4096 tokens in sets of two 1135 / 991 us,
+// of sixteen 254 / 231, 256 slices of AR(1) keys 183 / 170).
+template <typename T, bool WITH_W, int MODE> constexpr int merge_waves_per_simd() {
+    return sizeof(T) == 4 ? 2 : WITH_W && MODE == MERGE_FIXED ? 3 : 4;
+}
 template <typename T, bool WITH_W, int MODE, int WAVES>
-__global__ __launch_bounds__(WAVES * WAVE, sizeof(T) == 2 ? 4 : 2) void merge_kernel(const T *__restrict__ K, const T *__restrict__ V,
+__global__ __launch_bounds__(WAVES * WAVE, (merge_waves_per_simd<T, WITH_W, MODE>())) void merge_kernel(const T *__restrict__ K, const T *__restrict__ V,
                                                             T *__restrict__ K_out, T *__restrict__ V_out, MergeArgs a)
 {
     using E = Elem<T>;
