@@ -185,6 +185,16 @@ __device__ __forceinline__ float rows4_sum(float v) {
     return __builtin_bit_cast(float, t0) + __builtin_bit_cast(float, t1);
 }
 
+// The same sum of two values at once: of a in rows 0 and 2, of b in rows 1 and 3, with the bits of rows4_sum.
+__device__ __forceinline__ float rows4_sum_pair(float a, float b) {
+    const auto r = __builtin_amdgcn_permlane16_swap(__builtin_bit_cast(uint32_t, a), __builtin_bit_cast(uint32_t, b), false, false);
+    const uint32_t r0 = r[0], r1 = r[1];
+    const uint32_t s = __builtin_bit_cast(uint32_t, __builtin_bit_cast(float, r0) + __builtin_bit_cast(float, r1));
+    const auto t = __builtin_amdgcn_permlane32_swap(s, s, false, false);
+    const uint32_t t0 = t[0], t1 = t[1];
+    return __builtin_bit_cast(float, t0) + __builtin_bit_cast(float, t1);
+}
+
 // Order-preserving map of a finite float onto uint32 (-0 and +0 map to the same key).
 __device__ __forceinline__ uint32_t sortable_key(float f) {
     uint32_t u = __builtin_bit_cast(uint32_t, f + 0.0f);

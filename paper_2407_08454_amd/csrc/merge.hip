@@ -324,21 +324,25 @@ template <typename T, bool WITH_W, int MODE> struct SetMerge {
         }
     }
     __device__ __forceinline__ void load_pivot(int p) { E::to_float(row_chunk<T>(Ks, p, c), kp); }
-    // the merged rows (each writer of a weight normalises its own: rows from lo + slot, of one wave)
+    // the merged rows.  The weights that are normalised here were written by other lanes, in a team by other waves: the caller puts a fence
+    // (a barrier in a team) between those stores and this.
     __device__ __forceinline__ void finish(SetSums &s, T *k_row, T *v_row) const {
         const int m = hi - lo;
         const float inv_g = 1.f / rows4_sum(s.g);
-        const float vscale = a.value_scale ? inv_g * (float)m : inv_g;
+        // Keys come out in the even rows of the wave, values in the odd ones.  us, two sums for every column / one: 512 slices of 4096 tokens in sets
+        // of two 826 / 725, of eight 252 / 236, 64 of 4096 in sets of three 80 / 68, 32 of 1000 AR(1) keys 16.5 / 15.3.  (What depends on the
+        // row is worked out here, for every set: kept across the sets it spills.)
+        int row = slot;
+        asm volatile("" : "+v"(row));
+        const float scale = (row & 1) && a.value_scale ? inv_g * (float)m : inv_g;
+        float out[8];
 #pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            s.k[e] = rows4_sum(s.k[e]) * inv_g;
-            s.v[e] = rows4_sum(s.v[e]) * vscale;
-        }
+        for (int e = 0; e < 8; ++e) out[e] = rows4_sum_pair(s.k[e], s.v[e]) * scale;
         // (the hint keeps the merged rows, which nothing reads soon, out of the caches that hold the keys for their second sweep and what is
         // left of the inputs: merge of 128 slices of 2048 tokens 45.2 / 44.5 us without / with it, 64 of 4096 in fp32 83 / 71, 32 of 16000
         // 85.5 / 74.5, 1600 of 500 114 / 107.5, 1024 of 4096 588 / 574)
-        if (slot == 0) E::store_stream(k_row, c, E::from_float(s.k));
-        if (slot == 1) E::store_stream(v_row, c, E::from_float(s.v));
+        const Raw merged = E::from_float(out);
+        if (row < 2) E::store_stream(row == 0 ? k_row : v_row, c, merged);
         if (WITH_W) {
             for (int i = lane; i < m; i += WAVE) wo[lo + i] *= inv_g;
         }
