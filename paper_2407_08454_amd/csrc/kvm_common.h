@@ -230,8 +230,11 @@ __device__ __forceinline__ void load_rows_once(const T *slice, int j0, int n, in
 // 32768 80 / 70, of 8 of 4000 for 131072 84 / 77, of 128 of 1000 fp16 tokens for 16384 100 / 95; their decode-time scores and a read of the merged rows 41 /
 // 32, 32 / 26, 47 / 40; full caches as before.
 constexpr long long LLC_BYTES = 256ll << 20;                 // last-level cache
+inline long long token_bytes(const kvm_shape &sh) {          // one token's keys in all slices
+    return (long long)sh.B * sh.H_kv * HEAD_DIM * (sh.dtype == KVM_F32 ? 4 : 2);
+}
 inline int stream_length(const kvm_shape &sh, long long bytes) {
-    const long long per_token = (long long)sh.B * sh.H_kv * HEAD_DIM * (sh.dtype == KVM_F32 ? 4 : 2);
+    const long long per_token = token_bytes(sh);
     return (int)((bytes + per_token - 1) / per_token);       // (below 2^20: a token has at least 256 bytes)
 }
 

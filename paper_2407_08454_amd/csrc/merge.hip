@@ -50,6 +50,13 @@ constexpr int MERGE_GROUPED_TILES = 128;                     // per slice
 // beyond, where the waves of a workgroup that wait for the slowest leave their places empty: 100 of 1000 26.5 / 29.5, 32 of 4000
 // 26.6 / 28.7, 64 of 8000 75 / 91, 1024 of 4096 577 / 980.
 constexpr long long MERGE_TEAM_TOKENS = 3 << 15;
+// The merged rows go out with the non-temporal hint where keys, values and the compacted cache come to more than the last-level cache holds:
+// that keeps the keys for their second sweep and what is left of the inputs in it.  In smaller launches who reads the compacted cache
+// next, the attention of the next token, finds it in the cache.  Budget 0.5, us, compaction / compaction and a read of the merged rows, plain / hint:
+// 40 slices of 3000 fp16 tokens (29 MiB of keys) 43.4 / 43.2 and 59.4 / 60.4, 64 of 4096 (64 MiB) 63.8 / 63.5 and 86.4 / 87.1, 96 of them 91.4 / 84.5 and
+// 119.5 / 115.6, 128 110.8 / 106.7 and 146.5 / 144.3; fp32: 40 of 3000 57.6 / 57.9 and 76.5 / 77.9, 64 of 3000 83.2 / 79.2 and 107.2 / 106.9; merge alone,
+// 1024 of 4096 in fp16 567 / 550, in fp32 1100 / 1068.
+static bool streams_rows(const kvm_shape &sh, int cap_rows) { return 2 * token_bytes(sh) * ((long long)sh.N + cap_rows) >= LLC_BYTES; }
 // Sets of more than LONG_SET_MIN tokens are left to merge_long_kernel, which puts a whole workgroup
 // on each of them: one wave would stream such a set for hundreds of dependent round trips while
 // the rest of the chip has nothing to do (identical keys make one set of a whole slice).
@@ -117,6 +124,28 @@ __device__ __forceinline__ typename Elem<T>::Raw row_chunk(const T *slice, int r
     const uint32_t at = (uint32_t)row * (uint32_t)(HEAD_DIM * sizeof(T)) + (uint32_t)c * (uint32_t)(8 * sizeof(T));
     return Elem<T>::load(reinterpret_cast<const T *>(reinterpret_cast<const char *>(slice) + at), 0);
 }
+
+// A row that is copied: lane c of 16 moves the pieces c, c + 16 of 16 bytes, so that every store of a wave writes whole rows or half rows
+// (where an fp32 lane stored its 32 bytes in two, each store wrote every other 16 bytes, and the non-temporal hint sent them out like that: copies of all
+// tokens of 64 slices of 4096 in fp32, plain / that with the hint / this 105 / 93 / 86 us, of 512 slices 806 / 916 / 851; merge of 1024 of AR(1) keys
+// 1148 / 1110 / 1068).
+template <typename T> struct CopiedRow {
+    u32x4 piece[sizeof(T) / 2];
+    __device__ __forceinline__ void load(const T *slice, int row, int c) {
+        const uint32_t at = (uint32_t)row * (uint32_t)(HEAD_DIM * sizeof(T)) + (uint32_t)c * 16u;
+#pragma unroll
+        for (int h = 0; h < (int)sizeof(T) / 2; ++h)
+            piece[h] = *reinterpret_cast<const u32x4 *>(reinterpret_cast<const char *>(slice) + at + 256 * h);
+    }
+    template <bool STREAM> __device__ __forceinline__ void store(T *row, int c) const {
+        u32x4 *p = reinterpret_cast<u32x4 *>(row) + c;
+#pragma unroll
+        for (int h = 0; h < (int)sizeof(T) / 2; ++h) {
+            if constexpr (STREAM) __builtin_nontemporal_store(piece[h], p + 16 * h);
+            else p[16 * h] = piece[h];
+        }
+    }
+};
 
 // Squared distance of 8 elements, summed over the 16 lanes of the row.
 __device__ __forceinline__ float sq_dist16(const float *kp, const float *x) {
@@ -326,7 +355,7 @@ template <typename T, bool WITH_W, int MODE> struct SetMerge {
     __device__ __forceinline__ void load_pivot(int p) { E::to_float(row_chunk<T>(Ks, p, c), kp); }
     // the merged rows.  The weights that are normalised here were written by other lanes, in a team by other waves: the caller puts a fence
     // (a barrier in a team) between those stores and this.
-    __device__ __forceinline__ void finish(SetSums &s, T *k_row, T *v_row) const {
+    template <bool STREAM> __device__ __forceinline__ void finish(SetSums &s, T *k_row, T *v_row) const {
         const int m = hi - lo;
         const float inv_g = 1.f / rows4_sum(s.g);
         // Keys come out in the even rows of the wave, values in the odd ones.  us, two sums for every column / one: 512 slices of 4096 tokens in sets
@@ -338,11 +367,10 @@ template <typename T, bool WITH_W, int MODE> struct SetMerge {
         float out[8];
 #pragma unroll
         for (int e = 0; e < 8; ++e) out[e] = rows4_sum_pair(s.k[e], s.v[e]) * scale;
-        // (the hint keeps the merged rows, which nothing reads soon, out of the caches that hold the keys for their second sweep and what is
-        // left of the inputs: merge of 128 slices of 2048 tokens 45.2 / 44.5 us without / with it, 64 of 4096 in fp32 83 / 71, 32 of 16000
-        // 85.5 / 74.5, 1600 of 500 114 / 107.5, 1024 of 4096 588 / 574)
-        const Raw merged = E::from_float(out);
-        if (row < 2) E::store_stream(row == 0 ? k_row : v_row, c, merged);
+        if (row < 2) {
+            if constexpr (STREAM) E::store_stream(row == 0 ? k_row : v_row, c, E::from_float(out));
+            else E::store(row == 0 ? k_row : v_row, c, E::from_float(out));
+        }
         if (WITH_W) {
             for (int i = lane; i < m; i += WAVE) wo[lo + i] *= inv_g;
         }
@@ -357,7 +385,7 @@ template <typename T, bool WITH_W, int MODE> struct SetMerge {
 // wave's arithmetic took as long as its loads: us, before / now, this and the sums on swaps instead of LDS moves together, one slice
 // of 512 fp32 tokens 15.1 / 13.6, 1 of 16000 17.4 / 14.2, 32 of 2000 31.8 / 29.4, 1600 of 500 in bf16, now four waves a SIMD
 // instead of three, 115 / 103.)
-template <typename T, bool WITH_W, int MODE, bool ANY_LENGTH>
+template <typename T, bool WITH_W, int MODE, bool ANY_LENGTH, bool STREAM>
 __device__ __forceinline__ void merge_one_set(const T *Ks, const T *Vs, T *k_row, T *v_row, float *wo, int lo, int hi, int p,
                                               const MergeArgs &a, int lane, float *set_w)
 {
@@ -395,7 +423,7 @@ __device__ __forceinline__ void merge_one_set(const T *Ks, const T *Vs, T *k_row
         wave_lds_fence();                                     // the next set's distances come to the same place
     }
     if (WITH_W) wave_lds_fence();
-    set.finish(s, k_row, v_row);
+    set.template finish<STREAM>(s, k_row, v_row);
 }
 
 // The same for a set of more than SPLIT_SET_MIN tokens by four waves of a workgroup, one part each.  All threads of the workgroup call
@@ -424,7 +452,7 @@ __device__ __forceinline__ void merge_set_team(const T *Ks, const T *Vs, T *k_ro
     __syncthreads();
     if (part_id == 0 && hi > lo) {
         for (int q = 0; q < SPLIT_PARTS - 1; ++q) add_parked(s, sh.part[q] + lane);
-        set.finish(s, k_row, v_row);
+        set.template finish<false>(s, k_row, v_row);
     }
 }
 
@@ -435,12 +463,10 @@ __device__ __forceinline__ void merge_set_team(const T *Ks, const T *Vs, T *k_ro
 template <typename T, bool WITH_W, int MODE> constexpr int merge_waves_per_simd() {
     return sizeof(T) == 4 ? 2 : WITH_W && MODE == MERGE_FIXED ? 3 : 4;
 }
-template <typename T, bool WITH_W, int MODE, int WAVES>
+template <typename T, bool WITH_W, int MODE, int WAVES, bool STREAM>
 __global__ __launch_bounds__(WAVES * WAVE, (merge_waves_per_simd<T, WITH_W, MODE>())) void merge_kernel(const T *__restrict__ K, const T *__restrict__ V,
                                                             T *__restrict__ K_out, T *__restrict__ V_out, MergeArgs a)
 {
-    using E = Elem<T>;
-    using Raw = typename E::Raw;
     constexpr int US = 4;                      // row groups (of 4 rows) in flight in runs of singleton sets
     constexpr bool TEAM = WAVES == SPLIT_PARTS;
     __shared__ float set_w[WAVES][TEAM ? SPLIT_SET_MIN : LONG_SET_MIN + PARKED];   // (merge_one_set)
@@ -496,23 +522,23 @@ __global__ __launch_bounds__(WAVES * WAVE, (merge_waves_per_simd<T, WITH_W, MODE
         if ((single_mask >> i) & 1ull) {
             const unsigned long long others = ~(single_mask >> i);        // (no bit of the mask is set beyond cnt)
             const int run = min(others ? __builtin_ctzll(others) : WAVE, 4 * US);
-            Raw rk[US], rv[US];
+            CopiedRow<T> rk[US], rv[US];
             int src[US];
 #pragma unroll
             for (int u = 0; u < US; ++u) {
                 const int r = 4 * u + slot;
                 src[u] = __shfl(my_start, i + min(r, run - 1), WAVE);
                 if (r < run) {
-                    rk[u] = row_chunk<T>(Ks, src[u], c);
-                    rv[u] = row_chunk<T>(Vs, src[u], c);
+                    rk[u].load(Ks, src[u], c);
+                    rv[u].load(Vs, src[u], c);
                 }
             }
 #pragma unroll
             for (int u = 0; u < US; ++u) {
                 const int r = 4 * u + slot;
                 if (r < run) {
-                    E::store_stream(Ko + (size_t)(s_lo + i + r) * HEAD_DIM, c, rk[u]);
-                    E::store_stream(Vo + (size_t)(s_lo + i + r) * HEAD_DIM, c, rv[u]);
+                    rk[u].template store<STREAM>(Ko + (size_t)(s_lo + i + r) * HEAD_DIM, c);
+                    rv[u].template store<STREAM>(Vo + (size_t)(s_lo + i + r) * HEAD_DIM, c);
                     if (WITH_W && c == 0) wo[src[u]] = 1.f;
                 }
             }
@@ -531,7 +557,7 @@ __global__ __launch_bounds__(WAVES * WAVE, (merge_waves_per_simd<T, WITH_W, MODE
             ++i;
             continue;
         }
-        merge_one_set<T, WITH_W, MODE, !TEAM>(Ks, Vs, Ko + (size_t)(s_lo + i) * HEAD_DIM, Vo + (size_t)(s_lo + i) * HEAD_DIM, wo, lo, hi, p,
+        merge_one_set<T, WITH_W, MODE, !TEAM, STREAM>(Ks, Vs, Ko + (size_t)(s_lo + i) * HEAD_DIM, Vo + (size_t)(s_lo + i) * HEAD_DIM, wo, lo, hi, p,
                                               a, lane, set_w[wave]);
         ++i;
     }
@@ -706,7 +732,7 @@ __global__ __launch_bounds__(LONG_SET_BLOCK) __attribute__((amdgpu_waves_per_eu(
     }
 }
 
-template <typename T, int WAVES>
+template <typename T, int WAVES, bool STREAM>
 static void launch_merge_t(const kvm_shape &sh, const void *K, const void *V, void *K_out, void *V_out,
                            const MergeArgs &a, hipStream_t st)
 {
@@ -716,13 +742,13 @@ static void launch_merge_t(const kvm_shape &sh, const void *K, const void *V, vo
         hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(WAVES * WAVE), 0, st, (const T *)K, (const T *)V, (T *)K_out, (T *)V_out, a);
     };
     if (a.w_opt) {
-        if (a.mode == MERGE_AVERAGE) run(merge_kernel<T, true, MERGE_AVERAGE, WAVES>);
-        else if (a.mode == MERGE_FIXED) run(merge_kernel<T, true, MERGE_FIXED, WAVES>);
-        else run(merge_kernel<T, true, MERGE_ADAPTIVE, WAVES>);
+        if (a.mode == MERGE_AVERAGE) run(merge_kernel<T, true, MERGE_AVERAGE, WAVES, STREAM>);
+        else if (a.mode == MERGE_FIXED) run(merge_kernel<T, true, MERGE_FIXED, WAVES, STREAM>);
+        else run(merge_kernel<T, true, MERGE_ADAPTIVE, WAVES, STREAM>);
     } else {
-        if (a.mode == MERGE_AVERAGE) run(merge_kernel<T, false, MERGE_AVERAGE, WAVES>);
-        else if (a.mode == MERGE_FIXED) run(merge_kernel<T, false, MERGE_FIXED, WAVES>);
-        else run(merge_kernel<T, false, MERGE_ADAPTIVE, WAVES>);
+        if (a.mode == MERGE_AVERAGE) run(merge_kernel<T, false, MERGE_AVERAGE, WAVES, STREAM>);
+        else if (a.mode == MERGE_FIXED) run(merge_kernel<T, false, MERGE_FIXED, WAVES, STREAM>);
+        else run(merge_kernel<T, false, MERGE_ADAPTIVE, WAVES, STREAM>);
     }
 }
 
@@ -768,10 +794,17 @@ kvm_status launch_merge(const kvm_shape &sh, const kvm_params &pr, int cap_rows,
     a.inv_two_sigma_sq = a.mode == MERGE_FIXED ? 1.f / (2.f * pr.sigma * pr.sigma) : 0.f;
     a.value_scale = pr.value_scale_by_set_size;
     const bool team = (long long)sh.B * sh.H_kv * sh.N <= MERGE_TEAM_TOKENS;
+    const bool stream = streams_rows(sh, cap_rows);
+    const auto launch = [&](auto elem) {
+        using T = decltype(elem);
+        if (team) launch_merge_t<T, 4, false>(sh, K, V, K_out, V_out, a, st);
+        else if (stream) launch_merge_t<T, 1, true>(sh, K, V, K_out, V_out, a, st);
+        else launch_merge_t<T, 1, false>(sh, K, V, K_out, V_out, a, st);
+    };
     switch (sh.dtype) {
-    case KVM_F32: team ? launch_merge_t<float, 4>(sh, K, V, K_out, V_out, a, st) : launch_merge_t<float, 1>(sh, K, V, K_out, V_out, a, st); break;
-    case KVM_F16: team ? launch_merge_t<half_t, 4>(sh, K, V, K_out, V_out, a, st) : launch_merge_t<half_t, 1>(sh, K, V, K_out, V_out, a, st); break;
-    default: team ? launch_merge_t<bf16_t, 4>(sh, K, V, K_out, V_out, a, st) : launch_merge_t<bf16_t, 1>(sh, K, V, K_out, V_out, a, st); break;
+    case KVM_F32: launch(float()); break;
+    case KVM_F16: launch(half_t()); break;
+    default: launch(bf16_t()); break;
     }
     kvm_status rc = check_launch("merge_kernel");
     if (rc != KVM_OK || sh.N <= LONG_SET_MIN) return rc;          // (no slice can hold a long set)
@@ -947,7 +980,7 @@ __global__ __launch_bounds__(REFRESH_BLOCK, 4) void refresh_kernel(const T *__re
                 continue;
             }
             const int p = min(max(piv[s], lo), hi - 1);
-            merge_one_set<T, false, MODE, false>(Ks, Vs, Ko + (size_t)s * HEAD_DIM, Vo + (size_t)s * HEAD_DIM, nullptr, lo, hi, p, a, lane,
+            merge_one_set<T, false, MODE, false, false>(Ks, Vs, Ko + (size_t)s * HEAD_DIM, Vo + (size_t)s * HEAD_DIM, nullptr, lo, hi, p, a, lane,
                                                  set_w[wave]);
         }
         __syncthreads();

@@ -512,8 +512,8 @@ def test_mass_append_continues_the_prefill_pass():
 @pytest.mark.parametrize("dtype,H", [("f16", 64), ("bf16", 32), ("f32", 16)])
 def test_streamed_launches_give_the_bits_of_small_ones(dtype, H, cut):
     """From 128 MiB of keys (decode-time scores) and 256 MiB (scan) on, rows are read with the non-temporal hint, each slice
-    by its own length: with its second row shorter by `cut` a batch streams in both kernels, in one, in none of that row.  Nothing
-    else differs, so every slice has the bits it gets in a call of its own, ragged last tiles included."""
+    by its own length: with its second row shorter by `cut` a batch streams in both kernels, in one, in none of that row; the
+    merge writes with the hint where its rows and the caches come to 256 MiB.  Nothing else differs, so every slice has the bits it gets in a call of its own, ragged last tiles included."""
     B, N = 2, 16381 if dtype == "f32" else 16384
     esz = 4 if dtype == "f32" else 2
     _say(f"streamed launches: {dtype}, {B * H} slices of {N} ({B * H * N * 128 * esz >> 20} MiB of keys)")
@@ -530,8 +530,11 @@ def test_streamed_launches_give_the_bits_of_small_ones(dtype, H, cut):
         kb.kvm_attn_mass_append(shape, q_part, K_part, buf.mass, buf.ws)
         kb.kvm_identify_sets(shape, params, K_part, buf.mass, buf.set_id, buf.set_start, buf.pivot, buf.n_sets, buf.sim,
                              buf.status, buf.ws)
-        results.append([t[-1, -1].cpu() for t in (buf.mass, buf.sim, buf.set_id, buf.set_start, buf.pivot)])
-    for name, a, b in zip(("mass", "sim", "set_id", "set_start", "pivot"), *results):
+        kb.kvm_merge(shape, params, K_part, K_part, buf.set_start, buf.pivot, buf.n_sets, buf.K_out, buf.V_out, None, buf.ws)
+        rows = int(buf.n_sets[-1, -1])
+        results.append([t[-1, -1].cpu() for t in (buf.mass, buf.sim, buf.set_id, buf.set_start, buf.pivot)] +
+                       [t[-1, -1, :rows].cpu() for t in (buf.K_out, buf.V_out)])
+    for name, a, b in zip(("mass", "sim", "set_id", "set_start", "pivot", "K_out", "V_out"), *results):
         assert torch.equal(a, b), name
 
 
