@@ -253,6 +253,23 @@ def test_mass_fp32_smallest_launches(G, lens, N, copies):
         assert (np.abs(got[b, :, :n] - want[b, :, :n]) <= (1e-5 + 8 * 2.0 ** -24 * math.sqrt(N)) * want[b, :, :n]).all()
 
 
+def test_mass_fp32_split_rule():
+    """Where the fp32 split launches change kernels: up to 256 blocks of 32 rows 16 rows and eight waves a workgroup, up to 384 blocks
+    16 rows and four waves, beyond 32 rows.  One slice repeated: the same bits within a range, other orders of the fp32 sums and
+    so other bits on its other side (all three add up the same 1000 terms: 8 * 2^-24 sqrt(N) of a sum, and the exponent's 1e-5)."""
+    N = 1000                                                  # 32 blocks a slice
+    _say("mass, fp32 split rule")
+    Q, K, _ = _slices(37, 1, 1, [N], N, 128, 1, "f32")
+    bits = {c: gu.gpu_mass(Q, K, "f32", copies=c, kernels=["attn_lse_split_kernel", "attn_colsum_split_kernel"]) for c in (1, 8, 9, 12, 13, 16)}
+    for a, b in ((1, 8), (9, 12), (13, 16)):
+        assert np.array_equal(bits[a], bits[b]), (a, b)
+    for a, b in ((8, 9), (12, 13), (8, 13)):
+        assert not np.array_equal(bits[a], bits[b]), (a, b)
+    want = ref.attn_mass(Q, K, "f32")
+    for c in bits:
+        assert (np.abs(bits[c] - want) <= (1e-5 + 8 * 2.0 ** -24 * math.sqrt(N)) * want).all(), c
+
+
 @pytest.mark.parametrize("dtype,G,lens,N,copies,kernels", [
     ("f16", 1, [2304, 0, 2048, 1, 1793, 1025, 257, 512], 2304, 7, ["attn_lse_kernel", "attn_colsum_kernel"]),
     ("bf16", 2, [2100, 1800, 1, 0, 700, 2304], 2304, 9, ["attn_lse_kernel", "attn_colsum_kernel"]),
@@ -1192,6 +1209,34 @@ def test_merge_sets_of_two_batches(dtype):
     assert np.abs(b.w.cpu().numpy() - rw).max() <= gu.TOL
 
 
+def test_merge_rounds_bf16_rows_like_the_storage_type():
+    """The merged rows' rounding to bf16, on means that are exact in fp32: of two equal rows the row itself for every finite pattern whose
+    sum does not overflow, subnormals among them; of two neighbours, half way between them, the even one; NaN stays NaN."""
+    _say("merge: rounding of bf16 rows")
+    x = np.arange(65536, dtype=np.uint16).reshape(512, 128)
+    up = np.minimum(x.astype(np.uint32) + 1, 65535).astype(np.uint16)
+    params = kb.make_params(1.0, 0.0, 0.0, value_scale_by_set_size=False, enforce_budget=False, weights=kb.KVM_WEIGHTS_AVERAGE)
+    n, M = 1024, 512
+    starts = np.full((1, 1, n + 1), n, np.int32)
+    starts[..., :M] = 2 * np.arange(M)
+    pivot = np.full((1, 1, n), -1, np.int32)
+    pivot[..., :M] = starts[..., :M]
+    for other in (x, up):
+        rows = np.stack([x, other], 1).reshape(1, 1, n, 128)
+        Ko, Vo, _, _, _ = gu.gpu_merge(rows, rows, "bf16", params, starts, pivot, np.full((1, 1), M, np.int32))
+        f = (rows.astype(np.uint32) << 16).view(np.float32).reshape(M, 2, 128)
+        with np.errstate(all="ignore"):
+            mean = (f[:, 0] + f[:, 1]) * np.float32(0.5)
+            exact = (f[:, 0].astype(np.float64) + f[:, 1]) * 0.5
+        u = mean.view(np.uint32)
+        want = ((u + 0x7FFF + ((u >> 16) & 1)) & 0xFFFF0000).astype(np.uint32).view(np.float32)
+        sure, nan = np.isfinite(f).all(axis=1) & (mean == exact), np.isnan(f).any(axis=1)
+        assert sure.mean() > 0.98
+        for got in (Ko[0, 0, :M], Vo[0, 0, :M]):
+            assert np.array_equal(got[sure].astype(np.float32), want[sure])
+            assert np.isnan(got[nan]).all()
+
+
 @pytest.mark.parametrize("N,copies,rows", [(1, 20200, 13), (40, 600, 13), (100, 210, 13), (256, 80, 13), (700, 29, 13), (4096, 22, 3), (4097, 22, 3)])
 def test_merge_of_large_launches_of_short_slices(N, copies, rows):
     """Launches of more than 2^18 tokens deal out slices of up to 128 tiles in groups of eight, each group starting at
@@ -1865,6 +1910,18 @@ def _same_outputs(a, b, what):
             for h in range(M.shape[1]):
                 m = int(M[bb, h])
                 assert torch.equal(a[k][bb, h, :m], b[k][bb, h, :m]), f"{what}: {k} differs in slice ({bb},{h})"
+
+
+def test_stream_handle_with_and_without_torchs_raw_call(monkeypatch):
+    """The binding asks torch for the current stream's handle alone where it can; the public way has to give the same one."""
+    _say("binding: the current stream's handle")
+    side = torch.cuda.Stream()
+    for stream in (torch.cuda.default_stream(), side):
+        with torch.cuda.stream(stream):
+            assert kb._stream() == stream.cuda_stream
+            with monkeypatch.context() as m:
+                m.setattr(kb, "_current_raw_stream", None)
+                assert kb._stream() == stream.cuda_stream
 
 
 @pytest.mark.parametrize("rule", ["adjacent", "anchor"])
