@@ -159,8 +159,9 @@ size_t kvm_workspace_bytes(const kvm_shape *shape, const kvm_params *params);
  * B * H_kv * G.  The same slice in a call that covers fewer or more slices can
  * therefore differ in the last bits of its scores (about 1e-6 of a score), and
  * with them the top-k and pivot choices of kvm_identify_sets where two scores tie
- * that closely.  (16-bit types: the change lies between 128 and 384 workgroups of 256
- * rows, by length; fp32: at 128 workgroups of 128 rows.)
+ * that closely.  (16-bit types: the order changes between 128 and 384 workgroups of 256
+ * rows, by length, and for long rows also at 512 workgroups of 64 rows; fp32: at 256 and
+ * 384 blocks of 32 rows and at 128 workgroups of 128 rows; counted over all slices.)
  */
 kvm_status kvm_attn_mass(const kvm_shape *shape, const void *Q, const void *K, float *mass,
                          void *ws, size_t ws_bytes, void *stream);

@@ -519,7 +519,8 @@ constexpr int SPLIT16 = 16;              // added to the waves: the fp32 kernels
 // of 4096), 256 workgroups 84 / 108 (64 of 1000).  The kernels of 16 rows, both passes, 32 rows / 16 rows and four waves / eight: one slice
 // of 130 16.9 / 11.2 / 11.9, of 1000 44 / 31 / 28.5, of 4000 145 / 100 / 85.5, 8 of 1000 (256 workgroups of 32 rows) 45.5 / 39.7 / 36.5,
 // 16 of 512 (256, short chains) 27.0 / 23.7 / 25.4, 32 of 200 18.2 / 14.8 / 18.5, 4 of 3000 (376) 112 / 103 / 113; and 16 of 1000 (512) 55 / 58 /
-// 65: hence up to 384, eight waves where every workgroup has a compute unit to itself and its chain is long.
+// 65: hence up to 384 blocks of 32 rows, and eight waves, whose workgroups of 130 KB of LDS take a compute unit each, where the up to 512 of
+// them (two of 16 rows a block) are through in two rounds and the chain is long.
 // Eight waves instead of four halve the chain but leave one workgroup per compute unit: worth it where all of them
 // are resident in two rounds and the chain is long (8 slices of 1000, G = 4, column sums: 30 with four, 24 with
 // eight; of 4096: 117 and 93; 32 slices of 1000, chain of 32: 15 and 17).

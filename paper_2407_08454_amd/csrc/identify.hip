@@ -586,7 +586,8 @@ __global__ __launch_bounds__(SEG_BLOCK) void segment_kernel(SegArgs a)
 // What bounds it is one long dependent chain per slice, not a rate: so scans run on DPP moves instead of
 // cross-lane LDS traffic, every wave scans the histograms and the waves' totals for itself instead of waiting for
 // the one that does, a digit of the select that settles the threshold ends it, and a step that only ties or the budget
-// rule need is taken only then: six barriers for a slice without either, where there were 25.
+// rule need is taken only then: three barriers and one for every digit that is needed (one to four) in a slice without either, where
+// there were 25.  (With sixteen tokens a thread the compiler keeps 25 of the 128 registers' values in scratch.)
 
 // Copies of the radix select's histogram for the first digit.  The leading byte of scores and similarities takes
 // only a handful of values, and LDS atomics of a wave on one address are served one after the other: lane l counts
@@ -1316,7 +1317,8 @@ kvm_status launch_identify(const kvm_shape &sh, const kvm_params &pr, int cap_ro
         // Four tokens a thread, eight and sixteen only where 1024 threads are not enough: the chain of a thread is what a slice
         // waits for, also where the launch fills the chip.  us, sixteen a thread (first form of this kernel: 25 barriers) / four: one
         // slice of 512 tokens 15.7 / 6.9, 32 of 1000 15.9 / 7.6, 32 of 4000 15.9 / 9.0, 256 of 4000 19.9 / 11.4, 1024 of 4096 35.6 / 23.7,
-        // 1600 of 500 31.4 / 11.6; eight a thread instead of four: 1024 of 4096 26.5, 400 of 2000 11.2 against 10.6.
+        // 1600 of 500 31.4 / 11.6; eight a thread instead of four: 1024 of 4096 26.5, 400 of 2000 11.2 against 10.6.  First form / eight a thread:
+        // 32 of 8192 23.5 / 16.2, 1024 of them 73 / 65; / sixteen, spills and all: one of 9000 29.4 / 21.8, 1024 of 9000 136 / 110, of 16384 176 / 151.
         const auto run = [&](auto kernel, int block) {
             hipLaunchKernelGGL(kernel, dim3((unsigned)slices), dim3(block), 0, st, a);
         };
