@@ -295,9 +295,10 @@ __device__ __forceinline__ void rowstat_update(const f32x16 &acc, float c, float
 // pass 1 with the reference held: 16 more terms exp2(c s - mc) of a row's sum, no maximum and
 // no rescaling.  Any reference gives the same log-sum-exp as long as no term overflows and the sum is not scaled
 // to nothing when it is put on a higher reference: exp2 flushes its results below 2^-126 to zero, so a sum above the reference
-// by that much would be lost whole.  The caller checks the held sums against HELD_SUM_MAX before it does that: what a sum up to there
-// can lose is below 2^-62 of the row's.
-constexpr float HELD_SUM_MAX = 0x1p64f;
+// by that much would be lost whole.  The caller checks the held sums against HELD_SUM_MAX before it does that: a sum up to there
+// can lose 2^-30 of the row's, also where all of a row's partial sums do far below the rounding of fp32, and scores have to lie 66 natural
+// orders above the first keys' before a row is worked out again.
+constexpr float HELD_SUM_MAX = 0x1p96f;
 __device__ __forceinline__ void rowsum_held(const f32x16 &acc, float c, float mc, float &l_run) {
     float p0 = __builtin_amdgcn_exp2f(fmaf(acc[0], c, -mc)), p1 = __builtin_amdgcn_exp2f(fmaf(acc[1], c, -mc));
 #pragma unroll

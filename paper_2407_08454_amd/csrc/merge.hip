@@ -309,7 +309,7 @@ template <typename T, bool WITH_W, int MODE> struct SetMerge {
     }
     // a set of up to 16 tokens is read once: all loads issued together, both sweeps from registers.  (Left alone, the compiler
     // moves the pivot's load and the wait for it ahead of the branch on the length, and in fp16 takes the rows of the fixed mode
-    // one by one, a round trip each: 512 slices of 4096 tokens in sets of three, fixed sigma, fp16, 880 / 544 us.)
+    // one by one, a round trip each: 512 slices of 4096 tokens in sets of three, fixed sigma, fp16, 880 / 483 us.)
     __device__ __forceinline__ void sums_short(int p, SetSums &s) {
         if constexpr (sizeof(T) == 2) asm volatile("");
         clear(s);

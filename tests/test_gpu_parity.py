@@ -212,14 +212,14 @@ def _check_held_reference(got, want):
     assert np.abs(got[~big]).max(initial=0.0) <= 2e-6
 
 
-HELD_ORDERS = [40.0, 63.5, 64.5, 100.0, 126.3, 126.9, 128.5, 300.0]
+HELD_ORDERS = [40.0, 63.5, 64.5, 95.0, 97.0, 100.0, 126.3, 126.9, 128.5, 300.0]
 
 
 @pytest.mark.parametrize("dtype", ["f16", "bf16"])
 @pytest.mark.parametrize("orders", HELD_ORDERS)
 @pytest.mark.parametrize("n", [600, 2100])                    # four waves a workgroup, eight
 def test_mass_split_held_reference(dtype, orders, n):
-    """The split row statistics hold a wave's reference from its first block on: late keys around and beyond the 2^64 at
+    """The split row statistics hold a wave's reference from its first block on: late keys around and beyond the 2^96 at
     which a workgroup starts again with the maximum updated, in one wave or in two, after it or on its last block."""
     _say(f"mass, held reference: {dtype} {orders} binary orders, n={n}")
     Q, K, want = _held_reference_case(dtype, orders, n)
@@ -231,7 +231,7 @@ def test_mass_split_held_reference(dtype, orders, n):
 @pytest.mark.parametrize("n,copies", [(600, 26), (2100, 11)])
 def test_mass_full_held_reference(dtype, orders, n, copies):
     """The full row statistics hold the reference of the first 64 keys to the diagonal, and leave a tile whose held sums
-    passed 2^64 to the repeat launch."""
+    passed 2^96 to the repeat launch."""
     _say(f"mass, held reference in full launches: {dtype} {orders} binary orders, n={n}")
     Q, K, want = _held_reference_case(dtype, orders, n)
     _check_held_reference(gu.gpu_mass(Q, K, dtype, copies=copies, kernels=["attn_lse_kernel", "attn_lse_redo_kernel"]), want)
