@@ -46,7 +46,7 @@ typedef enum {
     KVM_OK = 0,
     KVM_ERR_INVALID_ARG = 1,  /* null pointer, negative size, ratio outside [0,1], ...      */
     KVM_ERR_UNSUPPORTED = 2,  /* d != 128, unknown dtype or sigma mode                      */
-    KVM_ERR_WORKSPACE = 3,    /* ws == NULL or ws_bytes < kvm_workspace_bytes()             */
+    KVM_ERR_WORKSPACE = 3,    /* ws == NULL or ws_bytes < kvm_workspace_bytes(shape, NULL)  */
     KVM_ERR_LAUNCH = 4        /* the HIP runtime refused a launch; see kvm_last_error()     */
 } kvm_status;
 
@@ -138,6 +138,10 @@ int32_t kvm_out_capacity(const kvm_shape *shape, const kvm_params *params);
  * Bytes of device workspace that is enough for any of the three calls on this
  * shape (256-byte aligned pointer expected).  Host call; 0 on invalid
  * arguments.  Contents need no initialisation and are not preserved.
+ * With params, what a program that runs the pass should bring: where short sequences (up
+ * to 4096 tokens in fp32, up to 2048 in 16-bit types) are scored in a single pass, the room for it is included, and
+ * kvm_attn_mass takes that pass when it finds the room.  With params == NULL the least
+ * that every call accepts.
  */
 size_t kvm_workspace_bytes(const kvm_shape *shape, const kvm_params *params);
 
@@ -161,7 +165,9 @@ size_t kvm_workspace_bytes(const kvm_shape *shape, const kvm_params *params);
  * with them the top-k and pivot choices of kvm_identify_sets where two scores tie
  * that closely.  (16-bit types: the order changes between 128 and 384 workgroups of 256
  * rows, by length, and for long rows also at 512 workgroups of 64 rows; fp32: at 256 and
- * 384 blocks of 32 rows and at 128 workgroups of 128 rows; counted over all slices.)
+ * 384 blocks of 32 rows and at 128 workgroups of 128 rows; counted over all slices.  The single pass
+ * over short sequences of the same length (seq_lens == NULL) adds in an order of its own, in which the number of slices counts too: a
+ * workspace with or without the room for it, see kvm_workspace_bytes, is another such choice.)
  */
 kvm_status kvm_attn_mass(const kvm_shape *shape, const void *Q, const void *K, float *mass,
                          void *ws, size_t ws_bytes, void *stream);
@@ -176,7 +182,8 @@ kvm_status kvm_attn_mass(const kvm_shape *shape, const void *Q, const void *K, f
  *              the order of the fp32 additions (a few 1e-7)
  * Pass sim to kvm_identify_sets as sim_opt with params.sim_given = 1 (adjacent rule).  Other
  * arguments, workspace, result and errors as for kvm_attn_mass; mass is bit for bit the same.
- * (fp32 caches: the similarities come from the same streaming scan kvm_identify_sets uses.)
+ * (fp32 caches, and scores from the single pass: the similarities come from the same streaming scan
+ * kvm_identify_sets uses.)
  */
 kvm_status kvm_attn_mass_sim(const kvm_shape *shape, const void *Q, const void *K, float *mass, float *sim,
                              void *ws, size_t ws_bytes, void *stream);

@@ -1,0 +1,505 @@
+// The aggregated scores of short sequences in one score pass (Section 2.4 Eq. (1), Section 4.2 Eq. (7)).
+//
+//   attn_single_kernel       exponentials, row sums and column sums of 32 rows (fp32: 16) at a time, from one QK^T
+//   attn_single_sum_kernel   adds the column sums of a slice's workgroups up, in their order
+//
+// The two passes of attn_mass.hip and attn_split.hip form the score matrix twice, with an exponential a score each time, because
+// a row's sum has to be known before its terms can go to the columns.  Up to 2048 keys (fp32: 4096) the terms of 32 (16) rows fit
+// the registers of a workgroup, though: its waves share the keys out, each keeps exp2(c s - r) of its own, r a reference of the
+// rows, the waves exchange their parts of the row sums, and each term goes to its column with one multiplication.  Half the
+// matrix work and half the exponentials; the price is that every key tile is read for 32 rows instead of 64 to 512.
+//
+// What bounds it (32 rows, 1024 slices of 1000 fp16 tokens): the 32 KB of keys that four SIMDs take in for 32x32 scores each are
+// 550 cycles of the path from the caches (60 bytes a cycle and compute unit, measured), their arithmetic is 400 cycles of the vector
+// ALU and 256 of the matrix pipe, and the exchange of the row sums leaves a wave idle once in 32 rows; the counters show the vector ALU
+// busy for half of the time, with two waves a SIMD (250 registers).  64 rows a workgroup would halve the traffic and were
+// twice as slow: eight waves then hold one compute unit, and nothing covers their exchanges.  fp32 is matrix time.
+// us, both passes / this: 1024 slices of 1000 fp16 tokens 460 / 365, 256 of them 128 / 85, 8 of them 20.5 / 13.3; 1024 of 512
+// 139 / 104, of 250 55 / 37, of 128 35 / 21; 32 of 2000 62 / 46; fp32: 256 of 1000 592 / 343, 32 of 4096 1055 / 755, one of 512 19.4 / 13.
+#include <algorithm>
+#include <type_traits>
+
+#include "attn_tile.h"
+
+namespace kvm {
+
+template <typename T> struct Single;
+// 16-bit types: 32 rows as two operands of the 16x16x32 MFMA against tiles of 32 keys; fp32: 16 rows and keys, 16x16x4.
+template <typename T> struct SingleHalf {
+    static constexpr int CH = 16, FRAGS = 4, SUB = 2;         // 16-byte chunks a row, fragments a lane and 16 rows, 16 keys a tile
+};
+template <> struct Single<half_t> : SingleHalf<half_t> {
+    static __device__ __forceinline__ f32x4 mma(const u32x4 &a, const u32x4 &b, const f32x4 &c) {
+        return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, a), __builtin_bit_cast(f16x8, b), c, 0, 0, 0);
+    }
+};
+template <> struct Single<bf16_t> : SingleHalf<bf16_t> {
+    static __device__ __forceinline__ f32x4 mma(const u32x4 &a, const u32x4 &b, const f32x4 &c) {
+        return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
+    }
+};
+template <> struct Single<float> {
+    static constexpr int CH = 32, FRAGS = 8, SUB = 1;
+    static __device__ __forceinline__ f32x4 mma(const u32x4 &a, const u32x4 &b, f32x4 c) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const uint32_t ai = a[i], bi = b[i];
+            c = __builtin_amdgcn_mfma_f32_16x16x4f32(__builtin_bit_cast(float, ai), __builtin_bit_cast(float, bi), c, 0, 0, 0);
+        }
+        return c;
+    }
+};
+
+// A row's terms are formed against one reference for all rows of the unit, the log-sum-exp of the unit before (of its first row).
+// Row sums between these bounds lose nothing by it: no term overflows, and one below 2^-126, which exp2 flushes to zero, is below 2^-94 of the
+// sum.  Other rows (the scores would have to move by 22 natural orders down or 66 up within a unit's distance) get a reference of their own.
+constexpr float SUM_MIN = 0x1p-32f;
+
+// s_waitcnt lgkmcnt(0) alone
+__device__ __forceinline__ void wait_lds() { __builtin_amdgcn_s_waitcnt(15 | (7 << 4) | (3 << 14)); }
+
+// f(0), f(1), .. f(N-1) with constant arguments
+template <int I, int N, typename F> __device__ __forceinline__ void static_for(F &&f) {
+    if constexpr (I < N) {
+        f(std::integral_constant<int, I>{});
+        static_for<I + 1, N>(f);
+    }
+}
+
+// 64 times 16 bytes of the `bytes` bytes at base (scalars) into consecutive LDS slots; what lies beyond reads as zeros
+__device__ __forceinline__ void load_lds(const char *base, int bytes, int lane_offset, int offset, u32x4 *dst) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc((void *)base, 0, bytes, 0x00027000);
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lptr_t)dst, 16, lane_offset, offset, 0, 0);
+#endif
+}
+
+// lane N of each row of 16 lanes, in all of them
+template <int N> __device__ __forceinline__ float row16_lane(float v) { return dpp_f<0x150 + N>(v); }
+
+// (max, sum) of a row and of more of its scores, in the reference of the larger maximum
+__device__ __forceinline__ void join(float &m0, float &l0, float m1, float l1, float c) {
+    const float m = fmaxf(m0, m1);
+    l0 = l0 * __builtin_amdgcn_exp2f((m0 - m) * c) + l1 * __builtin_amdgcn_exp2f((m1 - m) * c);
+    m0 = m;
+}
+
+// Units of work of a slice: a group of rows of one query head, counted off from the longest.  Workgroup p of P takes the units
+// p, 2P-1-p, 2P+p, ..: a long one, then short ones.
+template <typename T, int RT, int W, int NT, int OCC>
+__global__ __launch_bounds__(W * WAVE, OCC) void attn_single_kernel(
+    const T *__restrict__ Q, const T *__restrict__ K, float *__restrict__ out, int n_slices, int G, uint32_t inv_G, int n, int n_pad,
+    int P, float c)
+{
+    using A = Single<T>;
+    static_assert(RT == A::SUB, "one tile on the diagonal");
+    constexpr int SUB = A::SUB, ROWS = 16 * RT, KEYS = 16 * SUB, FR = A::FRAGS, CH = A::CH, R = 4 * RT;
+    constexpr int SLOTS = KEYS * CH, LOADS = SLOTS / WAVE, ROWS_PER_LOAD = WAVE / CH, ROW_BYTES = HEAD_DIM * (int)sizeof(T);
+    __shared__ u32x4 stage[W][SLOTS];
+    __shared__ __attribute__((aligned(16))) float part[2][W][ROWS];
+    __shared__ u32x4 rows_q[ROWS * CH];
+
+    const int lane = threadIdx.x & 63, group = lane >> 4, col = lane & 15;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    int slice, p;
+    if (n_slices >= 64) {
+        const int idx = blockIdx.x >> 3;
+        slice = (idx / P) * 8 + (blockIdx.x & 7);
+        p = idx % P;
+        if (slice >= n_slices) return;
+    } else {
+        slice = blockIdx.x % n_slices;
+        p = blockIdx.x / n_slices;
+    }
+    const int groups = (n + ROWS - 1) / ROWS, units = groups * G;
+    const char *Ks = reinterpret_cast<const char *>(K + (size_t)slice * n * HEAD_DIM);
+    const char *Qs = reinterpret_cast<const char *>(Q + (size_t)slice * G * n * HEAD_DIM);
+
+    // Rows [16 m, 16 m + 16) of a matrix into 16 rows of LDS, HALF load instructions; chunk ch of row r goes to position ch ^ r, which
+    // is done on the source side (the instruction writes 64 consecutive slots).  Rows past the slice's last one read as zeros.
+    constexpr int HALF = 16 * CH / WAVE;
+    int voff[HALF];
+#pragma unroll
+    for (int i = 0; i < HALF; ++i) {
+        const int row = i * ROWS_PER_LOAD + lane / CH, pos = lane % CH;
+        voff[i] = row * ROW_BYTES + ((pos ^ row) * 16);
+    }
+    int slot[FR];
+#pragma unroll
+    for (int f = 0; f < FR; ++f) slot[f] = col * CH + ((4 * f + group) ^ col);
+
+    auto issue = [&](int t) __attribute__((always_inline)) {
+        asm volatile("" : "+s"(t));                           // (or the offsets of all tiles are kept in registers from unit to unit)
+#pragma unroll
+        for (int i = 0; i < LOADS; ++i)
+            load_lds(Ks, n * ROW_BYTES, voff[i % HALF], (t * KEYS + 16 * (i / HALF)) * ROW_BYTES, stage[wave] + i * WAVE);
+    };
+
+    // unit o: its first tile, and its rows, which are dealt to the waves (rows past the end repeat the last one: sums that count for nothing)
+    u32x4 qf[RT][FR];
+    int head = 0, q0 = 0, cnt = 0, diag = 0;
+    auto begin = [&](int o) __attribute__((always_inline)) {
+        const int rank = G == 1 ? o : (int)__umulhi((uint32_t)o, inv_G);
+        head = o - rank * G;
+        q0 = (groups - 1 - rank) * ROWS;
+        diag = q0 / KEYS;                                     // key tile on the diagonal
+        cnt = (diag + W - wave) / W;                          // tiles of this wave: wave, wave + W, ..
+        if (cnt > 0) issue(wave);
+    };
+    auto load_rows = [&]() __attribute__((always_inline)) {
+        const char *Qg = Qs + (size_t)head * n * ROW_BYTES;
+        const int lane_now = fresh_lane();
+#pragma unroll
+        for (int i = 0; i < ROWS * CH / WAVE / W; ++i) {
+            const int j = i * W + wave, row = j * ROWS_PER_LOAD + lane_now / CH, pos = lane_now % CH;
+            load_lds(Qg, n * ROW_BYTES, min(row, n - 1 - q0) * ROW_BYTES + ((pos ^ (row & 15)) * 16), q0 * ROW_BYTES, rows_q + j * WAVE);
+        }
+    };
+    auto read_rows = [&]() __attribute__((always_inline)) {
+        const int lane_now = fresh_lane();                    // (addresses that need not stay in registers)
+#pragma unroll
+        for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+            for (int f = 0; f < FR; ++f) qf[rt][f] = rows_q[(lane_now & 15) * CH + ((4 * f + (lane_now >> 4)) ^ (lane_now & 15)) + 16 * CH * rt];
+        wait_lds();
+#pragma unroll
+        for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+            for (int f = 0; f < FR; ++f) asm volatile("" : "+v"(qf[rt][f]));
+    };
+    auto read_frags = [&](u32x4 (*kf)[FR]) __attribute__((always_inline)) {
+#pragma unroll
+        for (int j = 0; j < SUB; ++j)
+#pragma unroll
+            for (int f = 0; f < FR; ++f) kf[j][f] = stage[wave][slot[f] + 16 * CH * j];
+    };
+    auto scores = [&](const u32x4 (*kf)[FR], f32x4 (*s)[RT]) __attribute__((always_inline)) {
+#pragma unroll
+        for (int j = 0; j < SUB; ++j) {
+#pragma unroll
+            for (int rt = 0; rt < RT; ++rt) s[j][rt] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int f = 0; f < FR; ++f)
+#pragma unroll
+                for (int rt = 0; rt < RT; ++rt) s[j][rt] = A::mma(qf[rt][f], kf[j][f], s[j][rt]);
+        }
+    };
+    auto mask = [&](f32x4 (*s)[RT]) __attribute__((always_inline)) {      // the tile on the diagonal: keys after their row
+        const int lane_now = fresh_lane();
+        const int ahead = (lane_now & 15) - 4 * (lane_now >> 4);
+#pragma unroll
+        for (int j = 0; j < SUB; ++j)
+#pragma unroll
+            for (int r = 0; r < R; ++r)
+                if (16 * (r / 4) + r % 4 < 16 * j + ahead) s[j][r / 4][r % 4] = -INFINITY;
+    };
+
+    float colsum[NT][SUB];
+#pragma unroll
+    for (int i = 0; i < NT; ++i)
+#pragma unroll
+        for (int j = 0; j < SUB; ++j) colsum[i][j] = 0.f;
+    int covered = 0;
+    float base = 0.f;                                         // the reference; the first: the score of the first unit's first row with key 0
+    if (p < units) {
+        begin(p);
+        load_rows();
+        covered = cnt;
+        const T *q = reinterpret_cast<const T *>(Qs) + ((size_t)head * n + q0) * HEAD_DIM;
+        const typename Elem<T>::Raw first_row = Elem<T>::load(q, col), first_key = Elem<T>::load(reinterpret_cast<const T *>(Ks), col);
+        const float dot = c * row16_sum(RowDot<T>::dot(first_row, first_key));
+        if (fabsf(dot) < 0x1p60f) base = __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, dot)));
+    }
+    int par = 0;
+    uint64_t redo = 0;
+    for (int k = 0, o = p; o < units;) {
+        float l[R];
+        f32x4 t_[NT][SUB][RT];
+        const int q0_now = q0, cnt_now = cnt, diag_now = diag;
+        wait_vmcnt<0>();                                      // the wave's part of the rows and its first tile are here
+        barrier_no_fence();
+        read_rows();
+        if (cnt > 0) {
+            u32x4 kf[SUB][FR];
+            read_frags(kf);
+            wait_lds();
+            if (1 < cnt) issue(W + wave);
+            scores(kf, t_[0]);
+        }
+#pragma unroll
+        for (int r = 0; r < R; ++r) l[r] = 0.f;
+        auto terms = [&](f32x4 *s) __attribute__((always_inline)) {
+#pragma unroll
+            for (int r = 0; r < R; ++r) s[r / 4][r % 4] = __builtin_amdgcn_exp2f(fmaf(s[r / 4][r % 4], c, -base));
+#pragma unroll
+            for (int r = 0; r < R; ++r) l[r] += s[r / 4][r % 4];
+        };
+        // The terms of a tile are formed under the LDS reads of the next one and between its MFMAs.
+        static_for<1, NT + 1>([&](auto ic) __attribute__((always_inline)) {
+            constexpr int i = ic;
+            if (i < NT && i < cnt) {
+                if constexpr (i < NT) {
+                    wait_vmcnt<0>();
+                    u32x4 kf[SUB][FR];
+                    read_frags(kf);
+                    if constexpr (SUB > 1) terms(t_[i - 1][0]);
+                    __builtin_amdgcn_sched_barrier(0);
+                    wait_lds();
+                    if (i + 1 < NT && i + 1 < cnt) issue((i + 1) * W + wave);
+                    scores(kf, t_[i]);
+                    terms(t_[i - 1][SUB - 1]);
+                    if constexpr (sizeof(T) == 2) {
+#pragma unroll
+                        for (int q = 0; q < 4 * RT; ++q) {
+                            __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);   // MFMA
+                            __builtin_amdgcn_sched_group_barrier(0x002, 2, 0);   // VALU
+                            __builtin_amdgcn_sched_group_barrier(0x400, 1, 0);   // TRANS
+                        }
+                    }
+                }
+            } else if (i == cnt) {
+                if ((i - 1) * W + wave == diag_now) mask(t_[i - 1]);
+#pragma unroll
+                for (int j = 0; j < SUB; ++j) terms(t_[i - 1][j]);
+                asm volatile("");                             // (keeps the ends of all tiles apart: merged, they address t_ by a variable, in scratch)
+            }
+        });
+        // the next unit's first tile is on its way while this one's sums are exchanged, its rows while the terms go to the columns
+        ++k;
+        o = k * P + ((k & 1) ? P - 1 - p : p);
+        if (o < units) begin(o);
+#pragma unroll
+        for (int r = 0; r < R; ++r) l[r] = row16_sum(l[r]);
+        if (const int lane_w = fresh_lane(); (lane_w & 15) == 0) {
+#pragma unroll
+            for (int rt = 0; rt < RT; ++rt)
+                *reinterpret_cast<f32x4 *>(&part[par][wave][16 * rt + (lane_w >> 4) * 4]) = f32x4{l[4 * rt], l[4 * rt + 1], l[4 * rt + 2], l[4 * rt + 3]};
+        }
+        wait_lds();
+        barrier_no_fence();                                   // (and every wave has long read this unit's rows)
+        if (o < units) load_rows();
+        // lane `col` of a row of lanes adds up the sum of that row's own score row col
+        const int lane_now = fresh_lane();
+        const int myrow = 16 * ((lane_now >> 2) & (RT - 1)) + 4 * (lane_now >> 4) + (lane_now & 3);
+        float sum = part[par][0][myrow];
+#pragma unroll
+        for (int w = 1; w < W; ++w) sum += part[par][w][myrow];
+        const bool counts = q0_now + myrow < n;
+        const float first = __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, sum)));
+        if (__ballot(counts && !(sum >= SUM_MIN && sum <= HELD_SUM_MAX)) == 0) {   // (the same rows in every wave)
+            const float inv = counts ? 1.0f / sum : 0.f;
+            float wgt[R];
+            static_for<0, R>([&](auto ic) __attribute__((always_inline)) { wgt[ic] = row16_lane<ic>(inv); });
+            static_for<0, NT>([&](auto ic) __attribute__((always_inline)) {
+                constexpr int i = ic;
+                if (i < cnt_now) {
+#pragma unroll
+                    for (int j = 0; j < SUB; ++j)
+#pragma unroll
+                        for (int r = 0; r < R; ++r) colsum[i][j] = fmaf(t_[i][j][r / 4][r % 4], wgt[r], colsum[i][j]);
+                }
+            });
+        } else {
+            redo |= 1ull << (k - 1);
+        }
+        base += fminf(fmaxf(__log2f(first), -100.f), 100.f);
+        par ^= 1;
+    }
+    // Units whose rows no common reference fitted: the statistics of their rows with a maximum of their own, then the terms from them, in two
+    // more walks over the tiles.
+    for (; redo; redo &= redo - 1) {
+        const int k = __builtin_ctzll(redo);
+        __syncthreads();                                      // nobody reads the rows or sums of the unit before
+        begin(k * P + ((k & 1) ? P - 1 - p : p));
+        load_rows();
+        wait_vmcnt<0>();
+        __syncthreads();
+        read_rows();
+        float m[R], l[R];
+#pragma unroll
+        for (int r = 0; r < R; ++r) { m[r] = M_INIT; l[r] = 0.f; }
+        f32x4 s[SUB][RT];
+        auto scores_of = [&](int i) __attribute__((always_inline)) {
+            issue(i * W + wave);
+            wait_vmcnt<0>();
+            u32x4 kf[SUB][FR];
+            read_frags(kf);
+            wait_lds();
+            scores(kf, s);
+            if (i * W + wave == diag) mask(s);
+        };
+#pragma clang loop unroll(disable)
+        for (int i = 0; i < cnt; ++i) {
+            scores_of(i);
+#pragma unroll
+            for (int j = 0; j < SUB; ++j)
+#pragma unroll
+                for (int r = 0; r < R; ++r) join(m[r], l[r], s[j][r / 4][r % 4], 1.f, c);
+        }
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            join(m[r], l[r], dpp_f<0xB1>(m[r]), dpp_f<0xB1>(l[r]), c);
+            join(m[r], l[r], dpp_f<0x4E>(m[r]), dpp_f<0x4E>(l[r]), c);
+            join(m[r], l[r], dpp_f<0x141>(m[r]), dpp_f<0x141>(l[r]), c);
+            join(m[r], l[r], dpp_f<0x140>(m[r]), dpp_f<0x140>(l[r]), c);
+        }
+        if (col == 0) {
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                part[0][wave][16 * (r / 4) + 4 * group + r % 4] = m[r];
+                part[1][wave][16 * (r / 4) + 4 * group + r % 4] = l[r];
+            }
+        }
+        __syncthreads();
+        const int myrow = 16 * ((col >> 2) & (RT - 1)) + 4 * group + (col & 3);
+        float mm = part[0][0][myrow], ll = part[1][0][myrow];
+        for (int w = 1; w < W; ++w) join(mm, ll, part[0][w][myrow], part[1][w][myrow], c);
+        const float stat = q0 + myrow < n ? mm * c + __log2f(ll) : INFINITY;
+        float L[R];
+        static_for<0, R>([&](auto ic) __attribute__((always_inline)) { L[ic] = row16_lane<ic>(stat); });
+#pragma clang loop unroll(disable)
+        for (int i = 0; i < cnt; ++i) {
+            scores_of(i);
+#pragma unroll
+            for (int j = 0; j < SUB; ++j) {
+                float v = 0.f;
+#pragma unroll
+                for (int r = 0; r < R; ++r) v += __builtin_amdgcn_exp2f(fmaf(s[j][r / 4][r % 4], c, -L[r]));
+                static_for<0, NT>([&](auto ic) __attribute__((always_inline)) { colsum[ic][j] += ic == i ? v : 0.f; });
+            }
+        }
+    }
+    float *dst = out + ((size_t)slice * P + p) * n_pad;
+    static_for<0, NT>([&](auto ic) __attribute__((always_inline)) {
+        constexpr int i = ic;
+        if (i < covered) {
+#pragma unroll
+            for (int j = 0; j < SUB; ++j) {
+                const float v = rows4_sum(colsum[i][j]);
+                if (lane < 16) dst[(i * W + wave) * KEYS + 16 * j + lane] = v;
+            }
+        }
+    });
+}
+
+// mass[j] = sum over the workgroups p, in order, of their column sums; workgroup p holds the keys up to the last row of its first unit
+__global__ __launch_bounds__(256) void attn_single_sum_kernel(const float *__restrict__ part, float *__restrict__ mass, int G, int n, int n_pad,
+                                                               int P, int rows, int blocks_per_slice)
+{
+    __shared__ float sums[4][64];
+    const int slice = blockIdx.x / blocks_per_slice, j0 = (blockIdx.x % blocks_per_slice) * 64;
+    const int lane = threadIdx.x & 63, q = threadIdx.x >> 6, j = j0 + lane;
+    // key j is in the first unit of workgroup p, row group (n - 1) / rows - p / G, or above it
+    const int count = min(P, ((n - 1) / rows - j / rows + 1) * G);
+    const float *src = part + (size_t)slice * P * n_pad + j;
+    float s = 0.f;
+    if (j < n)
+        for (int p = q; p < count; p += 4) s += src[(size_t)p * n_pad];
+    sums[q][lane] = s;
+    __syncthreads();
+    if (q == 0 && j < n) mass[(size_t)slice * n + j] = (sums[0][lane] + sums[1][lane]) + (sums[2][lane] + sums[3][lane]);
+}
+
+// ------------------------------------------------------------------------------------------
+// host side
+// ------------------------------------------------------------------------------------------
+
+struct SinglePlan {
+    int waves = 0, tiles = 0, parts = 0;                     // waves of a workgroup, key tiles of a wave, workgroups of a slice
+};
+
+static int single_rows(const kvm_shape &sh) { return sh.dtype == KVM_F32 ? 16 : 32; }
+static int single_stride(int N) { return (N + 31) / 32 * 32; }
+
+// parts == 0: the two passes are the better choice.
+//   waves, tiles  the fewest registers that hold the terms of the longest row; fewer waves a workgroup are more workgroups a compute unit
+//          that cover each other's exchanges (1024 slices of 250 fp16 tokens, us, two waves of four tiles / four of four 37 / 47; of 128, one wave / two 21 / 23)
+//   parts  two rounds of the workgroups that the chip holds, at least four a slice, or the slices that run at a time on an XCD outgrow its
+//          L2 (1024 slices of 1000, us, 2 / 4 / 6 / 16 / 32 parts 417 / 380 / 387 / 425 / 481; 32 of them 32 parts 16, 8 parts 18.8 without the sum),
+//          and no more than 64 units each (see redo)
+// Longer rows.  16-bit types from 1025 tokens on: eight waves fill a compute unit alone, which a full launch of the other kernels beats (1024
+// slices of 1100 489 / 597, of 2000 1262 / 1271; 256 of 2000 329 / 320), and a small one does not (128 of 2048 170 / 156, 96 of 1500 104 / 98, 8
+// of 2000 33 / 22): up to 2^18 query rows.  fp32: 256 of 4096 8110 / 6140.
+// Batches of differing lengths would gain as well (512 slices of 250 to 1000 tokens 142 / 94) and keep the two passes: there the column-sum
+// kernels also write the similarities of kvm_attn_mass_sim, whose scores are bit for bit those of kvm_attn_mass.
+constexpr long long SINGLE_LONG_ROWS = 1ll << 18;
+
+static SinglePlan single_plan(const kvm_shape &sh)
+{
+    SinglePlan pl;
+    const bool f32 = sh.dtype == KVM_F32;
+    const long long slices = (long long)sh.B * sh.H_kv;
+    if (sh.seq_lens || sh.N > (f32 ? 4096 : 2048) || sh.G > 1024) return pl;   // (inv_G is exact for up to 2^32 / G units)
+    if (!f32 && sh.N > 1024 && slices * sh.G * sh.N > SINGLE_LONG_ROWS) return pl;
+    int resident;                                            // workgroups a compute unit holds
+    if (f32) {
+        pl.waves = sh.N <= 1024 ? 4 : 8;
+        pl.tiles = sh.N <= 256 ? 4 : sh.N <= 512 ? 8 : sh.N <= 2048 ? 16 : 32;
+        resident = sh.N <= 512 ? 3 : sh.N <= 1024 ? 2 : 1;
+    } else {
+        pl.waves = sh.N <= 128 ? 1 : sh.N <= 256 ? 2 : sh.N <= 1024 ? 4 : 8;
+        pl.tiles = sh.N <= 512 ? 4 : 8;
+        resident = sh.N <= 128 ? 9 : sh.N <= 256 ? 6 : sh.N <= 512 ? 3 : sh.N <= 1024 ? 2 : 1;
+    }
+    const long long units = (long long)((sh.N + single_rows(sh) - 1) / single_rows(sh)) * sh.G;
+    const long long parts = std::min(units, std::max({4ll, (2 * 256 * resident + slices - 1) / slices, (units + 63) / 64}));
+    const long long limit = 1ll << 32;                       // threads of a launch
+    if ((slices + 7) * parts * pl.waves * WAVE >= limit || slices * ((sh.N + 63) / 64) * 256 >= limit) return SinglePlan();
+    pl.parts = (int)parts;
+    return pl;
+}
+
+// Workspace of the single pass (0: not taken): the workgroups' column sums.
+size_t attn_single_bytes(const kvm_shape &sh)
+{
+    return (size_t)sh.B * sh.H_kv * single_plan(sh).parts * single_stride(sh.N) * sizeof(float);
+}
+
+template <typename T, int W, int NT, int OCC>
+static void single_t(const kvm_shape &sh, const void *Q, const void *K, float *part, int P, float c, hipStream_t st)
+{
+    const int n_kv = sh.B * sh.H_kv;
+    const long long blocks = (n_kv >= 64 ? (n_kv + 7ll) / 8 * 8 : n_kv) * P;
+    hipLaunchKernelGGL((attn_single_kernel<T, sizeof(T) == 2 ? 2 : 1, W, NT, OCC>), dim3((unsigned)blocks), dim3(W * WAVE), 0, st, (const T *)Q,
+                       (const T *)K, part, n_kv, sh.G, (uint32_t)((0x100000000ull + sh.G - 1) / sh.G), sh.N,
+                       single_stride(sh.N), P, c);
+}
+
+template <typename T>
+static void single_dispatch(const SinglePlan &pl, const kvm_shape &sh, const void *Q, const void *K, float *part, float c, hipStream_t st)
+{
+    if constexpr (sizeof(T) == 2) {
+        if (pl.waves == 1) single_t<T, 1, 4, 3>(sh, Q, K, part, pl.parts, c, st);
+        else if (pl.waves == 2) single_t<T, 2, 4, 3>(sh, Q, K, part, pl.parts, c, st);
+        else if (pl.waves == 4 && pl.tiles == 4) single_t<T, 4, 4, 3>(sh, Q, K, part, pl.parts, c, st);
+        else if (pl.waves == 4) single_t<T, 4, 8, 2>(sh, Q, K, part, pl.parts, c, st);
+        else single_t<T, 8, 8, 2>(sh, Q, K, part, pl.parts, c, st);
+    } else {
+        if (pl.tiles == 4) single_t<T, 4, 4, 3>(sh, Q, K, part, pl.parts, c, st);
+        else if (pl.tiles == 8) single_t<T, 4, 8, 3>(sh, Q, K, part, pl.parts, c, st);
+        else if (pl.waves == 4) single_t<T, 4, 16, 2>(sh, Q, K, part, pl.parts, c, st);
+        else if (pl.tiles == 16) single_t<T, 8, 16, 2>(sh, Q, K, part, pl.parts, c, st);
+        else single_t<T, 8, 32, 2>(sh, Q, K, part, pl.parts, c, st);
+    }
+}
+
+kvm_status launch_attn_single(const kvm_shape &sh, const void *Q, const void *K, float *mass, float *part, hipStream_t st)
+{
+    const float c = (float)(1.4426950408889634 / sqrt((double)sh.d));
+    const SinglePlan pl = single_plan(sh);
+    {
+        ProfScope prof("attn_single_kernel", st);
+        if (sh.dtype == KVM_F32) single_dispatch<float>(pl, sh, Q, K, part, c, st);
+        else if (sh.dtype == KVM_F16) single_dispatch<half_t>(pl, sh, Q, K, part, c, st);
+        else single_dispatch<bf16_t>(pl, sh, Q, K, part, c, st);
+        kvm_status rc = check_launch("attn_single_kernel");
+        if (rc != KVM_OK) return rc;
+    }
+    ProfScope prof("attn_single_sum_kernel", st);
+    const int n_kv = sh.B * sh.H_kv, per = (sh.N + 63) / 64;
+    hipLaunchKernelGGL(attn_single_sum_kernel, dim3((unsigned)((long long)per * n_kv)), dim3(256), 0, st, (const float *)part, mass, sh.G, sh.N,
+                       single_stride(sh.N), pl.parts, single_rows(sh), per);
+    return check_launch("attn_single_sum_kernel");
+}
+
+}  // namespace kvm

@@ -139,6 +139,12 @@ static size_t ws_identify(const kvm_shape *sh)
     return 3 * align_up(tok * sizeof(float), 256) + align_up(tok, 256);
 }
 
+// what every call accepts; the single score pass asks for room beyond it
+static size_t ws_plain(const kvm_shape *sh, int cap)
+{
+    return std::max(std::max(ws_attn(sh), ws_identify(sh)), merge_refresh_workspace_bytes(*sh, cap)) + 256;
+}
+
 }  // namespace kvm
 
 using namespace kvm;
@@ -180,9 +186,9 @@ size_t kvm_workspace_bytes(const kvm_shape *shape, const kvm_params *params)
     if (check_shape(shape, "kvm_workspace_bytes") != KVM_OK) return 0;
     // (the refresh of a compacted cache needs two ints per output row on top of what kvm_merge asks for; without
     // params the capacity is taken as N)
-    const int cap = params && check_params(params, "kvm_workspace_bytes") == KVM_OK ? capacity(shape, params) : shape->N;
-    const size_t a = ws_attn(shape), b = ws_identify(shape), c = merge_refresh_workspace_bytes(*shape, cap);
-    return (a > b ? (a > c ? a : c) : (b > c ? b : c)) + 256;
+    if (!params || check_params(params, "kvm_workspace_bytes") != KVM_OK) return ws_plain(shape, shape->N);
+    const size_t single = attn_single_bytes(*shape);
+    return single ? ws_plain(shape, shape->N) + single : ws_plain(shape, capacity(shape, params));
 }
 
 static kvm_status attn_mass_entry(const char *who, const kvm_shape *shape, const void *Q, const void *K, const float *row_lse,
@@ -204,6 +210,13 @@ static kvm_status attn_mass_entry(const char *who, const kvm_shape *shape, const
     if (!ws || ws_bytes < ws_attn(shape)) {
         set_error("%s: workspace of %zu bytes needed, %zu given", who, ws_attn(shape), ws ? ws_bytes : (size_t)0);
         return KVM_ERR_WORKSPACE;
+    }
+    if (!with_lse) {
+        const size_t single = attn_single_bytes(*shape);
+        if (single && ws_bytes >= ws_plain(shape, shape->N) + single) {
+            rc = launch_attn_single(*shape, Q, K, mass, (float *)ws, (hipStream_t)stream);
+            return rc == KVM_OK && with_sim ? launch_cosine_scan(*shape, K, sim, (hipStream_t)stream) : rc;
+        }
     }
     return launch_attn_mass(*shape, Q, K, with_lse ? row_lse : nullptr, mass, (float *)ws, with_sim ? sim : nullptr,
                             (hipStream_t)stream);

@@ -408,6 +408,114 @@ def test_mass_split_launch_of_every_slice_count(dtype, N, G, lengths):
     gu.assert_mass_close(alone[0].view(torch.float32).cpu().numpy()[:, None], ref.attn_mass(Q, K, dtype, G=G, seq_lens=lens), lens, N)
 
 
+def _single_pass(Q, K, dtype, G=1, copies=1, sim=False):
+    """Scores of `copies` copies of the slices with the workspace of a program that runs the whole pass (all of the same
+    length: short sequences then take the single score pass), which come out with the same bits; the kernels' names."""
+    Qd, Kd = gu.to_dev(Q, dtype).repeat(copies, 1, 1, 1), gu.to_dev(K, dtype).repeat(copies, 1, 1, 1)
+    sh = kb.make_shape(Kd, G)
+    ws = torch.full((kb.kvm_workspace_bytes(sh, kb.kvm_params_for_budget(0.5)),), 255, dtype=torch.uint8, device="cuda")
+    mass = torch.full((2,) + Kd.shape[:3], float("nan"), dtype=torch.float32, device="cuda")
+    if sim:
+        names = gu.kernels_of(lambda: kb.kvm_attn_mass_sim(sh, Qd, Kd, mass[0], mass[1], ws))
+    else:
+        names = gu.kernels_of(lambda: kb.kvm_attn_mass(sh, Qd, Kd, mass[0], ws))
+    torch.cuda.synchronize()
+    bits = mass[0].view(torch.int32).view(copies, -1)
+    assert torch.equal(bits, bits[:1].expand_as(bits))
+    return mass[:, :Q.shape[0]].cpu().numpy(), names
+
+
+# the tiles of 16 and 32 rows and keys, the numbers of waves and of tiles a wave (128, 256, 512, 1024 tokens), the longest rows
+@pytest.mark.parametrize("dtype,N,G,copies", [
+    ("f16", 1, 1, 1), ("bf16", 31, 3, 1), ("f16", 32, 1, 70), ("f32", 15, 2, 1), ("f32", 17, 1, 66), ("f16", 33, 4, 3), ("bf16", 128, 1, 9),
+    ("f16", 129, 2, 1), ("f32", 256, 1, 65), ("f32", 257, 3, 1), ("f16", 256, 1, 64), ("bf16", 257, 1, 2), ("f16", 511, 8, 1), ("f16", 513, 1, 33),
+    ("f32", 513, 1, 2), ("bf16", 1000, 4, 1), ("f16", 1024, 1, 65), ("f32", 1025, 1, 2), ("bf16", 1025, 1, 1), ("f16", 2048, 2, 1),
+    ("f32", 2049, 1, 1), ("f32", 4096, 1, 1)])
+def test_mass_single_pass(dtype, N, G, copies):
+    """The scores of short sequences from one score pass, against the oracle (fp32 sums of N terms: 8 * 2^-24 sqrt(N) of a column's
+    sum, and the exponent's own 1e-5), against the two passes that the smallest workspace leaves, and the same bits with
+    the similarities asked for."""
+    _say(f"mass, single pass: {dtype} N={N} G={G} x{copies}")
+    Q, K, _ = _slices(41, 2, 1, [N, N], N, 128, G, dtype)
+    want = ref.attn_mass(Q, K, dtype, G=G)
+    (got, _), names = _single_pass(Q, K, dtype, G, copies)
+    assert names == {"attn_single_kernel", "attn_single_sum_kernel"}
+    tol = 1e-5 + 8 * 2.0 ** -24 * math.sqrt(N)
+    assert (np.abs(got - want) <= tol * want).all()
+    two = gu.gpu_mass(Q, K, dtype, G=G, copies=copies)        # (a workspace without the room)
+    assert (np.abs(got - two) <= tol * want).all()
+    (again, sim), names = _single_pass(Q, K, dtype, G, copies, sim=True)
+    assert "attn_single_kernel" in names and "cosine_scan_kernel" in names
+    assert np.array_equal(again.view(np.int32), got.view(np.int32))
+    cap = kb.kvm_out_capacity(kb.make_shape(gu.to_dev(K, dtype), G), kb.kvm_params_for_budget(0.5))
+    np.testing.assert_allclose(sim, ref.identify_sets(K, want, dtype, 0.5, 0.17, 0.12, 0.75, True, cap)["sim"], atol=2e-6)
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16", "f32"])
+@pytest.mark.parametrize("orders", HELD_ORDERS + [-40.0, -300.0, 1000.0])
+def test_mass_single_pass_reference(dtype, orders):
+    """Rows whose scores lie far from the reference that the rows before left: the sums that leave 2^-32 .. 2^96 are worked
+    out again with a maximum of their own (one slice, one unit of rows a workgroup, and 45, several).  An fp32 rounding
+    of a score of `orders` binary orders is 2^-24 of it: the rows' statistics and terms within 4 of those."""
+    _say(f"mass, single pass, scores {orders} binary orders off, {dtype}")
+    Q, K, want = _held_reference_case(dtype, orders, 600)
+    tol = 1e-5 + 4 * abs(orders) * 2.0 ** -24 * math.log(2.0)
+    for copies in (1, 45):
+        (got, _), names = _single_pass(Q, K, dtype, copies=copies)
+        assert "attn_single_kernel" in names and np.isfinite(got).all()
+        big = want > 1e-6
+        assert (np.abs(got[big] - want[big]) / want[big]).max() <= tol
+        assert np.abs(got[~big]).max(initial=0.0) <= 2e-6
+
+
+@pytest.mark.parametrize("dtype", ["f16", "f32"])
+@pytest.mark.parametrize("offset", [-3000.0, -60.0, 60.0, 3000.0])
+def test_mass_single_pass_common_offset(dtype, offset):
+    """All scores of a row moved by the same amount, and rising scores: the reference moves along.  (Tolerance: the scores'
+    own rounding, a few 2^-24 of their size each, sums of 128 products in fp32.)"""
+    n = 700
+    _say(f"mass, single pass, common offset {offset}, {dtype}")
+    rng = np.random.default_rng(3)
+    q, k = (rng.standard_normal((1, 2, n, 128)).astype(np.float32) for _ in range(2))
+    q[..., 0] = 20.0
+    k[:, 0, :, 0] = offset * math.sqrt(128.0) / 20.0
+    k[:, 1, :, 0] = np.linspace(0.0, 60.0, n, dtype=np.float32)
+    Q, K = synth.to_storage(q, dtype), synth.to_storage(k, dtype)
+    want = ref.attn_mass(Q, K, dtype)
+    (got, _), names = _single_pass(Q, K, dtype)
+    assert "attn_single_kernel" in names and np.isfinite(got).all()
+    big = want > 1e-6
+    assert (np.abs(got[big] - want[big]) / want[big]).max() <= 1e-5 + 16 * max(abs(offset), 110.0) * 2.0 ** -24
+    assert np.abs(got[~big]).max(initial=0.0) <= 2e-6
+
+
+def test_mass_single_pass_rule():
+    """Which calls take the single pass: enough workspace, no lengths, short rows; 16-bit rows beyond 1024 tokens up to 2^18
+    query rows.  (Sizes and names only: the launches of the rule's far sides are small.)"""
+    _say("mass, single pass rule")
+    params = kb.kvm_params_for_budget(0.5)
+
+    def takes(dtype, N, copies=1, G=1, lens=None, room=True):
+        K = torch.zeros((copies, 1, N, 128), dtype=gu.TORCH_DT[dtype], device="cuda")
+        Q = torch.zeros((copies, G, N, 128), dtype=gu.TORCH_DT[dtype], device="cuda")
+        sh = kb.make_shape(K, G, gu.lens_dev(lens))
+        least, most = kb.kvm_workspace_bytes(sh), kb.kvm_workspace_bytes(sh, params)
+        ws = torch.empty(most if room else most - 1, dtype=torch.uint8, device="cuda")
+        mass = torch.empty((copies, 1, N), dtype=torch.float32, device="cuda")
+        names = gu.kernels_of(lambda: kb.kvm_attn_mass(sh, Q, K, mass, ws))
+        single = "attn_single_kernel" in names
+        assert not single or most > least
+        n = N if lens is None else lens[0]
+        harmonic = G * np.cumsum((1.0 / np.arange(1, n + 1))[::-1])[::-1]
+        np.testing.assert_allclose(mass[0, 0, :n].cpu().numpy(), harmonic, rtol=1e-5)   # zero scores: sums of 1 / t
+        return single
+
+    assert takes("f16", 1024, 300) and takes("bf16", 2048) and takes("f32", 4096) and takes("f16", 40, G=1024)
+    assert not takes("f16", 2049) and not takes("f32", 4097) and not takes("f16", 8, G=1025)
+    assert not takes("f16", 700, lens=[700]) and not takes("f16", 700, room=False)
+    assert takes("f16", 1025, 255) and not takes("f16", 1025, 256) and not takes("bf16", 2048, 33, G=4)
+
+
 @pytest.mark.parametrize("dtype,n", [("f16", 100000), ("bf16", 70001), ("f32", 20000), ("f16", 131071), ("f16", 2 ** 22)])
 def test_mass_long_sequence_against_a_closed_form(dtype, n):
     """Too long for the oracle's n^2 loop, so the scores are given a shape whose column sums have
