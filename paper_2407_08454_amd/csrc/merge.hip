@@ -117,12 +117,20 @@ __device__ __forceinline__ void wave_lds_fence() {
     __builtin_amdgcn_wave_barrier();
 }
 
+// In the launches that stream their merged rows, 16-bit rows that are read once carry the hint too: values, and keys of single tokens and of
+// sets of up to 16.  It leaves the caches to the keys of the longer sets' second sweep.  us, without / with: sets and merge of 1600 slices of 500 bf16
+// tokens 148 / 140, 1024 of 2000 fp16 375 / 365, 1024 of 4096 747 / 736, 1600 of 4096 in bf16 1062 / 1050, 1024 of up to 16384 1823 / 1799.  Not
+// in fp32, where it costs time: 1024 of 4096 1474 / 1540.
+template <typename T, bool STREAM> constexpr bool reads_once() { return STREAM && sizeof(T) == 2; }
+
 // Chunk c of a row of a slice.  A slice has less than 2^32 bytes, so scalar base and 32-bit offset: half the address arithmetic and a
 // register instead of two.
-template <typename T>
+template <typename T, bool ONCE = false>
 __device__ __forceinline__ typename Elem<T>::Raw row_chunk(const T *slice, int row, int c) {
     const uint32_t at = (uint32_t)row * (uint32_t)(HEAD_DIM * sizeof(T)) + (uint32_t)c * (uint32_t)(8 * sizeof(T));
-    return Elem<T>::load(reinterpret_cast<const T *>(reinterpret_cast<const char *>(slice) + at), 0);
+    const T *row_at = reinterpret_cast<const T *>(reinterpret_cast<const char *>(slice) + at);
+    if constexpr (ONCE) return Elem<T>::load_stream(row_at, 0);
+    else return Elem<T>::load(row_at, 0);
 }
 
 // A row that is copied: lane c of 16 moves the pieces c, c + 16 of 16 bytes, so that every store of a wave writes whole rows or half rows
@@ -131,11 +139,12 @@ __device__ __forceinline__ typename Elem<T>::Raw row_chunk(const T *slice, int r
 // 1148 / 1110 / 1068).
 template <typename T> struct CopiedRow {
     u32x4 piece[sizeof(T) / 2];
-    __device__ __forceinline__ void load(const T *slice, int row, int c) {
+    template <bool ONCE> __device__ __forceinline__ void load(const T *slice, int row, int c) {
         const uint32_t at = (uint32_t)row * (uint32_t)(HEAD_DIM * sizeof(T)) + (uint32_t)c * 16u;
 #pragma unroll
         for (int h = 0; h < (int)sizeof(T) / 2; ++h)
-            piece[h] = *reinterpret_cast<const u32x4 *>(reinterpret_cast<const char *>(slice) + at + 256 * h);
+            if constexpr (ONCE) piece[h] = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(reinterpret_cast<const char *>(slice) + at + 256 * h));
+            else piece[h] = *reinterpret_cast<const u32x4 *>(reinterpret_cast<const char *>(slice) + at + 256 * h);
     }
     template <bool STREAM> __device__ __forceinline__ void store(T *row, int c) const {
         u32x4 *p = reinterpret_cast<u32x4 *>(row) + c;
@@ -191,10 +200,11 @@ __device__ __forceinline__ int part_rows(int m) { return ((m + 15) / 16 + SPLIT_
 
 // The steps of merging one set [lo, hi) with pivot p, 16 rows at a time, each for its rows [from, to) (counted from lo, from a
 // multiple of 16).
-template <typename T, bool WITH_W, int MODE> struct SetMerge {
+template <typename T, bool WITH_W, int MODE, bool STREAM> struct SetMerge {
     using E = Elem<T>;
     using Raw = typename E::Raw;
     static constexpr int U = MergeUnroll<T>::value;            // row groups (of 4 rows) in flight
+    static constexpr bool READ_ONCE = reads_once<T, STREAM>();
     const T *Ks, *Vs;
     float *wo;
     const MergeArgs &a;
@@ -205,9 +215,9 @@ template <typename T, bool WITH_W, int MODE> struct SetMerge {
         : Ks(Ks), Vs(Vs), wo(wo), a(a), lo(lo), hi(hi), lane(lane), slot(lane >> 4), c(lane & 15) {}
     // Rows past the end of the set are clamped to its last row and given weight zero, so
     // that every lane runs the same straight-line code.
-    __device__ __forceinline__ void load_rows(const T *base, int j0, Raw *r) const {
+    template <bool ONCE = false> __device__ __forceinline__ void load_rows(const T *base, int j0, Raw *r) const {
 #pragma unroll
-        for (int u = 0; u < U; ++u) r[u] = row_chunk<T>(base, min(j0 + 4 * u + slot, hi - 1), c);
+        for (int u = 0; u < U; ++u) r[u] = row_chunk<T, ONCE>(base, min(j0 + 4 * u + slot, hi - 1), c);
     }
     // distances to the pivot -> dist (LDS, one per row)
     __device__ __forceinline__ void batch_distances(int j0, const Raw *kr, float *dist) const {
@@ -277,7 +287,7 @@ template <typename T, bool WITH_W, int MODE> struct SetMerge {
         for (int j0 = lo + from; j0 < lo + to; j0 += 4 * U) {
             Raw kr[U], vr[U];
             load_rows(Ks, j0, kr);
-            load_rows(Vs, j0, vr);
+            load_rows<READ_ONCE>(Vs, j0, vr);
             __builtin_amdgcn_sched_barrier(0);                // (left alone, the compiler saves registers by taking the groups one by one)
             batch_sums(j0, kr, vr, w, s);
         }
@@ -295,7 +305,7 @@ template <typename T, bool WITH_W, int MODE> struct SetMerge {
     __device__ __forceinline__ void sums_pair(int p, float *set_w, SetSums &s) {
         Raw k1[U], v1[U];
         load_rows(Ks, lo + 4 * U, k1);
-        load_rows(Vs, lo + 4 * U, v1);
+        load_rows<READ_ONCE>(Vs, lo + 4 * U, v1);
         load_pivot(p);
         distances(0, 4 * U, set_w);
         batch_distances(lo + 4 * U, k1, set_w);
@@ -315,8 +325,8 @@ template <typename T, bool WITH_W, int MODE> struct SetMerge {
         clear(s);
         const Raw kp_raw = row_chunk<T>(Ks, p, c);
         Raw kr[U], vr[U];
-        load_rows(Ks, lo, kr);
-        load_rows(Vs, lo, vr);
+        load_rows<READ_ONCE>(Ks, lo, kr);
+        load_rows<READ_ONCE>(Vs, lo, vr);
         if (MODE == MERGE_FIXED) __builtin_amdgcn_sched_barrier(0);
         E::to_float(kp_raw, kp);
         if (MODE != MERGE_ADAPTIVE) {
@@ -355,7 +365,7 @@ template <typename T, bool WITH_W, int MODE> struct SetMerge {
     __device__ __forceinline__ void load_pivot(int p) { E::to_float(row_chunk<T>(Ks, p, c), kp); }
     // the merged rows.  The weights that are normalised here were written by other lanes, in a team by other waves: the caller puts a fence
     // (a barrier in a team) between those stores and this.
-    template <bool STREAM> __device__ __forceinline__ void finish(SetSums &s, T *k_row, T *v_row) const {
+    __device__ __forceinline__ void finish(SetSums &s, T *k_row, T *v_row) const {
         const int m = hi - lo;
         const float inv_g = 1.f / rows4_sum(s.g);
         // Keys come out in the even rows of the wave, values in the odd ones.  us, two sums for every column / one: 512 slices of 4096 tokens in sets
@@ -389,8 +399,8 @@ template <typename T, bool WITH_W, int MODE, bool ANY_LENGTH, bool STREAM>
 __device__ __forceinline__ void merge_one_set(const T *Ks, const T *Vs, T *k_row, T *v_row, float *wo, int lo, int hi, int p,
                                               const MergeArgs &a, int lane, float *set_w)
 {
-    SetMerge<T, WITH_W, MODE> set(Ks, Vs, wo, a, lo, hi, lane);
-    constexpr int BATCH = 4 * SetMerge<T, WITH_W, MODE>::U;
+    SetMerge<T, WITH_W, MODE, STREAM> set(Ks, Vs, wo, a, lo, hi, lane);
+    constexpr int BATCH = 4 * SetMerge<T, WITH_W, MODE, STREAM>::U;
     const int m = hi - lo;
     SetSums s;
     if (m <= BATCH) {
@@ -423,7 +433,7 @@ __device__ __forceinline__ void merge_one_set(const T *Ks, const T *Vs, T *k_row
         wave_lds_fence();                                     // the next set's distances come to the same place
     }
     if (WITH_W) wave_lds_fence();
-    set.template finish<STREAM>(s, k_row, v_row);
+    set.finish(s, k_row, v_row);
 }
 
 // The same for a set of more than SPLIT_SET_MIN tokens by four waves of a workgroup, one part each.  All threads of the workgroup call
@@ -436,7 +446,7 @@ template <typename T, bool WITH_W, int MODE>
 __device__ __forceinline__ void merge_set_team(const T *Ks, const T *Vs, T *k_row, T *v_row, float *wo, int lo, int hi, int p,
                                                const MergeArgs &a, int lane, int part_id, TeamShared &sh)
 {
-    SetMerge<T, WITH_W, MODE> set(Ks, Vs, wo, a, lo, hi, lane);
+    SetMerge<T, WITH_W, MODE, false> set(Ks, Vs, wo, a, lo, hi, lane);
     SetSums s;
     const int from = part_id * part_rows(hi - lo), to = min(from + part_rows(hi - lo), hi - lo);   // (may be empty)
     if (hi > lo) set.load_pivot(p);
@@ -452,7 +462,7 @@ __device__ __forceinline__ void merge_set_team(const T *Ks, const T *Vs, T *k_ro
     __syncthreads();
     if (part_id == 0 && hi > lo) {
         for (int q = 0; q < SPLIT_PARTS - 1; ++q) add_parked(s, sh.part[q] + lane);
-        set.template finish<false>(s, k_row, v_row);
+        set.finish(s, k_row, v_row);
     }
 }
 
@@ -529,8 +539,8 @@ __global__ __launch_bounds__(WAVES * WAVE, (merge_waves_per_simd<T, WITH_W, MODE
                 const int r = 4 * u + slot;
                 src[u] = __shfl(my_start, i + min(r, run - 1), WAVE);
                 if (r < run) {
-                    rk[u].load(Ks, src[u], c);
-                    rv[u].load(Vs, src[u], c);
+                    rk[u].template load<reads_once<T, STREAM>()>(Ks, src[u], c);
+                    rv[u].template load<reads_once<T, STREAM>()>(Vs, src[u], c);
                 }
             }
 #pragma unroll
