@@ -583,11 +583,115 @@ __global__ __launch_bounds__(WAVES * WAVE, (merge_waves_per_simd<T, WITH_W, MODE
     }
 }
 
-// Sets of more than LONG_SET_MIN tokens, one after the other, by all 64 sixteen-lane groups of a
-// 1024-thread workgroup per slice: group g takes the set's rows g, g + 64, ... (four of them in
-// flight), the distance sum and then the weighted sums are added up across the groups through
-// LDS.  Same arithmetic per row as merge_kernel; only the order of the fp32 additions differs.
-// The workgroup looks the long sets up in the maps itself (or takes the refresh's list), 4096 sets
+// One set of more than LONG_SET_MIN tokens by the 64 sixteen-lane groups of a 1024-thread workgroup: group g takes the set's rows
+// g, g + 64, ... (four of them in flight), the distance sum and then the weighted sums are added up across the groups through
+// LDS.  Same arithmetic per row as merge_one_set; only the order of the fp32 additions differs.  All threads call it together.
+struct LongShared {
+    float red[LONG_SET_BLOCK / WAVE][16][17];                 // per wave and chunk lane: 8 key sums, 8 value sums, weight sum
+    float red1[LONG_SET_BLOCK / WAVE];
+};
+template <typename T, bool WITH_W, int MODE>
+__device__ __forceinline__ void merge_long_set(const T *Ks, const T *Vs, T *k_row, T *v_row, float *wo, int lo, int hi, int p, const MergeArgs &a,
+                                               int tid, LongShared &sh)
+{
+    using E = Elem<T>;
+    using Raw = typename E::Raw;
+    constexpr int U = 4;                                     // rows of a group in flight
+    constexpr int GROUPS = LONG_SET_BLOCK / 16, WAVES = LONG_SET_BLOCK / WAVE;
+    const int lane = tid & 63, wave = tid >> 6, c = tid & 15, group = tid >> 4;
+    const int m = hi - lo;
+    float kp[8];
+    E::to_float(E::load(Ks + (size_t)p * HEAD_DIM, c), kp);
+    float inv_mean = 0.f;
+    if (MODE == MERGE_ADAPTIVE) {
+        float dsum = 0.f;
+        for (int j0 = lo + group; j0 < hi; j0 += GROUPS * U) {
+            Raw kr[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) kr[u] = E::load(Ks + (size_t)min(j0 + GROUPS * u, hi - 1) * HEAD_DIM, c);
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                float x[8];
+                E::to_float(kr[u], x);
+                const float dist = __builtin_amdgcn_sqrtf(sq_dist16(kp, x));
+                dsum += (j0 + GROUPS * u < hi) ? dist : 0.f;
+            }
+        }
+        dsum = rows4_sum(dsum);                           // the wave's four groups
+        __syncthreads();                                  // sh.red1 may still be read from the set before
+        if (lane == 0) sh.red1[wave] = dsum;
+        __syncthreads();
+        float total = 0.f;
+#pragma unroll
+        for (int w2 = 0; w2 < WAVES; ++w2) total += sh.red1[w2];
+        inv_mean = total > 0.f ? (float)m / total : 0.f;
+    }
+    float ak[8], av[8], gsum = 0.f;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) { ak[e] = 0.f; av[e] = 0.f; }
+    for (int j0 = lo + group; j0 < hi; j0 += GROUPS * U) {
+        Raw kr[U], vr[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const size_t row = (size_t)min(j0 + GROUPS * u, hi - 1) * HEAD_DIM;
+            kr[u] = E::load(Ks + row, c);
+            vr[u] = E::load(Vs + row, c);
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int row = j0 + GROUPS * u;
+            float x[8], v[8];
+            E::to_float(kr[u], x);
+            float g;
+            if (MODE == MERGE_AVERAGE) {
+                g = 1.f;
+            } else if (MODE == MERGE_FIXED) {
+                g = __expf(-sq_dist16(kp, x) * a.inv_two_sigma_sq);
+            } else {
+                const float r = __builtin_amdgcn_sqrtf(sq_dist16(kp, x)) * inv_mean;
+                g = __expf(-r * r);
+            }
+            g = row < hi ? g : 0.f;
+            gsum += g;
+            E::to_float(vr[u], v);
+#pragma unroll
+            for (int e = 0; e < 8; ++e) { ak[e] = fmaf(g, x[e], ak[e]); av[e] = fmaf(g, v[e], av[e]); }
+            if (WITH_W && c == 0 && row < hi) wo[row] = g;
+        }
+    }
+    gsum = rows4_sum(gsum);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) { ak[e] = rows4_sum(ak[e]); av[e] = rows4_sum(av[e]); }
+    __syncthreads();                                      // sh.red may still be read from the set before
+    if (lane < 16) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) { sh.red[wave][c][e] = ak[e]; sh.red[wave][c][8 + e] = av[e]; }
+        sh.red[wave][c][16] = gsum;
+    }
+    __syncthreads();
+    float gtot = 0.f;
+#pragma unroll
+    for (int w2 = 0; w2 < WAVES; ++w2) gtot += sh.red[w2][0][16];
+    const float inv_g = 1.f / gtot;
+    if (tid < 32) {                                       // lanes 0..15: the key row, 16..31: the value row
+        const bool is_v = tid >= 16;
+        const float scale = is_v && a.value_scale ? inv_g * (float)m : inv_g;
+        float out[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            float t = 0.f;
+#pragma unroll
+            for (int w2 = 0; w2 < WAVES; ++w2) t += sh.red[w2][c][(is_v ? 8 : 0) + e];
+            out[e] = t * scale;
+        }
+        E::store(is_v ? v_row : k_row, c, E::from_float(out));
+    }
+    if (WITH_W && c == 0) {                               // each writer normalises its own g_j
+        for (int row = lo + group; row < hi; row += GROUPS) wo[row] *= inv_g;
+    }
+}
+
+// Sets of more than LONG_SET_MIN tokens, one after the other, by a 1024-thread workgroup per slice.  The workgroup looks the long sets up in the maps itself (or takes the refresh's list), 4096 sets
 // at a time, in no particular order: each is merged on its own.  The registers of one workgroup per
 // compute unit are given to it outright (waves_per_eu), because the compiler otherwise saves them by
 // taking the four rows of a group one after the other; a set's number is moved to a scalar, because
@@ -598,16 +702,10 @@ template <typename T, bool WITH_W, int MODE>
 __global__ __launch_bounds__(LONG_SET_BLOCK) __attribute__((amdgpu_waves_per_eu(4, 4))) void merge_long_kernel(const T *__restrict__ K, const T *__restrict__ V,
                                                                 T *__restrict__ K_out, T *__restrict__ V_out, MergeArgs a)
 {
-    using E = Elem<T>;
-    using Raw = typename E::Raw;
-    constexpr int U = 4;                                     // rows of a group in flight
-    constexpr int GROUPS = LONG_SET_BLOCK / 16, WAVES = LONG_SET_BLOCK / WAVE;
-    __shared__ float red[WAVES][16][17];                     // per wave and chunk lane: 8 key sums, 8 value sums, weight sum
-    __shared__ float red1[WAVES];
+    __shared__ LongShared sums;
     __shared__ int found[LONG_SET_BLOCK * LONG_SET_LOOK], n_found[2];   // (two counters in turn: one is cleared while the other is read)
     const int slice = blockIdx.x;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int c = tid & 15, group = tid >> 4;
+    const int tid = threadIdx.x;
     const int n = clamp_len(a.seq_lens, slice / a.H, a.N);
     const int M = min(max(a.n_sets[slice], 0), a.cap_rows);
     const int32_t *sst = a.set_start + (size_t)slice * (a.cap_rows + 1);
@@ -646,97 +744,8 @@ __global__ __launch_bounds__(LONG_SET_BLOCK) __attribute__((amdgpu_waves_per_eu(
     for (int k = 0; k < n_long; ++k) {
         const int s = __builtin_amdgcn_readfirstlane(found[k]);   // scalar, and the loops below with it
         const int lo = min(max(sst[s], 0), n), hi = min(max(sst[s + 1], 0), n);
-        const int m = hi - lo;
         const int p = max(min(max(piv[s], lo), hi - 1), 0);   // (the bounds are read a second time: inside the slice whatever they are)
-        float kp[8];
-        E::to_float(E::load(Ks + (size_t)p * HEAD_DIM, c), kp);
-        float inv_mean = 0.f;
-        if (MODE == MERGE_ADAPTIVE) {
-            float dsum = 0.f;
-            for (int j0 = lo + group; j0 < hi; j0 += GROUPS * U) {
-                Raw kr[U];
-#pragma unroll
-                for (int u = 0; u < U; ++u) kr[u] = E::load(Ks + (size_t)min(j0 + GROUPS * u, hi - 1) * HEAD_DIM, c);
-#pragma unroll
-                for (int u = 0; u < U; ++u) {
-                    float x[8];
-                    E::to_float(kr[u], x);
-                    const float dist = __builtin_amdgcn_sqrtf(sq_dist16(kp, x));
-                    dsum += (j0 + GROUPS * u < hi) ? dist : 0.f;
-                }
-            }
-            dsum = rows4_sum(dsum);                           // the wave's four groups
-            __syncthreads();                                  // red1 may still be read from the set before
-            if (lane == 0) red1[wave] = dsum;
-            __syncthreads();
-            float total = 0.f;
-#pragma unroll
-            for (int w2 = 0; w2 < WAVES; ++w2) total += red1[w2];
-            inv_mean = total > 0.f ? (float)m / total : 0.f;
-        }
-        float ak[8], av[8], gsum = 0.f;
-#pragma unroll
-        for (int e = 0; e < 8; ++e) { ak[e] = 0.f; av[e] = 0.f; }
-        for (int j0 = lo + group; j0 < hi; j0 += GROUPS * U) {
-            Raw kr[U], vr[U];
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const size_t row = (size_t)min(j0 + GROUPS * u, hi - 1) * HEAD_DIM;
-                kr[u] = E::load(Ks + row, c);
-                vr[u] = E::load(Vs + row, c);
-            }
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const int row = j0 + GROUPS * u;
-                float x[8], v[8];
-                E::to_float(kr[u], x);
-                float g;
-                if (MODE == MERGE_AVERAGE) {
-                    g = 1.f;
-                } else if (MODE == MERGE_FIXED) {
-                    g = __expf(-sq_dist16(kp, x) * a.inv_two_sigma_sq);
-                } else {
-                    const float r = __builtin_amdgcn_sqrtf(sq_dist16(kp, x)) * inv_mean;
-                    g = __expf(-r * r);
-                }
-                g = row < hi ? g : 0.f;
-                gsum += g;
-                E::to_float(vr[u], v);
-#pragma unroll
-                for (int e = 0; e < 8; ++e) { ak[e] = fmaf(g, x[e], ak[e]); av[e] = fmaf(g, v[e], av[e]); }
-                if (WITH_W && c == 0 && row < hi) wo[row] = g;
-            }
-        }
-        gsum = rows4_sum(gsum);
-#pragma unroll
-        for (int e = 0; e < 8; ++e) { ak[e] = rows4_sum(ak[e]); av[e] = rows4_sum(av[e]); }
-        __syncthreads();                                      // red may still be read from the set before
-        if (lane < 16) {
-#pragma unroll
-            for (int e = 0; e < 8; ++e) { red[wave][c][e] = ak[e]; red[wave][c][8 + e] = av[e]; }
-            red[wave][c][16] = gsum;
-        }
-        __syncthreads();
-        float gtot = 0.f;
-#pragma unroll
-        for (int w2 = 0; w2 < WAVES; ++w2) gtot += red[w2][0][16];
-        const float inv_g = 1.f / gtot;
-        if (tid < 32) {                                       // lanes 0..15: the key row, 16..31: the value row
-            const bool is_v = tid >= 16;
-            const float scale = is_v && a.value_scale ? inv_g * (float)m : inv_g;
-            float out[8];
-#pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                float t = 0.f;
-#pragma unroll
-                for (int w2 = 0; w2 < WAVES; ++w2) t += red[w2][c][(is_v ? 8 : 0) + e];
-                out[e] = t * scale;
-            }
-            E::store((is_v ? Vo : Ko) + (size_t)s * HEAD_DIM, c, E::from_float(out));
-        }
-        if (WITH_W && c == 0) {                               // each writer normalises its own g_j
-            for (int row = lo + group; row < hi; row += GROUPS) wo[row] *= inv_g;
-        }
+        merge_long_set<T, WITH_W, MODE>(Ks, Vs, Ko + (size_t)s * HEAD_DIM, Vo + (size_t)s * HEAD_DIM, wo, lo, hi, p, a, tid, sums);
     }
     if (first + LONG_SET_BLOCK * LONG_SET_LOOK < candidates) __syncthreads();  // found is filled again; the cleared counter is seen
     }
@@ -833,7 +842,7 @@ kvm_status launch_merge(const kvm_shape &sh, const kvm_params &pr, int cap_rows,
 // the row only moves to its new index; the others are merged again.  Result: bit for bit what
 // merge_kernel / merge_long_kernel give on the new maps.
 //
-// refresh_kernel, one 512-thread workgroup per slice, three phases with a barrier between them:
+// refresh_kernel, one workgroup per slice, three phases with a barrier between them:
 //   compare   src[s] = row of the previous cache that new row s is (-1: merge again), the list
 //             of short sets to merge again, and the long ones in the layout merge_long_kernel
 //             reads (that kernel follows)
@@ -855,21 +864,26 @@ struct RefreshArgs {
 };
 
 constexpr int REFRESH_POSTED = 256;                          // sets that are merged again in one turn
-constexpr int REFRESH_BLOCK = 512;                           // two workgroups per compute unit (128 registers each)
+// Threads per slice: 512, two workgroups per compute unit (128 registers each), or 1024 where every slice has a compute unit to itself:
+// half as many batches to move one after the other, and the long sets are merged by the same workgroup instead of by a launch of their own.
+// Whole decode step, us, 512 / 1024: 32 slices of 3000 bf16 tokens, G = 4, 54.3 / 48.4, of 1000 41.8 / 38.9, 8 of 9000 81.8 / 75.0, of 2000 in fp32
+// 43.0 / 40.2, 256 of 2000 68.6 / 65.2, of 300 39.0 / 38.3, 240 of 4096 110.8 / 106.6.
+constexpr int REFRESH_BLOCK = 512, REFRESH_BLOCK_FEW = LONG_SET_BLOCK;
+constexpr long long REFRESH_FEW_SLICES = 256;
 template <typename T> struct MovePerGroup { static constexpr int value = 16 / sizeof(T); };   // rows a 16-lane group moves per batch
 
-template <typename T, int MODE>
-__global__ __launch_bounds__(REFRESH_BLOCK, 4) void refresh_kernel(const T *__restrict__ K, const T *__restrict__ V,
+template <typename T, int MODE, int BLOCK>
+__global__ __launch_bounds__(BLOCK, 4) void refresh_kernel(const T *__restrict__ K, const T *__restrict__ V,
                                                                 T *__restrict__ K_out, T *__restrict__ V_out, MergeArgs a,
                                                                 RefreshArgs r)
 {
     using E = Elem<T>;
     using Raw = typename E::Raw;
     constexpr int MOVE_PER_GROUP = MovePerGroup<T>::value;
-    constexpr int MOVE_BATCH = (REFRESH_BLOCK / 16) * MOVE_PER_GROUP;   // rows the workgroup moves per batch
+    constexpr int MOVE_BATCH = (BLOCK / 16) * MOVE_PER_GROUP;   // rows the workgroup moves per batch
     __shared__ int n_short, n_long, first_moved, any_up, any_down;
-    constexpr int TEAMS = REFRESH_BLOCK / WAVE / SPLIT_PARTS;
-    __shared__ float set_w[REFRESH_BLOCK / WAVE][SPLIT_SET_MIN];
+    constexpr int TEAMS = BLOCK / WAVE / SPLIT_PARTS;
+    __shared__ float set_w[BLOCK / WAVE][SPLIT_SET_MIN];
     __shared__ TeamShared team_mem[TEAMS];
     __shared__ int posted[REFRESH_POSTED], n_posted;
     const int slice = blockIdx.x;
@@ -894,7 +908,7 @@ __global__ __launch_bounds__(REFRESH_BLOCK, 4) void refresh_kernel(const T *__re
     __syncthreads();
     int my_first = M;
     bool my_up = false, my_down = false;
-    for (int s = tid; s < M; s += REFRESH_BLOCK) {
+    for (int s = tid; s < M; s += BLOCK) {
         const int lo = min(max(sst[s], 0), n), hi = min(max(sst[s + 1], 0), n);
         int from = -1;
         if (hi > lo) {
@@ -937,7 +951,7 @@ __global__ __launch_bounds__(REFRESH_BLOCK, 4) void refresh_kernel(const T *__re
     auto sources = [&](int bt, int *out) {                    // the batch's sources, before the direction filter
 #pragma unroll
         for (int u = 0; u < MOVE_PER_GROUP; ++u) {
-            const int row = bt * MOVE_BATCH + u * (REFRESH_BLOCK / 16) + group;
+            const int row = bt * MOVE_BATCH + u * (BLOCK / 16) + group;
             out[u] = row < M ? src[row] : -1;
         }
     };
@@ -945,7 +959,7 @@ __global__ __launch_bounds__(REFRESH_BLOCK, 4) void refresh_kernel(const T *__re
         bool any = false;
 #pragma unroll
         for (int u = 0; u < MOVE_PER_GROUP; ++u) {
-            s[u] = bt * MOVE_BATCH + u * (REFRESH_BLOCK / 16) + group;
+            s[u] = bt * MOVE_BATCH + u * (BLOCK / 16) + group;
             f[u] = f_next[u];
             if (!(up ? (f[u] >= 0 && f[u] < s[u]) : f[u] > s[u])) f[u] = -1;
             any |= f[u] >= 0;
@@ -980,7 +994,7 @@ __global__ __launch_bounds__(REFRESH_BLOCK, 4) void refresh_kernel(const T *__re
         __syncthreads();                                      // the list of the turn before has been read
         if (tid == 0) n_posted = 0;
         __syncthreads();
-        for (int k = base + wave; k < min(base + REFRESH_POSTED, cnt); k += REFRESH_BLOCK / WAVE) {
+        for (int k = base + wave; k < min(base + REFRESH_POSTED, cnt); k += BLOCK / WAVE) {
             const int s = __builtin_amdgcn_readfirstlane(list[1 + k]);
             if (s < 0 || s >= M) continue;                    // (the same for the whole wave)
             const int lo = min(max(sst[s], 0), n), hi = min(max(sst[s + 1], 0), n);
@@ -1003,23 +1017,37 @@ __global__ __launch_bounds__(REFRESH_BLOCK, 4) void refresh_kernel(const T *__re
                                            lane, wave % SPLIT_PARTS, team_mem[wave / SPLIT_PARTS]);
         }
     }
+    if constexpr (BLOCK == LONG_SET_BLOCK) {
+        __shared__ LongShared long_sums;
+        for (int k = 0; k < min(n_long, max_long); ++k) {     // (the same for the whole workgroup)
+            const int s = __builtin_amdgcn_readfirstlane(pl[1 + k]);
+            if (s < 0 || s >= M) continue;
+            const int lo = min(max(sst[s], 0), n), hi = min(max(sst[s + 1], 0), n);
+            if (hi <= lo) continue;
+            const int p = min(max(piv[s], lo), hi - 1);
+            merge_long_set<T, false, MODE>(Ks, Vs, Ko + (size_t)s * HEAD_DIM, Vo + (size_t)s * HEAD_DIM, nullptr, lo, hi, p, a, tid, long_sums);
+        }
+    }
 }
 
 template <typename T>
 static kvm_status launch_refresh_t(const kvm_shape &sh, const void *K, const void *V, void *K_out, void *V_out,
                                    const MergeArgs &ma, const RefreshArgs &ra, hipStream_t st)
 {
-    const dim3 grid((unsigned)((long long)sh.B * sh.H_kv)), block(REFRESH_BLOCK);
+    const long long slices = (long long)sh.B * sh.H_kv;
+    const bool few = slices <= REFRESH_FEW_SLICES;
     {
         ProfScope prof("refresh_kernel", st);
-        const T *k = (const T *)K, *v = (const T *)V;
-        T *ko = (T *)K_out, *vo = (T *)V_out;
-        if (ma.mode == MERGE_AVERAGE) hipLaunchKernelGGL((refresh_kernel<T, MERGE_AVERAGE>), grid, block, 0, st, k, v, ko, vo, ma, ra);
-        else if (ma.mode == MERGE_FIXED) hipLaunchKernelGGL((refresh_kernel<T, MERGE_FIXED>), grid, block, 0, st, k, v, ko, vo, ma, ra);
-        else hipLaunchKernelGGL((refresh_kernel<T, MERGE_ADAPTIVE>), grid, block, 0, st, k, v, ko, vo, ma, ra);
+        const auto run = [&](auto kernel) {
+            hipLaunchKernelGGL(kernel, dim3((unsigned)slices), dim3(few ? REFRESH_BLOCK_FEW : REFRESH_BLOCK), 0, st, (const T *)K, (const T *)V,
+                               (T *)K_out, (T *)V_out, ma, ra);
+        };
+        if (ma.mode == MERGE_AVERAGE) few ? run(refresh_kernel<T, MERGE_AVERAGE, REFRESH_BLOCK_FEW>) : run(refresh_kernel<T, MERGE_AVERAGE, REFRESH_BLOCK>);
+        else if (ma.mode == MERGE_FIXED) few ? run(refresh_kernel<T, MERGE_FIXED, REFRESH_BLOCK_FEW>) : run(refresh_kernel<T, MERGE_FIXED, REFRESH_BLOCK>);
+        else few ? run(refresh_kernel<T, MERGE_ADAPTIVE, REFRESH_BLOCK_FEW>) : run(refresh_kernel<T, MERGE_ADAPTIVE, REFRESH_BLOCK>);
     }
     kvm_status rc = check_launch("refresh_kernel");
-    if (rc != KVM_OK || sh.N <= LONG_SET_MIN) return rc;
+    if (rc != KVM_OK || few || sh.N <= LONG_SET_MIN) return rc;
     launch_merge_long_t<T>(sh, K, V, K_out, V_out, ma, st);
     return check_launch("merge_long_kernel");
 }

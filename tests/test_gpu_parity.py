@@ -1953,6 +1953,48 @@ def test_merge_refresh_random_map_changes():
                 f"case {case} ({dtype}, N={N}) slice {i}: refreshed rows differ from a full merge (M {int(old[3][i])} -> {M})"
 
 
+@pytest.mark.parametrize("dtype,mode", [("f16", "adaptive"), ("bf16", "fixed"), ("f32", "adaptive"), ("f32", "average")])
+@pytest.mark.parametrize("slices", [1, 256, 257])
+def test_merge_refresh_with_one_workgroup_size_or_the_other(dtype, mode, slices):
+    """Up to 256 slices a workgroup of 1024 threads refreshes a slice, its sets of more than 512 tokens too; beyond, one of 512
+    threads, and the long sets follow in a launch of their own.  Rows that move up and down over several batches, changed sets
+    of one, four and sixteen waves: the bits of a full merge of the new maps."""
+    _say(f"merge refresh, {slices} slices: {dtype} {mode}")
+    rng = np.random.default_rng(9)
+    old = [1] * 300 + [600, 513, 200, 129, 17, 5] + [1] * 200 + [40, 3] + [1] * 100
+    new = [1] * 290 + [4, 6] + [600, 514, 199, 129, 17, 5] + [1] * 200 + [20, 20, 3] + [1] * 100   # (same tokens, other sets)
+    n = sum(old)
+    assert sum(new) == n
+    params = kb.make_params(1.0, 0.0, 0.0, enforce_budget=False)
+    if mode == "fixed":
+        params.sigma_mode, params.sigma = kb.KVM_SIGMA_FIXED, 9.0
+    if mode == "average":
+        params.weights = kb.KVM_WEIGHTS_AVERAGE
+    _, K, V = _slices(44, 1, 1, [n], n, 128, 1, dtype, rho=0.9)
+    Kd, Vd = (gu.to_dev(x, dtype).expand(1, slices, n, 128).contiguous() for x in (K, V))
+    sh = kb.make_shape(Kd, 1, None)
+    b = kb.Buffers(sh, params, "cuda", gu.TORCH_DT[dtype])
+
+    def maps(sizes, shift):
+        starts = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int32)
+        piv = (starts[:-1] + np.minimum(np.asarray(sizes) - 1, np.where(np.asarray(sizes) > 500, shift, 0))).astype(np.int32)
+        out = [torch.full_like(t, f) for t, f in ((b.set_id, -1), (b.set_start, n), (b.pivot, -1), (b.n_sets, len(sizes)))]
+        for t, v in zip(out, (np.repeat(np.arange(len(sizes), dtype=np.int32), sizes), starts, piv)):
+            t[0, :, :len(v)] = torch.from_numpy(v).cuda()
+        return out
+
+    before, after = maps(old, 7), maps(new, 9)               # (the set of 600 tokens keeps its extent and changes its pivot)
+    kb.kvm_merge(sh, params, Kd, Vd, *before[1:], b.K_out, b.V_out, None, b.ws)
+    names = gu.kernels_of(lambda: kb.kvm_merge_refresh(sh, params, Kd, Vd, *before, *after[1:], b.K_out, b.V_out, None, b.ws))
+    assert ("merge_long_kernel" in names) == (slices > 256)
+    Kf, Vf = torch.zeros_like(b.K_out), torch.zeros_like(b.V_out)
+    kb.kvm_merge(sh, params, Kd, Vd, *after[1:], Kf, Vf, None, b.ws)
+    torch.cuda.synchronize()
+    M, bits = len(new), torch.int32 if dtype == "f32" else torch.int16
+    for got, want in ((b.K_out, Kf), (b.V_out, Vf)):
+        assert torch.equal(got[:, :, :M].view(bits), want[:, :, :M].view(bits))
+
+
 @pytest.mark.parametrize("dtype", ["f32", "f16", "bf16"])
 def test_evict_merge_values_matches_the_oracle(dtype):
     """Value-only merging (comparison workload): kept positions and keys bit-exact, the averaged values
