@@ -55,9 +55,6 @@ template <> struct Single<float> {
 // sum.  Other rows (the scores would have to move by 22 natural orders down or 66 up within a unit's distance) get a reference of their own.
 constexpr float SUM_MIN = 0x1p-32f;
 
-// s_waitcnt lgkmcnt(0) alone
-__device__ __forceinline__ void wait_lds() { __builtin_amdgcn_s_waitcnt(15 | (7 << 4) | (3 << 14)); }
-
 // f(0), f(1), .. f(N-1) with constant arguments
 template <int I, int N, typename F> __device__ __forceinline__ void static_for(F &&f) {
     if constexpr (I < N) {

@@ -47,6 +47,34 @@ template <typename T> struct Stream {
 // the wave's own tile has landed, and its LDS reads of the stage that is overwritten next are done
 __device__ __forceinline__ void wait_own_tile() { __builtin_amdgcn_s_waitcnt(7 << 4); }   // vmcnt(0) lgkmcnt(0)
 
+// The stationary rows [row0, row0 + 32 NBLK) of a workgroup, which all its waves hold: once from memory into LDS, the loads dealt to the
+// waves, and from there into every wave's registers.  (Straight from memory a fragment is 16 bytes of each of 32 rows, which the path to
+// the caches serves at 17 bytes a cycle and compute unit instead of 60, and every wave would ask for all of them.)  `space`: 1024 slots that
+// no load is under way to; the caller puts a barrier between this and the first load into them.  Rows past n_valid repeat the last valid one.
+// us, both passes, fragments from memory by every wave / this: 8 slices of 4096 tokens 61.7 / 52.2, 32 of them 189 / 172, 32 ragged ones of up to
+// 1000 23.4 / 19.7, 16 of them, G = 4, 40.5 / 34.7, one of 16384 132 / 129; fp32: 8 of up to 2000 89 / 88.
+template <typename T, int W>
+__device__ __forceinline__ void issue_stationary(const T *base, int row0, int n_valid, u32x4 *space, int wave, int lane) {
+    constexpr int CH = Mma<T>::CHUNKS;
+    const int last = n_valid - 1 - row0;
+    const char *first_row = reinterpret_cast<const char *>(base + (size_t)row0 * HEAD_DIM);
+#pragma unroll
+    for (int i = 0; i < 32 * Mma<T>::NBLK * CH / WAVE / W; ++i) {
+        const int j = i * W + wave, row = j * (WAVE / CH) + lane / CH, pos = lane % CH;
+        const uint32_t off = (uint32_t)(min(row, last) * (HEAD_DIM * (int)sizeof(T)) + ((pos ^ (row & (CH - 1))) * 16));
+        __builtin_amdgcn_global_load_lds((gptr_t)(first_row + off), (lptr_t)(space + j * WAVE), 16, 0, 0);
+    }
+}
+template <typename T>
+__device__ __forceinline__ void read_stationary(const u32x4 *space, int lane, u32x4 (*frags)[Mma<T>::FRAGS]) {
+    constexpr int CH = Mma<T>::CHUNKS;
+    const int row = lane & 31;
+#pragma unroll
+    for (int b = 0; b < Mma<T>::NBLK; ++b)
+#pragma unroll
+        for (int f = 0; f < Mma<T>::FRAGS; ++f) frags[b][f] = space[(32 * b + row) * CH + ((2 * f + (lane >> 5)) ^ (row & (CH - 1)))];
+}
+
 // scores of a streamed 32-row block against one stationary block
 template <typename T>
 __device__ __forceinline__ f32x16 stream_scores(const u32x4 *a, const u32x4 *bfrag) {
@@ -124,10 +152,15 @@ __global__ __launch_bounds__(W * WAVE, sizeof(T) == 2 && W == 4 ? 2 : 1) void at
         if (next < count) S::issue(Ks, next * 32, n, stage, lane);
         next += W;
     };
+    issue_stationary<T, W>(Qs, q0, n, lds_b[0], wave, lane);
     issue_next(lds_a[wave]);
+    if (wave < count) wait_vmcnt<S::LOADS>();                 // the rows are here, the first tile may be under way
+    else wait_vmcnt<0>();
+    barrier_no_fence();
     u32x4 qf[NB][M::FRAGS];
-#pragma unroll
-    for (int qb = 0; qb < NB; ++qb) load_stationary<T>(Qs, q0 + 32 * qb, n, lane, qf[qb]);
+    read_stationary<T>(lds_b[0], lane, qf);
+    wait_lds();
+    barrier_no_fence();
     float m_run[NB], l_run[NB];
 
     // 16-bit types: the reference of a wave's sums is the maximum of its first block and is held to the diagonal (see
@@ -243,10 +276,15 @@ __global__ __launch_bounds__(W * WAVE, sizeof(T) == 2 && W == 4 ? 2 : 1) void at
         next_qb += W;
         while (next_qb >= per_head) { next_qb -= per_head; ++next_g; }
     };
+    issue_stationary<T, W>(Ks, k0, n, lds_b[0], wave, lane);
     issue_next(lds_a[wave], lse_a[wave]);
+    if (wave < count) wait_vmcnt<S::LOADS + 1>();             // the rows are here, the first tile may be under way
+    else wait_vmcnt<0>();
+    barrier_no_fence();
     u32x4 kf[NB][M::FRAGS];
-#pragma unroll
-    for (int kb = 0; kb < NB; ++kb) load_stationary<T>(Ks, k0 + 32 * kb, n, lane, kf[kb]);
+    read_stationary<T>(lds_b[0], lane, kf);
+    wait_lds();
+    barrier_no_fence();
     if constexpr (sizeof(T) == 2) {
         if (sim_s) {                                          // the keys are here anyway: wave kb takes block kb's similarities
 #pragma unroll
@@ -325,15 +363,20 @@ struct Rows16 {
         const int row = lane & 15;
         return stage[row * CH + ((4 * f + (lane >> 4)) ^ row)];
     }
-    static __device__ __forceinline__ void stationary(const float *base, int row0, int n_valid, int lane, u32x4 *frags) {
-        const int row = row0 + (lane & 15);
+    // the stationary rows, as issue_stationary and read_stationary
+    template <int W> static __device__ __forceinline__ void issue_rows(const float *base, int row0, int n_valid, u32x4 *space, int wave, int lane) {
+        const int last = n_valid - 1 - row0;
+        const char *first_row = reinterpret_cast<const char *>(base + (size_t)row0 * HEAD_DIM);
 #pragma unroll
-        for (int f = 0; f < FRAGS; ++f) {
-            u32x4 v = {0u, 0u, 0u, 0u};
-            if (row < n_valid)
-                v = *reinterpret_cast<const u32x4 *>(reinterpret_cast<const char *>(base + (size_t)row * HEAD_DIM) + (4 * f + (lane >> 4)) * 16);
-            frags[f] = v;
+        for (int i = 0; i < SLOTS / WAVE / W; ++i) {
+            const int j = i * W + wave, row = 2 * j + lane / CH, pos = lane % CH;
+            const uint32_t off = (uint32_t)(min(row, last) * (HEAD_DIM * 4) + ((pos ^ row) * 16));
+            __builtin_amdgcn_global_load_lds((gptr_t)(first_row + off), (lptr_t)(space + j * WAVE), 16, 0, 0);
         }
+    }
+    static __device__ __forceinline__ void read_rows(const u32x4 *space, int lane, u32x4 *frags) {
+#pragma unroll
+        for (int f = 0; f < FRAGS; ++f) frags[f] = frag(space, f, lane);
     }
     // Result i of lane l is streamed row 4 (l / 16) + i, stationary row l % 16.  (Two chains: an MFMA does not wait for the one before.)
     static __device__ __forceinline__ f32x4 scores(const u32x4 *stage, const u32x4 *b, int lane) {
@@ -379,9 +422,15 @@ __global__ __launch_bounds__(W * WAVE, 1) void attn_lse_split16_kernel(
         if (next < count) Rows16::issue(Ks, next * 16, n, stage, lane);
         next += W;
     };
+    Rows16::issue_rows<W>(Q + (size_t)qslice * N * HEAD_DIM, q0, n, lds_b[0], wave, lane);
     issue_next(lds_a[wave]);
+    if (wave < count) wait_vmcnt<Rows16::SLOTS / WAVE>();
+    else wait_vmcnt<0>();
+    barrier_no_fence();
     u32x4 qf[Rows16::FRAGS];
-    Rows16::stationary(Q + (size_t)qslice * N * HEAD_DIM, q0, n, lane, qf);
+    Rows16::read_rows(lds_b[0], lane, qf);
+    wait_lds();
+    barrier_no_fence();
     float m_run = M_INIT, l_run = 0.f;
     auto step = [&](int t, const u32x4 *cur, u32x4 *nxt) {
         wait_own_tile();
@@ -460,9 +509,15 @@ __global__ __launch_bounds__(W * WAVE, 1) void attn_colsum_split16_kernel(
         next_qb += W;
         while (next_qb >= per_head) { next_qb -= per_head; ++next_g; }
     };
+    Rows16::issue_rows<W>(K + (size_t)kvslice * N * HEAD_DIM, k0, n, lds_b[0], wave, lane);
     issue_next(lds_a[wave], lse_a[wave]);
+    if (wave < count) wait_vmcnt<Rows16::SLOTS / WAVE + 1>();
+    else wait_vmcnt<0>();
+    barrier_no_fence();
     u32x4 kf[Rows16::FRAGS];
-    Rows16::stationary(K + (size_t)kvslice * N * HEAD_DIM, k0, n, lane, kf);
+    Rows16::read_rows(lds_b[0], lane, kf);
+    wait_lds();
+    barrier_no_fence();
     float part = 0.f;
     int qb_cur = wave % per_head;
     auto step = [&](const u32x4 *cur, const float *cur_lse, u32x4 *nxt, float *nxt_lse) {
@@ -505,7 +560,8 @@ constexpr int SPLIT16 = 16;              // added to the waves: the fp32 kernels
 // Waves per workgroup of a split launch; 0: the full kernels are the better choice.
 //   N, slices  stationary rows per slice, slices of the launch;  heads  streamed sequences per slice (G in the column sums, else 1)
 //   tiles      256-row (fp32: 128) tiles per slice of the full kernel;  full_wgs  workgroups it would launch
-// Measured per pass, full against split kernel, us: 32 slices of 1000 tokens f16 (128 full workgroups) 26 / 14; 8 slices of
+// Measured per pass, full against split kernel (whose waves then fetched their stationary rows each for itself; the split kernels
+// are 3 to 19 % faster now), us: 32 slices of 1000 tokens f16 (128 full workgroups) 26 / 14; 8 slices of
 // 4096 (64) 91 / 32, with G = 4 the column sums 341 / 92; 32 slices of 4096 (256) 96 / 92, 51 of 2500 (255) 84 / 64; one slice of
 // 16384 (32) 502 / 79, of 131072 (256) 12700 / 3100, 8 of 16384 with G = 4 (256) 2010 / 1220, although the column sums of such
 // lengths have a kernel of 512 keys a workgroup and read every tile eight times as often as that; but 96 of 2000 (384) 77 / 80 and 160 of 2048 (640) 114 / 140.

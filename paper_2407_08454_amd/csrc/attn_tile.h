@@ -61,6 +61,9 @@ template <int N> __device__ __forceinline__ void wait_vmcnt() {
     __builtin_amdgcn_s_waitcnt((N & 15) | (7 << 4) | (15 << 8) | ((N >> 4) << 14));
 }
 
+// s_waitcnt lgkmcnt(0) alone: the wave's LDS reads are in registers, its writes done
+__device__ __forceinline__ void wait_lds() { __builtin_amdgcn_s_waitcnt(15 | (7 << 4) | (3 << 14)); }
+
 // Workgroup barrier without the memory fence of __syncthreads(): the fence would wait for
 // every outstanding global_load_lds, i.e. for the tiles that are meant to stay in flight.
 // The LDS data a step needs is waited for explicitly with wait_vmcnt before the barrier.
