@@ -1995,6 +1995,53 @@ def test_merge_refresh_with_one_workgroup_size_or_the_other(dtype, mode, slices)
         assert torch.equal(got[:, :, :M].view(bits), want[:, :, :M].view(bits))
 
 
+@pytest.mark.parametrize("dtype,slices,sets", [("f16", 1, 1), ("f32", 1, 4096), ("f16", 1, 4097), ("bf16", 3, 9000), ("f32", 100, 1025),
+                                               ("f16", 257, 2048), ("bf16", 257, 2049), ("f32", 257, 4500)])
+def test_merge_refresh_of_many_sets(dtype, slices, sets):
+    """Every thread of a refresh compares four sets at a time, 4096 or 2048 a workgroup: numbers of sets at the edges of such a turn
+    and beyond it, mostly single tokens whose rows move by one, in both directions, past sets that were split and joined.  The
+    bits of a full merge of the new maps."""
+    _say(f"merge refresh of {sets} sets, {slices} slices: {dtype}")
+    rng = np.random.default_rng(sets)
+    new = np.ones(sets, np.int64)
+    new[rng.choice(sets, min(sets, 40), replace=False)] = rng.integers(2, 40, min(sets, 40))
+    old, i = [], 0
+    while i < sets:                                          # (one set in sixty was two, one pair in sixty was one set)
+        what = rng.integers(0, 60)
+        if what == 0 and new[i] > 1:
+            old += [1, int(new[i]) - 1]
+        elif what == 1 and i + 1 < sets:
+            old.append(int(new[i] + new[i + 1]))
+            i += 1
+        else:
+            old.append(int(new[i]))
+        i += 1
+    n = int(new.sum())
+    assert sum(old) == n
+    params = kb.make_params(1.0, 0.0, 0.0, enforce_budget=False)
+    _, K, V = _slices(45, 1, 1, [n], n, 128, 1, dtype, rho=0.9)
+    Kd, Vd = (gu.to_dev(x, dtype).expand(1, slices, n, 128).contiguous() for x in (K, V))
+    sh = kb.make_shape(Kd, 1, None)
+    b = kb.Buffers(sh, params, "cuda", gu.TORCH_DT[dtype])
+
+    def maps(sizes):
+        starts = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int32)
+        out = [torch.full_like(t, f) for t, f in ((b.set_id, -1), (b.set_start, n), (b.pivot, -1), (b.n_sets, len(sizes)))]
+        for t, v in zip(out, (np.repeat(np.arange(len(sizes), dtype=np.int32), sizes), starts, starts[:-1])):
+            t[0, :, :len(v)] = torch.from_numpy(v).cuda()
+        return out
+
+    before, after = maps(old), maps(new)
+    kb.kvm_merge(sh, params, Kd, Vd, *before[1:], b.K_out, b.V_out, None, b.ws)
+    kb.kvm_merge_refresh(sh, params, Kd, Vd, *before, *after[1:], b.K_out, b.V_out, None, b.ws)
+    Kf, Vf = torch.zeros_like(b.K_out), torch.zeros_like(b.V_out)
+    kb.kvm_merge(sh, params, Kd, Vd, *after[1:], Kf, Vf, None, b.ws)
+    torch.cuda.synchronize()
+    bits = torch.int32 if dtype == "f32" else torch.int16
+    for got, want in ((b.K_out, Kf), (b.V_out, Vf)):
+        assert torch.equal(got[:, :, :sets].view(bits), want[:, :, :sets].view(bits))
+
+
 @pytest.mark.parametrize("dtype", ["f32", "f16", "bf16"])
 def test_evict_merge_values_matches_the_oracle(dtype):
     """Value-only merging (comparison workload): kept positions and keys bit-exact, the averaged values
