@@ -379,7 +379,7 @@ kvm_status kvm_merge_refresh(const kvm_shape *shape, const kvm_params *params, c
         return KVM_ERR_WORKSPACE;
     }
     return launch_merge_refresh(*shape, *params, cap, K, V, prev_set_id, prev_set_start, prev_pivot, prev_n_sets, set_start, pivot,
-                                n_sets, K_out, V_out, n_changed_opt, (int32_t *)ws, (hipStream_t)stream);
+                                n_sets, K_out, V_out, n_changed_opt, (int32_t *)ws, ws_bytes, (hipStream_t)stream);
 }
 
 kvm_status kvm_merge_static(const kvm_shape *shape, const kvm_params *params, const void *K, const void *V,

@@ -272,7 +272,8 @@ size_t merge_refresh_workspace_bytes(const kvm_shape &sh, int cap_rows);
 kvm_status launch_merge_refresh(const kvm_shape &sh, const kvm_params &pr, int cap_rows, const void *K, const void *V,
                                 const int32_t *prev_set_id, const int32_t *prev_set_start, const int32_t *prev_pivot,
                                 const int32_t *prev_n_sets, const int32_t *set_start, const int32_t *pivot,
-                                const int32_t *n_sets, void *K_out, void *V_out, int32_t *n_changed, int32_t *ws, hipStream_t st);
+                                const int32_t *n_sets, void *K_out, void *V_out, int32_t *n_changed, int32_t *ws, size_t ws_bytes,
+                                hipStream_t st);
 size_t attn_single_bytes(const kvm_shape &sh);
 kvm_status launch_attn_single(const kvm_shape &sh, const void *Q, const void *K, float *mass, float *part, hipStream_t st);
 int attn_lse_stride(int N);

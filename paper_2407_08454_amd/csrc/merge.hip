@@ -172,6 +172,12 @@ __device__ __forceinline__ float sq_dist16(const float *kp, const float *x) {
 // branches and the compiler can interleave the independent rows.
 enum { MERGE_ADAPTIVE = 0, MERGE_FIXED = 1, MERGE_AVERAGE = 2 };
 
+// The part of a merged row that is written: all of keys and values, or the chunks [c0, c1) of one of them (which: 0 keys, 1 values).
+struct RowPart {
+    int which = -1, c0 = 0, c1 = 16;
+    __device__ __forceinline__ bool holds(int row, int c) const { return which < 0 || (row == which && c >= c0 && c < c1); }
+};
+
 // Partial sums of a set, of the rows a lane has seen (8 columns of every fourth row): keys, values, weights.
 struct SetSums { float k[8], v[8], g; };
 __device__ __forceinline__ void clear(SetSums &s) {
@@ -365,7 +371,7 @@ template <typename T, bool WITH_W, int MODE, bool STREAM> struct SetMerge {
     __device__ __forceinline__ void load_pivot(int p) { E::to_float(row_chunk<T>(Ks, p, c), kp); }
     // the merged rows.  The weights that are normalised here were written by other lanes, in a team by other waves: the caller puts a fence
     // (a barrier in a team) between those stores and this.
-    __device__ __forceinline__ void finish(SetSums &s, T *k_row, T *v_row) const {
+    __device__ __forceinline__ void finish(SetSums &s, T *k_row, T *v_row, const RowPart part) const {
         const int m = hi - lo;
         const float inv_g = 1.f / rows4_sum(s.g);
         // Keys come out in the even rows of the wave, values in the odd ones.  us, two sums for every column / one: 512 slices of 4096 tokens in sets
@@ -377,7 +383,7 @@ template <typename T, bool WITH_W, int MODE, bool STREAM> struct SetMerge {
         float out[8];
 #pragma unroll
         for (int e = 0; e < 8; ++e) out[e] = rows4_sum_pair(s.k[e], s.v[e]) * scale;
-        if (row < 2) {
+        if (row < 2 && part.holds(row, c)) {
             if constexpr (STREAM) E::store_stream(row == 0 ? k_row : v_row, c, E::from_float(out));
             else E::store(row == 0 ? k_row : v_row, c, E::from_float(out));
         }
@@ -397,7 +403,7 @@ template <typename T, bool WITH_W, int MODE, bool STREAM> struct SetMerge {
 // instead of three, 115 / 103.)
 template <typename T, bool WITH_W, int MODE, bool ANY_LENGTH, bool STREAM>
 __device__ __forceinline__ void merge_one_set(const T *Ks, const T *Vs, T *k_row, T *v_row, float *wo, int lo, int hi, int p,
-                                              const MergeArgs &a, int lane, float *set_w)
+                                              const MergeArgs &a, int lane, float *set_w, const RowPart part = RowPart())
 {
     SetMerge<T, WITH_W, MODE, STREAM> set(Ks, Vs, wo, a, lo, hi, lane);
     constexpr int BATCH = 4 * SetMerge<T, WITH_W, MODE, STREAM>::U;
@@ -433,7 +439,7 @@ __device__ __forceinline__ void merge_one_set(const T *Ks, const T *Vs, T *k_row
         wave_lds_fence();                                     // the next set's distances come to the same place
     }
     if (WITH_W) wave_lds_fence();
-    set.finish(s, k_row, v_row);
+    set.finish(s, k_row, v_row, part);
 }
 
 // The same for a set of more than SPLIT_SET_MIN tokens by four waves of a workgroup, one part each.  All threads of the workgroup call
@@ -444,7 +450,7 @@ struct TeamShared {
 };
 template <typename T, bool WITH_W, int MODE>
 __device__ __forceinline__ void merge_set_team(const T *Ks, const T *Vs, T *k_row, T *v_row, float *wo, int lo, int hi, int p,
-                                               const MergeArgs &a, int lane, int part_id, TeamShared &sh)
+                                               const MergeArgs &a, int lane, int part_id, TeamShared &sh, const RowPart part = RowPart())
 {
     SetMerge<T, WITH_W, MODE, false> set(Ks, Vs, wo, a, lo, hi, lane);
     SetSums s;
@@ -462,7 +468,7 @@ __device__ __forceinline__ void merge_set_team(const T *Ks, const T *Vs, T *k_ro
     __syncthreads();
     if (part_id == 0 && hi > lo) {
         for (int q = 0; q < SPLIT_PARTS - 1; ++q) add_parked(s, sh.part[q] + lane);
-        set.finish(s, k_row, v_row);
+        set.finish(s, k_row, v_row, part);
     }
 }
 
@@ -592,7 +598,7 @@ struct LongShared {
 };
 template <typename T, bool WITH_W, int MODE>
 __device__ __forceinline__ void merge_long_set(const T *Ks, const T *Vs, T *k_row, T *v_row, float *wo, int lo, int hi, int p, const MergeArgs &a,
-                                               int tid, LongShared &sh)
+                                               int tid, LongShared &sh, const RowPart part = RowPart())
 {
     using E = Elem<T>;
     using Raw = typename E::Raw;
@@ -684,7 +690,7 @@ __device__ __forceinline__ void merge_long_set(const T *Ks, const T *Vs, T *k_ro
             for (int w2 = 0; w2 < WAVES; ++w2) t += sh.red[w2][c][(is_v ? 8 : 0) + e];
             out[e] = t * scale;
         }
-        E::store(is_v ? v_row : k_row, c, E::from_float(out));
+        if (part.holds(is_v, c)) E::store(is_v ? v_row : k_row, c, E::from_float(out));
     }
     if (WITH_W && c == 0) {                               // each writer normalises its own g_j
         for (int row = lo + group; row < hi; row += GROUPS) wo[row] *= inv_g;
@@ -842,7 +848,7 @@ kvm_status launch_merge(const kvm_shape &sh, const kvm_params &pr, int cap_rows,
 // the row only moves to its new index; the others are merged again.  Result: bit for bit what
 // merge_kernel / merge_long_kernel give on the new maps.
 //
-// refresh_kernel, one workgroup per slice, three phases with a barrier between them:
+// refresh_kernel, one workgroup per slice (or two or four, see REFRESH_MAX_PARTS), three phases with a barrier between them:
 //   compare   src[s] = row of the previous cache that new row s is (-1: merge again), the list
 //             of short sets to merge again, and the long ones in the layout merge_long_kernel
 //             reads (that kernel follows)
@@ -861,6 +867,8 @@ struct RefreshArgs {
     int32_t *lists;        // (slices, cap_rows + 1): number of short sets to merge again, then their indices
     int32_t *long_list;    // what MergeArgs::long_list points to
     int32_t *n_changed;    // (slices) or NULL: sets merged again
+    int32_t *part_lists;   // (parts - 1, slices, cap_rows + 2 + max_long_sets): the lists of the workgroups of a slice beyond the first, long ones after the short
+    int parts;             // workgroups per slice: 1, or 2 or 4 (refresh_kernel<..., SPLIT>)
 };
 
 constexpr int REFRESH_POSTED = 256;                          // sets that are merged again in one turn
@@ -871,24 +879,37 @@ constexpr int REFRESH_LOOK = 4;                              // sets a thread co
 // 43.0 / 40.2, 256 of 2000 68.6 / 65.2, of 300 39.0 / 38.3, 240 of 4096 110.8 / 106.6.
 constexpr int REFRESH_BLOCK = 512, REFRESH_BLOCK_FEW = LONG_SET_BLOCK;
 constexpr long long REFRESH_FEW_SLICES = 256;
+constexpr int REFRESH_MAX_PARTS = 4;
 template <typename T> struct MovePerGroup { static constexpr int value = 16 / sizeof(T); };   // rows a 16-lane group moves per batch
+constexpr int REFRESH_MOVE_ROWS = REFRESH_BLOCK_FEW / 16 * MovePerGroup<half_t>::value;       // 16-bit rows of a batch of one workgroup a slice
+// Up to 128 slices, where compute units are left over, two or four workgroups share a slice by columns: one or two move and write keys, the
+// others values, half a row each where there are four.  No bytes are shared, so rows still move in place without waiting for another
+// workgroup; each compares the maps and merges the changed sets for itself, with lists of its own.  What a workgroup has to move is then a half or a
+// quarter (one compute unit moves about 0.1 TB/s), where it takes it more than two batches: below, the refresh is a chain of latencies
+// that does not get shorter (8 slices of 1000 bf16 tokens 16.0 / 17.5).  Four, not eight: a quarter of a 16-bit row would be half a cache line.
+// Refresh, us, one workgroup a slice / split: 32 slices of 3000 bf16 tokens 23.3 / 20.4, 8 of 2200 21.1 / 18.4, of 16384 54.7 / 30.8, 64 of 4096
+// 31.5 / 25.6, 128 38.6 / 35.3; fp32: 32 of 2000 28.5 / 21.4, 128 41.0 / 36.1, 8 of 2000 at 35 percent 16.8 / 14.7, 40 of 1100 22.2 / 19.2.
 
-template <typename T, int MODE, int BLOCK>
+template <typename T, int MODE, int BLOCK, bool SPLIT>
 __global__ __launch_bounds__(BLOCK, 4) void refresh_kernel(const T *__restrict__ K, const T *__restrict__ V,
                                                                 T *__restrict__ K_out, T *__restrict__ V_out, MergeArgs a,
                                                                 RefreshArgs r)
 {
     using E = Elem<T>;
     using Raw = typename E::Raw;
-    constexpr int MOVE_PER_GROUP = MovePerGroup<T>::value;
-    constexpr int MOVE_BATCH = (BLOCK / 16) * MOVE_PER_GROUP;   // rows the workgroup moves per batch
+    constexpr int MOVE_PER_GROUP = SPLIT ? 8 : MovePerGroup<T>::value;   // (split, one of keys and values)
     __shared__ int n_short, n_long, first_moved, any_up, any_down;
     constexpr int TEAMS = BLOCK / WAVE / SPLIT_PARTS;
     __shared__ float set_w[BLOCK / WAVE][SPLIT_SET_MIN];
     __shared__ TeamShared team_mem[TEAMS];
     __shared__ int posted[REFRESH_POSTED], n_posted;
-    const int slice = blockIdx.x;
-    const int tid = threadIdx.x, c = tid & 15, group = tid >> 4;
+    const int slice = SPLIT ? blockIdx.x % a.slices : blockIdx.x, part_id = SPLIT ? blockIdx.x / a.slices : 0;
+    const int tid = threadIdx.x;
+    const int lanes = SPLIT ? 32 / r.parts : 16;             // of a row that is moved
+    const int groups = BLOCK / lanes, group = tid / lanes, c = (part_id >> 1) * lanes + tid % lanes;
+    const int move_batch_rows = groups * MOVE_PER_GROUP;     // rows the workgroup moves per batch
+    RowPart part;
+    if (SPLIT) part.which = part_id & 1, part.c0 = (part_id >> 1) * lanes, part.c1 = part.c0 + lanes;
     const int n = clamp_len(a.seq_lens, slice / a.H, a.N);
     const int M = min(max(a.n_sets[slice], 0), a.cap_rows);
     const int M_old = min(max(r.prev_n_sets[slice], 0), a.cap_rows);
@@ -898,9 +919,13 @@ __global__ __launch_bounds__(BLOCK, 4) void refresh_kernel(const T *__restrict__
     const int32_t *opiv = r.prev_pivot + (size_t)slice * a.cap_rows;
     const int32_t *osid = r.prev_set_id + (size_t)slice * a.N;
     int32_t *src = r.src + (size_t)slice * a.cap_rows;
+    const int max_long = max_long_sets(a.N);
     int32_t *list = r.lists + (size_t)slice * (a.cap_rows + 1);
     int32_t *pl = r.long_list + (size_t)slice * a.list_stride;
-    const int max_long = max_long_sets(a.N);
+    if (SPLIT && part_id > 0) {
+        list = r.part_lists + ((size_t)(part_id - 1) * a.slices + slice) * (a.cap_rows + 2 + max_long);
+        pl = list + a.cap_rows + 1;
+    }
     T *Ko = K_out + (size_t)slice * a.cap_rows * HEAD_DIM;
     T *Vo = V_out + (size_t)slice * a.cap_rows * HEAD_DIM;
 
@@ -963,28 +988,29 @@ __global__ __launch_bounds__(BLOCK, 4) void refresh_kernel(const T *__restrict__
     if (tid == 0) {
         list[0] = cnt;
         pl[0] = min(n_long, max_long);
-        if (r.n_changed) r.n_changed[slice] = cnt + n_long;
+        if (r.n_changed && part_id == 0) r.n_changed[slice] = cnt + n_long;
     }
 
     // ---- move ---------------------------------------------------------------------------------
     // (a direction that no row takes is skipped as a whole: after one more token nearly all rows
     // that move go the same way)
-    const int b_lo = first / MOVE_BATCH, b_hi = (M - 1) / MOVE_BATCH;
+    const int b_lo = first / move_batch_rows, b_hi = (M - 1) / move_batch_rows;
+    T *const X = SPLIT && part.which == 1 ? Vo : Ko;
     int s[MOVE_PER_GROUP], f[MOVE_PER_GROUP], f_next[MOVE_PER_GROUP];
-    Raw rk[MOVE_PER_GROUP], rv[MOVE_PER_GROUP];
+    Raw rk[MOVE_PER_GROUP], rv[SPLIT ? 1 : MOVE_PER_GROUP];
     auto sources = [&](int bt, int *out) {                    // the batch's sources, before the direction filter
 #pragma unroll
         for (int u = 0; u < MOVE_PER_GROUP; ++u) {
-            const int row = bt * MOVE_BATCH + u * (BLOCK / 16) + group;
-            out[u] = row < M ? src[row] : -1;
+            const int row = bt * move_batch_rows + u * groups + group;
+            out[u] = src[min(row, M - 1)];                    // (rows move, so there are some)
         }
     };
     auto move_batch = [&](int bt, bool up, int bt_next, bool more) {
         bool any = false;
 #pragma unroll
         for (int u = 0; u < MOVE_PER_GROUP; ++u) {
-            s[u] = bt * MOVE_BATCH + u * (BLOCK / 16) + group;
-            f[u] = f_next[u];
+            s[u] = bt * move_batch_rows + u * groups + group;
+            f[u] = s[u] < M ? f_next[u] : -1;
             if (!(up ? (f[u] >= 0 && f[u] < s[u]) : f[u] > s[u])) f[u] = -1;
             any |= f[u] >= 0;
         }
@@ -992,11 +1018,17 @@ __global__ __launch_bounds__(BLOCK, 4) void refresh_kernel(const T *__restrict__
         if (!__syncthreads_or(any ? 1 : 0)) return;
 #pragma unroll
         for (int u = 0; u < MOVE_PER_GROUP; ++u)
-            if (f[u] >= 0) { rk[u] = E::load(Ko + (size_t)f[u] * HEAD_DIM, c); rv[u] = E::load(Vo + (size_t)f[u] * HEAD_DIM, c); }
+            if (f[u] >= 0) {
+                rk[u] = E::load(X + (size_t)f[u] * HEAD_DIM, c);
+                if constexpr (!SPLIT) rv[u] = E::load(Vo + (size_t)f[u] * HEAD_DIM, c);
+            }
         __syncthreads();                                      // every source row of the batch is in registers
 #pragma unroll
         for (int u = 0; u < MOVE_PER_GROUP; ++u)
-            if (f[u] >= 0) { E::store(Ko + (size_t)s[u] * HEAD_DIM, c, rk[u]); E::store(Vo + (size_t)s[u] * HEAD_DIM, c, rv[u]); }
+            if (f[u] >= 0) {
+                E::store(X + (size_t)s[u] * HEAD_DIM, c, rk[u]);
+                if constexpr (!SPLIT) E::store(Vo + (size_t)s[u] * HEAD_DIM, c, rv[u]);
+            }
     };
     if (moves_up) {                                           // new index above the old one: batches from the top down
         sources(b_hi, f_next);
@@ -1029,7 +1061,7 @@ __global__ __launch_bounds__(BLOCK, 4) void refresh_kernel(const T *__restrict__
             }
             const int p = min(max(piv[s], lo), hi - 1);
             merge_one_set<T, false, MODE, false, false>(Ks, Vs, Ko + (size_t)s * HEAD_DIM, Vo + (size_t)s * HEAD_DIM, nullptr, lo, hi, p, a, lane,
-                                                 set_w[wave]);
+                                                 set_w[wave], part);
         }
         __syncthreads();
         const int n_team = n_posted;
@@ -1038,7 +1070,7 @@ __global__ __launch_bounds__(BLOCK, 4) void refresh_kernel(const T *__restrict__
             const int lo = min(max(sst[s], 0), n), hi = k < n_team ? max(min(max(sst[s + 1], 0), n), lo) : lo;
             const int p = max(min(max(piv[s], lo), hi - 1), 0);
             merge_set_team<T, false, MODE>(Ks, Vs, Ko + (size_t)s * HEAD_DIM, Vo + (size_t)s * HEAD_DIM, nullptr, lo, min(hi, lo + LONG_SET_MIN), p, a,
-                                           lane, wave % SPLIT_PARTS, team_mem[wave / SPLIT_PARTS]);
+                                           lane, wave % SPLIT_PARTS, team_mem[wave / SPLIT_PARTS], part);
         }
     }
     if constexpr (BLOCK == LONG_SET_BLOCK) {
@@ -1049,7 +1081,7 @@ __global__ __launch_bounds__(BLOCK, 4) void refresh_kernel(const T *__restrict__
             const int lo = min(max(sst[s], 0), n), hi = min(max(sst[s + 1], 0), n);
             if (hi <= lo) continue;
             const int p = min(max(piv[s], lo), hi - 1);
-            merge_long_set<T, false, MODE>(Ks, Vs, Ko + (size_t)s * HEAD_DIM, Vo + (size_t)s * HEAD_DIM, nullptr, lo, hi, p, a, tid, long_sums);
+            merge_long_set<T, false, MODE>(Ks, Vs, Ko + (size_t)s * HEAD_DIM, Vo + (size_t)s * HEAD_DIM, nullptr, lo, hi, p, a, tid, long_sums, part);
         }
     }
 }
@@ -1063,12 +1095,18 @@ static kvm_status launch_refresh_t(const kvm_shape &sh, const void *K, const voi
     {
         ProfScope prof("refresh_kernel", st);
         const auto run = [&](auto kernel) {
-            hipLaunchKernelGGL(kernel, dim3((unsigned)slices), dim3(few ? REFRESH_BLOCK_FEW : REFRESH_BLOCK), 0, st, (const T *)K, (const T *)V,
-                               (T *)K_out, (T *)V_out, ma, ra);
+            hipLaunchKernelGGL(kernel, dim3((unsigned)(slices * ra.parts)), dim3(few ? REFRESH_BLOCK_FEW : REFRESH_BLOCK), 0, st, (const T *)K,
+                               (const T *)V, (T *)K_out, (T *)V_out, ma, ra);
         };
-        if (ma.mode == MERGE_AVERAGE) few ? run(refresh_kernel<T, MERGE_AVERAGE, REFRESH_BLOCK_FEW>) : run(refresh_kernel<T, MERGE_AVERAGE, REFRESH_BLOCK>);
-        else if (ma.mode == MERGE_FIXED) few ? run(refresh_kernel<T, MERGE_FIXED, REFRESH_BLOCK_FEW>) : run(refresh_kernel<T, MERGE_FIXED, REFRESH_BLOCK>);
-        else few ? run(refresh_kernel<T, MERGE_ADAPTIVE, REFRESH_BLOCK_FEW>) : run(refresh_kernel<T, MERGE_ADAPTIVE, REFRESH_BLOCK>);
+        const auto pick = [&](auto mode) {
+            constexpr int MODE = decltype(mode)::value;
+            if (ra.parts > 1) run(refresh_kernel<T, MODE, REFRESH_BLOCK_FEW, true>);
+            else if (few) run(refresh_kernel<T, MODE, REFRESH_BLOCK_FEW, false>);
+            else run(refresh_kernel<T, MODE, REFRESH_BLOCK, false>);
+        };
+        if (ma.mode == MERGE_AVERAGE) pick(std::integral_constant<int, MERGE_AVERAGE>());
+        else if (ma.mode == MERGE_FIXED) pick(std::integral_constant<int, MERGE_FIXED>());
+        else pick(std::integral_constant<int, MERGE_ADAPTIVE>());
     }
     kvm_status rc = check_launch("refresh_kernel");
     if (rc != KVM_OK || few || sh.N <= LONG_SET_MIN) return rc;
@@ -1081,10 +1119,24 @@ size_t merge_refresh_workspace_bytes(const kvm_shape &sh, int cap_rows)
     return (size_t)sh.B * sh.H_kv * ((size_t)merge_ws_stride(sh.N) + 2 * (size_t)cap_rows + 1) * sizeof(int32_t);
 }
 
+// Workgroups per slice of a refresh that has ws_bytes of workspace (the lists of the ones beyond the first stand behind the rest; the size that
+// kvm_workspace_bytes gives has room for four up to a budget of 0.65, for two always).
+static int refresh_parts(const kvm_shape &sh, int cap_rows, size_t ws_bytes)
+{
+    const size_t slices = (size_t)sh.B * sh.H_kv;
+    const size_t each = slices * ((size_t)cap_rows + 2 + max_long_sets(sh.N)) * sizeof(int32_t);   // lists of one more workgroup a slice
+    int parts = 1;
+    if (cap_rows <= 2 * REFRESH_MOVE_ROWS / (sh.dtype == KVM_F32 ? 2 : 1)) return parts;
+    while (parts < REFRESH_MAX_PARTS && (long long)slices * 2 * parts <= REFRESH_FEW_SLICES &&
+           merge_refresh_workspace_bytes(sh, cap_rows) + (2 * parts - 1) * each <= ws_bytes)
+        parts *= 2;
+    return parts;
+}
+
 kvm_status launch_merge_refresh(const kvm_shape &sh, const kvm_params &pr, int cap_rows, const void *K, const void *V,
                                 const int32_t *prev_set_id, const int32_t *prev_set_start, const int32_t *prev_pivot,
                                 const int32_t *prev_n_sets, const int32_t *set_start, const int32_t *pivot,
-                                const int32_t *n_sets, void *K_out, void *V_out, int32_t *n_changed, int32_t *ws, hipStream_t st)
+                                const int32_t *n_sets, void *K_out, void *V_out, int32_t *n_changed, int32_t *ws, size_t ws_bytes, hipStream_t st)
 {
     const size_t slices = (size_t)sh.B * sh.H_kv;
     if (slices == 0 || cap_rows == 0 || sh.N == 0) return KVM_OK;
@@ -1098,6 +1150,8 @@ kvm_status launch_merge_refresh(const kvm_shape &sh, const kvm_params &pr, int c
     ra.lists = ra.src + slices * cap_rows;
     ra.long_list = ws + long_list_offset(sh.N);
     ra.n_changed = n_changed;
+    ra.part_lists = ra.lists + slices * (cap_rows + 1);
+    ra.parts = refresh_parts(sh, cap_rows, ws_bytes);
     MergeArgs ma;
     ma.set_start = set_start;
     ma.pivot = pivot;

@@ -1995,12 +1995,13 @@ def test_merge_refresh_with_one_workgroup_size_or_the_other(dtype, mode, slices)
         assert torch.equal(got[:, :, :M].view(bits), want[:, :, :M].view(bits))
 
 
-@pytest.mark.parametrize("dtype,slices,sets", [("f16", 1, 1), ("f32", 1, 4096), ("f16", 1, 4097), ("bf16", 3, 9000), ("f32", 100, 1025),
-                                               ("f16", 257, 2048), ("bf16", 257, 2049), ("f32", 257, 4500)])
+@pytest.mark.parametrize("dtype,slices,sets", [("f16", 1, 1), ("f32", 1, 4096), ("f16", 1, 4097), ("bf16", 3, 9000), ("bf16", 64, 1030),
+                                               ("f32", 100, 1025), ("f16", 128, 1040), ("f32", 129, 1025), ("f16", 257, 2048), ("bf16", 257, 2049), ("f32", 257, 4500)])
 def test_merge_refresh_of_many_sets(dtype, slices, sets):
     """Every thread of a refresh compares four sets at a time, 4096 or 2048 a workgroup: numbers of sets at the edges of such a turn
-    and beyond it, mostly single tokens whose rows move by one, in both directions, past sets that were split and joined.  The
-    bits of a full merge of the new maps."""
+    and beyond it, mostly single tokens whose rows move by one, in both directions, past sets that were split and joined.  Up
+    to 64 slices four workgroups share a slice, up to 128 two, and one where the workspace has no room for more lists.  The bits of
+    a full merge of the new maps."""
     _say(f"merge refresh of {sets} sets, {slices} slices: {dtype}")
     rng = np.random.default_rng(sets)
     new = np.ones(sets, np.int64)
@@ -2033,13 +2034,20 @@ def test_merge_refresh_of_many_sets(dtype, slices, sets):
 
     before, after = maps(old), maps(new)
     kb.kvm_merge(sh, params, Kd, Vd, *before[1:], b.K_out, b.V_out, None, b.ws)
-    kb.kvm_merge_refresh(sh, params, Kd, Vd, *before, *after[1:], b.K_out, b.V_out, None, b.ws)
+    Ks, Vs = b.K_out.clone(), b.V_out.clone()
+    changed = torch.full((2, 1, slices), -1, dtype=torch.int32, device="cuda")
+    kb.kvm_merge_refresh(sh, params, Kd, Vd, *before, *after[1:], b.K_out, b.V_out, changed[0], b.ws)
+    least = slices * ((n + 63) // 64 + n // 513 + 3 + 2 * n + 1) * 4
+    kb.kvm_merge_refresh(sh, params, Kd, Vd, *before, *after[1:], Ks, Vs, changed[1], torch.empty(least, dtype=torch.uint8, device="cuda"))
     Kf, Vf = torch.zeros_like(b.K_out), torch.zeros_like(b.V_out)
     kb.kvm_merge(sh, params, Kd, Vd, *after[1:], Kf, Vf, None, b.ws)
     torch.cuda.synchronize()
     bits = torch.int32 if dtype == "f32" else torch.int16
-    for got, want in ((b.K_out, Kf), (b.V_out, Vf)):
+    for got, want in ((b.K_out, Kf), (b.V_out, Vf), (Ks, Kf), (Vs, Vf)):
         assert torch.equal(got[:, :, :sets].view(bits), want[:, :, :sets].view(bits))
+    kept = len(set(zip(before[1][0, 0].tolist(), before[1][0, 0, 1:len(old) + 1].tolist())) &
+               set(zip(after[1][0, 0].tolist(), after[1][0, 0, 1:sets + 1].tolist())))
+    assert bool((changed == sets - kept).all())
 
 
 @pytest.mark.parametrize("dtype", ["f32", "f16", "bf16"])
