@@ -1120,7 +1120,7 @@ size_t merge_refresh_workspace_bytes(const kvm_shape &sh, int cap_rows)
 }
 
 // Workgroups per slice of a refresh that has ws_bytes of workspace (the lists of the ones beyond the first stand behind the rest; the size that
-// kvm_workspace_bytes gives has room for four up to a budget of 0.65, for two always).
+// kvm_workspace_bytes gives has room for four up to a budget of 0.64, for two always).
 static int refresh_parts(const kvm_shape &sh, int cap_rows, size_t ws_bytes)
 {
     const size_t slices = (size_t)sh.B * sh.H_kv;
