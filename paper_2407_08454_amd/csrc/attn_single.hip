@@ -426,7 +426,7 @@ static SinglePlan single_plan(const kvm_shape &sh)
     SinglePlan pl;
     const bool f32 = sh.dtype == KVM_F32;
     const long long slices = (long long)sh.B * sh.H_kv;
-    if (sh.seq_lens || sh.N > (f32 ? 4096 : 2048) || sh.G > 1024) return pl;   // (inv_G is exact for up to 2^32 / G units)
+    if (slices * sh.N == 0 || sh.seq_lens || sh.N > (f32 ? 4096 : 2048) || sh.G > 1024) return pl;   // (inv_G is exact for up to 2^32 / G units)
     if (!f32 && sh.N > 1024 && slices * sh.G * sh.N > SINGLE_LONG_ROWS) return pl;
     int resident;                                            // workgroups a compute unit holds
     if (f32) {

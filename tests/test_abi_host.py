@@ -86,6 +86,14 @@ def test_capacity_and_workspace():
     assert kb.kvm_workspace_bytes(_shape(d=64), p) == 0
 
 
+@pytest.mark.parametrize("dtype", [kb.KVM_F32, kb.KVM_F16])
+@pytest.mark.parametrize("B,N", [(0, 1), (0, 100), (0, 2048), (0, 5000), (0, 0), (2, 0)])
+def test_workspace_of_a_batch_without_rows_or_tokens(B, N, dtype):
+    """Nothing to do is no error, for lengths with and without the single score pass."""
+    sh, p = _shape(B=B, N=N, dtype=dtype), kb.kvm_params_for_budget(0.5)
+    assert kb.kvm_workspace_bytes(sh, p) == kb.kvm_workspace_bytes(sh) > 0
+
+
 def test_host_detectable_errors_return_before_any_launch():
     lib = kb.load_library()
     p = kb.kvm_params_for_budget(0.5)
