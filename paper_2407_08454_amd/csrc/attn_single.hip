@@ -20,6 +20,7 @@
 #include <type_traits>
 
 #include "attn_tile.h"
+#include "row_window.h"
 
 namespace kvm {
 
@@ -63,11 +64,11 @@ template <int I, int N, typename F> __device__ __forceinline__ void static_for(F
     }
 }
 
-// 64 times 16 bytes of the `bytes` bytes at base (scalars) into consecutive LDS slots; what lies beyond reads as zeros
-__device__ __forceinline__ void load_lds(const char *base, int bytes, int lane_offset, int offset, u32x4 *dst) {
+// 64 times 16 bytes of a window (scalar) of the matrix at base into consecutive LDS slots; what lies beyond its end reads as zeros
+__device__ __forceinline__ void load_lds(const char *base, RowWindow w, int lane_offset, u32x4 *dst) {
 #if defined(__HIP_DEVICE_COMPILE__)
-    const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc((void *)base, 0, bytes, 0x00027000);
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lptr_t)dst, 16, lane_offset, offset, 0, 0);
+    const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc((void *)(base + w.begin), 0, w.bytes, 0x00027000);
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lptr_t)dst, 16, lane_offset, 0, 0, 0);
 #endif
 }
 
@@ -91,7 +92,7 @@ __global__ __launch_bounds__(W * WAVE, OCC) void attn_single_kernel(
     using A = Single<T>;
     static_assert(RT == A::SUB, "one tile on the diagonal");
     constexpr int SUB = A::SUB, ROWS = 16 * RT, KEYS = 16 * SUB, FR = A::FRAGS, CH = A::CH, R = 4 * RT;
-    constexpr int SLOTS = KEYS * CH, LOADS = SLOTS / WAVE, ROWS_PER_LOAD = WAVE / CH, ROW_BYTES = HEAD_DIM * (int)sizeof(T);
+    constexpr int SLOTS = KEYS * CH, ROW_BYTES = HEAD_DIM * (int)sizeof(T);
     __shared__ u32x4 stage[W][SLOTS];
     __shared__ __attribute__((aligned(16))) float part[2][W][ROWS];
     __shared__ u32x4 rows_q[ROWS * CH];
@@ -117,10 +118,7 @@ __global__ __launch_bounds__(W * WAVE, OCC) void attn_single_kernel(
     constexpr int HALF = 16 * CH / WAVE;
     int voff[HALF];
 #pragma unroll
-    for (int i = 0; i < HALF; ++i) {
-        const int row = i * ROWS_PER_LOAD + lane / CH, pos = lane % CH;
-        voff[i] = row * ROW_BYTES + ((pos ^ row) * 16);
-    }
+    for (int i = 0; i < HALF; ++i) voff[i] = row_of_lane(i, lane, CH) * ROW_BYTES + offset_in_row(row_of_lane(i, lane, CH), lane, CH);
     int slot[FR];
 #pragma unroll
     for (int f = 0; f < FR; ++f) slot[f] = col * CH + ((4 * f + group) ^ col);
@@ -128,8 +126,11 @@ __global__ __launch_bounds__(W * WAVE, OCC) void attn_single_kernel(
     auto issue = [&](int t) __attribute__((always_inline)) {
         asm volatile("" : "+s"(t));                           // (or the offsets of all tiles are kept in registers from unit to unit)
 #pragma unroll
-        for (int i = 0; i < LOADS; ++i)
-            load_lds(Ks, n * ROW_BYTES, voff[i % HALF], (t * KEYS + 16 * (i / HALF)) * ROW_BYTES, stage[wave] + i * WAVE);
+        for (int h = 0; h < SUB; ++h) {
+            const RowWindow w = row_window(n, t * KEYS + 16 * h, ROW_BYTES);
+#pragma unroll
+            for (int i = 0; i < HALF; ++i) load_lds(Ks, w, voff[i], stage[wave] + (h * HALF + i) * WAVE);
+        }
     };
 
     // unit o: its first tile, and its rows, which are dealt to the waves (rows past the end repeat the last one: sums that count for nothing)
@@ -146,10 +147,11 @@ __global__ __launch_bounds__(W * WAVE, OCC) void attn_single_kernel(
     auto load_rows = [&]() __attribute__((always_inline)) {
         const char *Qg = Qs + (size_t)head * n * ROW_BYTES;
         const int lane_now = fresh_lane();
+        const RowWindow w = row_window(n, q0, ROW_BYTES);
 #pragma unroll
         for (int i = 0; i < ROWS * CH / WAVE / W; ++i) {
-            const int j = i * W + wave, row = j * ROWS_PER_LOAD + lane_now / CH, pos = lane_now % CH;
-            load_lds(Qg, n * ROW_BYTES, min(row, n - 1 - q0) * ROW_BYTES + ((pos ^ (row & 15)) * 16), q0 * ROW_BYTES, rows_q + j * WAVE);
+            const int j = i * W + wave, row = row_of_lane(j, lane_now, CH);
+            load_lds(Qg, w, min(row, n - 1 - q0) * ROW_BYTES + offset_in_row(row, lane_now, CH), rows_q + j * WAVE);
         }
     };
     auto read_rows = [&]() __attribute__((always_inline)) {
