@@ -1,7 +1,7 @@
 // The aggregated scores of short sequences in one score pass (Section 2.4 Eq. (1), Section 4.2 Eq. (7)).
 //
 //   attn_single_kernel       exponentials, row sums and column sums of 32 rows (fp32: 16) at a time, from one QK^T
-//   attn_single_sum_kernel   adds the column sums of a slice's workgroups up, in their order
+//   attn_single_sum_kernel   adds the column sums of a slice's workgroups up, in their order (column_parts.h)
 //
 // The two passes of attn_mass.hip and attn_split.hip form the score matrix twice, with an exponential a score each time, because
 // a row's sum has to be known before its terms can go to the columns.  Up to 2048 keys (fp32: 4096) the terms of 32 (16) rows fit
@@ -20,6 +20,7 @@
 #include <type_traits>
 
 #include "attn_tile.h"
+#include "column_parts.h"
 #include "row_window.h"
 
 namespace kvm {
@@ -381,22 +382,10 @@ __global__ __launch_bounds__(W * WAVE, OCC) void attn_single_kernel(
     });
 }
 
-// mass[j] = sum over the workgroups p, in order, of their column sums; workgroup p holds the keys up to the last row of its first unit
-__global__ __launch_bounds__(256) void attn_single_sum_kernel(const float *__restrict__ part, float *__restrict__ mass, int G, int n, int n_pad,
-                                                               int P, int rows, int blocks_per_slice)
+__global__ __launch_bounds__(COLUMN_BLOCK) void attn_single_sum_kernel(ColumnParts a)
 {
     __shared__ float sums[4][64];
-    const int slice = blockIdx.x / blocks_per_slice, j0 = (blockIdx.x % blocks_per_slice) * 64;
-    const int lane = threadIdx.x & 63, q = threadIdx.x >> 6, j = j0 + lane;
-    // key j is in the first unit of workgroup p, row group (n - 1) / rows - p / G, or above it
-    const int count = min(P, ((n - 1) / rows - j / rows + 1) * G);
-    const float *src = part + (size_t)slice * P * n_pad + j;
-    float s = 0.f;
-    if (j < n)
-        for (int p = q; p < count; p += 4) s += src[(size_t)p * n_pad];
-    sums[q][lane] = s;
-    __syncthreads();
-    if (q == 0 && j < n) mass[(size_t)slice * n + j] = (sums[0][lane] + sums[1][lane]) + (sums[2][lane] + sums[3][lane]);
+    add_column_parts(a, blockIdx.x, sums);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -443,7 +432,8 @@ static SinglePlan single_plan(const kvm_shape &sh)
     const long long units = (long long)((sh.N + single_rows(sh) - 1) / single_rows(sh)) * sh.G;
     const long long parts = std::min(units, std::max({4ll, (2 * 256 * resident + slices - 1) / slices, (units + 63) / 64}));
     const long long limit = 1ll << 32;                       // threads of a launch
-    if ((slices + 7) * parts * pl.waves * WAVE >= limit || slices * ((sh.N + 63) / 64) * 256 >= limit) return SinglePlan();
+    if ((slices + 7) * parts * pl.waves * WAVE >= limit || slices * ((sh.N + 63) / 64 + (sh.N + 255) / 256) * COLUMN_BLOCK >= limit)
+        return SinglePlan();                                 // (the second launch may scan the keys as well)
     pl.parts = (int)parts;
     return pl;
 }
@@ -482,7 +472,8 @@ static void single_dispatch(const SinglePlan &pl, const kvm_shape &sh, const voi
     }
 }
 
-kvm_status launch_attn_single(const kvm_shape &sh, const void *Q, const void *K, float *mass, float *part, hipStream_t st)
+// sim != nullptr: the similarities as well.
+kvm_status launch_attn_single(const kvm_shape &sh, const void *Q, const void *K, float *mass, float *part, float *sim, hipStream_t st)
 {
     const float c = (float)(1.4426950408889634 / sqrt((double)sh.d));
     const SinglePlan pl = single_plan(sh);
@@ -494,10 +485,18 @@ kvm_status launch_attn_single(const kvm_shape &sh, const void *Q, const void *K,
         kvm_status rc = check_launch("attn_single_kernel");
         if (rc != KVM_OK) return rc;
     }
+    ColumnParts sums;
+    sums.part = part;
+    sums.mass = mass;
+    sums.G = sh.G;
+    sums.n = sh.N;
+    sums.n_pad = single_stride(sh.N);
+    sums.P = pl.parts;
+    sums.rows = single_rows(sh);
+    sums.blocks_per_slice = (sh.N + 63) / 64;
+    if (sim) return launch_cosine_scan_and_sums(sh, K, sim, sums, st);
     ProfScope prof("attn_single_sum_kernel", st);
-    const int n_kv = sh.B * sh.H_kv, per = (sh.N + 63) / 64;
-    hipLaunchKernelGGL(attn_single_sum_kernel, dim3((unsigned)((long long)per * n_kv)), dim3(256), 0, st, (const float *)part, mass, sh.G, sh.N,
-                       single_stride(sh.N), pl.parts, single_rows(sh), per);
+    hipLaunchKernelGGL(attn_single_sum_kernel, dim3((unsigned)((long long)sums.blocks_per_slice * sh.B * sh.H_kv)), dim3(COLUMN_BLOCK), 0, st, sums);
     return check_launch("attn_single_sum_kernel");
 }
 

@@ -17,6 +17,7 @@
 //   evict_select_kernel, gather_rows_kernel, gather_merge_values_kernel
 //                       comparison workloads (eviction by score; evicted values averaged into the
 //                       nearest kept token)
+#include "column_parts.h"
 #include "kvm_common.h"
 
 namespace kvm {
@@ -30,14 +31,24 @@ constexpr int COS_GROUPS = COS_BLOCK / 16;                  // 16-lane groups pe
 constexpr int COS_ROWS_PER_GROUP = 16;                      // consecutive rows per 16-lane group
 constexpr int COS_ROWS_PER_BLOCK = COS_GROUPS * COS_ROWS_PER_GROUP;
 
-
-
-template <typename T>
+// SUMS: the workgroups from scan_blocks on add up the column sums of the single score pass, which the scan does not depend on.  In a launch
+// of its own the scan cost short sequences more than the second score pass would have (kvm_attn_mass_sim, us, two passes that write
+// the similarities / single pass with sums and scan one after the other / in one launch: 32 slices of 128 fp16 tokens 10.6 / 12.6 / 10.4, of 1000
+// 23.7 / 23.9 / 19.8, 8 of 1000, G = 4, in bf16 29.4 / 30.7 / 26.3, 256 of 1000 128 / 90.6 / 89.6, 1024 of 1000 441 / 360 / 364).
+template <typename T, bool SUMS>
 __global__ __launch_bounds__(COS_BLOCK) void cosine_scan_kernel(const T *__restrict__ K, float *__restrict__ sim,
                                                                  float *__restrict__ inv_norm_out,
                                                                  const int32_t *__restrict__ seq_lens, int H, int N,
-                                                                 int tiles_per_slice, int stream_from)
+                                                                 int tiles_per_slice, int stream_from, ColumnParts columns, int scan_blocks)
 {
+    if constexpr (SUMS) {
+        static_assert(COS_BLOCK == COLUMN_BLOCK, "one launch");
+        if ((int)blockIdx.x >= scan_blocks) {
+            __shared__ float sums[4][64];
+            add_column_parts(columns, blockIdx.x - scan_blocks, sums);
+            return;
+        }
+    }
     typedef typename Elem<T>::Raw Raw;
     __shared__ Raw last_row[COS_GROUPS][16];                // the last row of every group, for its successor
 
@@ -1199,14 +1210,14 @@ kvm_status launch_evict(const kvm_shape &sh, const kvm_params &pr, int cap_rows,
 // anyway, and the stream runs at 6.0-6.5 TB/s instead of 5.1 (1 GiB: 208 us / 164-179).  Smaller launches keep the plain loads,
 // because the merge reads the same keys next and finds them in the cache (32 slices of 8192 tokens, 64 MiB: the same 16 us, but the
 // merge 46 / 54; at 192 MiB scan and merge 275 / 281, at 256 369 / 366, at 512 444 / 431).
-template <typename T>
-static void launch_cosine(const kvm_shape &sh, const void *K, float *sim, float *inv_norm, hipStream_t st)
+template <typename T, bool SUMS = false>
+static void launch_cosine(const kvm_shape &sh, const void *K, float *sim, float *inv_norm, hipStream_t st, const ColumnParts &sums = ColumnParts())
 {
     const int tiles = (sh.N + COS_ROWS_PER_BLOCK - 1) / COS_ROWS_PER_BLOCK;
-    const long long blocks = (long long)sh.B * sh.H_kv * tiles;
+    const long long blocks = (long long)sh.B * sh.H_kv * tiles, more = SUMS ? (long long)sh.B * sh.H_kv * sums.blocks_per_slice : 0;
     ProfScope prof("cosine_scan_kernel", st);
-    hipLaunchKernelGGL(cosine_scan_kernel<T>, dim3((unsigned)blocks), dim3(COS_BLOCK), 0, st, (const T *)K, sim, inv_norm,
-                       sh.seq_lens, sh.H_kv, sh.N, tiles, stream_length(sh, LLC_BYTES));
+    hipLaunchKernelGGL((cosine_scan_kernel<T, SUMS>), dim3((unsigned)(blocks + more)), dim3(COS_BLOCK), 0, st, (const T *)K, sim, inv_norm,
+                       sh.seq_lens, sh.H_kv, sh.N, tiles, stream_length(sh, LLC_BYTES), sums, (int)blocks);
 }
 
 template <typename T>
@@ -1242,6 +1253,16 @@ kvm_status launch_cosine_scan(const kvm_shape &sh, const void *K, float *sim, hi
     case KVM_F32: launch_cosine<float>(sh, K, sim, nullptr, st); break;
     case KVM_F16: launch_cosine<half_t>(sh, K, sim, nullptr, st); break;
     default: launch_cosine<bf16_t>(sh, K, sim, nullptr, st); break;
+    }
+    return check_launch("cosine_scan_kernel");
+}
+
+kvm_status launch_cosine_scan_and_sums(const kvm_shape &sh, const void *K, float *sim, const ColumnParts &sums, hipStream_t st)
+{
+    switch (sh.dtype) {
+    case KVM_F32: launch_cosine<float, true>(sh, K, sim, nullptr, st, sums); break;
+    case KVM_F16: launch_cosine<half_t, true>(sh, K, sim, nullptr, st, sums); break;
+    default: launch_cosine<bf16_t, true>(sh, K, sim, nullptr, st, sums); break;
     }
     return check_launch("cosine_scan_kernel");
 }

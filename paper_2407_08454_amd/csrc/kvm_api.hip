@@ -213,10 +213,8 @@ static kvm_status attn_mass_entry(const char *who, const kvm_shape *shape, const
     }
     if (!with_lse) {
         const size_t single = attn_single_bytes(*shape);
-        if (single && ws_bytes >= ws_plain(shape, shape->N) + single) {
-            rc = launch_attn_single(*shape, Q, K, mass, (float *)ws, (hipStream_t)stream);
-            return rc == KVM_OK && with_sim ? launch_cosine_scan(*shape, K, sim, (hipStream_t)stream) : rc;
-        }
+        if (single && ws_bytes >= ws_plain(shape, shape->N) + single)
+            return launch_attn_single(*shape, Q, K, mass, (float *)ws, with_sim ? sim : nullptr, (hipStream_t)stream);
     }
     return launch_attn_mass(*shape, Q, K, with_lse ? row_lse : nullptr, mass, (float *)ws, with_sim ? sim : nullptr,
                             (hipStream_t)stream);

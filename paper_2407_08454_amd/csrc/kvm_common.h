@@ -275,7 +275,7 @@ kvm_status launch_merge_refresh(const kvm_shape &sh, const kvm_params &pr, int c
                                 const int32_t *n_sets, void *K_out, void *V_out, int32_t *n_changed, int32_t *ws, size_t ws_bytes,
                                 hipStream_t st);
 size_t attn_single_bytes(const kvm_shape &sh);
-kvm_status launch_attn_single(const kvm_shape &sh, const void *Q, const void *K, float *mass, float *part, hipStream_t st);
+kvm_status launch_attn_single(const kvm_shape &sh, const void *Q, const void *K, float *mass, float *part, float *sim, hipStream_t st);
 int attn_lse_stride(int N);
 int attn_row_tiles(int N);
 

@@ -451,6 +451,16 @@ def test_mass_single_pass(dtype, N, G, copies):
     np.testing.assert_allclose(sim, ref.identify_sets(K, want, dtype, 0.5, 0.17, 0.12, 0.75, True, cap)["sim"], atol=2e-6)
 
 
+@pytest.mark.parametrize("dtype,N,G", [("f16", 64, 1), ("bf16", 257, 3), ("f32", 300, 2)])
+def test_mass_sim_single_pass_takes_two_launches(dtype, N, G):
+    """The similarities come from the launch that adds the column sums up: a scan of its own would cost short sequences more than
+    the second score pass that it replaces.  (Results: test_mass_single_pass.)"""
+    _say(f"mass and similarities, launches: {dtype} N={N} G={G}")
+    Q, K, _ = _slices(42, 1, 2, [N], N, 128, G, dtype)
+    _, names = _single_pass(Q, K, dtype, G, sim=True)
+    assert names == {"attn_single_kernel", "cosine_scan_kernel"}
+
+
 @pytest.mark.parametrize("dtype", ["f16", "bf16", "f32"])
 @pytest.mark.parametrize("orders", HELD_ORDERS + [-40.0, -300.0, 1000.0])
 def test_mass_single_pass_reference(dtype, orders):
