@@ -52,10 +52,14 @@ template <> struct Single<float> {
     }
 };
 
-// A row's terms are formed against one reference for all rows of the unit, the log-sum-exp of the unit before (of its first row).
-// Row sums between these bounds lose nothing by it: no term overflows, and one below 2^-126, which exp2 flushes to zero, is below 2^-94 of the
-// sum.  Other rows (the scores would have to move by 22 natural orders down or 66 up within a unit's distance) get a reference of their own.
-constexpr float SUM_MIN = 0x1p-32f;
+// A row's terms are formed against one reference for all rows of the unit: the least log-sum-exp of the unit before, which is of the same query
+// head (a workgroup stays with one).  Row sums between these bounds lose nothing by it: no term overflows, and one below 2^-126, which exp2
+// flushes to zero, is below 2^-94 of the sum.  Other rows (22 natural orders below the least one of the unit before, or 83 above it)
+// get a reference of their own, which costs their unit two more walks.
+// us, two passes / reference of the first row of the unit before, whichever head's / this, scores like N(0, s^2): 256 slices of 1000 fp16 tokens, G = 4,
+// s = 1 in every other head and 8 in the others 402 / 348 / 288, s = 20 538 / 614 / 300, s = 40 584 / 944 / 632; 32 of 1000, G = 1,
+// s = 20 30 / 38 / 25, s = 40 30 / 39 / 35; fp32, 8 of 1000, G = 4, s = 20 101 / 144 / 81, s = 40 101 / 150 / 138; s = 1: within 2 %.
+constexpr float SUM_MIN = 0x1p-32f, SUM_MAX = 0x1p120f;
 
 // f(0), f(1), .. f(N-1) with constant arguments
 template <int I, int N, typename F> __device__ __forceinline__ void static_for(F &&f) {
@@ -76,6 +80,17 @@ __device__ __forceinline__ void load_lds(const char *base, RowWindow w, int lane
 // lane N of each row of 16 lanes, in all of them
 template <int N> __device__ __forceinline__ float row16_lane(float v) { return dpp_f<0x150 + N>(v); }
 
+// the least of the four 16-lane rows of a wave (same lane position in each), in all of them
+__device__ __forceinline__ float rows4_min(float v) {
+    const uint32_t a = __builtin_bit_cast(uint32_t, v);
+    const auto r = __builtin_amdgcn_permlane16_swap(a, a, false, false);
+    const uint32_t r0 = r[0], r1 = r[1];
+    const uint32_t b = __builtin_bit_cast(uint32_t, fminf(__builtin_bit_cast(float, r0), __builtin_bit_cast(float, r1)));
+    const auto t = __builtin_amdgcn_permlane32_swap(b, b, false, false);
+    const uint32_t t0 = t[0], t1 = t[1];
+    return fminf(__builtin_bit_cast(float, t0), __builtin_bit_cast(float, t1));
+}
+
 // (max, sum) of a row and of more of its scores, in the reference of the larger maximum
 __device__ __forceinline__ void join(float &m0, float &l0, float m1, float l1, float c) {
     const float m = fmaxf(m0, m1);
@@ -83,12 +98,12 @@ __device__ __forceinline__ void join(float &m0, float &l0, float m1, float l1, f
     m0 = m;
 }
 
-// Units of work of a slice: a group of rows of one query head, counted off from the longest.  Workgroup p of P takes the units
-// p, 2P-1-p, 2P+p, ..: a long one, then short ones.
+// Units of work of a slice: a group of rows of one query head.  P workgroups share the slice, P a multiple of G; workgroup p takes units of head
+// p % G, counted off from the longest: r = p / G, 2S-1-r, 2S+r, .. with S = P / G, a long one, then short ones.
 template <typename T, int RT, int W, int NT, int OCC>
 __global__ __launch_bounds__(W * WAVE, OCC) void attn_single_kernel(
-    const T *__restrict__ Q, const T *__restrict__ K, float *__restrict__ out, int n_slices, int G, uint32_t inv_G, int n, int n_pad,
-    int P, float c)
+    const T *__restrict__ Q, const T *__restrict__ K, float *__restrict__ out, int n_slices, int G, int n, int n_pad,
+    int sharers, float c)
 {
     using A = Single<T>;
     static_assert(RT == A::SUB, "one tile on the diagonal");
@@ -100,6 +115,7 @@ __global__ __launch_bounds__(W * WAVE, OCC) void attn_single_kernel(
 
     const int lane = threadIdx.x & 63, group = lane >> 4, col = lane & 15;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int P = sharers * G;                                // workgroups of a slice, `sharers` of a head
     int slice, p;
     if (n_slices >= 64) {
         const int idx = blockIdx.x >> 3;
@@ -110,49 +126,52 @@ __global__ __launch_bounds__(W * WAVE, OCC) void attn_single_kernel(
         slice = blockIdx.x % n_slices;
         p = blockIdx.x / n_slices;
     }
-    const int groups = (n + ROWS - 1) / ROWS, units = groups * G;
+    const int units = (n + ROWS - 1) / ROWS, rank = G == 1 ? p : p / G;   // of a head: units, which of its workgroups
     const char *Ks = reinterpret_cast<const char *>(K + (size_t)slice * n * HEAD_DIM);
-    const char *Qs = reinterpret_cast<const char *>(Q + (size_t)slice * G * n * HEAD_DIM);
+    const char *Qs = reinterpret_cast<const char *>(Q + ((size_t)slice * G + (p - rank * G)) * n * HEAD_DIM);
 
     // Rows [16 m, 16 m + 16) of a matrix into 16 rows of LDS, HALF load instructions; chunk ch of row r goes to position ch ^ r, which
     // is done on the source side (the instruction writes 64 consecutive slots).  Rows past the slice's last one read as zeros.
     constexpr int HALF = 16 * CH / WAVE;
-    int voff[HALF];
+    // (The offsets of load i are those of load 0 with some bits turned, as are the slots of fragment f: where the terms fill the registers they
+    // are worked out each time.)
+    constexpr bool TIGHT = NT * SUB * RT > 16 && sizeof(T) == 4;
+    constexpr int OFFS = TIGHT ? 1 : HALF, SLOTS_KEPT = TIGHT ? 1 : FR, TURN = 16 * WAVE + 16 * (WAVE / CH);
+    int voff[OFFS], slot[SLOTS_KEPT];
 #pragma unroll
-    for (int i = 0; i < HALF; ++i) voff[i] = row_of_lane(i, lane, CH) * ROW_BYTES + offset_in_row(row_of_lane(i, lane, CH), lane, CH);
-    int slot[FR];
+    for (int i = 0; i < OFFS; ++i) voff[i] = row_of_lane(i, lane, CH) * ROW_BYTES + offset_in_row(row_of_lane(i, lane, CH), lane, CH);
 #pragma unroll
-    for (int f = 0; f < FR; ++f) slot[f] = col * CH + ((4 * f + group) ^ col);
+    for (int f = 0; f < SLOTS_KEPT; ++f) slot[f] = col * CH + ((4 * f + group) ^ col);
 
     auto issue = [&](int t) __attribute__((always_inline)) {
         asm volatile("" : "+s"(t));                           // (or the offsets of all tiles are kept in registers from unit to unit)
+        int first = voff[0];
+        if (TIGHT) asm volatile("" : "+v"(first));
 #pragma unroll
         for (int h = 0; h < SUB; ++h) {
             const RowWindow w = row_window(n, t * KEYS + 16 * h, ROW_BYTES);
 #pragma unroll
-            for (int i = 0; i < HALF; ++i) load_lds(Ks, w, voff[i], stage[wave] + (h * HALF + i) * WAVE);
+            for (int i = 0; i < HALF; ++i) load_lds(Ks, w, TIGHT ? first ^ i * TURN : voff[TIGHT ? 0 : i], stage[wave] + (h * HALF + i) * WAVE);
         }
     };
 
     // unit o: its first tile, and its rows, which are dealt to the waves (rows past the end repeat the last one: sums that count for nothing)
     u32x4 qf[RT][FR];
-    int head = 0, q0 = 0, cnt = 0, diag = 0;
+    int q0 = 0, cnt = 0, diag = 0;
+    auto unit = [&](int k) __attribute__((always_inline)) { return k * sharers + ((k & 1) ? sharers - 1 - rank : rank); };
     auto begin = [&](int o) __attribute__((always_inline)) {
-        const int rank = G == 1 ? o : (int)__umulhi((uint32_t)o, inv_G);
-        head = o - rank * G;
-        q0 = (groups - 1 - rank) * ROWS;
+        q0 = (units - 1 - o) * ROWS;
         diag = q0 / KEYS;                                     // key tile on the diagonal
         cnt = (diag + W - wave) / W;                          // tiles of this wave: wave, wave + W, ..
         if (cnt > 0) issue(wave);
     };
     auto load_rows = [&]() __attribute__((always_inline)) {
-        const char *Qg = Qs + (size_t)head * n * ROW_BYTES;
         const int lane_now = fresh_lane();
         const RowWindow w = row_window(n, q0, ROW_BYTES);
 #pragma unroll
         for (int i = 0; i < ROWS * CH / WAVE / W; ++i) {
             const int j = i * W + wave, row = row_of_lane(j, lane_now, CH);
-            load_lds(Qg, w, min(row, n - 1 - q0) * ROW_BYTES + offset_in_row(row, lane_now, CH), rows_q + j * WAVE);
+            load_lds(Qs, w, min(row, n - 1 - q0) * ROW_BYTES + offset_in_row(row, lane_now, CH), rows_q + j * WAVE);
         }
     };
     auto read_rows = [&]() __attribute__((always_inline)) {
@@ -171,7 +190,7 @@ __global__ __launch_bounds__(W * WAVE, OCC) void attn_single_kernel(
 #pragma unroll
         for (int j = 0; j < SUB; ++j)
 #pragma unroll
-            for (int f = 0; f < FR; ++f) kf[j][f] = stage[wave][slot[f] + 16 * CH * j];
+            for (int f = 0; f < FR; ++f) kf[j][f] = stage[wave][slot[TIGHT ? 0 : f] + 16 * CH * j];
     };
     auto scores = [&](const u32x4 (*kf)[FR], f32x4 (*s)[RT]) __attribute__((always_inline)) {
 #pragma unroll
@@ -182,6 +201,32 @@ __global__ __launch_bounds__(W * WAVE, OCC) void attn_single_kernel(
             for (int f = 0; f < FR; ++f)
 #pragma unroll
                 for (int rt = 0; rt < RT; ++rt) s[j][rt] = A::mma(qf[rt][f], kf[j][f], s[j][rt]);
+        }
+    };
+    // the scores of the tile that is in the stage; read() comes once its rows are in registers
+    auto stage_scores = [&](f32x4 (*s)[RT], auto read) __attribute__((always_inline)) {
+        if constexpr (TIGHT) {                                // half of the fragments at a time
+            s[0][0] = f32x4{0.f, 0.f, 0.f, 0.f};
+            int first = slot[0];
+            asm volatile("" : "+v"(first));
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                u32x4 kf[FR / 2];
+#pragma unroll
+                for (int f = 0; f < FR / 2; ++f) kf[f] = stage[wave][first ^ 4 * (h * (FR / 2) + f)];
+                __builtin_amdgcn_sched_barrier(0);
+                wait_lds();
+                if (h == 1) read();
+#pragma unroll
+                for (int f = 0; f < FR / 2; ++f) s[0][0] = A::mma(qf[0][h * (FR / 2) + f], kf[f], s[0][0]);
+                if (h == 0) __builtin_amdgcn_sched_barrier(0);
+            }
+        } else {
+            u32x4 kf[SUB][FR];
+            read_frags(kf);
+            wait_lds();
+            read();
+            scores(kf, s);
         }
     };
     auto mask = [&](f32x4 (*s)[RT]) __attribute__((always_inline)) {      // the tile on the diagonal: keys after their row
@@ -200,19 +245,19 @@ __global__ __launch_bounds__(W * WAVE, OCC) void attn_single_kernel(
 #pragma unroll
         for (int j = 0; j < SUB; ++j) colsum[i][j] = 0.f;
     int covered = 0;
-    float base = 0.f;                                         // the reference; the first: the score of the first unit's first row with key 0
-    if (p < units) {
-        begin(p);
+    float base = 0.f;                                         // the reference; the first: the first unit's first row, its largest score with four keys before it
+    if (rank < units) {
+        begin(rank);
         load_rows();
         covered = cnt;
-        const T *q = reinterpret_cast<const T *>(Qs) + ((size_t)head * n + q0) * HEAD_DIM;
-        const typename Elem<T>::Raw first_row = Elem<T>::load(q, col), first_key = Elem<T>::load(reinterpret_cast<const T *>(Ks), col);
-        const float dot = c * row16_sum(RowDot<T>::dot(first_row, first_key));
-        if (fabsf(dot) < 0x1p60f) base = __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, dot)));
+        const typename Elem<T>::Raw first_row = Elem<T>::load(reinterpret_cast<const T *>(Qs) + (size_t)q0 * HEAD_DIM, col);
+        const typename Elem<T>::Raw key = Elem<T>::load(reinterpret_cast<const T *>(Ks) + (size_t)((q0 * group) >> 2) * HEAD_DIM, col);
+        const float most = -c * rows4_min(-row16_sum(RowDot<T>::dot(first_row, key)));
+        if (fabsf(most) < 0x1p60f) base = most;
     }
     int par = 0;
     uint64_t redo = 0;
-    for (int k = 0, o = p; o < units;) {
+    for (int k = 0, o = rank; o < units;) {
         float l[R];
         f32x4 t_[NT][SUB][RT];
         const int q0_now = q0, cnt_now = cnt, diag_now = diag;
@@ -220,11 +265,7 @@ __global__ __launch_bounds__(W * WAVE, OCC) void attn_single_kernel(
         barrier_no_fence();
         read_rows();
         if (cnt > 0) {
-            u32x4 kf[SUB][FR];
-            read_frags(kf);
-            wait_lds();
-            if (1 < cnt) issue(W + wave);
-            scores(kf, t_[0]);
+            stage_scores(t_[0], [&]() __attribute__((always_inline)) { if (1 < cnt) issue(W + wave); });
         }
 #pragma unroll
         for (int r = 0; r < R; ++r) l[r] = 0.f;
@@ -240,13 +281,18 @@ __global__ __launch_bounds__(W * WAVE, OCC) void attn_single_kernel(
             if (i < NT && i < cnt) {
                 if constexpr (i < NT) {
                     wait_vmcnt<0>();
-                    u32x4 kf[SUB][FR];
-                    read_frags(kf);
-                    if constexpr (SUB > 1) terms(t_[i - 1][0]);
-                    __builtin_amdgcn_sched_barrier(0);
-                    wait_lds();
-                    if (i + 1 < NT && i + 1 < cnt) issue((i + 1) * W + wave);
-                    scores(kf, t_[i]);
+                    const auto next = [&]() __attribute__((always_inline)) { if (i + 1 < NT && i + 1 < cnt) issue((i + 1) * W + wave); };
+                    if constexpr (SUB > 1) {
+                        u32x4 kf[SUB][FR];
+                        read_frags(kf);
+                        terms(t_[i - 1][0]);
+                        __builtin_amdgcn_sched_barrier(0);
+                        wait_lds();
+                        next();
+                        scores(kf, t_[i]);
+                    } else {
+                        stage_scores(t_[i], next);
+                    }
                     terms(t_[i - 1][SUB - 1]);
                     if constexpr (sizeof(T) == 2) {
 #pragma unroll
@@ -266,7 +312,7 @@ __global__ __launch_bounds__(W * WAVE, OCC) void attn_single_kernel(
         });
         // the next unit's first tile is on its way while this one's sums are exchanged, its rows while the terms go to the columns
         ++k;
-        o = k * P + ((k & 1) ? P - 1 - p : p);
+        o = unit(k);
         if (o < units) begin(o);
 #pragma unroll
         for (int r = 0; r < R; ++r) l[r] = row16_sum(l[r]);
@@ -285,8 +331,12 @@ __global__ __launch_bounds__(W * WAVE, OCC) void attn_single_kernel(
 #pragma unroll
         for (int w = 1; w < W; ++w) sum += part[par][w][myrow];
         const bool counts = q0_now + myrow < n;
-        const float first = __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, sum)));
-        if (__ballot(counts && !(sum >= SUM_MIN && sum <= HELD_SUM_MAX)) == 0) {   // (the same rows in every wave)
+        float least = counts ? sum : INFINITY;                // of the unit's rows, in every lane
+        least = fminf(least, dpp_f<0xB1>(least));
+        least = fminf(least, dpp_f<0x4E>(least));
+        if (RT > 1) least = fminf(least, dpp_f<0x141>(least));
+        least = rows4_min(least);
+        if (__ballot(counts && !(sum >= SUM_MIN && sum <= SUM_MAX)) == 0) {   // (the same rows in every wave)
             const float inv = counts ? 1.0f / sum : 0.f;
             float wgt[R];
             static_for<0, R>([&](auto ic) __attribute__((always_inline)) { wgt[ic] = row16_lane<ic>(inv); });
@@ -302,7 +352,7 @@ __global__ __launch_bounds__(W * WAVE, OCC) void attn_single_kernel(
         } else {
             redo |= 1ull << (k - 1);
         }
-        base += fminf(fmaxf(__log2f(first), -100.f), 100.f);
+        base += fminf(fmaxf(__log2f(least), -100.f), 100.f);
         par ^= 1;
     }
     // Units whose rows no common reference fitted: the statistics of their rows with a maximum of their own, then the terms from them, in two
@@ -310,7 +360,7 @@ __global__ __launch_bounds__(W * WAVE, OCC) void attn_single_kernel(
     for (; redo; redo &= redo - 1) {
         const int k = __builtin_ctzll(redo);
         __syncthreads();                                      // nobody reads the rows or sums of the unit before
-        begin(k * P + ((k & 1) ? P - 1 - p : p));
+        begin(unit(k));
         load_rows();
         wait_vmcnt<0>();
         __syncthreads();
@@ -319,23 +369,20 @@ __global__ __launch_bounds__(W * WAVE, OCC) void attn_single_kernel(
 #pragma unroll
         for (int r = 0; r < R; ++r) { m[r] = M_INIT; l[r] = 0.f; }
         f32x4 s[SUB][RT];
-        auto scores_of = [&](int i) __attribute__((always_inline)) {
-            issue(i * W + wave);
+        auto scores_of = [&](int i, int next) __attribute__((always_inline)) {
             wait_vmcnt<0>();
-            u32x4 kf[SUB][FR];
-            read_frags(kf);
-            wait_lds();
-            scores(kf, s);
+            stage_scores(s, [&]() __attribute__((always_inline)) { if (next < cnt) issue(next * W + wave); });
             if (i * W + wave == diag) mask(s);
         };
 #pragma clang loop unroll(disable)
         for (int i = 0; i < cnt; ++i) {
-            scores_of(i);
+            scores_of(i, i + 1);
 #pragma unroll
             for (int j = 0; j < SUB; ++j)
 #pragma unroll
                 for (int r = 0; r < R; ++r) join(m[r], l[r], s[j][r / 4][r % 4], 1.f, c);
         }
+        if (cnt > 0) issue(wave);                             // for the second walk
 #pragma unroll
         for (int r = 0; r < R; ++r) {
             join(m[r], l[r], dpp_f<0xB1>(m[r]), dpp_f<0xB1>(l[r]), c);
@@ -359,7 +406,7 @@ __global__ __launch_bounds__(W * WAVE, OCC) void attn_single_kernel(
         static_for<0, R>([&](auto ic) __attribute__((always_inline)) { L[ic] = row16_lane<ic>(stat); });
 #pragma clang loop unroll(disable)
         for (int i = 0; i < cnt; ++i) {
-            scores_of(i);
+            scores_of(i, i + 1);
 #pragma unroll
             for (int j = 0; j < SUB; ++j) {
                 float v = 0.f;
@@ -404,7 +451,7 @@ static int single_stride(int N) { return (N + 31) / 32 * 32; }
 //          that cover each other's exchanges (1024 slices of 250 fp16 tokens, us, two waves of four tiles / four of four 37 / 47; of 128, one wave / two 21 / 23)
 //   parts  two rounds of the workgroups that the chip holds, at least four a slice, or the slices that run at a time on an XCD outgrow its
 //          L2 (1024 slices of 1000, us, 2 / 4 / 6 / 16 / 32 parts 417 / 380 / 387 / 425 / 481; 32 of them 32 parts 16, 8 parts 18.8 without the sum),
-//          and no more than 64 units each (see redo)
+//          as many for every head, and no more than 64 units each (see redo)
 // Longer rows.  16-bit types from 1025 tokens on: eight waves fill a compute unit alone, which a full launch of the other kernels beats (1024
 // slices of 1100 489 / 597, of 2000 1262 / 1271; 256 of 2000 329 / 320), and a small one does not (128 of 2048 170 / 156, 96 of 1500 104 / 98, 8
 // of 2000 33 / 22): up to 2^18 query rows.  fp32: 256 of 4096 8110 / 6140.
@@ -417,7 +464,7 @@ static SinglePlan single_plan(const kvm_shape &sh)
     SinglePlan pl;
     const bool f32 = sh.dtype == KVM_F32;
     const long long slices = (long long)sh.B * sh.H_kv;
-    if (slices * sh.N == 0 || sh.seq_lens || sh.N > (f32 ? 4096 : 2048) || sh.G > 1024) return pl;   // (inv_G is exact for up to 2^32 / G units)
+    if (slices * sh.N == 0 || sh.seq_lens || sh.N > (f32 ? 4096 : 2048) || sh.G > 1024) return pl;
     if (!f32 && sh.N > 1024 && slices * sh.G * sh.N > SINGLE_LONG_ROWS) return pl;
     int resident;                                            // workgroups a compute unit holds
     if (f32) {
@@ -429,8 +476,9 @@ static SinglePlan single_plan(const kvm_shape &sh)
         pl.tiles = sh.N <= 512 ? 4 : 8;
         resident = sh.N <= 128 ? 9 : sh.N <= 256 ? 6 : sh.N <= 512 ? 3 : sh.N <= 1024 ? 2 : 1;
     }
-    const long long units = (long long)((sh.N + single_rows(sh) - 1) / single_rows(sh)) * sh.G;
-    const long long parts = std::min(units, std::max({4ll, (2 * 256 * resident + slices - 1) / slices, (units + 63) / 64}));
+    const long long units = (sh.N + single_rows(sh) - 1) / single_rows(sh);   // of a head
+    const long long wanted = std::max(4ll, (2 * 256 * resident + slices - 1) / slices);
+    const long long parts = std::min(units, std::max((wanted + sh.G - 1) / sh.G, (units + 63) / 64)) * sh.G;
     const long long limit = 1ll << 32;                       // threads of a launch
     if ((slices + 7) * parts * pl.waves * WAVE >= limit || slices * ((sh.N + 63) / 64 + (sh.N + 255) / 256) * COLUMN_BLOCK >= limit)
         return SinglePlan();                                 // (the second launch may scan the keys as well)
@@ -450,8 +498,7 @@ static void single_t(const kvm_shape &sh, const void *Q, const void *K, float *p
     const int n_kv = sh.B * sh.H_kv;
     const long long blocks = (n_kv >= 64 ? (n_kv + 7ll) / 8 * 8 : n_kv) * P;
     hipLaunchKernelGGL((attn_single_kernel<T, sizeof(T) == 2 ? 2 : 1, W, NT, OCC>), dim3((unsigned)blocks), dim3(W * WAVE), 0, st, (const T *)Q,
-                       (const T *)K, part, n_kv, sh.G, (uint32_t)((0x100000000ull + sh.G - 1) / sh.G), sh.N,
-                       single_stride(sh.N), P, c);
+                       (const T *)K, part, n_kv, sh.G, sh.N, single_stride(sh.N), P / sh.G, c);
 }
 
 template <typename T>

@@ -94,6 +94,18 @@ def test_workspace_of_a_batch_without_rows_or_tokens(B, N, dtype):
     assert kb.kvm_workspace_bytes(sh, p) == kb.kvm_workspace_bytes(sh) > 0
 
 
+@pytest.mark.parametrize("dtype,tile", [(kb.KVM_F32, 16), (kb.KVM_F16, 32)])
+@pytest.mark.parametrize("slices,G,N", [(1, 1, 512), (8, 3, 1000), (300, 4, 1000), (1024, 8, 250), (1024, 1, 1000), (1, 1024, 100), (2, 5, 1)])
+def test_single_pass_gives_every_query_head_the_same_number_of_workgroups(slices, G, N, dtype, tile):
+    """A workgroup of the single score pass stays with one query head (the reference of its sums comes from its rows before), so
+    their number, one row of column sums each in the workspace, is a multiple of G, and no workgroup has more than 64 units of rows."""
+    sh, p = _shape(B=1, H_kv=slices, G=G, N=N, dtype=dtype), kb.kvm_params_for_budget(0.5)
+    room = kb.kvm_workspace_bytes(sh, p) - kb.kvm_workspace_bytes(sh)
+    parts, left = divmod(room, slices * ((N + 31) // 32 * 32) * 4)
+    units = (N + tile - 1) // tile
+    assert left == 0 and parts % G == 0 and (units + 63) // 64 <= parts // G <= units
+
+
 def test_host_detectable_errors_return_before_any_launch():
     lib = kb.load_library()
     p = kb.kvm_params_for_budget(0.5)

@@ -499,6 +499,25 @@ def test_mass_single_pass_common_offset(dtype, offset):
     assert np.abs(got[~big]).max(initial=0.0) <= 2e-6
 
 
+@pytest.mark.parametrize("dtype", ["f16", "bf16", "f32"])
+@pytest.mark.parametrize("scales", [(1.0, 8.0, 40.0, 0.1), (40.0, 40.0, 40.0, 40.0), (100.0, 1.0, 1.0, 100.0)])
+def test_mass_single_pass_heads_of_different_scale(dtype, scales):
+    """Query heads whose log-sum-exps lie far apart, and rows of one head that do (scores that spread like N(0, 40^2)), in launches of
+    one unit of rows a workgroup and of several.  (Tolerance as for a common offset; scores go up to five times the scale.)"""
+    _say(f"mass, single pass, heads scaled by {scales}, {dtype}")
+    n, G = 1000, len(scales)
+    Q, K, _ = _slices(46, 1, 1, [n], n, 128, G, "f32")
+    Q, K = synth.to_storage(Q * np.asarray(scales, np.float32).reshape(1, G, 1, 1), dtype), synth.to_storage(K, dtype)
+    want = ref.attn_mass(Q, K, dtype, G=G)
+    tol = 1e-5 + 16 * 5 * max(scales) / math.log(2.0) * 2.0 ** -24
+    for copies in (1, 9, 300):
+        (got, _), names = _single_pass(Q, K, dtype, G, copies=copies)
+        assert "attn_single_kernel" in names and np.isfinite(got).all()
+        big = want > 1e-6
+        assert (np.abs(got[big] - want[big]) / want[big]).max() <= tol
+        assert np.abs(got[~big]).max(initial=0.0) <= 2e-6
+
+
 def test_mass_single_pass_rule():
     """Which calls take the single pass: enough workspace, no lengths, short rows; 16-bit rows beyond 1024 tokens up to 2^18
     query rows.  (Sizes and names only: the launches of the rule's far sides are small.)"""
