@@ -40,6 +40,9 @@ template <> struct Single<bf16_t> : SingleHalf<bf16_t> {
         return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
     }
 };
+// fp32 scores are two sums of 64 products: as one of 128 they were less exact than those of the 16-row split kernels (error of the aggregated scores
+// against 64 bits, 2-norm, those / one sum / two: 4 slices of 1000, scores like N(0, 8^2), 4.9e-7 / 6.5e-7 / 3.8e-7, one of 500, N(0, 4^2),
+// 1.8e-7 / 2.6e-7 / 1.5e-7).  It costs 1 to 2 %, from 2049 tokens on 1 to 5 (32 of 4096 721 / 756 us).
 template <> struct Single<float> {
     static constexpr int CH = 32, FRAGS = 8, SUB = 1;
     static __device__ __forceinline__ f32x4 mma(const u32x4 &a, const u32x4 &b, f32x4 c) {
@@ -197,16 +200,26 @@ __global__ __launch_bounds__(W * WAVE, OCC) void attn_single_kernel(
         for (int j = 0; j < SUB; ++j) {
 #pragma unroll
             for (int rt = 0; rt < RT; ++rt) s[j][rt] = f32x4{0.f, 0.f, 0.f, 0.f};
+            if constexpr (sizeof(T) == 2) {
 #pragma unroll
-            for (int f = 0; f < FR; ++f)
+                for (int f = 0; f < FR; ++f)
 #pragma unroll
-                for (int rt = 0; rt < RT; ++rt) s[j][rt] = A::mma(qf[rt][f], kf[j][f], s[j][rt]);
+                    for (int rt = 0; rt < RT; ++rt) s[j][rt] = A::mma(qf[rt][f], kf[j][f], s[j][rt]);
+            } else {                                          // (two sums of 64 products, see Single<float>)
+                f32x4 half = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int f = 0; f < FR / 2; ++f) {
+                    s[j][0] = A::mma(qf[0][f], kf[j][f], s[j][0]);
+                    half = A::mma(qf[0][FR / 2 + f], kf[j][FR / 2 + f], half);
+                }
+                s[j][0] += half;
+            }
         }
     };
     // the scores of the tile that is in the stage; read() comes once its rows are in registers
     auto stage_scores = [&](f32x4 (*s)[RT], auto read) __attribute__((always_inline)) {
         if constexpr (TIGHT) {                                // half of the fragments at a time
-            s[0][0] = f32x4{0.f, 0.f, 0.f, 0.f};
+            f32x4 sum[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
             int first = slot[0];
             asm volatile("" : "+v"(first));
 #pragma unroll
@@ -218,9 +231,10 @@ __global__ __launch_bounds__(W * WAVE, OCC) void attn_single_kernel(
                 wait_lds();
                 if (h == 1) read();
 #pragma unroll
-                for (int f = 0; f < FR / 2; ++f) s[0][0] = A::mma(qf[0][h * (FR / 2) + f], kf[f], s[0][0]);
+                for (int f = 0; f < FR / 2; ++f) sum[h] = A::mma(qf[0][h * (FR / 2) + f], kf[f], sum[h]);
                 if (h == 0) __builtin_amdgcn_sched_barrier(0);
             }
+            s[0][0] = sum[0] + sum[1];
         } else {
             u32x4 kf[SUB][FR];
             read_frags(kf);

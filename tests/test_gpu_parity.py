@@ -518,6 +518,20 @@ def test_mass_single_pass_heads_of_different_scale(dtype, scales):
         assert np.abs(got[~big]).max(initial=0.0) <= 2e-6
 
 
+@pytest.mark.parametrize("slices,N,scale", [(2, 1000, 8.0), (1, 500, 4.0), (1, 3000, 4.0)])
+def test_mass_single_pass_fp32_is_as_exact_as_the_two_passes(slices, N, scale):
+    """Scores of some size, where the rounding of their sums of products shows: the error against the oracle, 2-norm, of the single
+    pass and of the two passes that the smallest workspace leaves.  (No larger; a tenth for the luck of one input.)"""
+    _say(f"mass, single pass, exactness in fp32, {slices} x {N}, scale {scale}")
+    Q, K, _ = _slices(47, 1, slices, [N], N, 128, 1, "f32")
+    Q = (Q * np.float32(scale)).astype(np.float32)
+    want = ref.attn_mass(Q, K, "f32")
+    (one, _), names = _single_pass(Q, K, "f32")
+    assert "attn_single_kernel" in names
+    two = gu.gpu_mass(Q, K, "f32")
+    assert np.linalg.norm(one - want) <= 1.1 * np.linalg.norm(two - want)
+
+
 def test_mass_single_pass_rule():
     """Which calls take the single pass: enough workspace, no lengths, short rows; 16-bit rows beyond 1024 tokens up to 2^18
     query rows.  (Sizes and names only: the launches of the rule's far sides are small.)"""
