@@ -876,9 +876,11 @@ constexpr int REFRESH_LOOK = 4;                              // sets a thread co
 // Threads per slice: 512, two workgroups per compute unit (128 registers each), or 1024 where every slice has a compute unit to itself:
 // half as many batches to move one after the other, and the long sets are merged by the same workgroup instead of by a launch of their own.
 // Whole decode step, us, 512 / 1024: 32 slices of 3000 bf16 tokens, G = 4, 54.3 / 48.4, of 1000 41.8 / 38.9, 8 of 9000 81.8 / 75.0, of 2000 in fp32
-// 43.0 / 40.2, 256 of 2000 68.6 / 65.2, of 300 39.0 / 38.3, 240 of 4096 110.8 / 106.6.
+// 43.0 / 40.2, 256 of 2000 68.6 / 65.2, 240 of 4096 110.8 / 106.6.  Where no set can be long there is no launch to save and little to move, and
+// the larger workgroup only starts later (refresh: 128 slices of 100 fp16 tokens 11.4 / 12.8, of 300 15.6 / 16.6, one of 300 9.1 / 10.0).
 constexpr int REFRESH_BLOCK = 512, REFRESH_BLOCK_FEW = LONG_SET_BLOCK;
 constexpr long long REFRESH_FEW_SLICES = 256;
+static bool refresh_few(const kvm_shape &sh) { return (long long)sh.B * sh.H_kv <= REFRESH_FEW_SLICES && sh.N > LONG_SET_MIN; }
 constexpr int REFRESH_MAX_PARTS = 4;
 template <typename T> struct MovePerGroup { static constexpr int value = 16 / sizeof(T); };   // rows a 16-lane group moves per batch
 constexpr int REFRESH_MOVE_ROWS = REFRESH_BLOCK_FEW / 16 * MovePerGroup<half_t>::value;       // 16-bit rows of a batch of one workgroup a slice
@@ -1091,9 +1093,9 @@ static kvm_status launch_refresh_t(const kvm_shape &sh, const void *K, const voi
                                    const MergeArgs &ma, const RefreshArgs &ra, hipStream_t st)
 {
     const long long slices = (long long)sh.B * sh.H_kv;
-    const bool few = slices <= REFRESH_FEW_SLICES;
+    const bool few = refresh_few(sh);
     {
-        ProfScope prof("refresh_kernel", st);
+        ProfScope prof(ra.parts > 2 ? "refresh_kernel_4" : ra.parts > 1 ? "refresh_kernel_2" : few ? "refresh_kernel_few" : "refresh_kernel", st);
         const auto run = [&](auto kernel) {
             hipLaunchKernelGGL(kernel, dim3((unsigned)(slices * ra.parts)), dim3(few ? REFRESH_BLOCK_FEW : REFRESH_BLOCK), 0, st, (const T *)K,
                                (const T *)V, (T *)K_out, (T *)V_out, ma, ra);
@@ -1126,7 +1128,7 @@ static int refresh_parts(const kvm_shape &sh, int cap_rows, size_t ws_bytes)
     const size_t slices = (size_t)sh.B * sh.H_kv;
     const size_t each = slices * ((size_t)cap_rows + 2 + max_long_sets(sh.N)) * sizeof(int32_t);   // lists of one more workgroup a slice
     int parts = 1;
-    if (cap_rows <= 2 * REFRESH_MOVE_ROWS / (sh.dtype == KVM_F32 ? 2 : 1)) return parts;
+    if (!refresh_few(sh) || cap_rows <= 2 * REFRESH_MOVE_ROWS / (sh.dtype == KVM_F32 ? 2 : 1)) return parts;
     while (parts < REFRESH_MAX_PARTS && (long long)slices * 2 * parts <= REFRESH_FEW_SLICES &&
            merge_refresh_workspace_bytes(sh, cap_rows) + (2 * parts - 1) * each <= ws_bytes)
         parts *= 2;

@@ -2038,6 +2038,24 @@ def test_merge_refresh_with_one_workgroup_size_or_the_other(dtype, mode, slices)
         assert torch.equal(got[:, :, :M].view(bits), want[:, :, :M].view(bits))
 
 
+@pytest.mark.parametrize("slices,N,kernel", [(1, 512, "refresh_kernel"), (1, 513, "refresh_kernel_few"), (256, 300, "refresh_kernel"),
+                                             (256, 513, "refresh_kernel_few"), (257, 513, "refresh_kernel")])
+def test_merge_refresh_workgroup_size(slices, N, kernel):
+    """1024 threads a slice up to 256 slices, where a set can be longer than 512 tokens; 512 otherwise.  Unchanged maps: the rows
+    stay as they are."""
+    _say(f"merge refresh, {slices} slices of {N}: {kernel}")
+    K = gu.randn_gpu((1, slices, N, 128), torch.float16, 48)
+    sh, params = kb.make_shape(K, 1, None), kb.kvm_params_for_budget(0.5)
+    b = kb.Buffers(sh, params, "cuda", torch.float16)
+    b.mass.copy_(torch.rand_like(b.mass))
+    kb.kvm_identify_sets(sh, params, K, b.mass, b.set_id, b.set_start, b.pivot, b.n_sets, None, b.status, b.ws)
+    kb.kvm_merge(sh, params, K, K, b.set_start, b.pivot, b.n_sets, b.K_out, b.V_out, None, b.ws)
+    Ks, maps = b.K_out.clone(), [t.clone() for t in (b.set_id, b.set_start, b.pivot, b.n_sets)]
+    names = gu.kernels_of(lambda: kb.kvm_merge_refresh(sh, params, K, K, *maps, b.set_start, b.pivot, b.n_sets, b.K_out, b.V_out, None, b.ws))
+    assert kernel in names
+    assert torch.equal(b.K_out.view(torch.int16), Ks.view(torch.int16))
+
+
 @pytest.mark.parametrize("dtype,slices,sets", [("f16", 1, 1), ("f32", 1, 4096), ("f16", 1, 4097), ("bf16", 3, 9000), ("bf16", 64, 1030),
                                                ("f32", 100, 1025), ("f16", 128, 1040), ("f32", 129, 1025), ("f16", 257, 2048), ("bf16", 257, 2049), ("f32", 257, 4500)])
 def test_merge_refresh_of_many_sets(dtype, slices, sets):
