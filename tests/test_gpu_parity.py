@@ -2060,9 +2060,9 @@ def test_merge_refresh_workgroup_size(slices, N, kernel):
                                                ("f32", 100, 1025), ("f16", 128, 1040), ("f32", 129, 1025), ("f16", 257, 2048), ("bf16", 257, 2049), ("f32", 257, 4500)])
 def test_merge_refresh_of_many_sets(dtype, slices, sets):
     """Every thread of a refresh compares four sets at a time, 4096 or 2048 a workgroup: numbers of sets at the edges of such a turn
-    and beyond it, mostly single tokens whose rows move by one, in both directions, past sets that were split and joined.  Up
-    to 64 slices four workgroups share a slice, up to 128 two, and one where the workspace has no room for more lists.  The bits of
-    a full merge of the new maps."""
+    and beyond it, mostly single tokens whose rows move by one, in both directions, past sets that were split and joined.  With the
+    whole workspace, where few slices of this many rows find room for two workgroups each, and with the smallest, one each
+    (test_merge_refresh_shared_slices asks for every number).  The bits of a full merge of the new maps."""
     _say(f"merge refresh of {sets} sets, {slices} slices: {dtype}")
     rng = np.random.default_rng(sets)
     new = np.ones(sets, np.int64)
@@ -2109,6 +2109,57 @@ def test_merge_refresh_of_many_sets(dtype, slices, sets):
     kept = len(set(zip(before[1][0, 0].tolist(), before[1][0, 0, 1:len(old) + 1].tolist())) &
                set(zip(after[1][0, 0].tolist(), after[1][0, 0, 1:sets + 1].tolist())))
     assert bool((changed == sets - kept).all())
+
+
+@pytest.mark.parametrize("dtype,mode", [("f16", "adaptive"), ("bf16", "fixed"), ("f32", "adaptive"), ("f16", "average"), ("f32", "fixed")])
+@pytest.mark.parametrize("parts,slices", [(1, 3), (2, 3), (4, 3), (2, 65), (2, 128), (4, 64), (1, 129)])
+def test_merge_refresh_shared_slices(dtype, mode, parts, slices):
+    """One, two or four workgroups a slice, by the lists that the workspace has room for: rows that move over three or more batches in both
+    directions, changed sets of a wave, of four waves and of the whole workgroup.  The bits of a full merge of the new maps, and the
+    number of changed sets from one of the workgroups."""
+    sets = 3300 if slices <= 3 else 2100
+    _say(f"merge refresh, {slices} slices by {parts} workgroups each: {dtype} {mode}")
+    few, many = sets // 3, sets - sets // 3
+    old = [1] * few + [3, 40] + [1] * few + [600, 200, 513, 20] + [1] * many
+    new = [1] * few + [20, 20, 3] + [1] * (few - 6) + [4, 2] + [601, 199, 130, 383, 20] + [1] * (many - 9) + [5, 4]
+    # (from old to new the rows of the middle move down by two and those of the end up by one)
+    n = sum(old)
+    assert n == sum(new) and len(new) > 2 * 1024
+    params = kb.make_params(1.0, 0.0, 0.0, enforce_budget=False)
+    if mode == "fixed":
+        params.sigma_mode, params.sigma = kb.KVM_SIGMA_FIXED, 9.0
+    if mode == "average":
+        params.weights = kb.KVM_WEIGHTS_AVERAGE
+    _, K, V = _slices(49, 1, 1, [n], n, 128, 1, dtype, rho=0.9)
+    Kd, Vd = (gu.to_dev(x, dtype).expand(1, slices, n, 128).contiguous() for x in (K, V))
+    sh = kb.make_shape(Kd, 1, None)
+    b = kb.Buffers(sh, params, "cuda", gu.TORCH_DT[dtype])
+
+    def maps(sizes):
+        starts = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int32)
+        out = [torch.full_like(t, f) for t, f in ((b.set_id, -1), (b.set_start, n), (b.pivot, -1), (b.n_sets, len(sizes)))]
+        for t, v in zip(out, (np.repeat(np.arange(len(sizes), dtype=np.int32), sizes), starts, starts[:-1])):
+            t[0, :, :len(v)] = torch.from_numpy(v).cuda()
+        return out
+
+    # the lists of one workgroup a slice, and behind them those of every further one
+    lists = slices * ((n + 63) // 64 + n // 513 + 3 + 2 * n + 1) + (parts - 1) * slices * (n + 2 + n // 513 + 1)
+    bits = torch.int32 if dtype == "f32" else torch.int16
+    ends = set(zip(np.cumsum([0] + old).tolist(), np.cumsum(old).tolist()))
+    for here, there in ((old, new), (new, old)):
+        before, after = maps(here), maps(there)
+        kb.kvm_merge(sh, params, Kd, Vd, *before[1:], b.K_out, b.V_out, None, b.ws)
+        changed = torch.full((1, slices), -1, dtype=torch.int32, device="cuda")
+        ws = torch.empty(4 * lists, dtype=torch.uint8, device="cuda")
+        names = gu.kernels_of(lambda: kb.kvm_merge_refresh(sh, params, Kd, Vd, *before, *after[1:], b.K_out, b.V_out, changed, ws))
+        assert names == {"refresh_kernel_few" if parts == 1 else f"refresh_kernel_{parts}"}
+        Kf, Vf = torch.zeros_like(b.K_out), torch.zeros_like(b.V_out)
+        kb.kvm_merge(sh, params, Kd, Vd, *after[1:], Kf, Vf, None, b.ws)
+        torch.cuda.synchronize()
+        for got, want in ((b.K_out, Kf), (b.V_out, Vf)):
+            assert torch.equal(got[:, :, :len(there)].view(bits), want[:, :, :len(there)].view(bits))
+        kept = len(ends & set(zip(np.cumsum([0] + new).tolist(), np.cumsum(new).tolist())))
+        assert bool((changed == len(there) - kept).all())
 
 
 @pytest.mark.parametrize("dtype", ["f32", "f16", "bf16"])
