@@ -863,7 +863,7 @@ kvm_status launch_merge(const kvm_shape &sh, const kvm_params &pr, int cap_rows,
 
 struct RefreshArgs {
     const int32_t *prev_set_id, *prev_set_start, *prev_pivot, *prev_n_sets;
-    int32_t *src;          // (slices, cap_rows)
+    int32_t *src;          // (slices, cap_rows), written alike by all workgroups of a slice (see REFRESH_MAX_PARTS)
     int32_t *lists;        // (slices, cap_rows + 1): number of short sets to merge again, then their indices
     int32_t *long_list;    // what MergeArgs::long_list points to
     int32_t *n_changed;    // (slices) or NULL: sets merged again
@@ -885,8 +885,10 @@ constexpr int REFRESH_MAX_PARTS = 4;
 template <typename T> struct MovePerGroup { static constexpr int value = 16 / sizeof(T); };   // rows a 16-lane group moves per batch
 constexpr int REFRESH_MOVE_ROWS = REFRESH_BLOCK_FEW / 16 * MovePerGroup<half_t>::value;       // 16-bit rows of a batch of one workgroup a slice
 // Up to 128 slices, where compute units are left over, two or four workgroups share a slice by columns: one or two move and write keys, the
-// others values, half a row each where there are four.  No bytes are shared, so rows still move in place without waiting for another
-// workgroup; each compares the maps and merges the changed sets for itself, with lists of its own.  What a workgroup has to move is then a half or a
+// others values, half a row each where there are four.  No bytes of the rows are shared, so they still move in place without waiting for another
+// workgroup; each compares the maps and merges the changed sets for itself, with lists of its own.  The sources (src) they do share: every
+// workgroup of a slice writes all of them and reads what it wrote, the same values as the others, since they follow from the maps alone.  What
+// depends on the workgroup must not go there.  What a workgroup has to move is then a half or a
 // quarter (one compute unit moves about 0.1 TB/s), where it takes it more than two batches: below, the refresh is a chain of latencies
 // that does not get shorter (8 slices of 1000 bf16 tokens 16.0 / 17.5).  Four, not eight: a quarter of a 16-bit row would be half a cache line.
 // Refresh, us, one workgroup a slice / split: 32 slices of 3000 bf16 tokens 23.3 / 20.4, 8 of 2200 21.1 / 18.4, of 16384 54.7 / 30.8, 64 of 4096
@@ -965,7 +967,7 @@ __global__ __launch_bounds__(BLOCK, 4) void refresh_kernel(const T *__restrict__
             const int lo = min(max(start[u], 0), n), hi = min(max(end[u], 0), n);
             const bool same = hi > lo && so[u] >= 0 && so[u] < M_old && o_start[u] == start[u] && o_end[u] == end[u] && o_p[u] == p[u];
             const int from = same ? so[u] : -1;
-            src[s] = from;
+            src[s] = from;                                    // (from the maps alone: the same from every workgroup of the slice)
             if (from < 0) {
                 if (hi - lo > LONG_SET_MIN) {
                     const int k = atomicAdd(&n_long, 1);
