@@ -101,6 +101,34 @@ __device__ __forceinline__ void join(float &m0, float &l0, float m1, float l1, f
     m0 = m;
 }
 
+// blockIdx -> (slice, workgroup of the slice).  Workgroups are dealt round-robin to the eight XCDs, each with its own L2.  Eight slices that take turns
+// keep each on one of them; what is left over by whole eights goes out before them as four, two and one, which leave a slice on two,
+// four or all eight.  (In turn as they are, 33 or 57 slices put every slice on every XCD; rounded up to whole eights with empty workgroups, 65
+// slices keep one XCD an eighth longer than the others.  us, those / this, each with its best number of workgroups: 57 slices of 1000 fp16 tokens 40 / 25,
+// 33 of 2000 80 / 46, 100 of 1000 38.9 / 35.9.)  From 64 slices on an eight's
+// workgroups go out together, or too many keys are asked for at a time.
+struct SingleBlock { int slice, p; };
+__device__ __forceinline__ SingleBlock single_block(int n_slices, int P) {
+    int i = blockIdx.x;
+    if (n_slices < 8) return {i % n_slices, i / n_slices};
+    const int rest = n_slices & 7, whole = n_slices - rest;
+    if (i < rest * P) {
+        int first = whole, size = 4;
+        for (; size > 1; size >>= 1) {
+            if (!(rest & size)) continue;
+            if (i < size * P) break;
+            i -= size * P;
+            first += size;
+        }
+        return {first + i % size, i / size};
+    }
+    i -= rest * P;
+    if (whole < 64) return {i % whole, i / whole};
+    const int eight = i / (8 * P);
+    i -= eight * 8 * P;
+    return {8 * eight + (i & 7), i >> 3};
+}
+
 // Units of work of a slice: a group of rows of one query head.  P workgroups share the slice, P a multiple of G; workgroup p takes units of head
 // p % G, counted off from the longest: r = p / G, 2S-1-r, 2S+r, .. with S = P / G, a long one, then short ones.
 template <typename T, int RT, int W, int NT, int OCC>
@@ -119,16 +147,8 @@ __global__ __launch_bounds__(W * WAVE, OCC) void attn_single_kernel(
     const int lane = threadIdx.x & 63, group = lane >> 4, col = lane & 15;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int P = sharers * G;                                // workgroups of a slice, `sharers` of a head
-    int slice, p;
-    if (n_slices >= 64) {
-        const int idx = blockIdx.x >> 3;
-        slice = (idx / P) * 8 + (blockIdx.x & 7);
-        p = idx % P;
-        if (slice >= n_slices) return;
-    } else {
-        slice = blockIdx.x % n_slices;
-        p = blockIdx.x / n_slices;
-    }
+    const SingleBlock sb = single_block(n_slices, P);
+    const int slice = sb.slice, p = sb.p;
     const int units = (n + ROWS - 1) / ROWS, rank = G == 1 ? p : p / G;   // of a head: units, which of its workgroups
     const char *Ks = reinterpret_cast<const char *>(K + (size_t)slice * n * HEAD_DIM);
     const char *Qs = reinterpret_cast<const char *>(Q + ((size_t)slice * G + (p - rank * G)) * n * HEAD_DIM);
@@ -494,7 +514,7 @@ static SinglePlan single_plan(const kvm_shape &sh)
     const long long wanted = std::max(4ll, (2 * 256 * resident + slices - 1) / slices);
     const long long parts = std::min(units, std::max((wanted + sh.G - 1) / sh.G, (units + 63) / 64)) * sh.G;
     const long long limit = 1ll << 32;                       // threads of a launch
-    if ((slices + 7) * parts * pl.waves * WAVE >= limit || slices * ((sh.N + 63) / 64 + (sh.N + 255) / 256) * COLUMN_BLOCK >= limit)
+    if (slices * parts * pl.waves * WAVE >= limit || slices * ((sh.N + 63) / 64 + (sh.N + 255) / 256) * COLUMN_BLOCK >= limit)
         return SinglePlan();                                 // (the second launch may scan the keys as well)
     pl.parts = (int)parts;
     return pl;
@@ -510,7 +530,7 @@ template <typename T, int W, int NT, int OCC>
 static void single_t(const kvm_shape &sh, const void *Q, const void *K, float *part, int P, float c, hipStream_t st)
 {
     const int n_kv = sh.B * sh.H_kv;
-    const long long blocks = (n_kv >= 64 ? (n_kv + 7ll) / 8 * 8 : n_kv) * P;
+    const long long blocks = (long long)n_kv * P;
     hipLaunchKernelGGL((attn_single_kernel<T, sizeof(T) == 2 ? 2 : 1, W, NT, OCC>), dim3((unsigned)blocks), dim3(W * WAVE), 0, st, (const T *)Q,
                        (const T *)K, part, n_kv, sh.G, sh.N, single_stride(sh.N), P / sh.G, c);
 }

@@ -451,6 +451,19 @@ def test_mass_single_pass(dtype, N, G, copies):
     np.testing.assert_allclose(sim, ref.identify_sets(K, want, dtype, 0.5, 0.17, 0.12, 0.75, True, cap)["sim"], atol=2e-6)
 
 
+@pytest.mark.parametrize("dtype,N,G", [("f16", 300, 1), ("bf16", 70, 3), ("f32", 100, 2)])
+@pytest.mark.parametrize("slices", [1, 2, 5, 7, 8, 9, 15, 33, 57, 63, 65, 68, 71, 103])
+def test_mass_single_pass_of_every_slice_count(dtype, N, G, slices):
+    """Whole eights of slices take turns and what is left over goes out before them in fours, twos and ones: every slice gets all of its
+    workgroups, with the same bits, and the oracle's scores."""
+    _say(f"mass, single pass, {slices} slices: {dtype} N={N} G={G}")
+    Q, K, _ = _slices(50, 1, 1, [N], N, 128, G, dtype)
+    want = ref.attn_mass(Q, K, dtype, G=G)
+    (got, _), names = _single_pass(Q, K, dtype, G, slices)
+    assert "attn_single_kernel" in names
+    assert (np.abs(got - want) <= (1e-5 + 8 * 2.0 ** -24 * math.sqrt(N)) * want).all()
+
+
 @pytest.mark.parametrize("dtype,N,G", [("f16", 64, 1), ("bf16", 257, 3), ("f32", 300, 2)])
 def test_mass_sim_single_pass_takes_two_launches(dtype, N, G):
     """The similarities come from the launch that adds the column sums up: a scan of its own would cost short sequences more than
