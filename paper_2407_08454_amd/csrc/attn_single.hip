@@ -17,6 +17,7 @@
 // us, both passes / this: 1024 slices of 1000 fp16 tokens 460 / 365, 256 of them 128 / 85, 8 of them 20.5 / 13.3; 1024 of 512
 // 139 / 104, of 250 55 / 37, of 128 35 / 21; 32 of 2000 62 / 46; fp32: 256 of 1000 592 / 343, 32 of 4096 1055 / 755, one of 512 19.4 / 13.
 #include <algorithm>
+#include <climits>
 #include <type_traits>
 
 #include "attn_tile.h"
@@ -483,15 +484,33 @@ static int single_stride(int N) { return (N + 31) / 32 * 32; }
 // parts == 0: the two passes are the better choice.
 //   waves, tiles  the fewest registers that hold the terms of the longest row; fewer waves a workgroup are more workgroups a compute unit
 //          that cover each other's exchanges (1024 slices of 250 fp16 tokens, us, two waves of four tiles / four of four 37 / 47; of 128, one wave / two 21 / 23)
-//   parts  two rounds of the workgroups that the chip holds, at least four a slice, or the slices that run at a time on an XCD outgrow its
-//          L2 (1024 slices of 1000, us, 2 / 4 / 6 / 16 / 32 parts 417 / 380 / 387 / 425 / 481; 32 of them 32 parts 16, 8 parts 18.8 without the sum),
-//          as many for every head, and no more than 64 units each (see redo)
-// Longer rows.  16-bit types from 1025 tokens on: eight waves fill a compute unit alone, which a full launch of the other kernels beats (1024
-// slices of 1100 489 / 597, of 2000 1262 / 1271; 256 of 2000 329 / 320), and a small one does not (128 of 2048 170 / 156, 96 of 1500 104 / 98, 8
-// of 2000 33 / 22): up to 2^18 query rows.  fp32: 256 of 4096 8110 / 6140.
+//   parts  as many as fill one to eight rounds of the workgroups that the chip holds, whichever takes the least: rounds times (the largest share
+//          of units, in key tiles of a wave, each unit three more for its exchange, and three for a workgroup's start), and a twentieth of a
+//          tile for every row of column sums beyond 32 that the sum kernel reads.  (Two rounds rounded up run into a third: us, two passes / that /
+//          this, 36 slices of 1000 fp16 tokens 21.4 / 21.9 / 17.5, 40 of 2000 63 / 64.5 / 54.7, 200 of 1200 121 / 140 / 120; fp32, 33 of 2000 534 / 252 / 191.)  At least four a slice, or the slices that run at a time on an XCD outgrow its L2 (1024 slices of 1000, us,
+//          1 / 2 / 4 / 8 / 16 / 32 parts 659 / 363 / 327 / 351 / 389 / 451), as many for every head, and no more than 64 units each (see redo)
+// Longer rows.  16-bit types from 1025 tokens on: eight waves fill a compute unit alone, which a full launch of the other kernels beats (us, two passes /
+// this: 1024 slices of 1100 467 / 577, 520 of 1100 229 / 267, 300 of 1200 1.04 times as long here), and a small one does not (200 of 1200 121 / 120, 128 of
+// 2048 168 / 158, 96 of 1500 104 / 97, 40 of 2000 63 / 55, 8 of 2000 30 / 21; G = 4: 33 of 1500 115 / 109, 24 of 1500 94 / 92): up to 2^18
+// query rows.  Longest against the split kernels at 33 to 72 heads of 1025 to 1280 tokens, up to 8 % (52 of 1030 29.6 / 31.8).  From 1300 tokens on the
+// line would lie further out (256 of 2000 311 / 298).  fp32: 256 of 4096 8170 / 6120.
 // Batches of differing lengths would gain as well (512 slices of 250 to 1000 tokens 142 / 94) and keep the two passes: there the column-sum
 // kernels also write the similarities of kvm_attn_mass_sim, whose scores are bit for bit those of kvm_attn_mass.
 constexpr long long SINGLE_LONG_ROWS = 1ll << 18;
+
+constexpr int SINGLE_ROUNDS = 8, SINGLE_UNIT = 3, SINGLE_START = 3;
+
+// the largest share of a head's units that one of its workgroups has, in key tiles of a wave
+static int single_share(int units, int sharers, int waves)
+{
+    int first = 0, last = 0;                                 // of the workgroups 0 and sharers - 1: the others lie between
+    for (int u = 0, k = 0; u < units; u += sharers, ++k) {
+        const int near = (k & 1) ? u + sharers - 1 : u, far = 2 * u + sharers - 1 - near;
+        if (near < units) first += (units - near + waves - 1) / waves + SINGLE_UNIT;
+        if (far < units) last += (units - far + waves - 1) / waves + SINGLE_UNIT;
+    }
+    return std::max(first, last);
+}
 
 static SinglePlan single_plan(const kvm_shape &sh)
 {
@@ -511,8 +530,16 @@ static SinglePlan single_plan(const kvm_shape &sh)
         resident = sh.N <= 128 ? 9 : sh.N <= 256 ? 6 : sh.N <= 512 ? 3 : sh.N <= 1024 ? 2 : 1;
     }
     const long long units = (sh.N + single_rows(sh) - 1) / single_rows(sh);   // of a head
-    const long long wanted = std::max(4ll, (2 * 256 * resident + slices - 1) / slices);
-    const long long parts = std::min(units, std::max((wanted + sh.G - 1) / sh.G, (units + 63) / 64)) * sh.G;
+    const long long slots = 256ll * resident, heads = slices * sh.G, least = std::min(units, std::max((4ll + sh.G - 1) / sh.G, (units + 63) / 64));
+    long long sharers = units, best = LLONG_MAX;
+    for (long long rounds = 1, last = 0; rounds <= SINGLE_ROUNDS && last < units; ++rounds) {
+        const long long s = std::min(units, std::max(least, rounds * slots / heads));
+        if (s == last) continue;
+        last = s;
+        const long long cost = (heads * s + slots - 1) / slots * (single_share((int)units, (int)s, pl.waves) + SINGLE_START) * 20 + std::max(0ll, s * sh.G - 32);
+        if (cost < best) best = cost, sharers = s;
+    }
+    const long long parts = sharers * sh.G;
     const long long limit = 1ll << 32;                       // threads of a launch
     if (slices * parts * pl.waves * WAVE >= limit || slices * ((sh.N + 63) / 64 + (sh.N + 255) / 256) * COLUMN_BLOCK >= limit)
         return SinglePlan();                                 // (the second launch may scan the keys as well)

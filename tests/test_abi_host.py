@@ -106,6 +106,17 @@ def test_single_pass_gives_every_query_head_the_same_number_of_workgroups(slices
     assert left == 0 and parts % G == 0 and (units + 63) // 64 <= parts // G <= units
 
 
+@pytest.mark.parametrize("slices,G,N,dtype,resident", [(36, 1, 1000, kb.KVM_F16, 2), (40, 1, 1000, kb.KVM_BF16, 2), (57, 4, 1000, kb.KVM_F16, 2),
+                                                       (33, 1, 2000, kb.KVM_F16, 1), (57, 1, 2000, kb.KVM_F16, 1), (200, 1, 1200, kb.KVM_F16, 1),
+                                                       (300, 1, 500, kb.KVM_F16, 3), (33, 1, 2000, kb.KVM_F32, 1), (65, 1, 1000, kb.KVM_F32, 2)])
+def test_single_pass_fills_its_last_round(slices, G, N, dtype, resident):
+    """The workgroups of the single score pass have about the same work each, so a last round of a few of them costs a whole one: at
+    least three quarters of it, of 256 compute units with `resident` workgroups each, are filled."""
+    sh, p = _shape(B=1, H_kv=slices, G=G, N=N, dtype=dtype), kb.kvm_params_for_budget(0.5)
+    groups = (kb.kvm_workspace_bytes(sh, p) - kb.kvm_workspace_bytes(sh)) // ((N + 31) // 32 * 32 * 4)
+    assert groups > 0 and (groups % (256 * resident) == 0 or groups % (256 * resident) >= 192 * resident)
+
+
 def test_host_detectable_errors_return_before_any_launch():
     lib = kb.load_library()
     p = kb.kvm_params_for_budget(0.5)
