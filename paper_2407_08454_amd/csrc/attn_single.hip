@@ -494,9 +494,11 @@ static int single_stride(int N) { return (N + 31) / 32 * 32; }
 // 2048 168 / 158, 96 of 1500 104 / 97, 40 of 2000 63 / 55, 8 of 2000 30 / 21; G = 4: 33 of 1500 115 / 109, 24 of 1500 94 / 92): up to 2^18
 // query rows.  Longest against the split kernels at 33 to 72 heads of 1025 to 1280 tokens, up to 8 % (52 of 1030 29.6 / 31.8).  From 1300 tokens on the
 // line would lie further out (256 of 2000 311 / 298).  fp32: 256 of 4096 8170 / 6120.
+// And 513 to 768 tokens, where the other kernels' three row tiles are full and six key tiles a wave are held in the registers of eight: from 2^20 keys on
+// (1024 slices of 700 0.94 times as long as two passes, of 768 0.96; 1800 of 700 1.05, 2048 of 768 1.07; G = 4: 520 of 700 1.02).
 // Batches of differing lengths would gain as well (512 slices of 250 to 1000 tokens 142 / 94) and keep the two passes: there the column-sum
 // kernels also write the similarities of kvm_attn_mass_sim, whose scores are bit for bit those of kvm_attn_mass.
-constexpr long long SINGLE_LONG_ROWS = 1ll << 18;
+constexpr long long SINGLE_LONG_ROWS = 1ll << 18, SINGLE_MID_KEYS = 1ll << 20;
 
 constexpr int SINGLE_ROUNDS = 8, SINGLE_UNIT = 3, SINGLE_START = 3;
 
@@ -519,6 +521,7 @@ static SinglePlan single_plan(const kvm_shape &sh)
     const long long slices = (long long)sh.B * sh.H_kv;
     if (slices * sh.N == 0 || sh.seq_lens || sh.N > (f32 ? 4096 : 2048) || sh.G > 1024) return pl;
     if (!f32 && sh.N > 1024 && slices * sh.G * sh.N > SINGLE_LONG_ROWS) return pl;
+    if (!f32 && sh.N > 512 && sh.N <= 768 && slices * sh.N > SINGLE_MID_KEYS) return pl;
     int resident;                                            // workgroups a compute unit holds
     if (f32) {
         pl.waves = sh.N <= 1024 ? 4 : 8;

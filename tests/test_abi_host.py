@@ -117,6 +117,16 @@ def test_single_pass_fills_its_last_round(slices, G, N, dtype, resident):
     assert groups > 0 and (groups % (256 * resident) == 0 or groups % (256 * resident) >= 192 * resident)
 
 
+@pytest.mark.parametrize("dtype,N,slices,single", [(kb.KVM_F16, 700, 1497, True), (kb.KVM_F16, 700, 1498, False), (kb.KVM_BF16, 512, 3000, True),
+                                                   (kb.KVM_F16, 513, 2045, False), (kb.KVM_F16, 768, 1366, False), (kb.KVM_F16, 769, 3000, True),
+                                                   (kb.KVM_F32, 700, 3000, True)])
+def test_single_pass_leaves_full_row_tiles_to_the_two_passes(dtype, N, slices, single):
+    """513 to 768 tokens of 16 bit: two passes from 2^20 keys on.  (By the room that the workspace has for it.)"""
+    sh = _shape(B=1, H_kv=slices, N=N, dtype=dtype)
+    least = kb.kvm_workspace_bytes(sh)
+    assert (kb.kvm_workspace_bytes(sh, kb.make_params(1.0, 0.0, 0.0, enforce_budget=False)) > least) == single
+
+
 def test_host_detectable_errors_return_before_any_launch():
     lib = kb.load_library()
     p = kb.kvm_params_for_budget(0.5)
