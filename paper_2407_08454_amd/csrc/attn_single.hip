@@ -12,10 +12,12 @@
 // What bounds it (32 rows, 1024 slices of 1000 fp16 tokens): the 32 KB of keys that four SIMDs take in for 32x32 scores each are
 // 550 cycles of the path from the caches (60 bytes a cycle and compute unit, measured), their arithmetic is 400 cycles of the vector
 // ALU and 256 of the matrix pipe, and the exchange of the row sums leaves a wave idle once in 32 rows; the counters show the vector ALU
-// busy for half of the time, with two waves a SIMD (250 registers).  64 rows a workgroup would halve the traffic and were
-// twice as slow: eight waves then hold one compute unit, and nothing covers their exchanges.  fp32 is matrix time.
-// us, both passes / this: 1024 slices of 1000 fp16 tokens 460 / 365, 256 of them 128 / 85, 8 of them 20.5 / 13.3; 1024 of 512
-// 139 / 104, of 250 55 / 37, of 128 35 / 21; 32 of 2000 62 / 46; fp32: 256 of 1000 592 / 343, 32 of 4096 1055 / 755, one of 512 19.4 / 13.
+// busy for half of the time, with two waves a SIMD (256 registers).  64 rows a workgroup would halve the traffic and were
+// twice as slow: eight waves then hold one compute unit, and nothing covers their exchanges.  fp32 is matrix time; its rows
+// of more than 2048 tokens spill 43 of their 256 registers, most of them around the last tiles of the longest rows.
+// us, both passes / this with its sum kernel: 1024 slices of 1000 fp16 tokens 436 / 334, 256 of them 118 / 77, 32 of them 19.0 / 16.0, 8 of them 18.1 /
+// 12.2; 1024 of 512 134 / 99, of 250 53 / 32, of 128 33 / 20; 32 of 2000 51 / 42; 8 of 1000, G = 4, in bf16 28.3 / 19.5; fp32: 256 of 1000 587 /
+// 348, 32 of 4096 1052 / 750, one of 512 18.0 / 12.7.
 #include <algorithm>
 #include <climits>
 #include <type_traits>
@@ -483,7 +485,7 @@ static int single_stride(int N) { return (N + 31) / 32 * 32; }
 
 // parts == 0: the two passes are the better choice.
 //   waves, tiles  the fewest registers that hold the terms of the longest row; fewer waves a workgroup are more workgroups a compute unit
-//          that cover each other's exchanges (1024 slices of 250 fp16 tokens, us, two waves of four tiles / four of four 37 / 47; of 128, one wave / two 21 / 23)
+//          that cover each other's exchanges (1024 slices of 250 fp16 tokens, us, two waves of four tiles / four of four 37 / 47; of 128, one wave / two 21 / 23, both before the other changes to this kernel)
 //   parts  as many as fill one to eight rounds of the workgroups that the chip holds, whichever takes the least: rounds times (the largest share
 //          of units, in key tiles of a wave, each unit three more for its exchange, and three for a workgroup's start), and a twentieth of a
 //          tile for every row of column sums beyond 32 that the sum kernel reads.  (Two rounds rounded up run into a third: us, two passes / that /

@@ -560,19 +560,21 @@ constexpr int SPLIT16 = 16;              // added to the waves: the fp32 kernels
 // Waves per workgroup of a split launch; 0: the full kernels are the better choice.
 //   N, slices  stationary rows per slice, slices of the launch;  heads  streamed sequences per slice (G in the column sums, else 1)
 //   tiles      256-row (fp32: 128) tiles per slice of the full kernel;  full_wgs  workgroups it would launch
-// Measured per pass, full against split kernel (whose waves then fetched their stationary rows each for itself; the split kernels
-// are 3 to 19 % faster now), us: 32 slices of 1000 tokens f16 (128 full workgroups) 26 / 14; 8 slices of
-// 4096 (64) 91 / 32, with G = 4 the column sums 341 / 92; 32 slices of 4096 (256) 96 / 92, 51 of 2500 (255) 84 / 64; one slice of
-// 16384 (32) 502 / 79, of 131072 (256) 12700 / 3100, 8 of 16384 with G = 4 (256) 2010 / 1220, although the column sums of such
-// lengths have a kernel of 512 keys a workgroup and read every tile eight times as often as that; but 96 of 2000 (384) 77 / 80 and 160 of 2048 (640) 114 / 140.
+// Measured per pass, row statistics and column sums, full / split kernel, us (full_wgs in brackets): 32 slices of 1000 tokens f16 (128) 25.0, 25.9 / 12.8,
+// 12.7; 8 of 4096 (64) 84.9, 90.2 / 29.8, 29.1, with G = 4 the column sums 328 / 91; 32 of 4096 (256) 91.8, 96.6 / 88.5, 89.8; 51 of 2500 (255) 79.1, 82.8 /
+// 60.0, 58.7; one of 16384 (32) 312, 457 / 67, 73; of 131072 (256) 11340, 11820 / 2460, 2650; 8 of 16384 with G = 4 (256) column sums 1830 / 1290, although
+// the column sums of such lengths have a kernel of 512 keys a workgroup and read every tile eight times as often as that; but 160 of 2048 (640)
+// 110, 112 / 128, 125 and 24 of 2500 with G = 4 (480) row statistics 93.9 / 107.8.
 // Below 8 tiles a full workgroup's load is not evened out by pairing, and the split kernels still win at 384 (96 slices of
-// 1000: 36 / 29).  In one or two tiles the full kernels' chains are short as well, and the split ones need a chain, heads
-// after each other, to earn their traffic.  G = 1, column sums: 160 slices of 512 22.9 / 21.7, 176 of them 23.1 / 23.4; 128 of 256
-// 11.2 / 8.8, 192 of them 11.3 / 11.7; 256 of 128 8.1 / 8.4, of 64 6.7 / 6.4; both passes: 192 slices of 256 20.2 / 19.5, 256 of
-// them 21.8 / 25.6, 256 of 150 17.1 / 17.3.  G = 2: 256 slices of 256 19.1 / 18.6, 320 of them 23.1 / 24.3, 384 of 200
-// 22.5 / 23.0.  G = 4: 320 slices of 256 34.3 / 34.4, 384 of them 36.1 / 39.5, 384 of 200 34.2 / 31.8.
-// fp32, where the matrix pipe is sixteen times slower and the latencies hide behind it: 128 workgroups 289 / 168 (8 slices
-// of 4096), 256 workgroups 84 / 108 (64 of 1000).  The kernels of 16 rows, both passes, 32 rows / 16 rows and four waves / eight: one slice
+// 1000: 34.4, 36.2 / 26.0, 24.8).  In one or two tiles the full kernels' chains are short as well, and the split ones need a chain, heads
+// after each other, to earn their traffic.  G = 1: 160 slices of 512 (320) 21.0, 21.4 / 19.3, 16.2; 128 of 256 11.2, 11.4 / 7.9, 7.0, 192 of them
+// 11.4, 11.3 / 11.0, 10.0; 256 of 128 8.2, 8.0 / 7.2, 6.6, of 64 6.4, 6.6 / 6.4, 6.1.  Column sums, G = 2: 256 slices of 256 18.3 / 15.2; G = 4: 320 of
+// 256 33.9 / 30.0, 384 of 200 32.0 / 27.4, but 384 of 256 34.7 / 36.0.
+// These are the present kernels, whose stationary rows go through LDS; the lines were drawn with the ones before, 3 to 19 % slower, and lie short of
+// where the two sides meet now: 64 slices of 2500 (320) 83.3, 86.5 / 73.3, 71.6, 96 of 2000 (384) 75.1, 78.1 / 72.6, 70.3; 128 of 1000 (512) 35.9, 37.4 / 33.7,
+// 31.7; 192 of 512 (384) 22.2, 23.0 / 20.8, 18.1; 256 of 256 column sums 11.9 / 10.7; 384 of 200, G = 2, column sums 21.1 / 19.2.
+// fp32, where the matrix pipe is sixteen times slower and the latencies hide behind it: 8 slices of 4096 (128) 282, 287 / 167, 169, 32 of
+// 1000 (128) 82, 83 / 55, 55, 64 of them (256) 86, 87 / 104, 102.  The kernels of 16 rows, both passes, 32 rows / 16 rows and four waves / eight: one slice
 // of 130 16.9 / 11.2 / 11.9, of 1000 44 / 31 / 28.5, of 4000 145 / 100 / 85.5, 8 of 1000 (256 workgroups of 32 rows) 45.5 / 39.7 / 36.5,
 // 16 of 512 (256, short chains) 27.0 / 23.7 / 25.4, 32 of 200 18.2 / 14.8 / 18.5, 4 of 3000 (376) 112 / 103 / 113; and 16 of 1000 (512) 55 / 58 /
 // 65: hence up to 384 blocks of 32 rows, and eight waves, whose workgroups of 130 KB of LDS take a compute unit each, where the up to 512 of

@@ -119,7 +119,7 @@ __device__ __forceinline__ void wave_lds_fence() {
 
 // In the launches that stream their merged rows, 16-bit rows that are read once carry the hint too: values, and keys of single tokens and of
 // sets of up to 16.  It leaves the caches to the keys of the longer sets' second sweep.  us, without / with: sets and merge of 1600 slices of 500 bf16
-// tokens 148 / 140, 1024 of 2000 fp16 375 / 365, 1024 of 4096 747 / 736, 1600 of 4096 in bf16 1062 / 1050, 1024 of up to 16384 1823 / 1799.  Not
+// tokens 135 / 126, 1024 of 2000 fp16 376 / 367, 1024 of 4096 759 / 748, 1600 of 4096 in bf16 1085 / 1071, 640 of 16384 1751 / 1743.  Not
 // in fp32, where it costs time: 1024 of 4096 1474 / 1540.
 template <typename T, bool STREAM> constexpr bool reads_once() { return STREAM && sizeof(T) == 2; }
 
