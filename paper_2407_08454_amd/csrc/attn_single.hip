@@ -14,7 +14,7 @@
 // ALU and 256 of the matrix pipe, and the exchange of the row sums leaves a wave idle once in 32 rows; the counters show the vector ALU
 // busy for half of the time, with two waves a SIMD (256 registers).  64 rows a workgroup would halve the traffic and were
 // twice as slow: eight waves then hold one compute unit, and nothing covers their exchanges.  fp32 is matrix time; its rows
-// of more than 2048 tokens spill 43 of their 256 registers, most of them around the last tiles of the longest rows.
+// of more than 2048 tokens spill 55 of their 256 registers, most of them around the last tiles of the longest rows and the loops.
 // us, both passes / this with its sum kernel: 1024 slices of 1000 fp16 tokens 436 / 334, 256 of them 118 / 77, 32 of them 19.0 / 16.0, 8 of them 18.1 /
 // 12.2; 1024 of 512 134 / 99, of 250 53 / 32, of 128 33 / 20; 32 of 2000 51 / 42; 8 of 1000, G = 4, in bf16 28.3 / 19.5; fp32: 256 of 1000 587 /
 // 348, 32 of 4096 1052 / 750, one of 512 18.0 / 12.7.
@@ -438,9 +438,10 @@ __global__ __launch_bounds__(W * WAVE, OCC) void attn_single_kernel(
         const int myrow = 16 * ((col >> 2) & (RT - 1)) + 4 * group + (col & 3);
         float mm = part[0][0][myrow], ll = part[1][0][myrow];
         for (int w = 1; w < W; ++w) join(mm, ll, part[0][w][myrow], part[1][w][myrow], c);
-        const float stat = q0 + myrow < n ? mm * c + __log2f(ll) : INFINITY;
-        float L[R];
-        static_for<0, R>([&](auto ic) __attribute__((always_inline)) { L[ic] = row16_lane<ic>(stat); });
+        // (by maximum and sum, not by their log-sum-exp: rounded at 2^36, its error would be the exponent of an infinite term)
+        const float inv = q0 + myrow < n ? 1.0f / ll : 0.f;
+        float most[R], wgt[R];
+        static_for<0, R>([&](auto ic) __attribute__((always_inline)) { most[ic] = row16_lane<ic>(mm); wgt[ic] = row16_lane<ic>(inv); });
 #pragma clang loop unroll(disable)
         for (int i = 0; i < cnt; ++i) {
             scores_of(i, i + 1);
@@ -448,7 +449,7 @@ __global__ __launch_bounds__(W * WAVE, OCC) void attn_single_kernel(
             for (int j = 0; j < SUB; ++j) {
                 float v = 0.f;
 #pragma unroll
-                for (int r = 0; r < R; ++r) v += __builtin_amdgcn_exp2f(fmaf(s[j][r / 4][r % 4], c, -L[r]));
+                for (int r = 0; r < R; ++r) v = fmaf(__builtin_amdgcn_exp2f((s[j][r / 4][r % 4] - most[r]) * c), wgt[r], v);
                 static_for<0, NT>([&](auto ic) __attribute__((always_inline)) { colsum[ic][j] += ic == i ? v : 0.f; });
             }
         }

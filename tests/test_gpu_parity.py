@@ -531,6 +531,25 @@ def test_mass_single_pass_heads_of_different_scale(dtype, scales):
         assert np.abs(got[~big]).max(initial=0.0) <= 2e-6
 
 
+@pytest.mark.parametrize("dtype,size", [("f16", 6e4), ("f16", 1e4), ("bf16", 1e9), ("f32", 6e4), ("f32", 1e9)])
+def test_mass_single_pass_of_very_large_scores(dtype, size):
+    """One key and one query so large that every score with them is finite but decides its row alone: weights of one and zero, which
+    no rounding of a row's log-sum-exp (2^11 and more at these sizes) may turn into others."""
+    _say(f"mass, single pass, a row of {size}, {dtype}")
+    n = 300
+    rng = np.random.default_rng(51)
+    q, k = (rng.standard_normal((1, 2, n, 128)).astype(np.float32) for _ in range(2))
+    k[0, 0, n // 4], q[0, 0, n // 2] = size, size
+    Q, K = synth.to_storage(q, dtype), synth.to_storage(k, dtype)
+    want = ref.attn_mass(Q, K, dtype)
+    for copies in (1, 150):
+        (got, _), names = _single_pass(Q, K, dtype, copies=copies)
+        assert "attn_single_kernel" in names and np.isfinite(got).all()
+        big = want > 1e-6
+        assert (np.abs(got[big] - want[big]) / want[big]).max() <= 2e-5
+        assert np.abs(got[~big]).max(initial=0.0) <= 2e-6
+
+
 @pytest.mark.parametrize("slices,N,scale", [(2, 1000, 8.0), (1, 500, 4.0), (1, 3000, 4.0)])
 def test_mass_single_pass_fp32_is_as_exact_as_the_two_passes(slices, N, scale):
     """Scores of some size, where the rounding of their sums of products shows: the error against the oracle, 2-norm, of the single
